@@ -22,7 +22,7 @@ from paper_1810_09868_amd.model import Vgg19
 CONV = [(3, 64), (64, 64), (64, 128), (128, 128), (128, 256), (256, 256), (256, 256), (256, 256),
         (256, 512), (512, 512), (512, 512), (512, 512), (512, 512), (512, 512), (512, 512), (512, 512)]
 POOL_AFTER = (1, 3, 7, 11, 15)
-HIDDEN, CLASSES, LR = 4096, 1000, 0.01
+HIDDEN, CLASSES, LR = 4096, 1000, 1e-3  # (at 0.01 these random-label batches diverge after a few steps)
 
 
 def listed():
