@@ -142,10 +142,11 @@ int vgg_convert(int src_dtype, int dst_dtype, size_t n, const void *src, void *d
  * fp32 [Cout] or NULL.  Workspace is needed when Cin differs from
  * vgg_padded_channels(dtype, Cin) (a zero-padded copy of x is made there)
  * and for small problems (fewer pixel-by-channel tiles than half the chip's
- * compute units and a long contraction): several workgroups then share a
- * tile, each summing a range of input channels into fp32 partial results in
- * the workspace, and a second kernel adds them in a fixed order and applies
- * bias and f.  The query returns 0 when neither applies. */
+ * compute units and a long contraction): VGG_F32: several workgroups then
+ * share a tile, each summing a range of input channels into fp32 partial
+ * results in the workspace, and a second kernel adds them in a fixed order
+ * and applies bias and f (VGG_BF16 adds them inside a workgroup; the query
+ * answers as for VGG_F32 all the same).  It returns 0 when neither applies. */
 size_t vgg_conv3x3_fwd_workspace_bytes(int dtype, int N, int H, int W, int Cin, int Cout);
 int vgg_conv3x3_fwd(int dtype, int N, int H, int W, int Cin, int Cout, const void *x_nhwc,
                     const void *w_packed, const float *bias, void *y_nhwc, int relu, void *ws,
@@ -352,7 +353,11 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *       implicit GEMM with room for 384 / 448 / 192 halo rows, 4 / 5 the
  *       bf16 implicit GEMM with its weights in registers and room for
  *       384 / 448 halo rows, 6 / 7 the same with 320-pixel tiles and one
- *       workgroup per compute unit; weight
+ *       workgroup per compute unit, 8 / 9 with 128-pixel tiles and room for
+ *       224 / 384 halo rows, 10 / 11 those with nine taps of weights in
+ *       flight, 12 / 13 the bf16 kernel for launches of few tiles (64 pixels
+ *       x 32 channels, the contraction split over the four / eight waves of a
+ *       workgroup); weight
  *       gradient: 100 linear tiles, 114 / 116 patches 14 / 16 pixels wide,
  *       103 the kernel for at most three input channels (fp32); 116 / 117
  *       the bf16 kernel and its variant for at most 32 input channels, 118
@@ -362,8 +367,8 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *   [1] pixels per tile   [2] output channels per tile
  *   [3] 0: a tile is consecutive pixels, 1: a patch of one image
  *   [4] pixel tiles
- *   [5] workgroups that share one tile's contraction (forward, data gradient)
- *       or partial results that the fixed-order reduction adds (weight gradient)
+ *   [5] workgroups (kernels 12 / 13: waves of one workgroup) that share one
+ *       tile's contraction (forward, data gradient) or partial results that the fixed-order reduction adds (weight gradient)
  *   [6] workgroups of the main launch */
 #define VGG_PLAN_FWD 0
 #define VGG_PLAN_FWD_POOL 1

@@ -27,6 +27,7 @@ int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void
                   const void *mask, void *y, void *pool, unsigned char *argmax, int relu, void *part_ws, hipStream_t stream);
 size_t conv3x3_igemm_workspace(int dtype, int N, int H, int W, int CinP, int Cout);
 bool conv3x3_pool_fusable(int dtype, int H, int W, int Cout);
+bool conv3x3_pool_fused(int dtype, int N, int H, int W, int CinP, int Cout);
 bool conv_first_pair_ok(int dtype, int H, int W);
 int conv_first_pair(int N, int H, int W, int CinP1, const float *x, const void *w1, const float *b1, const void *w2,
                     const float *b2, void *y, void *pool, hipStream_t stream);
@@ -180,7 +181,7 @@ WsLayout ws_layout(const vgg_config *c, const PackedLayout &P, bool training)
         // which other workgroups of the same launch are still reading.
         int cur = 0;
         for (int l = 0; l < VGG19_NUM_CONV; ++l) {
-            const bool fuse = l > 0 && pool_after(l) && conv3x3_pool_fusable(c->dtype, L.H[l], L.W[l], kConvCh[l][1]);
+            const bool fuse = l > 0 && pool_after(l) && conv3x3_pool_fused(c->dtype, c->N, L.H[l], L.W[l], P.cinp[l], kConvCh[l][1]);
             L.act[l] = cur ? pB : pA; cur ^= 1;
             L.pooled[l] = L.argmax[l] = 0;
             if (fuse) L.pooled[l] = L.act[l];
@@ -280,7 +281,7 @@ void run_forward(const vgg_config *c, const PackedLayout &P, const WsLayout &L, 
         // On patch-tiled layers the 2x2 maximum (and, for training, its position) is taken in the
         // convolution's epilogue and the un-pooled tensor is never written: the backward pass needs
         // only the pooled tensor (next layer's input and ReLU mask) and the positions.
-        const bool fuse = l > 0 && pool_after(l) && conv3x3_pool_fusable(dt, L.H[l], L.W[l], kConvCh[l][1]);
+        const bool fuse = l > 0 && pool_after(l) && conv3x3_pool_fused(dt, N, L.H[l], L.W[l], P.cinp[l], kConvCh[l][1]);
         if (l == 0)   // (reads the NCHW batch itself; the padded NHWC copy above is only the weight gradient's operand)
             VGG_STEP(rec, K_CONV, conv_first(dt, N, c->H, c->W, P.cinp[0], x, pk + P.conv_w[0],
                                             reinterpret_cast<const float *>(pk + P.conv_b[0]), out, 1, s));

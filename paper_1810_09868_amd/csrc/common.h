@@ -233,9 +233,8 @@ __host__ __device__ __forceinline__ int tile_pixel(const TileGeom &g, const Tile
     return m < g.M ? m : -1;
 }
 
-// Host side: chooses the mode and fills the derived fields for tiles of
-// `rows` pixels (rows = 256 -> 16x16 patches, 128 -> 8x16).
-inline TileGeom make_tile_geom(int N, int H, int W, int rows)
+// Host side: the fields that do not depend on the mode.
+inline TileGeom base_tile_geom(int N, int H, int W, int rows)
 {
     TileGeom g;
     g.N = N; g.H = H; g.W = W; g.M = N * H * W; g.rows = rows;
@@ -243,16 +242,27 @@ inline TileGeom make_tile_geom(int N, int H, int W, int rows)
     g.dW = make_fast_div(W); g.dHW = make_fast_div(H * W);
     g.dWp = make_fast_div(W + 1); g.dHp = make_fast_div(H + 1);
     g.dTilesW = g.dTilesHW = make_fast_div(1);
-    if (H % g.TH == 0 && W % g.TW == 0) {
-        g.mode = 1;
-        g.tiles_w = W / g.TW;
-        g.tiles_hw = g.tiles_w * (H / g.TH);
-        g.dTilesW = make_fast_div(g.tiles_w); g.dTilesHW = make_fast_div(g.tiles_hw);
-        g.ntiles = N * g.tiles_hw;
-        g.pitch = g.TW + 2;
-        g.S = (g.TH + 2) * (g.TW + 2);
-        return g;
-    }
+    return g;
+}
+// Patches of rows / 16 x 16 pixels, sticking out of the image where they do not divide it.
+inline TileGeom make_patch_geom(int N, int H, int W, int rows)
+{
+    TileGeom g = base_tile_geom(N, H, W, rows);
+    g.mode = 1;
+    g.tiles_w = (W + g.TW - 1) / g.TW;
+    g.tiles_hw = g.tiles_w * ((H + g.TH - 1) / g.TH);
+    g.dTilesW = make_fast_div(g.tiles_w); g.dTilesHW = make_fast_div(g.tiles_hw);
+    g.ntiles = N * g.tiles_hw;
+    g.pitch = g.TW + 2;
+    g.S = (g.TH + 2) * (g.TW + 2);
+    return g;
+}
+// Chooses the mode for tiles of `rows` pixels (rows = 256 -> 16x16 patches, 128 -> 8x16): patches where they
+// divide the image, else consecutive pixels.
+inline TileGeom make_tile_geom(int N, int H, int W, int rows)
+{
+    if (H % (rows / kTileW) == 0 && W % kTileW == 0) return make_patch_geom(N, H, W, rows);
+    TileGeom g = base_tile_geom(N, H, W, rows);
     g.mode = 0;
     g.tiles_w = g.tiles_hw = 0;
     g.ntiles = (g.M + rows - 1) / rows;

@@ -54,6 +54,8 @@ struct ConvArgs {
     float *part;        // [ksplit][M][Cout] partial sums when the contraction is split over workgroups, else null
     int ksplit;         // workgroups per tile (>= 1)
     int kchunks;        // channel chunks per workgroup
+    int halo_bufs;      // conv3x3_small_bf16_kernel: halo buffers per wave
+    FastDiv dTiles;     // ... division by the number of pixel tiles
     TileGeom g;
 };
 
@@ -619,7 +621,7 @@ __global__ __launch_bounds__(WM *WN * 64, WM *WN == 8 ? 4 : 3) void conv3x3_igem
     }
     compute(kh, Bs + bb * b_bytes);
 
-    if (p.part) conv_partial_epilogue<BM, BN, WM, WN>(acc, p, org, n0, split);
+    if (sizeof(T) == 4 && p.part) conv_partial_epilogue<BM, BN, WM, WN>(acc, p, org, n0, split);
     else conv_epilogue<T, BM, BN, WM, WN>(acc, p, org, smem, n0);
 }
 
@@ -661,6 +663,7 @@ __global__ __launch_bounds__(WM *WN * 64, WM *WN == 8 ? 4 : 3) void conv3x3_igem
 // copies issued since the one waited for; the schedule is static, so the counts are constants.
 // ---------------------------------------------------------------------------
 constexpr int kWregHaloRows = 384;      // halo rows of the weights-in-registers kernel (64 KB of LDS) ...
+constexpr int kWregHaloRowsHalf = 224; // ... of its 128-pixel tiles (40 KB)
 constexpr int kWregHaloRowsBig = 448;   // ... and of its variant for tiles that straddle images (72 KB)
 __device__ const u32x4 kZeroBlock[128] = {};   // 2 KB of zeros: a halo slot outside the image walks through it chunk by chunk
 
@@ -672,7 +675,7 @@ __device__ __forceinline__ void for_each_step(F &&f, std::integer_sequence<int, 
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-template <int WM, int WN, int SA, int TM, int OCC>
+template <int WM, int WN, int SA, int TM, int OCC, int RB>
 __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(ConvArgs p)
 {
     typedef bf16_t T;
@@ -681,10 +684,13 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     constexpr int KC = 32;                       // channels per chunk (one 64-byte LDS row)
     constexpr int NQ = (SA * 5 + NT - 1) / NT;   // halo copies per thread and chunk
     constexpr int ABUF = NQ * NT * 16;           // bytes per halo buffer (>= SA * 80)
-    constexpr int TAPS = 9, RB = 3;              // taps of weight fragments in registers
+    constexpr int TAPS = 9;                      // RB: taps of weight fragments in registers, requested RB - 1 taps ahead
     constexpr int LA = NI % 4 == 0 ? 3 : 4, RA = LA + 1;
     static_assert(TAPS % RB == 0 && (TAPS * NI) % RA == 0, "ring positions must repeat every chunk");
-    static_assert(NJ <= NI - LA && NQ <= 3 * LA, "weight loads and halo copies share the slots after the MFMAs");
+    static_assert(NJ <= NI && NQ <= 3 * LA, "weight loads and halo copies share the slots after the MFMAs");
+    // halo copies (three per pixel block, from block NI - LA of the last tap on) issued before that tap's last weight load
+    constexpr int early = NJ - 1 > NI - LA ? 3 * (NJ - 1 - (NI - LA)) : 0, NQ_EARLY = early < NQ ? early : NQ;
+    static_assert(RB >= 2 && (RB - 1) * NJ + NQ <= 63, "wait counts fit the counter");
 
     extern __shared__ __align__(16) char smem[];   // [2][ABUF]
     const int tid = threadIdx.x;
@@ -751,7 +757,7 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     f32x4v acc[NI][NJ];
     {
         const int c0 = n0 + wn * 64 + g * 4;
-        if (!p.bias || p.part) {
+        if (!p.bias) {
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[0][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
         } else if ((p.Cout & 3) == 0) {
@@ -776,9 +782,9 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     const long long w_tap = (long long)KB * p.Cout * 32;            // next tap of the same chunk
     const long long w_c = 2ll * p.Cout * 32 - 8 * w_tap;            // last tap -> first tap of the next chunk
     const long long w_same = -8 * w_tap;                            // ... of the same chunk again (past the end)
-    load_w(p.w, bq[0]);
-    load_w(p.w + w_tap, bq[1]);
-    const char *wnext = p.w + 2 * w_tap;                            // the fragments requested next: tap 2 of chunk 0
+#pragma unroll
+    for (int t = 0; t + 1 < RB; ++t) load_w(p.w + t * w_tap, bq[t]);
+    const char *wnext = p.w + (RB - 1) * w_tap;                     // the fragments requested next: tap RB - 1 of chunk 0
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
@@ -795,15 +801,16 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
         const long long w_wrap = c + 1 < nchunks ? w_c : w_same;
         for_each_step([&](auto ic) {
             constexpr int t = decltype(ic)::value;
-            // This tap's four weight fragments were requested during tap t - 2; since then came the four of tap
-            // t + 1 and, when the end of a chunk lies in between, its NQ halo copies.
-            constexpr int younger = NJ + (t < 2 ? NQ : 0);
+            // This tap's four weight fragments were requested during tap t - (RB - 1); since then came those of
+            // the RB - 2 taps in between and, when the end of a chunk lies there too, its NQ halo copies (when the
+            // request was made in the chunk's last tap: those of them issued after the last of the four).
+            constexpr int younger = (RB - 2) * NJ + (t < RB - 2 ? NQ : t == RB - 2 ? NQ - NQ_EARLY : 0);
             u32x4 b0 = bq[t % RB][0], b1 = bq[t % RB][1], b2 = bq[t % RB][2], b3 = bq[t % RB][3];
             asm volatile("s_waitcnt vmcnt(%4)" : "+v"(b0), "+v"(b1), "+v"(b2), "+v"(b3) : "n"(younger));
             const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)wnext);
             const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)wnext >> 32));
             const unsigned long long sbase = ((unsigned long long)hi << 32) | lo;
-            wnext += (t + 2) % TAPS == TAPS - 1 ? w_wrap : w_tap;
+            wnext += (t + RB - 1) % TAPS == TAPS - 1 ? w_wrap : w_tap;
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
@@ -829,7 +836,7 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
                 acc[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b1), a, acc[i][1], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (i < NJ)
-                    asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(bq[(t + 2) % RB][i]) : "v"(voff[i]), "s"(sbase) : "memory");
+                    asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(bq[(t + RB - 1) % RB][i]) : "v"(voff[i]), "s"(sbase) : "memory");
                 if (copying && (i - first_next) * 3 < NQ) copy_slot(ab, (i - first_next) * 3);
                 __builtin_amdgcn_sched_barrier(0);
                 acc[i][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b2), a, acc[i][2], 0, 0, 0);
@@ -907,7 +914,210 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     }
 }
 
-template <int WM, int WN, int SA, int TM = 4, int OCC = 2>
+// ---------------------------------------------------------------------------
+// bf16, launches with fewer tiles than the chip has SIMDs to fill (small batches): a workgroup of G waves owns
+// 64 pixels x 16 NJ channels, and its waves share the contraction, wave g taking the channel chunks g, g + G, ...
+// with all nine taps.  What bounds such a launch is not the matrix pipe but the chain launch -> first loads ->
+// multiply -> combine, so the kernel has one of each: a wave copies its own chunk's halo into its own LDS
+// region and requests all nine taps' weights at once (9 NJ fragments in registers, plain loads; a tap's
+// registers are refilled for the wave's next chunk as soon as its MFMAs are issued), no barrier until the end,
+// and the waves' sums meet in LDS instead of in a partial-sum buffer that a second launch has to read.
+// LDS rows are 64 bytes, segment s of row q at s ^ ((q >> 1) & 3): conflict-free for the fragment reads of
+// v_mfma_f32_16x16x32_bf16 (lane 16 g + q reads segment g of pixel q).
+// ---------------------------------------------------------------------------
+constexpr int kSmallPx = 64;         // pixels per tile
+constexpr int kSmallHaloRows = 256;  // most halo rows of a tile (the launch picks patches where consecutive pixels need more)
+
+template <int NJ, int G>
+__global__ __launch_bounds__(G * 64, G / 4) void conv3x3_small_bf16_kernel(ConvArgs p)
+{
+    typedef bf16_t T;
+    constexpr int NI = 4, BN = NJ * 16, KC = 32, TAPS = 9;
+    constexpr int RP = BN + 4;                    // floats per row of the combine buffer
+    constexpr int MAXPX = kSmallHaloRows / 64;    // halo rows per lane
+    extern __shared__ __align__(16) char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = lane & 15, g = lane >> 4;
+    // (each XCD takes a contiguous range of tiles, pixel tiles fastest: the weights, the larger operand here, are
+    // then read into one L2 only)
+    const int nblk = gridDim.x, xcd = blockIdx.x & 7;
+    const int bid = xcd * (nblk >> 3) + min(xcd, nblk & 7) + (blockIdx.x >> 3);
+    const int tile_n = fast_div(bid, p.dTiles), tile_m = bid - tile_n * p.g.ntiles;
+    const int n0 = tile_n * BN;
+    const TileOrigin org = tile_origin(p.g, tile_m);
+    const int pitch = p.g.pitch, nchunks = p.CinP / KC;
+    const size_t xrow = (size_t)p.CinP * sizeof(T);
+
+    // weight fragment (tap t, chunk c, channels ch .. ch + 15): see conv3x3_igemm_wreg_kernel
+    const int KB = p.CinP / 16;
+    const size_t w_tap = (size_t)KB * p.Cout * 32;
+    unsigned voff[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)   // channels past Cout are never stored
+        voff[j] = (unsigned)min(n0 + j * 16 + q, p.Cout - 1) * 32u + (g & 1) * 16 + (unsigned)(g >> 1) * p.Cout * 32u;
+    u32x4 bw[TAPS][NJ];
+    auto load_w = [&](int c, int t) __attribute__((always_inline)) {
+        const char *sb = p.w + t * w_tap + (size_t)c * 2 * p.Cout * 32;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) bw[t][j] = *reinterpret_cast<const u32x4 *>(sb + voff[j]);
+    };
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t) load_w(min(wv, nchunks - 1), t);
+
+    // The pixel behind halo row `lane + 64 j` is found once, by one lane; a copy (16 rows x 64 bytes) fetches
+    // the row number of its lanes from there.
+    int px[MAXPX];
+#pragma unroll
+    for (int j = 0; j < MAXPX; ++j) {
+        const int row = lane + 64 * j;
+        px[j] = row < p.g.S ? halo_pixel(p.g, org, row) : -1;
+    }
+    const int bufs = p.rowsA * kDataBytes;                            // bytes of one halo buffer (rowsA a multiple of 16)
+    char *As = smem + wv * p.halo_bufs * bufs;                        // this wave's one or two buffers
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)As);
+    auto copy = [&](int c, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 4 * MAXPX; ++k) {
+            if (k * 16 < p.rowsA) {
+                const int row = k * 16 + (lane >> 2);
+                const int pk = __shfl(px[k >> 2], row & 63, kWave);
+                const int seg = (lane & 3) ^ ((row >> 1) & 3);
+                const char *src = pk < 0 ? reinterpret_cast<const char *>(kZeroRow) : p.x + (size_t)pk * xrow + (size_t)c * kDataBytes;
+                src += seg * 16;
+                const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + buf * bufs + k * 1024);
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "m0", "memory");
+            }
+        }
+    };
+    if (wv < nchunks) copy(wv, 0);
+
+    int hrow[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        int m;
+        tile_row(p.g, org, i * 16 + q, m, hrow[i]);
+    }
+    f32x4v acc[NI][NJ];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
+
+    int buf = 0;
+    for (int c = wv; c < nchunks; c += G) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this chunk's halo has landed (and its weights)
+        const int cn = c + G;
+        if (p.halo_bufs == 2 && cn < nchunks) copy(cn, buf ^ 1);
+        const char *A = As + buf * bufs;
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t) {
+            bf16x8 a[NI];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int row = hrow[i] + (t / 3) * pitch + t % 3;
+                a[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(A + row * kDataBytes + ((g ^ (row >> 1)) & 3) * 16));
+            }
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bw[t][j]), a[i], acc[i][j], 0, 0, 0);
+            if (cn < nchunks) load_w(cn, t);
+        }
+        if (p.halo_bufs == 2) buf ^= 1;
+        else if (cn < nchunks) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // (one buffer: this chunk's reads are done)
+            copy(cn, 0);
+        }
+    }
+
+    // Combine: sums to LDS, [wave][pixel][channel], then each thread adds the G values of its four channels in a
+    // fixed order (bias first), applies ReLU / mask, and stores; with a pool, of the four pixels of a window.
+    __syncthreads();
+    float *red = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            *reinterpret_cast<f32x4v *>(red + (size_t)(wv * kSmallPx + i * 16 + q) * RP + j * 16 + g * 4) = acc[i][j];
+    __syncthreads();
+    const float lo = p.relu ? 0.f : -__builtin_inff();
+    T *y = reinterpret_cast<T *>(p.y), *pool = reinterpret_cast<T *>(p.pool);
+    const T *mask = reinterpret_cast<const T *>(p.mask);
+    auto value = [&](int row, int c4, T(&out)[4]) __attribute__((always_inline)) {   // four channels of tile row `row`
+        const int col = n0 + c4 * 4;
+        f32x4v s = {0.f, 0.f, 0.f, 0.f};
+        if (p.bias) s = *reinterpret_cast<const f32x4v *>(p.bias + col);
+#pragma unroll
+        for (int w = 0; w < G; ++w) s += *reinterpret_cast<const f32x4v *>(red + (size_t)(w * kSmallPx + row) * RP + c4 * 4);
+        const int m = tile_pixel(p.g, org, row);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] = f32_to_bf16(fmaxf(s[e], lo));
+        if (m >= 0 && mask) {
+            T mk[4];
+            __builtin_memcpy(mk, mask + (size_t)m * p.Cout + col, 8);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (!(bf16_to_f32(mk[e]) > 0.f)) out[e] = (T)0;
+        }
+        if (m >= 0 && y) __builtin_memcpy(y + (size_t)m * p.Cout + col, out, 8);
+    };
+    constexpr int C4 = BN / 4;
+    if (!pool) {
+#pragma unroll
+        for (int u0 = 0; u0 < kSmallPx * C4; u0 += G * 64) {
+            const int u = u0 + tid, row = u / C4, c4 = u % C4;
+            T out[4];
+            if (u < kSmallPx * C4 && n0 + c4 * 4 < p.Cout) value(row, c4, out);
+        }
+        return;
+    }
+    // (patch tiles of 4 x 16 pixels: sixteen windows)
+    for (int u = tid; u < kSmallPx / 4 * C4; u += G * 64) {
+        const int win = u / C4, c4 = u % C4, dy = win >> 3, dx = win & 7;
+        const int ph = (org.h0 >> 1) + dy, pw = (org.w0 >> 1) + dx;
+        if (n0 + c4 * 4 >= p.Cout || 2 * ph >= p.g.H || 2 * pw >= p.g.W) continue;
+        T best[4];
+        unsigned char which[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            T v[4];
+            value((2 * dy + (k >> 1)) * kTileW + 2 * dx + (k & 1), c4, v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (k == 0 || bf16_to_f32(v[e]) > bf16_to_f32(best[e])) { best[e] = v[e]; which[e] = (unsigned char)k; }
+        }
+        const size_t at = (((size_t)org.n * (p.g.H >> 1) + ph) * (p.g.W >> 1) + pw) * p.Cout + n0 + c4 * 4;
+        __builtin_memcpy(pool + at, best, 8);
+        if (p.argmax) __builtin_memcpy(p.argmax + at, which, 4);
+    }
+}
+
+// LDS bytes of a launch with one or two halo buffers per wave
+template <int NJ, int G>
+static size_t conv_small_lds(int S, int bufs)
+{
+    const size_t halo = (size_t)G * bufs * round_up16(S) * kDataBytes, red = (size_t)G * kSmallPx * (NJ * 16 + 4) * 4;
+    return halo > red ? halo : red;
+}
+template <int NJ, int G>
+static int launch_conv_small(const ConvArgs &a0, const TileGeom &g, hipStream_t stream)
+{
+    ConvArgs a = a0;
+    a.g = g;
+    a.tiles_n = (a.Cout + NJ * 16 - 1) / (NJ * 16);
+    a.rowsA = round_up16(g.S);
+    a.dTiles = make_fast_div(g.ntiles);
+    // a second halo buffer when a wave has more than one chunk and it fits
+    a.halo_bufs = a.CinP / 32 > G && conv_small_lds<NJ, G>(g.S, 2) <= 160 * 1024 ? 2 : 1;
+    auto kern = conv3x3_small_bf16_kernel<NJ, G>;
+    if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return VGG_ERR_LAUNCH;
+    const size_t lds = conv_small_lds<NJ, G>(g.S, a.halo_bufs);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g.ntiles * a.tiles_n)), dim3(G * 64), lds, stream, a);
+    return launch_status();
+}
+
+template <int WM, int WN, int SA, int TM = 4, int OCC = 2, int RB = 3>
 static int launch_conv_wreg(const ConvArgs &a0, const TileGeom &g, hipStream_t stream)
 {
     ConvArgs a = a0;
@@ -917,7 +1127,7 @@ static int launch_conv_wreg(const ConvArgs &a0, const TileGeom &g, hipStream_t s
     a.tiles_n = (a.Cout + BN - 1) / BN;
     a.rowsA = SA;
     const size_t lds = (size_t)2 * NQ * NT * 16;   // (more than the epilogue's staging blocks)
-    auto kern = conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC>;
+    auto kern = conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB>;
     if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return VGG_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.g.ntiles * a.tiles_n)), dim3(NT), lds, stream, a);
     return launch_status();
@@ -957,10 +1167,9 @@ static int launch_conv(const ConvArgs &a0, int N, int H, int W, hipStream_t stre
 }
 
 // Sums the partial results of a split contraction: y = f(bias + sum over splits), f = ReLU and/or the
-// (mask > 0) factor, converted to T.  One thread per four channels.
-template <typename T>
+// (mask > 0) factor (fp32).  One thread per four channels.
 __global__ __launch_bounds__(256) void conv_split_finish_kernel(const float *__restrict__ part, const float *__restrict__ bias,
-                                                                const T *__restrict__ mask, T *__restrict__ y, size_t quads,
+                                                                const float *__restrict__ mask, float *__restrict__ y, size_t quads,
                                                                 int Cout, int ksplit, int relu)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -973,78 +1182,136 @@ __global__ __launch_bounds__(256) void conv_split_finish_kernel(const float *__r
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         s[e] = fmaxf(s[e], lo);
-        if (mask && !(Elem<T>::load(mask + i * 4 + e) > 0.f)) s[e] = 0.f;
+        if (mask && !(mask[i * 4 + e] > 0.f)) s[e] = 0.f;
     }
     store4(y + i * 4, s[0], s[1], s[2], s[3]);
 }
 
-// Which kernel a shape gets, and whether its contraction is split over several workgroups per tile.
+// Which kernel a shape gets (the codes vgg_conv3x3_plan reports), and whether its contraction is split over
+// several workgroups per tile.
+enum ConvKernel {
+    kStaged = 0, kDma, kDmaBig, kDmaHalf,       // register-staged; direct-to-LDS with 384 / 448 / 192 halo rows
+    kWreg, kWregBig, kWregTall, kWregTallBig,   // weights in registers: 256- and 320-pixel tiles, 384 / 448 halo rows
+    kWregHalf, kWregHalfBig,                    // ... 128-pixel tiles, 224 / 384 halo rows
+    kWregDeep, kWregDeepBig,                    // ... with nine taps of weights in flight
+    kSmall4, kSmall8                            // 64 x 32 tiles, the contraction split over four / eight waves
+};
 struct ConvPlan {
     TileGeom g;
-    bool narrow, dma, dma_big, half, wreg, tall;
+    int kernel;
+    int bn;              // channels per tile
     int ksplit, kchunks;
 };
+
+// Split of the contraction over workgroups (fp32; for bf16 only the size of the workspace that callers bring,
+// see conv3x3_igemm_workspace).  Small batches: fewer tiles than CUs, each walking the whole contraction alone.
+// Then several workgroups share a tile, each taking a range of channel chunks (at least two), and a second
+// kernel adds their partial sums.
+static void conv_split(int dtype, const TileGeom &g, int CinP, int Cout, int &ksplit, int &kchunks)
+{
+    const int chunks = CinP * dtype_size(dtype) / kDataBytes;
+    const bool narrow = Cout <= 64 || g.ntiles * ((Cout + 127) / 128) < 512;
+    const int total = g.ntiles * ((Cout + (narrow ? 63 : 127)) / (narrow ? 64 : 128));
+    ksplit = 1; kchunks = chunks;
+    // Measured: pays when at most half the CUs would have a workgroup and a tile's contraction is
+    // long enough (a bf16 chunk takes a quarter of the time of an fp32 one).
+    if (g.S <= kDmaHaloRowsBig && Cout % 4 == 0 && total <= 128 && chunks >= (dtype == VGG_BF16 ? 8 : 4)) {
+        int want = (512 + total - 1) / total;   // two workgroups per CU
+        if (want > chunks / 2) want = chunks / 2;
+        kchunks = (chunks + want - 1) / want;
+        ksplit = (chunks + kchunks - 1) / kchunks;
+    }
+}
+
+// Tiles of the small-problem kernel: consecutive pixels, or patches where their halo is the smaller one (56 wide:
+// 240 halo rows against 108) or a pool is to be fused, and they stick out of the image by at most a quarter.
+static TileGeom conv_small_geom(int N, int H, int W, bool pool)
+{
+    const TileGeom lin = make_tile_geom(N, H, W, kSmallPx), patch = make_patch_geom(N, H, W, kSmallPx);
+    const bool fits = patch.ntiles * 4 <= lin.ntiles * 5, cheaper = (long)patch.ntiles * patch.S < (long)lin.ntiles * lin.S;
+    return lin.mode == 0 && ((fits && (cheaper || pool)) || lin.S > kSmallHaloRows) ? patch : lin;
+}
 
 static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bool pool)
 {
     ConvPlan c;
-    c.narrow = Cout <= 64;
     c.g = make_tile_geom(N, H, W, 256);
-    c.dma = c.g.S <= kDmaHaloRows;
-    c.dma_big = !c.dma && c.g.S <= kDmaHaloRowsBig;
+    const bool dma = c.g.S <= kDmaHaloRows, dma_big = !dma && c.g.S <= kDmaHaloRowsBig;
+    const int cols = (Cout + 127) / 128, wide_tiles = c.g.ntiles * cols;
+    const int chunks = CinP * dtype_size(dtype) / kDataBytes;
     // Too few 256x128 tiles to give every CU two workgroups (the 14x14 layers): 64-wide column tiles
     // double the workgroup count and three of them fit on a CU.
-    if (c.g.ntiles * ((Cout + 127) / 128) < 512) c.narrow = true;
-    // Small batches: fewer tiles than CUs, each walking the whole contraction alone.  Then several
-    // workgroups share a tile, each taking a range of channel chunks (at least two), and a second
-    // kernel adds their partial sums.
-    const int chunks = CinP * dtype_size(dtype) / kDataBytes;
-    const int total = c.g.ntiles * ((Cout + (c.narrow ? 63 : 127)) / (c.narrow ? 64 : 128));
+    const bool narrow = Cout <= 64 || wide_tiles < 512;
     c.ksplit = 1; c.kchunks = chunks;
-    // Measured: pays when at most half the CUs would have a workgroup and a tile's contraction is
-    // long enough (a bf16 chunk takes a quarter of the time of an fp32 one).
-    if ((c.dma || c.dma_big) && !pool && Cout % 4 == 0 && total <= 128 &&
-        chunks >= (dtype == VGG_BF16 ? 8 : 4)) {
-        int want = (512 + total - 1) / total;   // two workgroups per CU
-        if (want > chunks / 2) want = chunks / 2;
-        c.kchunks = (chunks + want - 1) / want;
-        c.ksplit = (chunks + c.kchunks - 1) / c.kchunks;
+    c.kernel = dma ? kDma : (dma_big ? kDmaBig : kStaged);
+    c.bn = narrow ? 64 : 128;
+    if (dtype == VGG_F32) {
+        if (!pool) conv_split(dtype, c.g, CinP, Cout, c.ksplit, c.kchunks);
+        // fp32, 64-wide tiles, a launch of only a few workgroups per CU (the 14x14 layers at batch 100: 616
+        // on 768 slots): 128-pixel tiles double the count and even out the load, +15 % there.
+        const int total = c.g.ntiles * ((Cout + 63) / 64);
+        if (c.ksplit == 1 && narrow && (dma || dma_big) && !pool && total >= 256 && total < 2048) {
+            const TileGeom h = make_tile_geom(N, H, W, 128);
+            if (h.S <= kDmaHaloRowsHalf) { c.g = h; c.kernel = kDmaHalf; }
+        }
+        return c;
     }
-    // fp32, 64-wide tiles, a launch of only a few workgroups per CU (the 14x14 layers at batch 100: 616
-    // on 768 slots): 128-pixel tiles double the count and even out the load, +15 % there.  (bf16 loses
-    // 5 % the same way: its workgroups are short enough that the smaller tile's overhead weighs more.)
-    c.half = false;
-    if (dtype == VGG_F32 && c.narrow && (c.dma || c.dma_big) && !pool && c.ksplit == 1 && total >= 256 && total < 2048) {
-        const TileGeom h = make_tile_geom(N, H, W, 128);
-        if (h.S <= kDmaHaloRowsHalf) { c.g = h; c.half = true; }
-    }
-    // bf16, 128-wide column tiles, whole contraction in one workgroup: the kernel that keeps the weights in
-    // registers (its 256-pixel tile and halo are those of the direct-to-LDS kernels, so dma / dma_big decide
-    // the halo size here as well)
-    c.wreg = dtype == VGG_BF16 && !c.narrow && (c.dma || c.dma_big) && c.ksplit == 1;
-    // bf16, a launch that 256-pixel tiles cannot spread evenly (the 14x14 layers at batch 100: 308 tiles of 128
-    // channels, so some CUs would get two workgroups and the rest one): 320-pixel tiles, five pixel blocks per
-    // wave and one workgroup per CU with all its registers, when that gives every CU at most one tile.
-    c.tall = false;
-    if (dtype == VGG_BF16 && Cout > 64 && !pool && c.ksplit == 1 && c.g.ntiles * ((Cout + 127) / 128) < 512) {
-        const TileGeom t = make_tile_geom(N, H, W, 320);
-        const int tiles = t.ntiles * ((Cout + 127) / 128);
-        if (t.S <= kWregHaloRowsBig && tiles > 128 && tiles <= 256) {
+    // bf16.  Few tiles and at least four channel chunks: the waves of a workgroup share the contraction (64 x 32
+    // tiles; eight waves where every CU gets at most one workgroup and every wave still two chunks).  Measured
+    // against the best of the other kernels (us): 512 -> 512 at 14x14, batch 1 (128 tiles) 9.3 / 13.5; at 28x28,
+    // batch 1 (224) 10.1 / 19.3, batch 2 (448) 15.1 / 22; batch 4 (896) 28 / 26: the line lies at 512 tiles.
+    if (Cout % 4 == 0 && chunks >= 4 && wide_tiles < 512) {
+        const TileGeom t = conv_small_geom(N, H, W, pool);
+        const int tiles = t.ntiles * ((Cout + 31) / 32);
+        if (tiles <= 512 && (!pool || t.mode == 1)) {
             c.g = t;
-            c.tall = c.wreg = true;
-            c.narrow = c.half = false;
-            c.dma = t.S <= kWregHaloRows;
-            c.dma_big = !c.dma;
+            c.kernel = tiles <= 256 && chunks >= 16 ? kSmall8 : kSmall4;
+            c.bn = 32;
+            return c;
+        }
+    }
+    // Weights in registers: more than 64 output channels, and a contraction of at least three chunks unless
+    // there is a tile for every CU (below that the 64-wide direct-to-LDS launch is as fast).  The tile by the time of the CU with most of them, in units of
+    // a 256-pixel tile's (one wave per SIMD multiplies nearly as fast as two, so a CU's tiles simply add up):
+    // 320 pixels cost 1.25, 128 pixels 0.56.  Measured (us) for 512 channels, 256 / 320 / 128 pixels: 28x28 batch
+    // 10 (124, 100, 248 tiles) 44 / 54 / 35, batch 16 (196, 160, 392) 46 / 55 / 50, batch 32 (392, 316, 784) 88 /
+    // 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.
+    if (Cout > 64 && (dma || dma_big) && (!narrow || chunks >= 3 || wide_tiles >= 256)) {
+        c.kernel = dma ? kWreg : kWregBig;
+        c.bn = 128;
+        if (!narrow) return c;
+        auto rounds = [](int tiles) { return (tiles + 255) / 256; };
+        float best = (float)rounds(wide_tiles);
+        if (!pool) {
+            const TileGeom t = make_tile_geom(N, H, W, 320);
+            const float cost = 1.25f * rounds(t.ntiles * cols);
+            if (t.S <= kWregHaloRowsBig && cost < best) {
+                best = cost;
+                c.g = t;
+                c.kernel = t.S <= kWregHaloRows ? kWregTall : kWregTallBig;
+            }
+        }
+        const TileGeom t = make_tile_geom(N, H, W, 128);
+        const int tiles = t.ntiles * cols;
+        if (t.S <= kWregHaloRows && 0.56f * rounds(tiles) < best) {
+            c.g = t;
+            const bool big = t.S > kWregHaloRowsHalf;
+            // (one tile per CU, alone there: with two taps of weights ahead each tap waits for L2; nine taps ahead
+            // 36 -> 31.6 at 28x28 batch 10, 35 -> 27.4 at 14x14 batch 32; no gain on eight chunks)
+            if (tiles <= 256 && chunks >= 12) c.kernel = big ? kWregDeepBig : kWregDeep;
+            else c.kernel = big ? kWregHalfBig : kWregHalf;
         }
     }
     return c;
 }
 
-// Bytes of partial sums conv3x3_igemm needs for this shape (0: the contraction is not split).
+// Bytes of partial sums conv3x3_igemm needs for this shape (0: none).  bf16: what the shapes whose contraction
+// was once split over workgroups needed; nothing is written there, but callers size and pass their buffers by it.
 size_t conv3x3_igemm_workspace(int dtype, int N, int H, int W, int CinP, int Cout)
 {
-    const ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, false);
-    return c.ksplit > 1 ? round_up((size_t)c.ksplit * N * H * W * Cout * 4, 256) : 0;
+    int ksplit, kchunks;
+    conv_split(dtype, make_tile_geom(N, H, W, 256), CinP, Cout, ksplit, kchunks);
+    return ksplit > 1 ? round_up((size_t)ksplit * N * H * W * Cout * 4, 256) : 0;
 }
 
 // For inspection: {kernel (0 register-staged, 1 / 2 / 3 direct-to-LDS with 384 / 448 / 192 halo rows), pixels per
@@ -1053,14 +1320,13 @@ size_t conv3x3_igemm_workspace(int dtype, int N, int H, int W, int CinP, int Cou
 void conv3x3_igemm_plan_info(int dtype, int N, int H, int W, int CinP, int Cout, bool pool, int info[7])
 {
     const ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool);
-    const int bn = c.narrow ? 64 : 128;
-    info[0] = c.wreg ? (c.dma ? 4 : 5) + (c.tall ? 2 : 0) : (c.half ? 3 : (c.dma ? 1 : (c.dma_big ? 2 : 0)));
+    info[0] = c.kernel;
     info[1] = c.g.rows;
-    info[2] = bn;
+    info[2] = c.bn;
     info[3] = c.g.mode;
     info[4] = c.g.ntiles;
-    info[5] = c.ksplit;
-    info[6] = c.g.ntiles * ((Cout + bn - 1) / bn) * c.ksplit;
+    info[5] = c.kernel == kSmall8 ? 8 : (c.kernel == kSmall4 ? 4 : c.ksplit);
+    info[6] = c.g.ntiles * ((Cout + c.bn - 1) / c.bn) * c.ksplit;
 }
 
 bool conv3x3_pool_fusable(int dtype, int H, int W, int Cout)
@@ -1068,14 +1334,24 @@ bool conv3x3_pool_fusable(int dtype, int H, int W, int Cout)
     return H % 16 == 0 && W % kTileW == 0 && Cout % (16 / dtype_size(dtype)) == 0;
 }
 
+// Whether conv3x3_igemm takes a pool for this shape: besides the sizes above, the launches of the small-problem
+// kernel that run on patches (the model's 56x56, 28x28 and 14x14 layers at small batches).
+bool conv3x3_pool_fused(int dtype, int N, int H, int W, int CinP, int Cout)
+{
+    if (conv3x3_pool_fusable(dtype, H, W, Cout)) return true;
+    if (dtype != VGG_BF16 || H % 2 || W % 2 || Cout % 8) return false;
+    const int k = conv_plan(dtype, N, H, W, CinP, Cout, true).kernel;
+    return k == kSmall4 || k == kSmall8;
+}
+
 // x: [N*H*W][CinP], w: [9][Cout][CinP] (elements of dtype); y: [N*H*W][Cout].
-// pool (optional): 2x2 max of y, only when conv3x3_pool_fusable(); y may then be null; argmax (optional, with pool).
+// pool (optional): 2x2 max of y, only when conv3x3_pool_fused(); y may then be null; argmax (optional, with pool).
 // part_ws: conv3x3_igemm_workspace() bytes, or null (then the contraction is never split).
 int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void *x, const void *w,
                   const float *bias, const void *mask, void *y, void *pool, unsigned char *argmax, int relu, void *part_ws,
                   hipStream_t stream)
 {
-    if (pool && !conv3x3_pool_fusable(dtype, H, W, Cout)) return VGG_ERR_UNSUPPORTED;
+    if (pool && !conv3x3_pool_fused(dtype, N, H, W, CinP, Cout)) return VGG_ERR_UNSUPPORTED;
     ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool != nullptr);
     if (!part_ws || !y) { c.ksplit = 1; c.kchunks = CinP * dtype_size(dtype) / kDataBytes; }
     ConvArgs a;
@@ -1090,46 +1366,53 @@ int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void
     a.relu = relu; a.tiles_n = 0; a.rowsA = 0;
     a.part = c.ksplit > 1 ? static_cast<float *>(part_ws) : nullptr;
     a.ksplit = c.ksplit; a.kchunks = c.kchunks;
-    const bool narrow = c.narrow, dma = c.dma, dma_big = c.dma_big;
+    const bool narrow = c.bn == 64;
     const TileGeom &g = c.g;
-    int rc;
+    int rc = VGG_ERR_UNSUPPORTED;
     if (dtype == VGG_F32) {
-        if (c.half)
-            rc = launch_conv_dma<float, 128, 64, 4, 1, kDmaHaloRowsHalf>(a, g, stream);
-        else if (dma)
+        switch (c.kernel) {
+        case kDmaHalf: rc = launch_conv_dma<float, 128, 64, 4, 1, kDmaHaloRowsHalf>(a, g, stream); break;
+        case kDma:
             rc = narrow ? launch_conv_dma<float, 256, 64, 4, 1, kDmaHaloRows>(a, g, stream)
                         : launch_conv_dma<float, 256, 128, 4, 2, kDmaHaloRows>(a, g, stream);
-        else if (dma_big)
+            break;
+        case kDmaBig:
             rc = narrow ? launch_conv_dma<float, 256, 64, 4, 1, kDmaHaloRowsBig>(a, g, stream)
                         : launch_conv_dma<float, 256, 128, 4, 2, kDmaHaloRowsBig>(a, g, stream);
-        else
+            break;
+        default:
             rc = narrow ? launch_conv<float, 256, 64, 4, 1>(a, N, H, W, stream)
                         : launch_conv<float, 256, 128, 4, 2>(a, N, H, W, stream);
+        }
     } else {
-        // (weights in registers)
-        if (c.tall)
-            rc = dma ? launch_conv_wreg<2, 2, kWregHaloRows, 5, 1>(a, g, stream) : launch_conv_wreg<2, 2, kWregHaloRowsBig, 5, 1>(a, g, stream);
-        else if (c.wreg && c.ksplit == 1)
-            rc = dma ? launch_conv_wreg<2, 2, kWregHaloRows>(a, g, stream) : launch_conv_wreg<2, 2, kWregHaloRowsBig>(a, g, stream);
-        else if (dma)
+        switch (c.kernel) {
+        case kWreg: rc = launch_conv_wreg<2, 2, kWregHaloRows>(a, g, stream); break;
+        case kWregBig: rc = launch_conv_wreg<2, 2, kWregHaloRowsBig>(a, g, stream); break;
+        case kWregTall: rc = launch_conv_wreg<2, 2, kWregHaloRows, 5, 1>(a, g, stream); break;
+        case kWregTallBig: rc = launch_conv_wreg<2, 2, kWregHaloRowsBig, 5, 1>(a, g, stream); break;
+        case kWregHalf: rc = launch_conv_wreg<2, 2, kWregHaloRowsHalf, 2, 3>(a, g, stream); break;
+        case kWregHalfBig: rc = launch_conv_wreg<2, 2, kWregHaloRows, 2, 2>(a, g, stream); break;
+        case kWregDeep: rc = launch_conv_wreg<2, 2, kWregHaloRowsHalf, 2, 1, 9>(a, g, stream); break;
+        case kWregDeepBig: rc = launch_conv_wreg<2, 2, kWregHaloRows, 2, 1, 9>(a, g, stream); break;
+        case kSmall4: rc = launch_conv_small<2, 4>(a, g, stream); break;
+        case kSmall8: rc = launch_conv_small<2, 8>(a, g, stream); break;
+        case kDma:
             rc = narrow ? launch_conv_dma<bf16_t, 256, 64, 4, 1, kDmaHaloRows>(a, g, stream)
                         : launch_conv_dma<bf16_t, 256, 128, 4, 2, kDmaHaloRows>(a, g, stream);
-        else if (dma_big)
+            break;
+        case kDmaBig:
             rc = narrow ? launch_conv_dma<bf16_t, 256, 64, 4, 1, kDmaHaloRowsBig>(a, g, stream)
                         : launch_conv_dma<bf16_t, 256, 128, 4, 2, kDmaHaloRowsBig>(a, g, stream);
-        else
+            break;
+        default:
             rc = narrow ? launch_conv<bf16_t, 256, 64, 4, 1>(a, N, H, W, stream)
                         : launch_conv<bf16_t, 256, 128, 4, 2>(a, N, H, W, stream);
+        }
     }
     if (rc != VGG_OK || c.ksplit == 1) return rc;
     const size_t quads = (size_t)N * H * W * Cout / 4;
-    const dim3 grid((unsigned)((quads + 255) / 256));
-    if (dtype == VGG_F32)
-        hipLaunchKernelGGL(conv_split_finish_kernel<float>, grid, dim3(256), 0, stream, a.part, bias,
-                           static_cast<const float *>(mask), static_cast<float *>(y), quads, Cout, c.ksplit, relu);
-    else
-        hipLaunchKernelGGL(conv_split_finish_kernel<bf16_t>, grid, dim3(256), 0, stream, a.part, bias,
-                           static_cast<const bf16_t *>(mask), static_cast<bf16_t *>(y), quads, Cout, c.ksplit, relu);
+    hipLaunchKernelGGL(conv_split_finish_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, a.part, bias,
+                       static_cast<const float *>(mask), static_cast<float *>(y), quads, Cout, c.ksplit, relu);
     return launch_status();
 }
 

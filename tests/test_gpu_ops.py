@@ -348,6 +348,55 @@ def test_conv3x3_bf16_320_pixel_tiles_element_by_element():
     assert max_rel_err(from_nhwc(dx), ref * (from_nhwc(xsrc) > 0)) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("shape,kernel", [
+    ((1, 14, 14, 512, 512), 13),    # eight waves, two chunks each; consecutive pixels that end inside a tile
+    ((2, 30, 44, 128, 36), 12),     # one chunk per wave; patches that stick out on both sides; a ragged channel tile
+    ((5, 16, 48, 160, 100), 12),    # five chunks for four waves; patches that divide the image (the pool can be fused)
+    ((1, 56, 56, 288, 64), 12),     # nine chunks, two halo buffers
+    ((12, 7, 9, 544, 260), 13),     # seventeen chunks for eight waves; tiles that cross images
+    ((3, 5, 130, 128, 72), 12),     # an image row longer than a tile's halo: patches
+    ((41, 14, 14, 384, 512), 10),   # 128-pixel tiles, nine taps of weights ahead (252 tiles)
+    ((9, 30, 57, 384, 200), 11),    # ... with the larger halo
+    ((9, 24, 16, 96, 512), 8),      # 128-pixel patches
+    ((6, 30, 57, 96, 200), 9),      # 128 consecutive pixels, the larger halo, a ragged channel tile
+])
+def test_conv3x3_bf16_small_and_medium_launches(shape, kernel):
+    """The kernels that launches of few tiles take, at the edges of their tiles and splits: forward and masked data
+    gradient (of the layer with the channel counts exchanged) against the oracle, element by element, nothing
+    written past the tensors; fused pool against the separate one where the sizes allow it."""
+    dtype = B.BF16
+    N, H, W, Cin, Cout = shape
+    assert B.vgg_conv3x3_plan(B.PLAN_FWD, dtype, N, H, W, Cin, Cout)[0] == kernel
+    d = synth.conv_layer_inputs(N, H, W, Cin, Cout, seed=sum(shape))
+    x, n = to_nhwc(d["x"], dtype), N * H * W * Cout
+    wp = _pack(dtype, d["w"])
+    buf = torch.full((n + 4096,), -7.0, dtype=TDT[dtype], device="cuda")
+    y = buf[:n].view(N, H, W, Cout)
+    ws = ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(dtype, N, H, W, Cin, Cout))
+    B.vgg_conv3x3_fwd(dtype, N, H, W, Cin, Cout, x, wp, dev(d["b"]), y, 1, ws)
+    torch.cuda.synchronize()
+    assert max_rel_err(from_nhwc(y), R.conv3x3_fwd(d["x"], d["w"], d["b"], relu=True)) <= TOL[dtype]
+    assert (buf[n:] == -7.0).all()
+    if H % 16 == 0 and W % 16 == 0 and Cout % 8 == 0:
+        y2 = torch.empty_like(y)
+        po = torch.empty((N, H // 2, W // 2, Cout), dtype=TDT[dtype], device="cuda")
+        arg = torch.empty((N, H // 2, W // 2, Cout), dtype=torch.uint8, device="cuda")
+        po_chk, arg_chk = torch.empty_like(po), torch.empty_like(arg)
+        B.vgg_conv3x3_fwd_pool(dtype, N, H, W, Cin, Cout, x, wp, dev(d["b"]), y2, po, 1, ws, argmax=arg)
+        B.vgg_maxpool2x2(dtype, N, H, W, Cout, y2, po_chk, arg_chk)
+        torch.cuda.synchronize()
+        assert torch.equal(po.view(torch.int16), po_chk.view(torch.int16)) and torch.equal(arg, arg_chk)
+    d = synth.conv_layer_inputs(N, H, W, Cout, Cin, seed=sum(shape) + 1)
+    assert B.vgg_conv3x3_plan(B.PLAN_BWD_DATA, dtype, N, H, W, Cout, Cin)[0] == kernel
+    xs = to_nhwc(d["x"], dtype)
+    ws = ws_bytes(B.vgg_conv3x3_bwd_data_workspace_bytes(dtype, N, H, W, Cout, Cin))
+    buf.fill_(-7.0)
+    B.vgg_conv3x3_bwd_data(dtype, N, H, W, Cout, Cin, to_nhwc(d["dy"], dtype), _pack(dtype, d["w"], flip=1), xs, y, ws)
+    torch.cuda.synchronize()
+    assert max_rel_err(from_nhwc(y), R.conv3x3_bwd_data(d["dy"], d["w"]) * (from_nhwc(xs) > 0)) <= TOL[dtype]
+    assert (buf[n:] == -7.0).all()
+
+
 @pytest.mark.parametrize("shape", FULL_SIZE_LAYERS)
 def test_conv3x3_bf16_full_size_on_sampled_pixels(shape):
     """Forward and data gradient at the benchmark's sizes, in the launch configuration it times; the oracle
