@@ -652,20 +652,24 @@ __global__ __launch_bounds__(WM *WN * 64, WM *WN == 8 ? 4 : 3) void conv3x3_igem
 // block, LA blocks ahead into a ring of LA + 1.  The halo of a chunk is copied by global_load_lds_dwordx4
 // into one of two buffers a whole chunk ahead; rows are 80 bytes (64 data + 16 pad, conflict-free fragment
 // reads at addresses that are a per-lane base plus an offset per tap); the copy treats a buffer as
-// consecutive 16-byte slots, slot s = row s / 5, segment s % 5, every lane supplying the source address of
-// its slot (pad slots and rows outside the image read a block of zeros).  Once the last halo fragment of a
+// consecutive 16-byte slots, slot s = row s / 5, segment s % 5, every lane supplying the 32-bit offset of its
+// slot from a scalar base that moves on by a chunk (slots outside the image are zeroed once and their lanes sit
+// out: half the address registers of per-lane pointers, which is what lets every epilogue live in registers).
+// Once the last halo fragment of a
 // chunk has been requested (LA blocks before the chunk ends) the workgroup synchronises, reads on from the
 // other buffer and copies the halo of the chunk after next into the one it has left.
 // Every other instruction of a step is issued right after an MFMA, in its shadow: a wave issues in order,
 // and issued as a block before the MFMAs they would leave the matrix pipe idle whenever the SIMD's other
 // wave is not multiplying.
 // All vector-memory waits are written by hand (the loads are inline assembly), counting the loads and
-// copies issued since the one waited for; the schedule is static, so the counts are constants.
+// copies issued since the one waited for; the schedule is static, so the counts are constants.  A variant must
+// not spill: a load in flight over a spilled register would be lost.
+// The result leaves from registers, also pooled or masked: 128 -> 128 at 112x112, batch 32, masked 139 -> 130 us
+// against the transposing pass through LDS.
 // ---------------------------------------------------------------------------
 constexpr int kWregHaloRows = 384;      // halo rows of the weights-in-registers kernel (64 KB of LDS) ...
 constexpr int kWregHaloRowsHalf = 224; // ... of its 128-pixel tiles (40 KB)
 constexpr int kWregHaloRowsBig = 448;   // ... and of its variant for tiles that straddle images (72 KB)
-__device__ const u32x4 kZeroBlock[128] = {};   // 2 KB of zeros: a halo slot outside the image walks through it chunk by chunk
 
 template <typename F, int... S>
 __device__ __forceinline__ void for_each_step(F &&f, std::integer_sequence<int, S...>)
@@ -675,7 +679,11 @@ __device__ __forceinline__ void for_each_step(F &&f, std::integer_sequence<int, 
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-template <int WM, int WN, int SA, int TM, int OCC, int RB>
+// EPI: how the tile leaves, a kernel of its own each (the main loop has no register to spare for what the others
+// would keep alive across it).
+enum ConvEpilogue { kEpiPlain, kEpiMasked, kEpiPooled, kEpiGeneral };
+
+template <int WM, int WN, int SA, int TM, int OCC, int RB, int EPI>
 __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(ConvArgs p)
 {
     typedef bf16_t T;
@@ -707,24 +715,38 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     const int nchunks = p.CinP / KC;
     const size_t xrow = (size_t)p.CinP * sizeof(T);
 
-    // source of each of this lane's halo slots (chunk 0)
-    const char *asrc[NQ];
+    // Halo copies: 32-bit offset of each of this lane's slots from the tile's first halo pixel (a scalar base that
+    // moves on by a chunk), and the lanes that copy.  Slots of pixels outside the image are zeroed here, once, in
+    // both buffers, and their lanes sit the copies out; the lanes of pad slots, which nobody reads, copy from the base, so that no copy
+    // is ever without a lane (the waits below count copies).
+    const int px0 = p.g.mode ? (org.n * p.g.H + max(org.h0 - 1, 0)) * p.g.W + max(org.w0 - 1, 0) : max(org.m0 - p.g.W - 2, 0);
+    unsigned aoff[NQ];
+    unsigned long long alanes[NQ];
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
         const int slot = (k * NW + wv) * 64 + lane;
         const int row = slot / 5, seg = slot - row * 5;
         const int px = (row < p.g.S && seg < 4) ? halo_pixel(p.g, org, row) : -1;
-        asrc[k] = px < 0 ? reinterpret_cast<const char *>(kZeroBlock) : p.x + (size_t)px * xrow + seg * 16;
+        aoff[k] = px < 0 ? 0u : (unsigned)(px - px0) * (unsigned)xrow + seg * 16;
+        alanes[k] = __ballot(px >= 0 || seg == 4);
+        if (px < 0 && seg < 4) {
+            *reinterpret_cast<u32x4 *>(smem + slot * 16) = u32x4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<u32x4 *>(smem + ABUF + slot * 16) = u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    unsigned long long abase;
+    {
+        const unsigned long long v = (unsigned long long)(uintptr_t)(p.x + (size_t)px0 * xrow);
+        abase = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(v >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((unsigned)v);
     }
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
     auto copy_slot = [&](int buf, int k) __attribute__((always_inline)) {
         const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + buf * ABUF + (k * NW + wv) * 1024);
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(asrc[k]) : "m0", "memory");
+        // (every lane of the wave is active where this is called)
+        asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
+                     : : "s"(dst), "v"(aoff[k]), "s"(abase), "s"(alanes[k]) : "m0", "memory");
     };
-    auto next_chunk = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) asrc[k] += KC * sizeof(T);
-    };
+    auto next_chunk = [&]() __attribute__((always_inline)) { abase += KC * sizeof(T); };
 
     // byte address (inside a buffer) of tap (0,0) of this lane's pixels, its 16 bytes of the row included
     int arow[NI];
@@ -853,7 +875,7 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the weight loads and halo copies issued past the end
 
     const int wrow0 = wm * (TM * 32);
-    if (p.pool || p.mask || !p.y || (p.Cout & 7)) {
+    if (EPI == kEpiGeneral || (p.Cout & 7)) {   // pooled and un-pooled result, or a channel count that 16-byte stores do not divide
         conv_epilogue_impl<T, BM, BN, WM, WN>(
             [&](int i, int j0, char *epi, float lo) __attribute__((always_inline)) {
                 // (bf16: a pass is all 64 columns of the wave; pixel block i of 32 rows = 16-pixel blocks 2 i, 2 i + 1)
@@ -877,38 +899,130 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
             p, org, smem, n0);
         return;
     }
-    // Plain store epilogue (no pool, no mask): straight from registers.  A lane holds four consecutive channels
-    // of a pixel per accumulator; lanes 16 apart (the next four channels of the same pixel) swap the values of
-    // one of two pixel blocks (v_permlane16_swap: the even row of 16 lanes ends up with eight channels of the
-    // first block, the odd row with eight channels of the second) and store 16 bytes each.
-    {
-        const float lo = p.relu ? 0.f : -__builtin_inff();
+    // Straight from registers, without LDS or a barrier.  A lane holds four consecutive channels of a pixel per
+    // accumulator; lanes 16 apart (the next four channels of the same pixel) swap the values of one of two
+    // accumulators (v_permlane16_swap: the even row of 16 lanes ends up with eight channels of the first, the odd
+    // row with eight channels of the second) and store 16 bytes each.
+    // (the lane number is taken afresh, so that no address of the epilogue is formed before the main loop and held
+    // across it)
+    int le;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(le));
+    const int qe = le & 15, ge = le >> 4;
+    const float lo = p.relu ? 0.f : -__builtin_inff();
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    auto pack = [&](const f32x4v &t, unsigned(&x)[2]) __attribute__((always_inline)) {   // ReLU, round
+        const f32x2_t v0 = {fmaxf(t[0], lo), fmaxf(t[1], lo)}, v1 = {fmaxf(t[2], lo), fmaxf(t[3], lo)};
+        x[0] = __builtin_bit_cast(unsigned, __builtin_convertvector(v0, bf16x2_t));
+        x[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(v1, bf16x2_t));
+    };
+    auto swap16 = [](unsigned(&x0)[2], unsigned(&x1)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const auto sw = __builtin_amdgcn_permlane16_swap(x0[k], x1[k], false, false);
+            x0[k] = sw[0];
+            x1[k] = sw[1];
+        }
+        return u32x4{x0[0], x0[1], x1[0], x1[1]};
+    };
+    if (EPI == kEpiPlain || EPI == kEpiMasked) {
+        // (mask > 0) factor: the 16 bytes of the mask behind each store, requested one pixel-block pair ahead
         T *y = reinterpret_cast<T *>(p.y);
+        const T *mask = reinterpret_cast<const T *>(p.mask);
+        const int col0 = n0 + wn * 64 + (ge >> 1) * 8;
+        u32x4 mk[2][NJ];
+        int mrow[2];
+        auto request = [&](int ip) __attribute__((always_inline)) {
+            const int m = tile_pixel(p.g, org, wrow0 + (2 * ip + (ge & 1)) * 16 + qe);
+            mrow[ip & 1] = m;
+            if (EPI == kEpiMasked) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    if (m >= 0 && col0 + j * 16 < p.Cout)
+                        mk[ip & 1][j] = *reinterpret_cast<const u32x4 *>(mask + (size_t)m * p.Cout + col0 + j * 16);
+            }
+        };
+        request(0);
 #pragma unroll
         for (int ip = 0; ip < NI / 2; ++ip) {
-            const int m = tile_pixel(p.g, org, wrow0 + (2 * ip + (g & 1)) * 16 + q);
+            if (ip + 1 < NI / 2) request(ip + 1);
+            const int m = mrow[ip & 1];
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
-                typedef float f32x2_t __attribute__((ext_vector_type(2)));
-                typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-                unsigned x[2][2];
+                unsigned x0[2], x1[2];
+                pack(acc[2 * ip][j], x0);
+                pack(acc[2 * ip + 1][j], x1);
+                u32x4 v = swap16(x0, x1);
+                if (EPI == kEpiMasked) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const unsigned w = mk[ip & 1][j][k];
+                        const unsigned keep = (__uint_as_float(w << 16) > 0.f ? 0xffffu : 0u) |
+                                              (__uint_as_float(w & 0xffff0000u) > 0.f ? 0xffff0000u : 0u);
+                        v[k] &= keep;
+                    }
+                }
+                if (m >= 0 && col0 + j * 16 < p.Cout) *reinterpret_cast<u32x4 *>(y + (size_t)m * p.Cout + col0 + j * 16) = v;
+            }
+        }
+        return;
+    }
+    // 2x2 maximum of the rounded values (patch tiles: a 16-pixel block is one patch row, so a window is two blocks
+    // of the wave and two neighbouring lanes).  Even lanes serve the windows of rows 4 b, 4 b + 1, odd lanes those
+    // of rows 4 b + 2, 4 b + 3; the four values in window order, a later one only when strictly greater.
+    {
+        T *pool = reinterpret_cast<T *>(p.pool);
+        const bool odd = qe & 1;
+        auto xchg = [](float v) __attribute__((always_inline)) {   // the neighbouring lane's value (DPP quad permute 1, 0, 3, 2)
+            return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
+        };
+#pragma unroll
+        for (int b = 0; b < NI / 4; ++b) {
+            const int ph = (org.h0 + wrow0 / kTileW + 4 * b) / 2 + (odd ? 1 : 0), pw = (org.w0 >> 1) + (qe >> 1);
+            const bool in = 2 * ph < p.g.H && 2 * pw < p.g.W;
+            const size_t at = (((size_t)org.n * (p.g.H >> 1) + ph) * (p.g.W >> 1) + pw) * p.Cout;
+#pragma unroll
+            for (int j = 0; j < NJ; j += 2) {
+                unsigned best[2][2], which[2];
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const f32x4v &t = acc[2 * ip + h][j];
-                    const f32x2_t v0 = {fmaxf(t[0], lo), fmaxf(t[1], lo)};
-                    const f32x2_t v1 = {fmaxf(t[2], lo), fmaxf(t[3], lo)};
-                    x[h][0] = __builtin_bit_cast(unsigned, __builtin_convertvector(v0, bf16x2_t));
-                    x[h][1] = __builtin_bit_cast(unsigned, __builtin_convertvector(v1, bf16x2_t));
-                }
+                    unsigned x[4][2];
 #pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const auto sw = __builtin_amdgcn_permlane16_swap(x[0][k], x[1][k], false, false);
-                    x[0][k] = sw[0];
-                    x[1][k] = sw[1];
+                    for (int r = 0; r < 4; ++r) pack(acc[4 * b + r][j + h], x[r]);
+                    which[h] = 0;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        unsigned out = 0;
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            float v[4];   // rows 4 b .. 4 b + 3 of this lane's pixel column
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) v[r] = __uint_as_float(e ? x[r][k] & 0xffff0000u : x[r][k] << 16);
+                            // what the neighbour serves of mine goes to it, what I serve of its comes here
+                            const float own0 = odd ? v[2] : v[0], own1 = odd ? v[3] : v[1];
+                            const float got0 = xchg(odd ? v[0] : v[2]), got1 = xchg(odd ? v[1] : v[3]);
+                            const float w0 = odd ? got0 : own0, w1 = odd ? own0 : got0, w2 = odd ? got1 : own1, w3 = odd ? own1 : got1;
+                            float m = w0;
+                            unsigned a = 0;
+                            if (w1 > m) { m = w1; a = 1; }
+                            if (w2 > m) { m = w2; a = 2; }
+                            if (w3 > m) { m = w3; a = 3; }
+                            out |= e ? __float_as_uint(m) : __float_as_uint(m) >> 16;
+                            which[h] |= a << (8 * (2 * k + e));
+                        }
+                        best[h][k] = out;
+                    }
                 }
-                const u32x4 v = {x[0][0], x[0][1], x[1][0], x[1][1]};
-                const int col = n0 + wn * 64 + j * 16 + (g >> 1) * 8;
-                if (m >= 0 && col < p.Cout) *reinterpret_cast<u32x4 *>(y + (size_t)m * p.Cout + col) = v;
+                const u32x4 v = swap16(best[0], best[1]);
+                const auto sw = __builtin_amdgcn_permlane16_swap(which[0], which[1], false, false);
+                const int col = n0 + wn * 64 + (j + (ge & 1)) * 16 + (ge >> 1) * 8;
+                if (in && col < p.Cout) {
+                    *reinterpret_cast<u32x4 *>(pool + at + col) = v;
+                    if (p.argmax) {
+                        typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+                        *reinterpret_cast<u32x2_t *>(p.argmax + at + col) = u32x2_t{sw[0], sw[1]};
+                    }
+                }
             }
         }
     }
@@ -1127,10 +1241,16 @@ static int launch_conv_wreg(const ConvArgs &a0, const TileGeom &g, hipStream_t s
     a.tiles_n = (a.Cout + BN - 1) / BN;
     a.rowsA = SA;
     const size_t lds = (size_t)2 * NQ * NT * 16;   // (more than the epilogue's staging blocks)
-    auto kern = conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB>;
-    if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return VGG_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.g.ntiles * a.tiles_n)), dim3(NT), lds, stream, a);
-    return launch_status();
+    auto launch = [&](auto kern) {
+        if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return (int)VGG_ERR_LAUNCH;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(a.g.ntiles * a.tiles_n)), dim3(NT), lds, stream, a);
+        return launch_status();
+    };
+    if ((a.pool && a.y) || (a.Cout & 7)) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiGeneral>);
+    if constexpr (TM % 2 == 0)   // (320-pixel tiles are never patches)
+        if (a.pool) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPooled>);
+    if (a.mask) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiMasked>);
+    return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPlain>);
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int SA>
@@ -1276,7 +1396,9 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // 320 pixels cost 1.25, 128 pixels 0.56.  Measured (us) for 512 channels, 256 / 320 / 128 pixels: 28x28 batch
     // 10 (124, 100, 248 tiles) 44 / 54 / 35, batch 16 (196, 160, 392) 46 / 55 / 50, batch 32 (392, 316, 784) 88 /
     // 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.
-    if (Cout > 64 && (dma || dma_big) && (!narrow || chunks >= 3 || wide_tiles >= 256)) {
+    // (that kernel's halo offsets inside a tile are 32 bits: at most 18 image rows of a patch, or 320 + 2 rows)
+    const bool reach = (size_t)(20 * (size_t)W + 512) * CinP * sizeof(bf16_t) < ((size_t)1 << 32);
+    if (Cout > 64 && (dma || dma_big) && reach && (!narrow || chunks >= 3 || wide_tiles >= 256)) {
         c.kernel = dma ? kWreg : kWregBig;
         c.bn = 128;
         if (!narrow) return c;
