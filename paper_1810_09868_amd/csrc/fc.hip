@@ -26,19 +26,6 @@ template <> struct FcMma<bf16_t> {
     }
 };
 
-// Four consecutive floats row[c..c+3] with zeros at and beyond column C.  The
-// vector path needs the row to be 16-byte aligned (C a multiple of 4).
-__device__ __forceinline__ uint4 load_row4(const float *row, int c, int C, bool vec)
-{
-    if (vec && c + 3 < C) return *reinterpret_cast<const uint4 *>(row + c);
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (c < C) v.x = __float_as_uint(row[c]);
-    if (c + 1 < C) v.y = __float_as_uint(row[c + 1]);
-    if (c + 2 < C) v.z = __float_as_uint(row[c + 2]);
-    if (c + 3 < C) v.w = __float_as_uint(row[c + 3]);
-    return v;
-}
-
 // ------------------------------------------------------------------ forward
 // Workgroup: 128 batch rows x 128 outputs x a range of 64-byte K units.
 // Wave w owns outputs [32w, 32w+32) and all four 32-row blocks.  The
@@ -237,85 +224,107 @@ int fc_forward(int dtype, int N, int In, int Out, const void *a_, const void *w,
 }
 
 // ------------------------------------------------- backward: dW = dz^T * a
-// fp32.  Workgroup: 128 (o) x 128 (i) block of dW; the batch is the
-// contraction index, staged through LDS 32 rows at a time.  Wave (wo, wi)
-// owns a 64x64 sub-block = 2x2 MFMA tiles.
-__global__ __launch_bounds__(256) void fc_dw_kernel(const float *__restrict__ a, const float *__restrict__ dz,
-                                                    float *__restrict__ dw, int N, int In, int Out)
+// fp32; bound by its MFMAs and, under them, by writing dW.  Workgroup: 128 (o) x 128 (i) block of dW; the batch is
+// the contraction index, staged through LDS 32 rows at a time, and no MFMA step is taken past the last row.  Wave w
+// owns outputs [32 w, 32 w + 32) and all 128 inputs: lane r reads four consecutive inputs with one 16-byte LDS read
+// and feeds them to four MFMA column tiles, so accumulator tile j of lane r holds input 4 r + j and the stores are
+// 16 bytes, 512 contiguous per row; 64 accumulator registers, so that four workgroups share a CU and some store
+// while others multiply.  (Operands straight from L2 without LDS: the loads between the MFMAs hold up their issue,
+// MFMA busy 0.47.)  25088 -> 4096, batch 100: 274 -> 224 us (128 rows were multiplied for 100, 4 bytes stored per
+// lane); MFMA busy 0.67.
+// VEC: In is a multiple of 4; otherwise the four inputs are written one by one.
+
+// Four floats row[c..c+3], zeros at and beyond column C.  vec: the row is 16-byte aligned (C a multiple of 4).
+__device__ __forceinline__ f32x4 load_row4(const float *row, int c, int C, bool vec)
+{
+    if (vec && c + 3 < C) return *reinterpret_cast<const f32x4 *>(row + c);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (c < C) v[0] = row[c];
+    if (c + 1 < C) v[1] = row[c + 1];
+    if (c + 2 < C) v[2] = row[c + 2];
+    if (c + 3 < C) v[3] = row[c + 3];
+    return v;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(256, 4) void fc_dw_kernel(const float *__restrict__ a, const float *__restrict__ dz,
+                                                       float *__restrict__ dw, int N, int In, int Out)
 {
     constexpr int ROW = 128 * 4 + 16;
-    __shared__ __align__(16) char Ds[32 * ROW];
-    __shared__ __align__(16) char As[32 * ROW];
+    __shared__ __align__(16) char lds[66 * ROW];
+    char *const Ds = lds, *const As = lds + 32 * ROW;   // 32 rows each (and two that are read but not used)
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int r = lane & 31, kp = lane >> 5;
-    const int wo = wv & 1, wi = wv >> 1;
     const int tiles_i = (In + 127) / 128;
     const int i0 = (blockIdx.x % tiles_i) * 128, o0 = (blockIdx.x / tiles_i) * 128;
 
-    f32x16 acc[2][2];
+    f32x16 acc[4];
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
+        for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
 
-    // The 32 batch rows of a step are requested one step ahead; barriers without the fence of
+    // The 32 batch rows of a pass are requested one pass ahead; barriers without the fence of
     // __syncthreads(), which would wait for those loads.
     auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    uint4 vd[4], va[4];
+    const int seg = tid & 31, row_t = tid >> 5;
+    f32x4 vd[4], va[4];
     auto request = [&](int n0) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int idx = tid + q * 256;
-            const int seg = idx & 31, row = idx >> 5;
-            vd[q] = make_uint4(0, 0, 0, 0);
-            va[q] = make_uint4(0, 0, 0, 0);
-            if (n0 + row < N) {
-                vd[q] = load_row4(dz + (size_t)(n0 + row) * Out, o0 + seg * 4, Out, (Out & 3) == 0);
-                va[q] = load_row4(a + (size_t)(n0 + row) * In, i0 + seg * 4, In, (In & 3) == 0);
+            const int row = n0 + row_t + 8 * q;
+            vd[q] = va[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (row < N) {
+                vd[q] = load_row4(dz + (size_t)row * Out, o0 + seg * 4, Out, (Out & 3) == 0);
+                va[q] = load_row4(a + (size_t)row * In, i0 + seg * 4, In, (In & 3) == 0);
             }
         }
     };
     request(0);
     for (int n0 = 0; n0 < N; n0 += 32) {
-        barrier();  // the previous step's fragment reads are done
+        barrier();  // the previous pass's fragment reads are done
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int idx = tid + q * 256;
-            const int seg = idx & 31, row = idx >> 5;
-            *reinterpret_cast<uint4 *>(Ds + row * ROW + seg * 16) = vd[q];
-            *reinterpret_cast<uint4 *>(As + row * ROW + seg * 16) = va[q];
+            const int row = row_t + 8 * q;
+            *reinterpret_cast<f32x4 *>(Ds + row * ROW + seg * 16) = vd[q];
+            *reinterpret_cast<f32x4 *>(As + row * ROW + seg * 16) = va[q];
         }
         barrier();  // the staged rows are visible
         if (n0 + 32 < N) request(n0 + 32);
-#pragma unroll 4
-        for (int s = 0; s < 16; ++s) {
-            const int n = 2 * s + kp;
-            float af[2], bf[2];
+        // Four steps at a time (rows past the batch are zeros), each one's operands read while the step before it is
+        // multiplied; the last read of a pass is one step past what it needs (LDS past Ds is As; past As: padding).
+        const char *ds = Ds + kp * ROW + (wv * 32 + r) * 4, *as = As + kp * ROW + r * 16;
+        const int steps = min((N - n0 + 1) / 2, 16);
+        float d = *reinterpret_cast<const float *>(ds);
+        f32x4 x = *reinterpret_cast<const f32x4 *>(as);
+        for (int s = 0; s < steps; s += 4) {
 #pragma unroll
-            for (int x = 0; x < 2; ++x) af[x] = *reinterpret_cast<const float *>(Ds + n * ROW + (wo * 64 + x * 32 + r) * 4);
+            for (int k = 0; k < 4; ++k) {
+                const float dc = d;
+                const f32x4 xc = x;
+                d = *reinterpret_cast<const float *>(ds + 2 * (s + k + 1) * ROW);
+                x = *reinterpret_cast<const f32x4 *>(as + 2 * (s + k + 1) * ROW);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int y = 0; y < 2; ++y) bf[y] = *reinterpret_cast<const float *>(As + n * ROW + (wi * 64 + y * 32 + r) * 4);
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[x], bf[y], acc[x][y], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            const int i = i0 + wi * 64 + y * 32 + r;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int o = o0 + wo * 64 + x * 32 + (e >> 2) * 8 + kp * 4 + (e & 3);
-                // (streamed out: 411 MB for the first dense layer, re-read only by the update, long after it has left every cache)
-                if (o < Out && i < In) __builtin_nontemporal_store(acc[x][y][e], &dw[(size_t)o * In + i]);
+                for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(dc, xc[j], acc[j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+    }
+    const int ic = i0 + 4 * r;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int o = o0 + wv * 32 + (e >> 2) * 8 + kp * 4 + (e & 3);
+        if (o >= Out) continue;
+        float *dst = dw + (size_t)o * In + ic;
+        // (streamed out: 411 MB for the first dense layer, re-read only by the update, long after it has left every cache)
+        if (VEC) {
+            if (ic < In) __builtin_nontemporal_store(f32x4{acc[0][e], acc[1][e], acc[2][e], acc[3][e]}, reinterpret_cast<f32x4 *>(dst));
+        } else
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (ic + j < In) __builtin_nontemporal_store(acc[j][e], dst + j);
+    }
 }
 
 // db[o] = sum_n dz[n][o].  A workgroup owns 64 outputs; each of its four waves sums every fourth row and
@@ -337,144 +346,166 @@ __global__ __launch_bounds__(256) void fc_db_kernel(const float *__restrict__ dz
 }
 
 // --------------------------------------------------- backward: da = dz * W
-// fp32.  Workgroup: 128 batch rows x 256 inputs x a range of outputs (the
-// contraction index).  Wave (wr, wc) owns rows [64wr, 64wr+64) and the 128
-// inputs [128wc, 128wc+128).  A lane loads four consecutive inputs of one
-// weight row with one 16-byte load and feeds them to four different MFMA
-// column tiles, so accumulator tile j of lane r holds input 4r+j of the
-// wave's 128: the stores are 16-byte vectors as well.
+// fp32; bound by its MFMAs at batch 100, by streaming W at small batches.  Workgroup: 16 NB batch rows x 256 inputs x
+// a range of outputs (the contraction index); wave w owns 64 of the inputs.  v_mfma_f32_16x16x4_f32: rows come in
+// sixteens, so 100 rows cost 112, not 128, and ten cost 16.  A weight is used by one lane only and goes straight to
+// its register, sixteen outputs per unit, a unit ahead; the dz rows, which all four waves need, go through LDS 64
+// outputs (four units) at a time.  (Straight from the caches they held up the MFMAs' issue: 16 segments of 64 bytes
+// per load.)  Lane 16 g + c loads inputs 4 c .. 4 c + 3 of weight row o = 4 g + e with one 16-byte load and feeds
+// them to four MFMA column tiles, and outputs 4 g .. 4 g + 3 of batch row c: step e contracts outputs 4 g + e.
+// Accumulator tile j of lane c holds input 4 c + j: the stores are 16 bytes.  25088 -> 4096, batch 100: 324 -> 220 us, MFMA busy 0.74;
+// batch 10: 69 us, 5.9 TB/s.
 struct FcDaArgs {
     const float *dz;  // [N][Out]
     const float *w;   // [Out][In]
     float *part;      // [splits][N][In]
     int N, In, Out;
     int tiles_i, tiles_m, o_per_split;
+    int nb;           // 16-row blocks per row tile
 };
 
 // VEC: In is a multiple of 4, so a lane's four inputs are one aligned 16-byte load and store; otherwise
-// they are read and written one by one, with zeros beyond the row's end.
-template <bool VEC>
-__global__ __launch_bounds__(256) void fc_da_kernel(FcDaArgs p)
+// they are read and written one by one.
+template <int NB, bool VEC>
+__global__ __launch_bounds__(256, 2) void fc_da_kernel(FcDaArgs p)
 {
-    __shared__ __align__(16) char Ds[128 * kFcRow];  // dz rows, 16 outputs per chunk
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int r = lane & 31, khalf = lane >> 5;
-    const int wr = wv & 1, wc = wv >> 1;
+    constexpr int AHEAD = 1;   // units of weights in flight
+    constexpr int ROW = 64 * 4 + 16, Q = NB * 4;   // LDS row of 64 outputs; values of a pass per thread
+    __shared__ __align__(16) char Ds[2][NB * 16 * ROW];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
     int b = blockIdx.x;
     const int ti = b % p.tiles_i; b /= p.tiles_i;
     const int tm = b % p.tiles_m; b /= p.tiles_m;
     const int split = b;
-    const int row0 = tm * 128;
-    const int icol = ti * 256 + wc * 128 + 4 * r;  // first of this lane's 4 inputs
-    const bool iok = icol < p.In;
+    const int row0 = tm * NB * 16;
+    const int ic = ti * 256 + wv * 64 + 4 * c;  // first of this lane's 4 inputs (clamped where there are none)
     const int o_begin = split * p.o_per_split, o_end = min(o_begin + p.o_per_split, p.Out);
+    const float *wp = p.w + (VEC ? min(ic, p.In - 4) : 0);
 
-    f32x16 acc[2][4];
+    typedef float f32x4m __attribute__((ext_vector_type(4)));
+    f32x4m acc[NB][4];
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < NB; ++x)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[x][j][e] = 0.f;
+        for (int j = 0; j < 4; ++j) acc[x][j] = f32x4m{0.f, 0.f, 0.f, 0.f};
 
-    // Operands of a chunk of 16 outputs are requested one chunk ahead: the weight stream from HBM never
-    // pauses for the staging and the MFMAs.  The barriers are issued without the fence that
-    // __syncthreads() carries (it would wait for the loads in flight); they only order LDS accesses.
     auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    f32x4 w_next[2][4];
-    uint4 dz_next[2];
-    auto request = [&](int oc) __attribute__((always_inline)) {
+    // dz, outputs o .. o + 63, to registers and on to LDS, one value per lane and load: a wave reads 256 contiguous
+    // bytes of a row whatever its alignment (past the range: zeros; rows past the batch: the last row, never stored)
+    float dn[Q];
+    auto load_dz = [&](int o) __attribute__((always_inline)) {
+        const int col = min(o + lane, p.Out - 1);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int idx = tid + q * 256;
-            const int seg = idx & 3, row = idx >> 2;
-            dz_next[q] = make_uint4(0, 0, 0, 0);
-            if (row0 + row < p.N)
-                dz_next[q] = load_row4(p.dz + (size_t)(row0 + row) * p.Out, oc + seg * 4, o_end, (p.Out & 3) == 0);
-        }
-#pragma unroll
-        for (int g = 0; g < 2; ++g)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                // this lane's four contraction indices of half g: oc + 8g + 4*khalf + e
-                const int o = oc + g * 8 + khalf * 4 + e;
-                w_next[g][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                if (iok && o < o_end) {
-                    const float *wp = p.w + (size_t)o * p.In + icol;
-                    if (VEC) w_next[g][e] = *reinterpret_cast<const f32x4 *>(wp);
-                    else
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) w_next[g][e][j] = icol + j < p.In ? wp[j] : 0.f;
-                }
-            }
+        for (int k = 0; k < Q; ++k) dn[k] = p.dz[(size_t)min(row0 + wv + 4 * k, p.N - 1) * p.Out + col];
     };
-    if (o_begin < o_end) request(o_begin);
-    for (int oc = o_begin; oc < o_end; oc += 16) {
-        barrier();  // the previous chunk's fragment reads are done
+    auto store_dz = [&](int o, int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int idx = tid + q * 256;
-            *reinterpret_cast<uint4 *>(Ds + (idx >> 2) * kFcRow + (idx & 3) * 16) = dz_next[q];
+        for (int k = 0; k < Q; ++k)
+            *reinterpret_cast<float *>(Ds[buf] + (wv + 4 * k) * ROW + lane * 4) = o + lane < o_end ? dn[k] : 0.f;
+    };
+    // weights of outputs o .. o + 15 (past the range: its last row again; dz is zero there, see below for the weight)
+    struct Unit { f32x4 w[4]; };
+    auto load_w = [&](int o, Unit &v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float *src = wp + (size_t)min(o + 4 * g + e, o_end - 1) * p.In;
+            if (VEC) v.w[e] = *reinterpret_cast<const f32x4 *>(src);
+            else
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v.w[e][j] = src[min(ic + j, p.In - 1)];
         }
-        f32x4 wv4[2][4];
+        __builtin_amdgcn_sched_barrier(0);   // (the scheduler would move the requests behind the MFMAs that follow)
+    };
+    auto multiply = [&](const Unit &v, int buf, int h) __attribute__((always_inline)) {
+        // (each block's dz fragment is read while the block before it is multiplied)
+        const char *d0 = Ds[buf] + c * ROW + h * 64 + g * 16;
+        f32x4 d[2];
+        d[0] = *reinterpret_cast<const f32x4 *>(d0);
 #pragma unroll
-        for (int g = 0; g < 2; ++g)
+        for (int x = 0; x < NB; ++x) {
+            if (x + 1 < NB) d[(x + 1) & 1] = *reinterpret_cast<const f32x4 *>(d0 + (x + 1) * 16 * ROW);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) wv4[g][e] = w_next[g][e];
-        barrier();  // the staged rows are visible
-        if (oc + 16 < o_end) request(oc + 16);
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const f32x4 af = *reinterpret_cast<const f32x4 *>(Ds + (wr * 64 + x * 32 + r) * kFcRow + g * 32 + khalf * 16);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        acc[x][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[e], wv4[g][e][j], acc[x][j], 0, 0, 0);
-            }
+                for (int j = 0; j < 4; ++j)
+                    acc[x][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[x & 1][e], v.w[e][j], acc[x][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
-    }
-    if (iok) {
+    };
+    if (o_begin < o_end) {
+        Unit v[4];   // (two or three of the four are in use at a time)
+        load_dz(o_begin);
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int h = 0; h < AHEAD; ++h) load_w(o_begin + 16 * h, v[h]);
+        store_dz(o_begin, 0);
+        barrier();
+        int buf = 0;
+        for (int o = o_begin; o < o_end; o += 64, buf ^= 1) {
+            const bool more = o + 64 < o_end;
+            if (more) load_dz(o + 64);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = row0 + wr * 64 + x * 32 + (e >> 2) * 8 + khalf * 4 + (e & 3);
-                if (row < p.N) {
-                    const f32x4 v = {acc[x][0][e], acc[x][1][e], acc[x][2][e], acc[x][3][e]};
-                    float *dst = p.part + ((size_t)split * p.N + row) * p.In + icol;
-                    if (VEC) *reinterpret_cast<f32x4 *>(dst) = v;
-                    else
+            for (int h = 0; h < 4; ++h) {
+                load_w(o + 16 * (h + AHEAD), v[(h + AHEAD) & 3]);
+                if (o + 64 > o_end) {   // the range's last pass: weights past its end are zero, whatever the last row holds
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (icol + j < p.In) dst[j] = v[j];
+                    for (int e = 0; e < 4; ++e)
+                        if (o + 16 * h + 4 * g + e >= o_end) v[h].w[e] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
+                multiply(v[h], buf, h);
             }
+            if (more) store_dz(o + 64, buf ^ 1);
+            barrier();   // every wave is done with this pass's rows, the next pass's are visible
+        }
     }
+    // accumulator layout: register e of lane 16 g + c = row 4 g + e, column c
+#pragma unroll
+    for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = row0 + x * 16 + 4 * g + e;
+            if (row >= p.N) continue;
+            float *dst = p.part + ((size_t)split * p.N + row) * p.In + ic;
+            if (VEC) {
+                if (ic < p.In) *reinterpret_cast<f32x4 *>(dst) = f32x4{acc[x][0][e], acc[x][1][e], acc[x][2][e], acc[x][3][e]};
+            } else
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (ic + j < p.In) dst[j] = acc[x][j][e];
+        }
 }
 
-// da = (sum over splits) [* (a > 0)]
-template <typename T>
-__global__ void fc_da_finish_kernel(const float *__restrict__ part, const T *__restrict__ a, T *__restrict__ da, size_t n,
+// da = (sum over splits) [* (a > 0)], V values per thread (V divides n)
+template <int V>
+__global__ void fc_da_finish_kernel(const float *__restrict__ part, const float *__restrict__ a, float *__restrict__ da, size_t n,
                                     int splits, int relu_mask)
 {
+    typedef float vec __attribute__((ext_vector_type(V)));
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float s = 0.f;
-    for (int k = 0; k < splits; ++k) s += part[(size_t)k * n + i];
-    if (relu_mask && !(Elem<T>::load(a + i) > 0.f)) s = 0.f;
-    Elem<T>::store(da + i, s);
+    if (i >= n / V) return;
+    vec s = reinterpret_cast<const vec *>(part)[i];
+    for (int k = 1; k < splits; ++k) s += reinterpret_cast<const vec *>(part + (size_t)k * n)[i];
+    if (relu_mask) {
+        const vec m = reinterpret_cast<const vec *>(a)[i];
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (!(m[v] > 0.f)) s[v] = 0.f;
+    }
+    reinterpret_cast<vec *>(da)[i] = s;
 }
 
-static void fc_da_plan(int N, int In, int Out, FcDaArgs &a)
+// fill: workgroups to aim at.  The workspace query takes the bound 512 rounded up to whole splits of the tiles, the
+// launch 512 rounded down: 512 is what two workgroups per CU hold, and 588 instead of 490 (25088 -> 4096) would
+// leave a second round of 76.
+static void fc_da_plan(int N, int In, int Out, FcDaArgs &a, bool launch)
 {
     a.N = N; a.In = In; a.Out = Out;
     a.tiles_i = (In + 255) / 256;
     a.tiles_m = (N + 127) / 128;
+    a.nb = ((N + 15) / 16 + a.tiles_m - 1) / a.tiles_m;
     const int tiles = a.tiles_i * a.tiles_m;
-    int splits = (512 + tiles - 1) / tiles;
+    int splits = launch ? 512 / tiles : (512 + tiles - 1) / tiles;
     const int max_splits = (Out + 63) / 64;
     if (splits > max_splits) splits = max_splits;
     if (splits < 1) splits = 1;
@@ -485,26 +516,40 @@ static int fc_da_splits(const FcDaArgs &a) { return (a.Out + a.o_per_split - 1) 
 size_t fc_bwd_workspace(int N, int In, int Out)
 {
     FcDaArgs a;
-    fc_da_plan(N, In, Out, a);
+    fc_da_plan(N, In, Out, a, false);
     return round_up((size_t)fc_da_splits(a) * N * In * 4, 256);
+}
+
+template <int NB>
+static void launch_fc_da(const FcDaArgs &p, int splits, hipStream_t s)
+{
+    if (p.nb != NB) {
+        if constexpr (NB > 1) launch_fc_da<NB - 1>(p, splits, s);
+        return;
+    }
+    const dim3 grid((unsigned)(p.tiles_i * p.tiles_m * splits));
+    if (p.In % 4 == 0) hipLaunchKernelGGL((fc_da_kernel<NB, true>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((fc_da_kernel<NB, false>), grid, dim3(256), 0, s, p);
 }
 
 int fc_backward(int N, int In, int Out, const float *a, const float *w, const float *dz, float *dw, float *db, float *da,
                 int relu_mask, void *ws, hipStream_t s)
 {
-    const int tiles_i = (In + 127) / 128, tiles_o = (Out + 127) / 128;
-    hipLaunchKernelGGL(fc_dw_kernel, dim3((unsigned)(tiles_i * tiles_o)), dim3(256), 0, s, a, dz, dw, N, In, Out);
+    const dim3 grid((unsigned)(((In + 127) / 128) * ((Out + 127) / 128)));
+    if (In % 4 == 0) hipLaunchKernelGGL(fc_dw_kernel<true>, grid, dim3(256), 0, s, a, dz, dw, N, In, Out);
+    else hipLaunchKernelGGL(fc_dw_kernel<false>, grid, dim3(256), 0, s, a, dz, dw, N, In, Out);
     if (db) hipLaunchKernelGGL(fc_db_kernel, dim3((Out + 63) / 64), dim3(256), 0, s, dz, db, N, Out);
     if (da) {
         FcDaArgs p;
-        fc_da_plan(N, In, Out, p);
+        fc_da_plan(N, In, Out, p, true);
         const int splits = fc_da_splits(p);
         p.dz = dz; p.w = w; p.part = static_cast<float *>(ws);
-        if (In % 4 == 0) hipLaunchKernelGGL(fc_da_kernel<true>, dim3((unsigned)(p.tiles_i * p.tiles_m * splits)), dim3(256), 0, s, p);
-        else hipLaunchKernelGGL(fc_da_kernel<false>, dim3((unsigned)(p.tiles_i * p.tiles_m * splits)), dim3(256), 0, s, p);
+        launch_fc_da<8>(p, splits, s);
         const size_t n = (size_t)N * In;
-        hipLaunchKernelGGL(fc_da_finish_kernel<float>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.part, a, da, n,
-                           splits, relu_mask);
+        if (In % 4 == 0)
+            hipLaunchKernelGGL(fc_da_finish_kernel<4>, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, p.part, a, da, n, splits, relu_mask);
+        else
+            hipLaunchKernelGGL(fc_da_finish_kernel<1>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.part, a, da, n, splits, relu_mask);
     }
     return launch_status();
 }

@@ -634,6 +634,27 @@ def test_fc_backward(dtype, shape):
         B.vgg_fc_bwd(dtype, N, In, Out, ad, wd, dev(dz), dw, None, da, 1, None)
 
 
+@pytest.mark.parametrize("N,In,Out", [(16, 260, 129), (17, 256, 64), (49, 1028, 3), (80, 132, 191), (97, 516, 257), (129, 252, 65),
+                                      (31, 129, 1), (112, 127, 66)])
+def test_fc_backward_fp32_tile_edges(N, In, Out):
+    """The fp32 backward kernels at the edges of their tiles (16-row blocks, 128- and 256-column tiles, 64-output
+    passes, odd rows, rows that are not 16-byte aligned): sums of at most 257 (129) products of N(0,1) values against
+    the oracle; the rounding of such a sum is below 1e-6 of the largest, the tolerance 1e-5."""
+    rng = np.random.default_rng(N + In + Out)
+    a, dz = rng.standard_normal((N, In)).astype(np.float32), rng.standard_normal((N, Out)).astype(np.float32)
+    w = rng.standard_normal((Out, In)).astype(np.float32)
+    dw_ref, db_ref, da_ref = R.fc_bwd(a, w, dz)
+    dw, da = torch.full((Out * In + 256,), -7.0, device="cuda"), torch.full((N * In + 256,), -7.0, device="cuda")
+    db = torch.empty((Out,), device="cuda")
+    ws = ws_bytes(B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out))
+    B.vgg_fc_bwd(B.F32, N, In, Out, dev(a), dev(w), dev(dz), dw, db, da, 1, ws)
+    torch.cuda.synchronize()
+    assert max_rel_err(dw[:Out * In].view(Out, In).cpu().numpy(), dw_ref) <= 1e-5
+    assert max_rel_err(da[:N * In].view(N, In).cpu().numpy(), da_ref * (a > 0)) <= 1e-5
+    assert max_rel_err(db.cpu().numpy(), db_ref) <= 1e-5
+    assert (dw[Out * In:] == -7.0).all() and (da[N * In:] == -7.0).all()
+
+
 @pytest.mark.parametrize("shape", [(100, 1000), (2, 10), (5, 64), (3, 129), (1, 10), (1, 1), (4, 5000)])
 def test_softmax_xent_sgd(shape):
     N, K = shape
