@@ -287,8 +287,9 @@ int vgg_fc_bwd(int dtype, int N, int In, int Out, const void *a, const void *w, 
 int vgg_softmax(int N, int K, const float *z, float *p, void *stream);
 /* loss[0] = -(1/N) sum_n log p[n,labels[n]];  dz = (p - onehot(labels))/N.
  * loss and dz may each be NULL.  Labels outside [0,K) contribute nothing
- * (labels live on the device and cannot be validated on the host).  ws needs
- * N floats when loss is requested (per-row terms, summed in a fixed order). */
+ * (labels live on the device and cannot be validated on the host).  ws must
+ * hold N floats when loss is requested; the per-row terms are summed in a
+ * fixed order and nothing is kept there. */
 int vgg_softmax_xent_bwd(int N, int K, const float *p, const int32_t *labels, float *loss,
                          float *dz, void *ws, size_t ws_bytes, void *stream);
 /* theta[i] -= lr * grad[i], i < n. */

@@ -50,8 +50,7 @@ int mfma_probe(int dtype, int random, int iters, float *sink, double *flops, hip
 int maxpool2x2(int dtype, int N, int H, int W, int C, const void *x, void *y, uint8_t *arg, hipStream_t s);
 int maxpool2x2_bwd(int dtype, int N, int H, int W, int C, const void *dy, const uint8_t *arg, void *dx, hipStream_t s);
 int softmax_rows(int N, int K, const float *z, float *p, hipStream_t s);
-int softmax_xent_bwd(int N, int K, const float *p, const int32_t *labels, float *loss, float *dz, float *rowloss,
-                     hipStream_t s);
+int softmax_xent_bwd(int N, int K, const float *p, const int32_t *labels, float *loss, float *dz, hipStream_t s);
 int sgd_update(size_t n, float *theta, const float *grad, float lr, hipStream_t s);
 int sgd_update_master(size_t n, float *theta, const float *grad, float lr, void *copy, int copy_dtype, hipStream_t s);
 int sgd_update_master_conv(SgdConvJobs &jobs, float lr, hipStream_t s);
@@ -140,7 +139,7 @@ struct WsLayout {
     size_t z1, z2, logits, probs, fcws;
     size_t convpart;                   // partial sums of convolutions whose contraction is split
     // training only
-    size_t dlogits, dz2, dz1, gA, gB, grads, wgws, fcbws, rowloss;
+    size_t dlogits, dz2, dz1, gA, gB, grads, wgws, fcbws;
     size_t wflip[VGG19_NUM_CONV];      // data-gradient operands (flipped, transposed weights) of layers 1..15
     size_t dflat32;                    // bf16 training: fp32 gradient with respect to the flattened pool output
     size_t wgws_bytes;                 // size of the weight gradients' partial-sum buffer at wgws
@@ -207,7 +206,7 @@ WsLayout ws_layout(const vgg_config *c, const PackedLayout &P, bool training)
     }
     L.convpart = b.take(cpart);
     for (int l = 0; l < VGG19_NUM_CONV; ++l) L.wflip[l] = 0;
-    L.dlogits = L.dz2 = L.dz1 = L.gA = L.gB = L.grads = L.wgws = L.fcbws = L.rowloss = L.dflat32 = L.wgws_bytes = 0;
+    L.dlogits = L.dz2 = L.dz1 = L.gA = L.gB = L.grads = L.wgws = L.fcbws = L.dflat32 = L.wgws_bytes = 0;
     if (training) {
         L.dlogits = b.take(N * c->classes * 4);
         L.dz2 = b.take(N * c->fc_hidden * 4);
@@ -232,7 +231,6 @@ WsLayout ws_layout(const vgg_config *c, const PackedLayout &P, bool training)
         L.wgws = b.take(wg);
         L.wgws_bytes = wg;
         L.fcbws = b.take(fb);
-        L.rowloss = b.take(N * 4);
     }
     L.total = b.off;
     return L;
@@ -331,7 +329,7 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
     run_forward(c, P, L, x, pk, lg, pr, true, ws, true, s, rec);
     char *gr = ws + L.grads;  // gradient block, same layout as the (master) parameters
     auto F = [](char *p) { return reinterpret_cast<float *>(p); };
-    VGG_STEP(rec, K_OTHER, softmax_xent_bwd(N, c->classes, pr, labels, loss, F(ws + L.dlogits), F(ws + L.rowloss), s));
+    VGG_STEP(rec, K_OTHER, softmax_xent_bwd(N, c->classes, pr, labels, loss, F(ws + L.dlogits), s));
     // dense layers, last to first; each data gradient is masked by (input > 0)
     const char *fc_in[3] = {ws + L.pooled[15], ws + L.z1, ws + L.z2};
     float *fc_dz[3] = {F(ws + L.dz1), F(ws + L.dz2), F(ws + L.dlogits)};
@@ -797,7 +795,7 @@ int vgg_softmax_xent_bwd(int N, int K, const float *p, const int32_t *labels, fl
     if (!p || !labels) return VGG_ERR_NULL;
     if (N <= 0 || K <= 0) return VGG_ERR_SHAPE;
     if (loss && (!ws || ws_bytes < (size_t)N * 4)) return VGG_ERR_WORKSPACE;
-    return softmax_xent_bwd(N, K, p, labels, loss, dz, static_cast<float *>(ws), (hipStream_t)stream);
+    return softmax_xent_bwd(N, K, p, labels, loss, dz, (hipStream_t)stream);
 }
 
 int vgg_sgd_update(size_t n, float *theta, const float *grad, float lr, void *stream)
