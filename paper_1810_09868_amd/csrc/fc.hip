@@ -158,6 +158,137 @@ __global__ __launch_bounds__(256) void fc_fwd_kernel(FcArgs p)
     }
 }
 
+// Small batches: bound by streaming the weights once.  Workgroup: 16 outputs x the whole contraction, sixteen waves
+// taking turns at 256-byte pieces of it, so that a workgroup reads 4 KB runs of its sixteen weight rows and every
+// weight goes straight to the lane that multiplies it; batch rows come in sixteens (the 128-row tile above multiplies
+// 118 rows of zeros for ten).  The waves' sums meet in LDS: no partial sums in memory and no second launch.
+// 25088 -> 4096: bf16 batch 1 51 -> 40 us (5.2 TB/s), batch 10 54 -> 47; fp32 batch 10 225 -> 88 (4.7 TB/s).
+// The lane layout is that of the 16-row MFMAs: lane 16 g + c holds 16 bytes (piece offset 64 e + 16 g) of weight row
+// c and of batch row c; any fixed pairing of contraction indices between the two is a valid order.
+constexpr int kFcSmallWaves = 16;
+
+// Rows of whole 16-byte segments, and: up to 16 batch rows always (measured ahead or level from 10 to 4096 outputs);
+// up to 32 rows every workgroup reads all of twice as many activations, which pays where the 128-row tile is bound
+// by its zeros (fp32: 25088 -> 4096 229 -> 145 us, 1000 -> 3000 22 -> 12) and not on few outputs with long rows (fp32
+// 25088 -> 300 65 / 119) or for bf16 beyond 4 KB rows (25088 -> 4096 59 / 73, 4096 -> 1000 level).
+static bool fc_small(int dtype, int N, int In, int Out)
+{
+    const size_t rowbytes = (size_t)In * dtype_size(dtype);
+    if (rowbytes % 16 || N > 32) return false;
+    if (N <= 16) return true;
+    return dtype == VGG_F32 ? Out >= 2048 || rowbytes <= 16384 : rowbytes <= 4096;
+}
+
+template <typename T, typename TZ, int NB>
+__global__ __launch_bounds__(kFcSmallWaves * 64) void fc_fwd_small_kernel(const char *__restrict__ a, const char *__restrict__ w,
+                                                                          const float *__restrict__ bias, TZ *__restrict__ z, int N,
+                                                                          int In, int Out, int relu)
+{
+    typedef float f32x4m __attribute__((ext_vector_type(4)));
+    constexpr int ROW = 256 + 16;                         // LDS bytes per batch row of a wave's piece
+    constexpr int kRed = NB * 16 * 17;                    // sums of a wave
+    static_assert(kRed * 4 <= NB * 16 * ROW, "the sums take the place of the activations");
+    extern __shared__ __align__(16) char smem[];          // [wave][NB * 16][ROW], later [wave][kRed]
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    const int o0 = blockIdx.x * 16;
+    const size_t rowbytes = (size_t)In * sizeof(T);
+    // (rows past the ends are clamped: what they yield is not stored)
+    const char *wrow = w + (size_t)min(o0 + c, Out - 1) * rowbytes;
+    char *As = smem + wv * (NB * 16 * ROW);
+    f32x4m acc[NB];
+#pragma unroll
+    for (int x = 0; x < NB; ++x) acc[x] = f32x4m{0.f, 0.f, 0.f, 0.f};
+    // A piece's weights as the MFMA wants them; its activations four whole rows per load (a load in the MFMA's layout
+    // touches sixteen rows), rearranged through the wave's own LDS block, which needs no barrier.
+    struct Piece { uint4 w[4], a[NB * 4]; };
+    const int pieces = (int)((rowbytes + 255) / 256);
+    auto load = [&](int k, Piece &v) __attribute__((always_inline)) {
+        // (past the row's end: its last 16 bytes again, and zeros for both operands below)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const size_t off = (size_t)k * 256 + e * 64 + g * 16;
+            v.w[e] = *reinterpret_cast<const uint4 *>(wrow + (off < rowbytes ? off : rowbytes - 16));
+        }
+        const size_t off = (size_t)k * 256 + c * 16, at = off < rowbytes ? off : rowbytes - 16;
+#pragma unroll
+        for (int i = 0; i < NB * 4; ++i) v.a[i] = *reinterpret_cast<const uint4 *>(a + (size_t)min(4 * i + g, N - 1) * rowbytes + at);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int k, Piece &v) __attribute__((always_inline)) {
+        if ((size_t)(k + 1) * 256 > rowbytes) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((size_t)k * 256 + e * 64 + g * 16 >= rowbytes) v.w[e] = make_uint4(0, 0, 0, 0);
+            if ((size_t)k * 256 + c * 16 >= rowbytes) {
+#pragma unroll
+                for (int i = 0; i < NB * 4; ++i) v.a[i] = make_uint4(0, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NB * 4; ++i) *reinterpret_cast<uint4 *>(As + (4 * i + g) * ROW + c * 16) = v.a[i];
+        uint4 af[NB][4];
+#pragma unroll
+        for (int x = 0; x < NB; ++x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) af[x][e] = *reinterpret_cast<const uint4 *>(As + (x * 16 + c) * ROW + e * 64 + g * 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                if constexpr (sizeof(T) == 2) {
+                    acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v.w[e]), __builtin_bit_cast(bf16x8, af[x][e]), acc[x], 0, 0, 0);
+                } else {
+                    const f32x4 wf = __builtin_bit_cast(f32x4, v.w[e]), xf = __builtin_bit_cast(f32x4, af[x][e]);
+#pragma unroll
+                    for (int k4 = 0; k4 < 4; ++k4) acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[k4], xf[k4], acc[x], 0, 0, 0);
+                }
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // two sets of registers taken in turn, a piece each, the next requested before the current one is multiplied
+    Piece v0, v1;
+    const int last = pieces - 1;
+    if (wv < pieces) load(wv, v0);
+    for (int k = wv; k < pieces; k += 2 * kFcSmallWaves) {   // (past the end: the last piece again, not used)
+        load(min(k + kFcSmallWaves, last), v1);
+        multiply(k, v0);
+        if (k + kFcSmallWaves >= pieces) break;
+        load(min(k + 2 * kFcSmallWaves, last), v0);
+        multiply(k + kFcSmallWaves, v1);
+    }
+    // register e of lane 16 g + c: output o0 + 4 g + e of batch row c (a wave's sums go to its own LDS block)
+    float *red = reinterpret_cast<float *>(smem);
+    constexpr int kWave = NB * 16 * ROW / 4;
+#pragma unroll
+    for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[wv * kWave + (x * 16 + c) * 17 + 4 * g + e] = acc[x][e];
+    __syncthreads();
+    for (int i = tid; i < NB * 256; i += kFcSmallWaves * 64) {
+        const int n = i >> 4, o = i & 15;
+        if (n >= N || o0 + o >= Out) continue;
+        float s = bias ? bias[o0 + o] : 0.f;
+#pragma unroll
+        for (int v = 0; v < kFcSmallWaves; ++v) s += red[v * kWave + n * 17 + o];
+        if (relu) s = fmaxf(s, 0.f);
+        Elem<TZ>::store(z + (size_t)n * Out + o0 + o, s);
+    }
+}
+
+template <typename T, typename TZ>
+static int launch_fc_small(const void *a, const void *w, const float *bias, void *z, int N, int In, int Out, int relu, hipStream_t s)
+{
+    auto launch = [&](auto kern, int nb) {
+        if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return (int)VGG_ERR_LAUNCH;
+        const size_t lds = (size_t)kFcSmallWaves * nb * 16 * (256 + 16);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((Out + 15) / 16)), dim3(kFcSmallWaves * 64), lds, s, (const char *)a, (const char *)w,
+                           bias, (TZ *)z, N, In, Out, relu);
+        return launch_status();
+    };
+    return N <= 16 ? launch(fc_fwd_small_kernel<T, TZ, 1>, 1) : launch(fc_fwd_small_kernel<T, TZ, 2>, 2);
+}
+
 // z = f(bias + sum over splits), converted to TZ.
 template <typename TZ>
 __global__ void fc_finish_kernel(const float *__restrict__ part, const float *__restrict__ bias, TZ *__restrict__ z, int N,
@@ -198,6 +329,13 @@ size_t fc_workspace(int dtype, int N, int In, int Out)
 int fc_forward(int dtype, int N, int In, int Out, const void *a_, const void *w, const float *bias, void *z, int z_dtype,
                int relu, void *ws, hipStream_t s)
 {
+    if (fc_small(dtype, N, In, Out)) {
+        if (dtype == VGG_BF16)
+            return z_dtype == VGG_BF16 ? launch_fc_small<bf16_t, bf16_t>(a_, w, bias, z, N, In, Out, relu, s)
+                                       : launch_fc_small<bf16_t, float>(a_, w, bias, z, N, In, Out, relu, s);
+        return z_dtype == VGG_BF16 ? launch_fc_small<float, bf16_t>(a_, w, bias, z, N, In, Out, relu, s)
+                                   : launch_fc_small<float, float>(a_, w, bias, z, N, In, Out, relu, s);
+    }
     FcArgs a;
     fc_plan(dtype, N, In, Out, a);
     const int splits = fc_splits(a);

@@ -634,6 +634,23 @@ def test_fc_backward(dtype, shape):
         B.vgg_fc_bwd(dtype, N, In, Out, ad, wd, dev(dz), dw, None, da, 1, None)
 
 
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("N,In,Out", [(1, 8, 3), (16, 264, 33), (17, 136, 130), (32, 520, 2050), (9, 4104, 16), (31, 2056, 17)])
+def test_fc_forward_small_batches(dtype, N, In, Out):
+    """The small-batch kernel at the edges of its tiles: one and two 16-row blocks, rows shorter than a 256-byte piece,
+    pieces for more and for fewer than its sixteen waves, a ragged last tile of outputs.  Operands rounded to the dtype
+    first, so that the sums (fp32, at most 4104 products) are all that differs: 1e-5 of the largest output."""
+    rng = np.random.default_rng(N * In + Out)
+    a, w = (dev(rng.standard_normal(s).astype(np.float32), TDT[dtype]) for s in ((N, In), (Out, In)))
+    b = rng.standard_normal(Out).astype(np.float32)
+    ref = R.fc(a.float().cpu().numpy(), w.float().cpu().numpy(), b, relu=True)
+    z = torch.full((N * Out + 64,), -7.0, device="cuda")
+    B.vgg_fc(dtype, N, In, Out, a, w, dev(b), z, B.F32, 1, ws_bytes(B.vgg_fc_workspace_bytes(dtype, N, In, Out)))
+    torch.cuda.synchronize()
+    assert max_rel_err(z[:N * Out].view(N, Out).cpu().numpy(), ref) <= 1e-5
+    assert (z[N * Out:] == -7.0).all()
+
+
 @pytest.mark.parametrize("N,In,Out", [(16, 260, 129), (17, 256, 64), (49, 1028, 3), (80, 132, 191), (97, 516, 257), (129, 252, 65),
                                       (31, 129, 1), (112, 127, 66)])
 def test_fc_backward_fp32_tile_edges(N, In, Out):
@@ -681,6 +698,11 @@ def test_softmax_xent_sgd(shape):
     torch.cuda.synchronize()
     ref = R.sgd(theta, grad, 0.01)
     assert np.abs(th.cpu().numpy() - ref).max() <= 1e-6
+
+
+@pytest.mark.parametrize("shape", [(301, 256), (7, 257), (3, 1024), (3, 1025), (2, 4096), (2, 4097)])
+def test_softmax_xent_at_the_row_lengths_where_the_kernel_changes(shape):
+    test_softmax_xent_sgd(shape)
 
 
 def test_layout_roundtrip_and_convert():
