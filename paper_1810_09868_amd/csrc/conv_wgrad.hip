@@ -51,7 +51,7 @@ struct WgradArgs {
 // Taps [T0, T0 + NT) of one wave: the main loop over the workgroup's tiles and the final sums.
 // S0: MFMA step before which the wave prepares the next tile's copies.
 // Patch tiles of the weight-gradient kernel: 4 rows x TW columns of one image (TW = 16 or 14, so that the
-// VGG widths 224, 112 and 56, 28 divide), halo 6 x (TW + 2).  Unlike the linear tiles (TW = 0, TileGeom
+// VGG widths 224, 112 and 56, 28 divide; what sticks out of the image is zero), halo 6 x (TW + 2).  Unlike the linear tiles (TW = 0, TileGeom
 // mode 0) their halo rows are an affine function of the tile row, so every x address of the main loop is
 // one per-lane base plus an immediate.  p.geo carries N, H, W, tiles_w, tiles_hw and their divisions.
 template <int TW>
@@ -491,18 +491,28 @@ void wgrad_launch_reduce(const float *part, float *out, size_t n, const float *p
     launch_reduce(part, out, n, part2, out2, n2, splits, stream);
 }
 
-// Patch width of the general kernel for an image size: 16 or 14 where the image width divides into
-// patches (the last patch row of an image may stick out at the bottom: at most three rows of zeros),
-// else 0 (linear tiles).
-static int wgrad_patch_width(int H, int W) { return H < 4 ? 0 : (W % 16 == 0 ? 16 : (W % 14 == 0 ? 14 : 0)); }
+// Patch width of the general kernel for an image size, 0: linear tiles.  16 or 14 where the image width divides into
+// patches (the last patch row of an image may stick out at the bottom: at most three rows of zeros); otherwise the one
+// of the two that pads less, when the padding costs less than what linear tiles pay: their halo (S rows for 64
+// pixels against 96 to 108, all of them copied) and 15 % for fetching halo rows across lanes.  64 -> 128 at 50x66, batch 10
+// (205 halo rows; patches pad by 10 %): 90 -> 69 us.
+static int wgrad_patch_width(int N, int H, int W)
+{
+    if (H < 4) return 0;
+    if (W % 16 == 0) return 16;
+    if (W % 14 == 0) return 14;
+    const int p16 = (W + 15) / 16 * 16, p14 = (W + 13) / 14 * 14, tw = p14 < p16 ? 14 : 16;
+    const double padded = (double)(p14 < p16 ? p14 : p16) * ((H + 3) / 4 * 4) / ((double)W * H);
+    return padded < 1.15 * make_tile_geom(N, H, W, kPK).S / (6 * (tw + 2)) ? tw : 0;
+}
 
 static void wgrad_plan(int N, int H, int W, int CinP, int Cout, WgradArgs &a, bool thin = false)
 {
     a.geo = make_tile_geom(N, H, W, kPK);
-    const int TW = thin ? 0 : wgrad_patch_width(H, W);
+    const int TW = thin ? 0 : wgrad_patch_width(N, H, W);
     if (TW != 0) {
         a.geo.mode = 1; a.geo.TH = 4; a.geo.TW = TW;
-        a.geo.tiles_w = W / TW;
+        a.geo.tiles_w = (W + TW - 1) / TW;
         a.geo.tiles_hw = a.geo.tiles_w * ((H + 3) / 4);
         a.geo.dTilesW = make_fast_div(a.geo.tiles_w);
         a.geo.dTilesHW = make_fast_div(a.geo.tiles_hw);
