@@ -368,8 +368,8 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *   [1] pixels per tile   [2] output channels per tile
  *   [3] 0: a tile is consecutive pixels, 1: a patch of one image
  *   [4] pixel tiles
- *   [5] workgroups (kernels 12 / 13: waves of one workgroup) that share one
- *       tile's contraction (forward, data gradient) or partial results that the fixed-order reduction adds (weight gradient)
+ *   [5] ranges in which a tile's contraction is summed (forward, data
+ *       gradient; kernels 1 and 2: by a workgroup each) or partial results that the fixed-order reduction adds (weight gradient)
  *   [6] workgroups of the main launch */
 #define VGG_PLAN_FWD 0
 #define VGG_PLAN_FWD_POOL 1

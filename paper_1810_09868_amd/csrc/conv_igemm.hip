@@ -621,7 +621,7 @@ __global__ __launch_bounds__(WM *WN * 64, WM *WN == 8 ? 4 : 3) void conv3x3_igem
     }
     compute(kh, Bs + bb * b_bytes);
 
-    if (sizeof(T) == 4 && p.part) conv_partial_epilogue<BM, BN, WM, WN>(acc, p, org, n0, split);
+    if (p.part) conv_partial_epilogue<BM, BN, WM, WN>(acc, p, org, n0, split);
     else conv_epilogue<T, BM, BN, WM, WN>(acc, p, org, smem, n0);
 }
 
@@ -683,7 +683,9 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 // would keep alive across it).
 enum ConvEpilogue { kEpiPlain, kEpiMasked, kEpiPooled, kEpiGeneral };
 
-template <int WM, int WN, int SA, int TM, int OCC, int RB, int EPI>
+// FOLD: the sums of every p.kchunks chunks are formed from zero and then added to the total (which starts at the bias),
+// as workgroups that share a contraction would add theirs.
+template <int WM, int WN, int SA, int TM, int OCC, int RB, int EPI, bool FOLD>
 __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(ConvArgs p)
 {
     typedef bf16_t T;
@@ -722,16 +724,28 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     const int px0 = p.g.mode ? (org.n * p.g.H + max(org.h0 - 1, 0)) * p.g.W + max(org.w0 - 1, 0) : max(org.m0 - p.g.W - 2, 0);
     unsigned aoff[NQ];
     unsigned long long alanes[NQ];
+    {
+        // The 64 slots of a copy lie in at most 14 rows.  Which pixel a row is takes some forty instructions, so it is
+        // found once, by one lane (lane 16 j + r: row r of copies j, j + 4, ...), and handed to the slots' lanes.
+        constexpr int NP = (NQ + 3) / 4;
+        int px[NP];
 #pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-        const int slot = (k * NW + wv) * 64 + lane;
-        const int row = slot / 5, seg = slot - row * 5;
-        const int px = (row < p.g.S && seg < 4) ? halo_pixel(p.g, org, row) : -1;
-        aoff[k] = px < 0 ? 0u : (unsigned)(px - px0) * (unsigned)xrow + seg * 16;
-        alanes[k] = __ballot(px >= 0 || seg == 4);
-        if (px < 0 && seg < 4) {
-            *reinterpret_cast<u32x4 *>(smem + slot * 16) = u32x4{0u, 0u, 0u, 0u};
-            *reinterpret_cast<u32x4 *>(smem + ABUF + slot * 16) = u32x4{0u, 0u, 0u, 0u};
+        for (int h = 0; h < NP; ++h) {
+            const int row = ((4 * h + (lane >> 4)) * NW + wv) * 64 / 5 + (lane & 15);
+            px[h] = row < p.g.S ? halo_pixel(p.g, org, row) : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+            const int first = (k * NW + wv) * 64, slot = first + lane;
+            const int row = slot / 5, seg = slot - row * 5;
+            const int pk = __shfl(px[k >> 2], (k & 3) * 16 + row - first / 5, kWave);
+            const bool in = pk >= 0 && seg < 4;
+            aoff[k] = in ? (unsigned)(pk - px0) * (unsigned)xrow + seg * 16 : 0u;
+            alanes[k] = __ballot(in || seg == 4);
+            if (!in && seg < 4) {
+                *reinterpret_cast<u32x4 *>(smem + slot * 16) = u32x4{0u, 0u, 0u, 0u};
+                *reinterpret_cast<u32x4 *>(smem + ABUF + slot * 16) = u32x4{0u, 0u, 0u, 0u};
+            }
         }
     }
     unsigned long long abase;
@@ -748,13 +762,19 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     };
     auto next_chunk = [&]() __attribute__((always_inline)) { abase += KC * sizeof(T); };
 
-    // byte address (inside a buffer) of tap (0,0) of this lane's pixels, its 16 bytes of the row included
+    // byte address (inside a buffer) of tap (0,0) of this lane's pixels, its 16 bytes of the row included (likewise:
+    // lane l finds the halo rows of tile rows l, l + 64, ... of the wave)
     int arow[NI];
+    {
+        constexpr int NR = (NI + 3) / 4;
+        int hr[NR];
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        int m, hrow;
-        tile_row(p.g, org, wm * (TM * 32) + i * 16 + q, m, hrow);
-        arow[i] = hrow * kRowBytes + g * 16;
+        for (int h = 0; h < NR; ++h) {
+            int m;
+            tile_row(p.g, org, wm * (TM * 32) + min(h * 64 + lane, TM * 32 - 1), m, hr[h]);
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i) arow[i] = __shfl(hr[i >> 2], (i & 3) * 16 + q, kWave) * kRowBytes + g * 16;
     }
 
     // weight fragment (tap t, chunk c, channels ch .. ch + 15): lane's 16 bytes at
@@ -813,6 +833,19 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     for (int i = 1; i < NI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = acc[0][j];
+    f32x4v total[FOLD ? NI : 1][NJ];
+    auto fold = [&](bool first) __attribute__((always_inline)) {
+        if constexpr (FOLD) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    total[i][j] = first ? acc[i][j] : total[i][j] + acc[i][j];
+                    acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+    };
+    fold(true);
 
     u32x4 af[RA];
 #pragma unroll
@@ -871,8 +904,15 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
                 __builtin_amdgcn_sched_barrier(0);
             }
         }, std::make_integer_sequence<int, TAPS>{});
+        if (FOLD && ((c + 1) % p.kchunks == 0 || c + 1 == nchunks)) fold(false);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the weight loads and halo copies issued past the end
+    if constexpr (FOLD) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) acc[i][j] = total[i][j];
+    }
 
     const int wrow0 = wm * (TM * 32);
     if (EPI == kEpiGeneral || (p.Cout & 7)) {   // pooled and un-pooled result, or a channel count that 16-byte stores do not divide
@@ -1030,8 +1070,8 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
 
 // ---------------------------------------------------------------------------
 // bf16, launches with fewer tiles than the chip has SIMDs to fill (small batches): a workgroup of G waves owns
-// 64 pixels x 16 NJ channels, and its waves share the contraction, wave g taking the channel chunks g, g + G, ...
-// with all nine taps.  What bounds such a launch is not the matrix pipe but the chain launch -> first loads ->
+// 64 pixels x 16 NJ channels, and its waves share the contraction: p.ksplit ranges of p.kchunks channel chunks, taken
+// by the waves in turn (wave w: w and w + G), each with all nine taps.  What bounds such a launch is not the matrix pipe but the chain launch -> first loads ->
 // multiply -> combine, so the kernel has one of each: a wave copies its own chunk's halo into its own LDS
 // region and requests all nine taps' weights at once (9 NJ fragments in registers, plain loads; a tap's
 // registers are refilled for the wave's next chunk as soon as its MFMAs are issued), no barrier until the end,
@@ -1042,8 +1082,8 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
 constexpr int kSmallPx = 64;         // pixels per tile
 constexpr int kSmallHaloRows = 256;  // most halo rows of a tile (the launch picks patches where consecutive pixels need more)
 
-template <int NJ, int G>
-__global__ __launch_bounds__(G * 64, G / 4) void conv3x3_small_bf16_kernel(ConvArgs p)
+template <int NJ, int G, bool TWO>   // TWO: waves may have two ranges
+__global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs p)
 {
     typedef bf16_t T;
     constexpr int NI = 4, BN = NJ * 16, KC = 32, TAPS = 9;
@@ -1060,6 +1100,12 @@ __global__ __launch_bounds__(G * 64, G / 4) void conv3x3_small_bf16_kernel(ConvA
     const int n0 = tile_n * BN;
     const TileOrigin org = tile_origin(p.g, tile_m);
     const int pitch = p.g.pitch, nchunks = p.CinP / KC;
+    // the chunk after c of this wave's ranges (nchunks: none)
+    auto next_of = [&](int c) __attribute__((always_inline)) {
+        const int n = c + 1, skip = n % p.kchunks == 0 ? (G - 1) * p.kchunks : 0;
+        return min(n + skip, nchunks);
+    };
+    const int c_first = min(wv * p.kchunks, nchunks);
     const size_t xrow = (size_t)p.CinP * sizeof(T);
 
     // weight fragment (tap t, chunk c, channels ch .. ch + 15): see conv3x3_igemm_wreg_kernel
@@ -1076,7 +1122,7 @@ __global__ __launch_bounds__(G * 64, G / 4) void conv3x3_small_bf16_kernel(ConvA
         for (int j = 0; j < NJ; ++j) bw[t][j] = *reinterpret_cast<const u32x4 *>(sb + voff[j]);
     };
 #pragma unroll
-    for (int t = 0; t < TAPS; ++t) load_w(min(wv, nchunks - 1), t);
+    for (int t = 0; t < TAPS; ++t) load_w(min(c_first, nchunks - 1), t);
 
     // The pixel behind halo row `lane + 64 j` is found once, by one lane; a copy (16 rows x 64 bytes) fetches
     // the row number of its lanes from there.
@@ -1103,13 +1149,14 @@ __global__ __launch_bounds__(G * 64, G / 4) void conv3x3_small_bf16_kernel(ConvA
             }
         }
     };
-    if (wv < nchunks) copy(wv, 0);
+    if (c_first < nchunks) copy(c_first, 0);
 
-    int hrow[NI];
+    int hrow[NI];   // halo row of tap (0,0) of this lane's pixels: lane l finds tile row l's
+    {
+        int m, h;
+        tile_row(p.g, org, lane, m, h);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        int m;
-        tile_row(p.g, org, i * 16 + q, m, hrow[i]);
+        for (int i = 0; i < NI; ++i) hrow[i] = __shfl(h, i * 16 + q, kWave);
     }
     f32x4v acc[NI][NJ];
 #pragma unroll
@@ -1117,10 +1164,24 @@ __global__ __launch_bounds__(G * 64, G / 4) void conv3x3_small_bf16_kernel(ConvA
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
 
+    // At most two ranges per wave (w and w + G): the first one's sums wait in registers.
+    f32x4v first[TWO ? NI : 1][NJ];
+    auto take = [&]() __attribute__((always_inline)) {
+        if constexpr (TWO) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    first[i][j] = acc[i][j];
+                    acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+    };
+    take();
     int buf = 0;
-    for (int c = wv; c < nchunks; c += G) {
+    for (int c = c_first; c < nchunks;) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this chunk's halo has landed (and its weights)
-        const int cn = c + G;
+        const int cn = next_of(c);
         if (p.halo_bufs == 2 && cn < nchunks) copy(cn, buf ^ 1);
         const char *A = As + buf * bufs;
 #pragma unroll
@@ -1143,17 +1204,27 @@ __global__ __launch_bounds__(G * 64, G / 4) void conv3x3_small_bf16_kernel(ConvA
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // (one buffer: this chunk's reads are done)
             copy(cn, 0);
         }
+        if (c + 1 == c_first + p.kchunks && wv + G < p.ksplit) take();
+        c = cn;
     }
 
-    // Combine: sums to LDS, [wave][pixel][channel], then each thread adds the G values of its four channels in a
-    // fixed order (bias first), applies ReLU / mask, and stores; with a pool, of the four pixels of a window.
+    // Combine: the ranges' sums go to LDS, [range][pixel][channel], in place of the halos; then each thread adds those
+    // of its four channels in a fixed order (bias first), applies ReLU / mask, and stores; with a pool, of the four
+    // pixels of a window.
     __syncthreads();
     float *red = reinterpret_cast<float *>(smem);
+    auto park = [&](const f32x4v(&v)[NI][NJ], int range) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            *reinterpret_cast<f32x4v *>(red + (size_t)(wv * kSmallPx + i * 16 + q) * RP + j * 16 + g * 4) = acc[i][j];
+            for (int j = 0; j < NJ; ++j)
+                *reinterpret_cast<f32x4v *>(red + (size_t)(range * kSmallPx + i * 16 + q) * RP + j * 16 + g * 4) = v[i][j];
+    };
+    if constexpr (TWO) {
+        const bool two = wv + G < p.ksplit;
+        if (two) park(first, wv);
+        if (wv < p.ksplit) park(acc, two ? wv + G : wv);
+    } else if (wv < p.ksplit) park(acc, wv);
     __syncthreads();
     const float lo = p.relu ? 0.f : -__builtin_inff();
     T *y = reinterpret_cast<T *>(p.y), *pool = reinterpret_cast<T *>(p.pool);
@@ -1162,8 +1233,7 @@ __global__ __launch_bounds__(G * 64, G / 4) void conv3x3_small_bf16_kernel(ConvA
         const int col = n0 + c4 * 4;
         f32x4v s = {0.f, 0.f, 0.f, 0.f};
         if (p.bias) s = *reinterpret_cast<const f32x4v *>(p.bias + col);
-#pragma unroll
-        for (int w = 0; w < G; ++w) s += *reinterpret_cast<const f32x4v *>(red + (size_t)(w * kSmallPx + row) * RP + c4 * 4);
+        for (int w = 0; w < p.ksplit; ++w) s += *reinterpret_cast<const f32x4v *>(red + (size_t)(w * kSmallPx + row) * RP + c4 * 4);
         const int m = tile_pixel(p.g, org, row);
 #pragma unroll
         for (int e = 0; e < 4; ++e) out[e] = f32_to_bf16(fmaxf(s[e], lo));
@@ -1208,30 +1278,32 @@ __global__ __launch_bounds__(G * 64, G / 4) void conv3x3_small_bf16_kernel(ConvA
 }
 
 // LDS bytes of a launch with one or two halo buffers per wave
-template <int NJ, int G>
-static size_t conv_small_lds(int S, int bufs)
+static size_t conv_small_lds(int G, int S, int bufs, int ksplit)
 {
-    const size_t halo = (size_t)G * bufs * round_up16(S) * kDataBytes, red = (size_t)G * kSmallPx * (NJ * 16 + 4) * 4;
+    const size_t halo = (size_t)G * bufs * round_up16(S) * kDataBytes, red = (size_t)ksplit * kSmallPx * (2 * 16 + 4) * 4;
     return halo > red ? halo : red;
 }
-template <int NJ, int G>
+template <int G>
 static int launch_conv_small(const ConvArgs &a0, const TileGeom &g, hipStream_t stream)
 {
+    constexpr int NJ = 2;
     ConvArgs a = a0;
     a.g = g;
     a.tiles_n = (a.Cout + NJ * 16 - 1) / (NJ * 16);
     a.rowsA = round_up16(g.S);
     a.dTiles = make_fast_div(g.ntiles);
     // a second halo buffer when a wave has more than one chunk and it fits
-    a.halo_bufs = a.CinP / 32 > G && conv_small_lds<NJ, G>(g.S, 2) <= 160 * 1024 ? 2 : 1;
-    auto kern = conv3x3_small_bf16_kernel<NJ, G>;
+    a.halo_bufs = a.CinP / 32 > G && conv_small_lds(G, g.S, 2, a.ksplit) <= 160 * 1024 ? 2 : 1;
+    auto kern = conv3x3_small_bf16_kernel<NJ, G, false>;
+    if constexpr (G == 4)
+        if (a.ksplit > G) kern = conv3x3_small_bf16_kernel<NJ, G, true>;
     if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return VGG_ERR_LAUNCH;
-    const size_t lds = conv_small_lds<NJ, G>(g.S, a.halo_bufs);
+    const size_t lds = conv_small_lds(G, g.S, a.halo_bufs, a.ksplit);
     hipLaunchKernelGGL(kern, dim3((unsigned)(g.ntiles * a.tiles_n)), dim3(G * 64), lds, stream, a);
     return launch_status();
 }
 
-template <int WM, int WN, int SA, int TM = 4, int OCC = 2, int RB = 3>
+template <int WM, int WN, int SA, int TM = 4, int OCC = 2, int RB = 3, bool FOLD = false>
 static int launch_conv_wreg(const ConvArgs &a0, const TileGeom &g, hipStream_t stream)
 {
     ConvArgs a = a0;
@@ -1246,11 +1318,11 @@ static int launch_conv_wreg(const ConvArgs &a0, const TileGeom &g, hipStream_t s
         hipLaunchKernelGGL(kern, dim3((unsigned)(a.g.ntiles * a.tiles_n)), dim3(NT), lds, stream, a);
         return launch_status();
     };
-    if ((a.pool && a.y) || (a.Cout & 7)) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiGeneral>);
-    if constexpr (TM % 2 == 0)   // (320-pixel tiles are never patches)
-        if (a.pool) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPooled>);
-    if (a.mask) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiMasked>);
-    return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPlain>);
+    if ((a.pool && a.y) || (a.Cout & 7)) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiGeneral, FOLD>);
+    if constexpr (TM % 2 == 0 && !FOLD)   // (320-pixel tiles are never patches; sums are not folded where a pool is fused)
+        if (a.pool) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPooled, FOLD>);
+    if (a.mask) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiMasked, FOLD>);
+    return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPlain, FOLD>);
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int SA>
@@ -1287,9 +1359,10 @@ static int launch_conv(const ConvArgs &a0, int N, int H, int W, hipStream_t stre
 }
 
 // Sums the partial results of a split contraction: y = f(bias + sum over splits), f = ReLU and/or the
-// (mask > 0) factor (fp32).  One thread per four channels.
+// (mask > 0) factor, converted to T.  One thread per four channels.
+template <typename T>
 __global__ __launch_bounds__(256) void conv_split_finish_kernel(const float *__restrict__ part, const float *__restrict__ bias,
-                                                                const float *__restrict__ mask, float *__restrict__ y, size_t quads,
+                                                                const T *__restrict__ mask, T *__restrict__ y, size_t quads,
                                                                 int Cout, int ksplit, int relu)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1302,7 +1375,7 @@ __global__ __launch_bounds__(256) void conv_split_finish_kernel(const float *__r
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         s[e] = fmaxf(s[e], lo);
-        if (mask && !(mask[i * 4 + e] > 0.f)) s[e] = 0.f;
+        if (mask && !(Elem<T>::load(mask + i * 4 + e) > 0.f)) s[e] = 0.f;
     }
     store4(y + i * 4, s[0], s[1], s[2], s[3]);
 }
@@ -1312,7 +1385,8 @@ __global__ __launch_bounds__(256) void conv_split_finish_kernel(const float *__r
 enum ConvKernel {
     kStaged = 0, kDma, kDmaBig, kDmaHalf,       // register-staged; direct-to-LDS with 384 / 448 / 192 halo rows
     kWreg, kWregBig, kWregTall, kWregTallBig,   // weights in registers: 256- and 320-pixel tiles, 384 / 448 halo rows
-    kWregHalf, kWregHalfBig,                    // ... 128-pixel tiles, 224 / 384 halo rows
+    kWregHalf, kWregHalfBig,                    // ... 128-pixel tiles, 224 / 384 halo rows (the sums folded per range
+                                                //     where the contraction is split)
     kWregDeep, kWregDeepBig,                    // ... with nine taps of weights in flight
     kSmall4, kSmall8                            // 64 x 32 tiles, the contraction split over four / eight waves
 };
@@ -1323,10 +1397,9 @@ struct ConvPlan {
     int ksplit, kchunks;
 };
 
-// Split of the contraction over workgroups (fp32; for bf16 only the size of the workspace that callers bring,
-// see conv3x3_igemm_workspace).  Small batches: fewer tiles than CUs, each walking the whole contraction alone.
-// Then several workgroups share a tile, each taking a range of channel chunks (at least two), and a second
-// kernel adds their partial sums.
+// Split of the contraction.  Small batches: fewer tiles than CUs, each walking the whole contraction alone.
+// Then the contraction is summed in ranges of (at least two) channel chunks, by a workgroup each, whose partial sums a
+// second kernel adds, or (bf16, more than 64 output channels) inside one workgroup in the same order.
 static void conv_split(int dtype, const TileGeom &g, int CinP, int Cout, int &ksplit, int &kchunks)
 {
     const int chunks = CinP * dtype_size(dtype) / kDataBytes;
@@ -1352,10 +1425,19 @@ static TileGeom conv_small_geom(int N, int H, int W, bool pool)
     return lin.mode == 0 && ((fits && (cheaper || pool)) || lin.S > kSmallHaloRows) ? patch : lin;
 }
 
+bool conv3x3_pool_fusable(int dtype, int H, int W, int Cout);
+
 static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bool pool)
 {
     ConvPlan c;
     c.g = make_tile_geom(N, H, W, 256);
+    if (c.g.S > kDmaHaloRowsBig) {
+        // wide images (from about 60 pixels): the halo of consecutive pixels does not fit the direct-to-LDS kernels;
+        // patches do, unless more than a third of their pixels would lie outside the image (bf16 128 -> 128 at
+        // 64x70, batch 10: 30 -> 19 us; fp32 64 -> 128 at 75x75, batch 20: 165 -> 149)
+        const TileGeom patch = make_patch_geom(N, H, W, 256);
+        if ((long)patch.ntiles * 256 <= (long)c.g.M * 3 / 2) c.g = patch;
+    }
     const bool dma = c.g.S <= kDmaHaloRows, dma_big = !dma && c.g.S <= kDmaHaloRowsBig;
     const int cols = (Cout + 127) / 128, wide_tiles = c.g.ntiles * cols;
     const int chunks = CinP * dtype_size(dtype) / kDataBytes;
@@ -1376,16 +1458,19 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         }
         return c;
     }
-    // bf16.  Few tiles and at least four channel chunks: the waves of a workgroup share the contraction (64 x 32
-    // tiles; eight waves where every CU gets at most one workgroup and every wave still two chunks).  Measured
-    // against the best of the other kernels (us): 512 -> 512 at 14x14, batch 1 (128 tiles) 9.3 / 13.5; at 28x28,
-    // batch 1 (224) 10.1 / 19.3, batch 2 (448) 15.1 / 22; batch 4 (896) 28 / 26: the line lies at 512 tiles.
-    if (Cout % 4 == 0 && chunks >= 4 && wide_tiles < 512) {
+    // bf16.  Shapes whose contraction is split (conv_split) form the same partial sums and add them in the same order,
+    // but inside a workgroup.  Few tiles: the waves of a workgroup share the ranges (64 x 32 tiles; eight waves where
+    // every CU gets at most one workgroup).  Measured against the best of the other kernels (us): 512 -> 512 at 14x14,
+    // batch 1 (128 tiles) 9.3 / 13.5; at 28x28, batch 1 (224) 10.1 / 19.3, batch 2 (448) 15.1 / 22; batch 4 (896)
+    // 28 / 35 against 256 -> 512 there 17.4 / 15.4: the line lies at 512 tiles, at 1024 for long contractions
+    // (at most 64 output channels have no 128-wide tile to go to).
+    if (!pool || !conv3x3_pool_fusable(dtype, H, W, Cout)) conv_split(dtype, c.g, CinP, Cout, c.ksplit, c.kchunks);
+    if (c.ksplit > 1) {
         const TileGeom t = conv_small_geom(N, H, W, pool);
-        const int tiles = t.ntiles * ((Cout + 31) / 32);
-        if (tiles <= 512 && (!pool || t.mode == 1)) {
+        const int tiles = t.ntiles * ((Cout + 31) / 32), G = tiles <= 256 && c.ksplit > 4 ? 8 : 4;
+        if (tiles <= (chunks >= 12 || Cout <= 64 ? 1024 : 512) && (!pool || t.mode == 1) && c.ksplit <= 8 && conv_small_lds(G, t.S, 1, c.ksplit) <= 160 * 1024) {
             c.g = t;
-            c.kernel = tiles <= 256 && chunks >= 16 ? kSmall8 : kSmall4;
+            c.kernel = G == 8 ? kSmall8 : kSmall4;
             c.bn = 32;
             return c;
         }
@@ -1398,6 +1483,9 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.
     // (that kernel's halo offsets inside a tile are 32 bits: at most 18 image rows of a patch, or 320 + 2 rows)
     const bool reach = (size_t)(20 * (size_t)W + 512) * CinP * sizeof(bf16_t) < ((size_t)1 << 32);
+    if (Cout <= 64 && c.ksplit > 1) return c;           // (split over workgroups, as fp32)
+    const int ksplit = c.ksplit, kchunks = c.kchunks;   // (of the kernels below only the 128-pixel tiles fold their sums)
+    c.ksplit = 1; c.kchunks = chunks;
     if (Cout > 64 && (dma || dma_big) && reach && (!narrow || chunks >= 3 || wide_tiles >= 256)) {
         c.kernel = dma ? kWreg : kWregBig;
         c.bn = 128;
@@ -1420,15 +1508,18 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
             const bool big = t.S > kWregHaloRowsHalf;
             // (one tile per CU, alone there: with two taps of weights ahead each tap waits for L2; nine taps ahead
             // 36 -> 31.6 at 28x28 batch 10, 35 -> 27.4 at 14x14 batch 32; no gain on eight chunks)
-            if (tiles <= 256 && chunks >= 12) c.kernel = big ? kWregDeepBig : kWregDeep;
-            else c.kernel = big ? kWregHalfBig : kWregHalf;
+            if (tiles <= 256 && chunks >= 12 && ksplit == 1) c.kernel = big ? kWregDeepBig : kWregDeep;
+            else {
+                c.kernel = big ? kWregHalfBig : kWregHalf;
+                c.ksplit = ksplit; c.kchunks = kchunks;
+            }
         }
     }
     return c;
 }
 
-// Bytes of partial sums conv3x3_igemm needs for this shape (0: none).  bf16: what the shapes whose contraction
-// was once split over workgroups needed; nothing is written there, but callers size and pass their buffers by it.
+// Bytes of partial sums conv3x3_igemm needs for this shape (0: none).  bf16 shapes whose partial sums meet inside a
+// workgroup leave it untouched, but callers size and pass their buffers by it.
 size_t conv3x3_igemm_workspace(int dtype, int N, int H, int W, int CinP, int Cout)
 {
     int ksplit, kchunks;
@@ -1447,8 +1538,8 @@ void conv3x3_igemm_plan_info(int dtype, int N, int H, int W, int CinP, int Cout,
     info[2] = c.bn;
     info[3] = c.g.mode;
     info[4] = c.g.ntiles;
-    info[5] = c.kernel == kSmall8 ? 8 : (c.kernel == kSmall4 ? 4 : c.ksplit);
-    info[6] = c.g.ntiles * ((Cout + c.bn - 1) / c.bn) * c.ksplit;
+    info[5] = c.ksplit;
+    info[6] = c.g.ntiles * ((Cout + c.bn - 1) / c.bn) * (c.kernel == kDma || c.kernel == kDmaBig ? c.ksplit : 1);
 }
 
 bool conv3x3_pool_fusable(int dtype, int H, int W, int Cout)
@@ -1475,7 +1566,8 @@ int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void
 {
     if (pool && !conv3x3_pool_fused(dtype, N, H, W, CinP, Cout)) return VGG_ERR_UNSUPPORTED;
     ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool != nullptr);
-    if (!part_ws || !y) { c.ksplit = 1; c.kchunks = CinP * dtype_size(dtype) / kDataBytes; }
+    const bool split = (c.kernel == kDma || c.kernel == kDmaBig) && c.ksplit > 1;   // over workgroups
+    if (split && (!part_ws || !y)) { c.ksplit = 1; c.kchunks = CinP * dtype_size(dtype) / kDataBytes; }
     ConvArgs a;
     a.x = static_cast<const char *>(x);
     a.w = static_cast<const char *>(w);
@@ -1486,7 +1578,7 @@ int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void
     a.argmax = pool ? argmax : nullptr;
     a.CinP = CinP; a.Cout = Cout;
     a.relu = relu; a.tiles_n = 0; a.rowsA = 0;
-    a.part = c.ksplit > 1 ? static_cast<float *>(part_ws) : nullptr;
+    a.part = split && c.ksplit > 1 ? static_cast<float *>(part_ws) : nullptr;
     a.ksplit = c.ksplit; a.kchunks = c.kchunks;
     const bool narrow = c.bn == 64;
     const TileGeom &g = c.g;
@@ -1512,12 +1604,16 @@ int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void
         case kWregBig: rc = launch_conv_wreg<2, 2, kWregHaloRowsBig>(a, g, stream); break;
         case kWregTall: rc = launch_conv_wreg<2, 2, kWregHaloRows, 5, 1>(a, g, stream); break;
         case kWregTallBig: rc = launch_conv_wreg<2, 2, kWregHaloRowsBig, 5, 1>(a, g, stream); break;
-        case kWregHalf: rc = launch_conv_wreg<2, 2, kWregHaloRowsHalf, 2, 3>(a, g, stream); break;
-        case kWregHalfBig: rc = launch_conv_wreg<2, 2, kWregHaloRows, 2, 2>(a, g, stream); break;
+        case kWregHalf:
+            rc = a.ksplit > 1 ? launch_conv_wreg<2, 2, kWregHaloRowsHalf, 2, 2, 3, true>(a, g, stream) : launch_conv_wreg<2, 2, kWregHaloRowsHalf, 2, 3>(a, g, stream);
+            break;
+        case kWregHalfBig:
+            rc = a.ksplit > 1 ? launch_conv_wreg<2, 2, kWregHaloRows, 2, 2, 3, true>(a, g, stream) : launch_conv_wreg<2, 2, kWregHaloRows, 2, 2>(a, g, stream);
+            break;
         case kWregDeep: rc = launch_conv_wreg<2, 2, kWregHaloRowsHalf, 2, 1, 9>(a, g, stream); break;
         case kWregDeepBig: rc = launch_conv_wreg<2, 2, kWregHaloRows, 2, 1, 9>(a, g, stream); break;
-        case kSmall4: rc = launch_conv_small<2, 4>(a, g, stream); break;
-        case kSmall8: rc = launch_conv_small<2, 8>(a, g, stream); break;
+        case kSmall4: rc = launch_conv_small<4>(a, g, stream); break;
+        case kSmall8: rc = launch_conv_small<8>(a, g, stream); break;
         case kDma:
             rc = narrow ? launch_conv_dma<bf16_t, 256, 64, 4, 1, kDmaHaloRows>(a, g, stream)
                         : launch_conv_dma<bf16_t, 256, 128, 4, 2, kDmaHaloRows>(a, g, stream);
@@ -1531,10 +1627,15 @@ int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void
                         : launch_conv<bf16_t, 256, 128, 4, 2>(a, N, H, W, stream);
         }
     }
-    if (rc != VGG_OK || c.ksplit == 1) return rc;
+    if (rc != VGG_OK || !a.part) return rc;
     const size_t quads = (size_t)N * H * W * Cout / 4;
-    hipLaunchKernelGGL(conv_split_finish_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, a.part, bias,
-                       static_cast<const float *>(mask), static_cast<float *>(y), quads, Cout, c.ksplit, relu);
+    const dim3 grid((unsigned)((quads + 255) / 256));
+    if (dtype == VGG_F32)
+        hipLaunchKernelGGL(conv_split_finish_kernel<float>, grid, dim3(256), 0, stream, a.part, bias,
+                           static_cast<const float *>(mask), static_cast<float *>(y), quads, Cout, c.ksplit, relu);
+    else
+        hipLaunchKernelGGL(conv_split_finish_kernel<bf16_t>, grid, dim3(256), 0, stream, a.part, bias,
+                           static_cast<const bf16_t *>(mask), static_cast<bf16_t *>(y), quads, Cout, c.ksplit, relu);
     return launch_status();
 }
 

@@ -350,11 +350,14 @@ def test_conv3x3_bf16_320_pixel_tiles_element_by_element():
 
 @pytest.mark.parametrize("shape,kernel", [
     ((1, 14, 14, 512, 512), 13),    # eight waves, two chunks each; consecutive pixels that end inside a tile
-    ((2, 30, 44, 128, 36), 12),     # one chunk per wave; patches that stick out on both sides; a ragged channel tile
-    ((5, 16, 48, 160, 100), 12),    # five chunks for four waves; patches that divide the image (the pool can be fused)
-    ((1, 56, 56, 288, 64), 12),     # nine chunks, two halo buffers
-    ((12, 7, 9, 544, 260), 13),     # seventeen chunks for eight waves; tiles that cross images
-    ((3, 5, 130, 128, 72), 12),     # an image row longer than a tile's halo: patches
+    ((2, 30, 44, 256, 36), 12),     # two chunks per wave; patches that stick out on both sides; a ragged channel tile
+    ((5, 16, 48, 288, 100), 12),    # nine chunks in three ranges; patches that divide the image (the pool can be fused)
+    ((1, 56, 56, 416, 64), 13),     # thirteen chunks in five ranges, the last one short
+    ((10, 14, 14, 512, 512), 12),   # eight ranges for four waves (496 tiles)
+    ((3, 30, 70, 96, 132), 9),      # an image row longer than the halo of 256 pixels
+    ((12, 7, 9, 544, 260), 13),     # seventeen chunks in six ranges for eight waves; tiles that cross images
+    ((4, 28, 28, 256, 516), 8),     # 128-pixel tiles, the sums folded over four ranges; a ragged channel tile
+    ((2, 56, 56, 256, 256), 9),     # ... with the larger halo
     ((41, 14, 14, 384, 512), 10),   # 128-pixel tiles, nine taps of weights ahead (252 tiles)
     ((9, 30, 57, 384, 200), 11),    # ... with the larger halo
     ((9, 24, 16, 96, 512), 8),      # 128-pixel patches
@@ -471,6 +474,16 @@ def _check_bwd_weight(dtype, shape, seed):
     B.vgg_conv3x3_bwd_weight(dtype, N, H, W, Cin, Cout, x, g, dwp2, db, ws)
     torch.cuda.synchronize()
     assert torch.equal(dwp, dwp2)
+
+
+@pytest.mark.parametrize("shape,kernel", [((3, 50, 66, 40, 72), 114), ((2, 9, 100, 16, 64), 116), ((1, 45, 60, 96, 36), 116),
+                                          ((2, 5, 31, 24, 68), 116), ((3, 13, 11, 64, 64), 100), ((2, 3, 130, 32, 64), 100)])
+def test_conv3x3_bwd_weight_fp32_patches_that_stick_out(shape, kernel):
+    """fp32 weight gradient on patches that the image does not divide into (both widths), and sizes next to the line
+    that keep linear tiles, against the oracle."""
+    N, H, W, Cin, Cout = shape
+    assert B.vgg_conv3x3_plan(B.PLAN_BWD_WEIGHT, B.F32, N, H, W, Cin, Cout)[0] == kernel
+    _check_bwd_weight(B.F32, shape, seed=sum(shape) + 4)
 
 
 @pytest.mark.parametrize("shape", [(37, 55, 16, 3, 8), (57, 9, 42, 3, 64), (9, 16, 48, 2, 16), (2, 224, 224, 3, 64)])
