@@ -267,15 +267,19 @@ inline TileGeom make_tile_geom(int N, int H, int W, int rows)
     g.tiles_w = g.tiles_hw = 0;
     g.ntiles = (g.M + rows - 1) / rows;
     g.pitch = W + 1;
-    const long HW = (long)H * W;
+    // Widest tile.  Where a tile starts inside an image repeats after HW / gcd(HW, rows) tiles, and a last, partial tile
+    // spans no more than the whole one it is the beginning of: one period is enough.
+    const int HW = H * W;
+    int gcd = HW;
+    for (int r = rows; r;) { const int t = gcd % r; gcd = r; r = t; }
+    const int tiles = g.ntiles < HW / gcd ? g.ntiles : HW / gcd;
+    auto q = [&](int m) {
+        const int n = m / HW, rem = m - n * HW, h = rem / W, w = rem - h * W;
+        return ((long)n * (H + 1) + h) * (W + 1) + w;
+    };
     long best = 0;
-    for (long m0 = 0; m0 < g.M; m0 += rows) {
-        long m1 = m0 + rows - 1;
-        if (m1 >= g.M) m1 = g.M - 1;
-        auto q = [&](long m) {
-            const long n = m / HW, rem = m % HW, h = rem / W, w = rem % W;
-            return (n * (H + 1) + h) * (W + 1) + w;
-        };
+    for (int t = 0; t < tiles; ++t) {
+        const int m0 = t * rows, m1 = g.M - m0 < rows ? g.M - 1 : m0 + rows - 1;
         const long span = q(m1) - q(m0);
         if (span > best) best = span;
     }
