@@ -12,15 +12,15 @@
 // receives element i%4 of the four 8-byte chunks that lanes i/4, i/4+4, i/4+8, i/4+12 point at.
 // Lane s of a group points at pixel s/4, channels 4(s%4).. of a 16-channel run: lane i then holds four
 // consecutive pixels of channel i.  Two such reads make a lane's eight pixels; the four 16-lane groups
-// of a wave take the four runs of eight pixels of two patch rows, so a fragment is 16 channels x the
-// 32 pixels of two patch rows.  A tap only shifts the pixel rows that the lanes point at, so all nine
+// of a wave take the four runs of eight pixels of the step's patch rows, so a fragment is 16 channels x the
+// 32 pixels of those rows.  A tap only shifts the pixel rows that the lanes point at, so all nine
 // taps are served from one staged halo.  (The 16x16x32 shape instead of 32x32x16: half the accumulator
 // traffic per multiply-add, which under the power this workload's operands draw is worth a few per
 // cent; same LDS reads, same registers.)
 //
-// A tile is a 4 x 16 patch of one image (patches may stick out at the right and bottom edge; what
-// is outside reads as zero) and its 6 x 18 halo: MFMA step s of a tile contracts the 32 pixels of
-// patch rows 2s and 2s + 1.  LDS rows are 160 bytes (64 channels + 32 bytes of padding); since the
+// A tile is a 4 x 16 or 8 x 8 patch of one image (patches may stick out at the right and bottom edge; what
+// is outside reads as zero) and its 6 x 18 or 10 x 10 halo: MFMA step s of a tile contracts the 32 pixels of
+// two patch rows of 16 or four of 8.  LDS rows are 160 bytes (64 channels + 32 bytes of padding); since the
 // patch geometry is fixed, every fragment address is one per-lane base plus an immediate.
 //
 // A workgroup (4 waves) owns a 64(co) x 64(ci) block of all nine taps and a range of tiles.  Wave
@@ -43,13 +43,11 @@ void wgrad_launch_reduce(const float *part, float *out, size_t n, const float *p
 
 namespace {
 
-constexpr int kTH = 4, kTW = 16;                 // patch
-constexpr int kP = kTH * kTW;                    // pixels per tile
-constexpr int kHW = kTW + 2;                     // halo width
-constexpr int kHaloRows = (kTH + 2) * kHW;       // 108
+constexpr int kP = 64;                           // pixels per tile
 constexpr int kRow = 160;                        // LDS bytes per pixel row
 constexpr int kGBytes = kP * kRow;               // 10240
-constexpr int kXBytes = kHaloRows * kRow;        // 17280
+constexpr int kMaxHaloRows = 6 * 18;             // of a 4 x 16 patch (8 x 8: 100)
+constexpr int kXBytes = kMaxHaloRows * kRow;     // 17280
 constexpr int kNW = 4;                           // waves
 constexpr int kOps = (kGBytes + kXBytes + kNW * 1024 - 1) / (kNW * 1024);  // copies per lane and tile: 7
 constexpr int kBuf = kOps * kNW * 1024;          // 28672 bytes per buffer (tail never read)
@@ -69,6 +67,7 @@ struct WgradBf16Args {
     int tiles_co, tiles_ci, splits, tiles_per_split, ntiles;
     int tiles_w, tiles_hw;
     int narrow;       // CinP <= 32: the waves of a tap group split the patch rows, not the channels
+    int tw;           // patch width: 16 or 8
     FastDiv dTilesW, dTilesHW;
 };
 
@@ -85,10 +84,12 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 // Taps [T0, T0 + NT) of one wave.  DB: this wave also sums g over the pixels.  NARROW: see above; NCI: x
 // fragments (16 input channels each) per tap.
-template <int T0, int NT, bool DB, bool NARROW, int NCI>
+template <int kTW, int T0, int NT, bool DB, bool NARROW, int NCI>
 __device__ __forceinline__ void wgrad_bf16_body(const WgradBf16Args &p, char *smem, int tco, int tci, int split)
 {
-    constexpr int NS = NARROW ? 1 : kTH / 2;                 // MFMA steps (pairs of patch rows) of this wave per tile
+    constexpr int kTH = kP / kTW, kHW = kTW + 2, kHaloRows = (kTH + 2) * kHW;
+    constexpr int RPS = 32 / kTW;                            // patch rows of an MFMA step: 2 of 16 pixels or 4 of 8
+    constexpr int NS = NARROW ? 1 : kTH / RPS;               // MFMA steps of this wave per tile
     constexpr int NCO = kCO / 16;                            // co fragments
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int wi = wv & 1;                                   // ci half of this wave (NARROW: its step)
@@ -140,13 +141,15 @@ __device__ __forceinline__ void wgrad_bf16_body(const WgradBf16Args &p, char *sm
         }
     };
 
-    // Fragment addresses.  Lane 16 G + i points at pixel dx = 8 (G & 1) + (i >> 2) (+4 for the second read) of
-    // patch row G >> 1 of the step's two, and at the 8-byte chunk i & 3 of a 32-byte run of 16 channels.
+    // Fragment addresses.  Lane 16 G + i points at pixel i >> 2 (+4 for the second read) of the step's G-th run of eight
+    // pixels (16 wide: half G & 1 of patch row G >> 1; 8 wide: patch row G), and at the 8-byte chunk i & 3 of a 32-byte
+    // run of 16 channels.
     const int G = lane >> 4, i = lane & 15;
-    const int g_off = ((G >> 1) * kTW + 8 * (G & 1) + (i >> 2)) * kRow + (i & 3) * 8 +
-                      (NARROW ? wi * 2 * kTW * kRow : 0);           // + co fragment * 32 + 32 s * kRow (+ 4 * kRow)
-    const int x_off = kGBytes + ((G >> 1) * kHW + 8 * (G & 1) + (i >> 2)) * kRow + (i & 3) * 8 +
-                      (NARROW ? wi * 2 * kHW * kRow : wi * 64);     // + x fragment * 32 + ((2 s + kh) * 18 + kw) * kRow (+ 4 * kRow)
+    const int rrow = kTW == 16 ? G >> 1 : G, rcol = kTW == 16 ? 8 * (G & 1) : 0;
+    const int g_off = (rrow * kTW + rcol + (i >> 2)) * kRow + (i & 3) * 8 +
+                      (NARROW ? wi * 32 * kRow : 0);                // + co fragment * 32 + 32 s * kRow (+ 4 * kRow)
+    const int x_off = kGBytes + (rrow * kHW + rcol + (i >> 2)) * kRow + (i & 3) * 8 +
+                      (NARROW ? wi * RPS * kHW * kRow : wi * 64);   // + x fragment * 32 + ((RPS s + kh) * kHW + kw) * kRow (+ 4 * kRow)
 
     const int t_begin = split * p.tiles_per_split;
     const int t_end = min(t_begin + p.tiles_per_split, p.ntiles);
@@ -166,12 +169,12 @@ __device__ __forceinline__ void wgrad_bf16_body(const WgradBf16Args &p, char *sm
         // Fragments are requested one MFMA group ahead of their use (the LDS latency of a transpose read
         // is longer than the MFMAs a fragment feeds, and only two waves share a SIMD).
         auto g_frag = [&](int s, int c) __attribute__((always_inline)) {
-            const char *a = B + g_off + c * 32 + (2 * kTW * s) * kRow;
+            const char *a = B + g_off + c * 32 + (32 * s) * kRow;
             return tr_fragment(a, a + 4 * kRow);
         };
         auto x_frag = [&](int s, int t, int d) __attribute__((always_inline)) {
             const int kh = (T0 + t) / 3, kw = (T0 + t) % 3;
-            const char *a = B + x_off + d * 32 + ((2 * s + kh) * kHW + kw) * kRow;
+            const char *a = B + x_off + d * 32 + ((RPS * s + kh) * kHW + kw) * kRow;
             return tr_fragment(a, a + 4 * kRow);
         };
         bf16x8 gf[NCO], gf_next[NCO], xf[NCI], xf_next[NCI];
@@ -248,6 +251,7 @@ __device__ __forceinline__ void wgrad_bf16_body(const WgradBf16Args &p, char *sm
     }
 }
 
+template <int TW>
 __global__ __launch_bounds__(kNW * 64, 2) void conv3x3_wgrad_bf16_kernel(WgradBf16Args p)
 {
     extern __shared__ __align__(16) char smem[];
@@ -263,19 +267,19 @@ __global__ __launch_bounds__(kNW * 64, 2) void conv3x3_wgrad_bf16_kernel(WgradBf
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (p.narrow) {
         if (p.XC <= 16) {   // (x holds at most 16 channels: one x fragment per tap)
-            if (group == 0) wgrad_bf16_body<0, 5, false, true, 1>(p, smem, tco, tci, split);
-            else if (p.dbpart) wgrad_bf16_body<5, 4, true, true, 1>(p, smem, tco, tci, split);   // each wave sums g over its own rows
-            else wgrad_bf16_body<5, 4, false, true, 1>(p, smem, tco, tci, split);
+            if (group == 0) wgrad_bf16_body<TW, 0, 5, false, true, 1>(p, smem, tco, tci, split);
+            else if (p.dbpart) wgrad_bf16_body<TW, 5, 4, true, true, 1>(p, smem, tco, tci, split);   // each wave sums g over its own rows
+            else wgrad_bf16_body<TW, 5, 4, false, true, 1>(p, smem, tco, tci, split);
             return;
         }
-        if (group == 0) wgrad_bf16_body<0, 5, false, true, 2>(p, smem, tco, tci, split);
-        else if (p.dbpart) wgrad_bf16_body<5, 4, true, true, 2>(p, smem, tco, tci, split);
-        else wgrad_bf16_body<5, 4, false, true, 2>(p, smem, tco, tci, split);
+        if (group == 0) wgrad_bf16_body<TW, 0, 5, false, true, 2>(p, smem, tco, tci, split);
+        else if (p.dbpart) wgrad_bf16_body<TW, 5, 4, true, true, 2>(p, smem, tco, tci, split);
+        else wgrad_bf16_body<TW, 5, 4, false, true, 2>(p, smem, tco, tci, split);
         return;
     }
-    if (group == 0) wgrad_bf16_body<0, 5, false, false, 2>(p, smem, tco, tci, split);
-    else if (p.dbpart && tci == 0 && wave == 2) wgrad_bf16_body<5, 4, true, false, 2>(p, smem, tco, tci, split);
-    else wgrad_bf16_body<5, 4, false, false, 2>(p, smem, tco, tci, split);
+    if (group == 0) wgrad_bf16_body<TW, 0, 5, false, false, 2>(p, smem, tco, tci, split);
+    else if (p.dbpart && tci == 0 && wave == 2) wgrad_bf16_body<TW, 5, 4, true, false, 2>(p, smem, tco, tci, split);
+    else wgrad_bf16_body<TW, 5, 4, false, false, 2>(p, smem, tco, tci, split);
 }
 
 // ---------------------------------------------------------------------------
@@ -393,8 +397,12 @@ inline int wgrad_thin_blocks(int units, int co_tiles)
 void wgrad_bf16_plan(int N, int H, int W, int CinP, int Cout, WgradBf16Args &a)
 {
     a.N = N; a.H = H; a.W = W; a.CinP = CinP; a.Cout = Cout;
-    a.tiles_w = (W + kTW - 1) / kTW;
-    a.tiles_hw = a.tiles_w * ((H + kTH - 1) / kTH);
+    // 4 x 16 patches, or 8 x 8 where those cover the image with fewer (56x56: 49 instead of 56, a row of 56 filling the
+    // last sixteen columns by half: 256 -> 256, batch 100, 338 -> 307 us; 512 -> 512 at 7x7, batch 4, 38 -> 26)
+    const int t16 = ((W + 15) / 16) * ((H + 3) / 4), t8 = ((W + 7) / 8) * ((H + 7) / 8);
+    a.tw = t8 < t16 ? 8 : 16;
+    a.tiles_w = (W + a.tw - 1) / a.tw;
+    a.tiles_hw = t8 < t16 ? t8 : t16;
     a.ntiles = N * a.tiles_hw;
     a.dTilesW = make_fast_div(a.tiles_w);
     a.dTilesHW = make_fast_div(a.tiles_hw);
@@ -492,7 +500,8 @@ int conv3x3_wgrad_bf16(int N, int H, int W, int CinP, int Cout, const bf16_t *x,
     const int np = wgrad_bf16_partials(a);
     a.dbpart = db ? reinterpret_cast<float *>(static_cast<char *>(ws) + round_up((size_t)np * nw * 4, 256)) : nullptr;
     const dim3 grid((unsigned)(a.tiles_co * a.tiles_ci * a.splits));
-    hipLaunchKernelGGL(conv3x3_wgrad_bf16_kernel, grid, dim3(kNW * 64), 2 * kBuf, stream, a);
+    if (a.tw == 8) hipLaunchKernelGGL(conv3x3_wgrad_bf16_kernel<8>, grid, dim3(kNW * 64), 2 * kBuf, stream, a);
+    else hipLaunchKernelGGL(conv3x3_wgrad_bf16_kernel<16>, grid, dim3(kNW * 64), 2 * kBuf, stream, a);
     if (hipGetLastError() != hipSuccess) return VGG_ERR_LAUNCH;
     wgrad_launch_reduce(a.part, dw, nw, a.dbpart, db, db ? (size_t)Cout : 0, np, stream);
     return launch_status();

@@ -476,6 +476,15 @@ def _check_bwd_weight(dtype, shape, seed):
     assert torch.equal(dwp, dwp2)
 
 
+@pytest.mark.parametrize("shape", [(2, 24, 40, 72, 64), (3, 21, 37, 40, 72), (2, 7, 7, 16, 40), (1, 56, 56, 24, 128), (5, 8, 6, 200, 136)])
+def test_conv3x3_bwd_weight_bf16_on_8x8_patches(shape):
+    """bf16 weight gradient at sizes that 8 x 8 patches cover with fewer than 4 x 16 ones: dividing the image and
+    sticking out of it, with wide and narrow (at most 16 and 32) input channels, against the oracle."""
+    N, H, W, Cin, Cout = shape
+    assert B.vgg_conv3x3_plan(B.PLAN_BWD_WEIGHT, B.BF16, N, H, W, Cin, Cout)[4] == N * -(-H // 8) * -(-W // 8)
+    _check_bwd_weight(B.BF16, shape, seed=sum(shape) + 5)
+
+
 @pytest.mark.parametrize("shape,kernel", [((3, 50, 66, 40, 72), 114), ((2, 9, 100, 16, 64), 116), ((1, 45, 60, 96, 36), 116),
                                           ((2, 5, 31, 24, 68), 116), ((3, 13, 11, 64, 64), 100), ((2, 3, 130, 32, 64), 100)])
 def test_conv3x3_bwd_weight_fp32_patches_that_stick_out(shape, kernel):
