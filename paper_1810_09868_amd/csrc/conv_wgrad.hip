@@ -469,6 +469,20 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *part, fl
     }
 }
 
+// The same for few splits, one thread per four outputs (n and n2 multiples of four): bound by reading the partials,
+// 75 MB for 512 workgroups of bf16 64 x 64 blocks, 16.3 us with four bytes per lane and load -> 13.3.
+__global__ __launch_bounds__(256) void wgrad_reduce4_kernel(const f32x4 *part, f32x4 *out, size_t n, const f32x4 *part2, f32x4 *out2,
+                                                            size_t n2, int splits)
+{
+    size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n + n2) return;
+    if (i >= n) { i -= n; part = part2; out = out2; n = n2; }
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int k = 0; k < splits; ++k) s += part[(size_t)k * n + i];
+    out[i] = s;
+}
+
 static void launch_reduce(const float *part, float *out, size_t n, const float *part2, float *out2, size_t n2, int splits,
                           hipStream_t stream)
 {
@@ -479,6 +493,10 @@ static void launch_reduce(const float *part, float *out, size_t n, const float *
     else if (splits >= 16)
         hipLaunchKernelGGL(wgrad_reduce_kernel<4>, dim3((unsigned)((total + 63) / 64)), dim3(256), 0, stream, part, out, n, part2,
                            out2, n2, splits);
+    else if (n % 4 == 0 && n2 % 4 == 0 && aligned16(out) && aligned16(out2))
+        hipLaunchKernelGGL(wgrad_reduce4_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, stream,
+                           reinterpret_cast<const f32x4 *>(part), reinterpret_cast<f32x4 *>(out), n / 4,
+                           reinterpret_cast<const f32x4 *>(part2), reinterpret_cast<f32x4 *>(out2), n2 / 4, splits);
     else
         hipLaunchKernelGGL(wgrad_reduce_kernel<1>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, part, out, n, part2,
                            out2, n2, splits);
