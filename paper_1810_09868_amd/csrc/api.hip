@@ -24,7 +24,8 @@ bool raise_lds_limit(const void *kernel)
 
 // kernels' host launchers (defined in the other translation units)
 int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void *x, const void *w, const float *bias,
-                  const void *mask, void *y, void *pool, unsigned char *argmax, int relu, void *part_ws, hipStream_t stream);
+                  const void *mask, void *y, void *pool, unsigned char *argmax, int relu, void *part_ws, size_t part_bytes,
+                  hipStream_t stream);
 size_t conv3x3_igemm_workspace(int dtype, int N, int H, int W, int CinP, int Cout);
 bool conv3x3_pool_fusable(int dtype, int H, int W, int Cout);
 bool conv3x3_pool_fused(int dtype, int N, int H, int W, int CinP, int Cout);
@@ -137,7 +138,7 @@ struct WsLayout {
     size_t pooled[VGG19_NUM_CONV];     // pool outputs (index = conv layer the pool follows)
     size_t argmax[VGG19_NUM_CONV];
     size_t z1, z2, logits, probs, fcws;
-    size_t convpart;                   // partial sums of convolutions whose contraction is split
+    size_t convpart, convpart_bytes;   // partial sums of convolutions whose contraction is split
     // training only
     size_t dlogits, dz2, dz1, gA, gB, grads, wgws, fcbws;
     size_t wflip[VGG19_NUM_CONV];      // data-gradient operands (flipped, transposed weights) of layers 1..15
@@ -205,6 +206,7 @@ WsLayout ws_layout(const vgg_config *c, const PackedLayout &P, bool training)
         if (s > cpart) cpart = s;
     }
     L.convpart = b.take(cpart);
+    L.convpart_bytes = cpart;
     for (int l = 0; l < VGG19_NUM_CONV; ++l) L.wflip[l] = 0;
     L.dlogits = L.dz2 = L.dz1 = L.gA = L.gB = L.grads = L.wgws = L.fcbws = L.dflat32 = L.wgws_bytes = 0;
     if (training) {
@@ -288,7 +290,7 @@ void run_forward(const vgg_config *c, const PackedLayout &P, const WsLayout &L, 
                                                reinterpret_cast<const float *>(pk + P.conv_b[l]), nullptr,
                                                fuse ? nullptr : out, fuse ? ws + L.pooled[l] : nullptr,
                                                fuse && training ? reinterpret_cast<uint8_t *>(ws + L.argmax[l]) : nullptr, 1,
-                                               ws + L.convpart, s));
+                                               ws + L.convpart, L.convpart_bytes, s));
         cur = out;
         if (fuse) {
             rec.skip(K_POOL);  // fused into the launch above; listed so that the plan still shows five pools
@@ -383,7 +385,7 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
         if (l > 0) {
             // data gradient = the same implicit GEMM with flipped, transposed weights; fused ReLU mask (x > 0)
             VGG_STEP(rec, K_DGRAD, conv3x3_igemm(dt, N, H, W, Cout, Cin, gbuf[cur], ws + L.wflip[l], nullptr, xin,
-                                                gbuf[cur ^ 1], nullptr, nullptr, 0, ws + L.convpart, s));
+                                                gbuf[cur ^ 1], nullptr, nullptr, 0, ws + L.convpart, L.convpart_bytes, s));
             cur ^= 1;
         }
     }
@@ -568,7 +570,7 @@ static int conv_fwd_common(int dtype, int N, int H, int W, int Cin, int Cout, co
         part += round_up((size_t)N * H * W * cp * dtype_size(dtype), 256);
     }
     if (!part_bytes) part = nullptr;
-    return conv3x3_igemm(dtype, N, H, W, cp, Cout, x, w, bias, nullptr, y, pooled, argmax, relu ? 1 : 0, part, s);
+    return conv3x3_igemm(dtype, N, H, W, cp, Cout, x, w, bias, nullptr, y, pooled, argmax, relu ? 1 : 0, part, part_bytes, s);
 }
 
 int vgg_conv3x3_fwd(int dtype, int N, int H, int W, int Cin, int Cout, const void *x, const void *w, const float *bias,
@@ -637,8 +639,9 @@ int vgg_conv3x3_bwd_data(int dtype, int N, int H, int W, int Cin, int Cout, cons
         g = ws;
         part += round_up((size_t)N * H * W * cp * dtype_size(dtype), 256);
     }
-    if (!conv3x3_igemm_workspace(dtype, N, H, W, cp, Cin)) part = nullptr;
-    return conv3x3_igemm(dtype, N, H, W, cp, Cin, g, w_tf, nullptr, relu_src, dx, nullptr, nullptr, 0, part, s);
+    const size_t part_bytes = conv3x3_igemm_workspace(dtype, N, H, W, cp, Cin);
+    if (!part_bytes) part = nullptr;
+    return conv3x3_igemm(dtype, N, H, W, cp, Cin, g, w_tf, nullptr, relu_src, dx, nullptr, nullptr, 0, part, part_bytes, s);
 }
 
 size_t vgg_conv3x3_bwd_weight_workspace_bytes(int dtype, int N, int H, int W, int Cin, int Cout)

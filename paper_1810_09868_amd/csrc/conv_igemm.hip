@@ -1397,9 +1397,9 @@ struct ConvPlan {
     int ksplit, kchunks;
 };
 
-// Split of the contraction.  Small batches: fewer tiles than CUs, each walking the whole contraction alone.
-// Then the contraction is summed in ranges of (at least two) channel chunks, by a workgroup each, whose partial sums a
-// second kernel adds, or (bf16, more than 64 output channels) inside one workgroup in the same order.
+// Split of the contraction, decided on tiles of 256 pixels.  Small batches: fewer tiles than CUs, each walking the whole
+// contraction alone.  Then the contraction is summed in ranges of (at least two) channel chunks, by a workgroup each,
+// whose partial sums a second kernel adds, or (bf16, more than 64 output channels) inside one workgroup in the same order.
 static void conv_split(int dtype, const TileGeom &g, int CinP, int Cout, int &ksplit, int &kchunks)
 {
     const int chunks = CinP * dtype_size(dtype) / kDataBytes;
@@ -1414,6 +1414,13 @@ static void conv_split(int dtype, const TileGeom &g, int CinP, int Cout, int &ks
         kchunks = (chunks + want - 1) / want;
         ksplit = (chunks + kchunks - 1) / kchunks;
     }
+}
+// The only place that says whether workgroups may share a tile through memory: the launch (conv_plan) and the query that
+// sizes the buffer of partial sums (conv3x3_igemm_workspace) both ask it.  Images whose consecutive pixels have a halo
+// beyond kDmaHaloRowsBig are never split that way, on whatever tiles they then run.
+static void conv_split_in_memory(int dtype, int N, int H, int W, int CinP, int Cout, int &ksplit, int &kchunks)
+{
+    conv_split(dtype, make_tile_geom(N, H, W, 256), CinP, Cout, ksplit, kchunks);
 }
 
 // Tiles of the small-problem kernel: consecutive pixels, or patches where their halo is the smaller one (56 wide:
@@ -1431,10 +1438,12 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
 {
     ConvPlan c;
     c.g = make_tile_geom(N, H, W, 256);
-    if (c.g.S > kDmaHaloRowsBig) {
+    const bool wide = c.g.S > kDmaHaloRowsBig;
+    if (wide && dtype == VGG_BF16) {
         // wide images (from about 60 pixels): the halo of consecutive pixels does not fit the direct-to-LDS kernels;
-        // patches do, unless more than a third of their pixels would lie outside the image (bf16 128 -> 128 at
-        // 64x70, batch 10: 30 -> 19 us; fp32 64 -> 128 at 75x75, batch 20: 165 -> 149)
+        // patches do, unless more than a third of their pixels would lie outside the image (128 -> 128 at
+        // 64x70, batch 10: 30 -> 19 us).  fp32 multiplies at a sixteenth of the rate and pays for every padded pixel:
+        // 0.8 to 1.6 times the staged kernel's time over 277 shapes, 0.98 on average, so it stays with that one.
         const TileGeom patch = make_patch_geom(N, H, W, 256);
         if ((long)patch.ntiles * 256 <= (long)c.g.M * 3 / 2) c.g = patch;
     }
@@ -1448,7 +1457,7 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     c.kernel = dma ? kDma : (dma_big ? kDmaBig : kStaged);
     c.bn = narrow ? 64 : 128;
     if (dtype == VGG_F32) {
-        if (!pool) conv_split(dtype, c.g, CinP, Cout, c.ksplit, c.kchunks);
+        if (!pool) conv_split_in_memory(dtype, N, H, W, CinP, Cout, c.ksplit, c.kchunks);
         // fp32, 64-wide tiles, a launch of only a few workgroups per CU (the 14x14 layers at batch 100: 616
         // on 768 slots): 128-pixel tiles double the count and even out the load, +15 % there.
         const int total = c.g.ntiles * ((Cout + 63) / 64);
@@ -1483,7 +1492,10 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.
     // (that kernel's halo offsets inside a tile are 32 bits: at most 18 image rows of a patch, or 320 + 2 rows)
     const bool reach = (size_t)(20 * (size_t)W + 512) * CinP * sizeof(bf16_t) < ((size_t)1 << 32);
-    if (Cout <= 64 && c.ksplit > 1) return c;           // (split over workgroups, as fp32)
+    if (Cout <= 64 && c.ksplit > 1) {                   // (split over workgroups, as fp32)
+        if (wide) { c.ksplit = 1; c.kchunks = chunks; }
+        return c;
+    }
     const int ksplit = c.ksplit, kchunks = c.kchunks;   // (of the kernels below only the 128-pixel tiles fold their sums)
     c.ksplit = 1; c.kchunks = chunks;
     if (Cout > 64 && (dma || dma_big) && reach && (!narrow || chunks >= 3 || wide_tiles >= 256)) {
@@ -1523,7 +1535,7 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
 size_t conv3x3_igemm_workspace(int dtype, int N, int H, int W, int CinP, int Cout)
 {
     int ksplit, kchunks;
-    conv_split(dtype, make_tile_geom(N, H, W, 256), CinP, Cout, ksplit, kchunks);
+    conv_split_in_memory(dtype, N, H, W, CinP, Cout, ksplit, kchunks);
     return ksplit > 1 ? round_up((size_t)ksplit * N * H * W * Cout * 4, 256) : 0;
 }
 
@@ -1559,15 +1571,16 @@ bool conv3x3_pool_fused(int dtype, int N, int H, int W, int CinP, int Cout)
 
 // x: [N*H*W][CinP], w: [9][Cout][CinP] (elements of dtype); y: [N*H*W][Cout].
 // pool (optional): 2x2 max of y, only when conv3x3_pool_fused(); y may then be null; argmax (optional, with pool).
-// part_ws: conv3x3_igemm_workspace() bytes, or null (then the contraction is never split).
+// part_ws: part_bytes of scratch; where conv3x3_igemm_workspace() asks for more than that (or it is null), the
+// contraction is not split over workgroups.
 int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void *x, const void *w,
                   const float *bias, const void *mask, void *y, void *pool, unsigned char *argmax, int relu, void *part_ws,
-                  hipStream_t stream)
+                  size_t part_bytes, hipStream_t stream)
 {
     if (pool && !conv3x3_pool_fused(dtype, N, H, W, CinP, Cout)) return VGG_ERR_UNSUPPORTED;
     ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool != nullptr);
     const bool split = (c.kernel == kDma || c.kernel == kDmaBig) && c.ksplit > 1;   // over workgroups
-    if (split && (!part_ws || !y)) { c.ksplit = 1; c.kchunks = CinP * dtype_size(dtype) / kDataBytes; }
+    if (split && (!part_ws || !y || part_bytes < (size_t)c.ksplit * N * H * W * Cout * 4)) { c.ksplit = 1; c.kchunks = CinP * dtype_size(dtype) / kDataBytes; }
     ConvArgs a;
     a.x = static_cast<const char *>(x);
     a.w = static_cast<const char *>(w);

@@ -202,3 +202,31 @@ def test_convolution_plan_query():
     assert B.vgg_conv3x3_plan(B.PLAN_FWD, B.BF16, 1, 14, 14, 512, 512)[5] > 1
     assert B.vgg_conv3x3_fwd_workspace_bytes(B.BF16, 1, 14, 14, 512, 512) > 0
     assert B.vgg_conv3x3_fwd_workspace_bytes(B.BF16, 100, 14, 14, 512, 512) == 0
+
+
+def test_partial_sums_of_a_split_convolution_fit_what_the_query_asks_for():
+    # Kernels 0 .. 3 split a contraction over workgroups, whose partial sums ([ranges][pixels][channels] fp32) go to the
+    # caller's scratch.  Launch and query have to agree for every layer of the network, forward and data gradient, on
+    # images of any shape: the whole passes size one region by the query and hand it to every layer.
+    chans = [(64, 64), (64, 128), (128, 128), (128, 256), (256, 256), (256, 512), (512, 512)]
+    stage = [0, 1, 1, 2, 2, 3, 3, 4]
+    split = 0
+    for dtype in (B.F32, B.BF16):
+        for h, w in [(32 * a, 32 * b) for a in (1, 2, 3, 5, 7, 8, 11, 19, 24, 32) for b in (1, 3, 7, 11, 12, 13, 24, 25, 31, 32)]:
+            for n in (1, 2, 3, 5, 8):
+                if n * h * w > 1 << 21:
+                    continue
+                for (ci, co), s in zip(chans + [(512, 512)], stage):
+                    hh, ww = h >> s, w >> s
+                    for op, k, m, q in ((B.PLAN_FWD, ci, co, B.vgg_conv3x3_fwd_workspace_bytes),
+                                        (B.PLAN_BWD_DATA, co, ci, B.vgg_conv3x3_bwd_data_workspace_bytes)):
+                        info = B.vgg_conv3x3_plan(op, dtype, n, hh, ww, ci, co)
+                        if info[0] <= 3 and info[5] > 1:
+                            split += 1
+                            need = info[5] * n * hh * ww * m * 4
+                            assert q(dtype, n, hh, ww, ci, co) >= need, (dtype, op, n, hh, ww, ci, co, info)
+    assert split > 100
+    # a wide image is not split in memory: its single calls need no scratch
+    for n, h, w, ci, co in ((1, 56, 96, 256, 256), (1, 24, 200, 256, 256), (1, 97, 97, 128, 128)):
+        assert B.vgg_conv3x3_plan(B.PLAN_FWD, B.F32, n, h, w, ci, co)[5] == 1
+        assert B.vgg_conv3x3_fwd_workspace_bytes(B.F32, n, h, w, ci, co) == 0

@@ -424,6 +424,43 @@ def test_train_step_equals_chained_single_op_calls(size, dtype):
             assert torch.equal(a, b), (k, l, float((a - b).abs().max()))
 
 
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("shp", [(1, 96, 800, 64, 10), (1, 224, 384, 64, 10), (2, 64, 416, 64, 10)])
+def test_wide_images_stay_inside_the_workspace(shp, dtype):
+    """Whole passes on images far from square, whose middle layers have rows too long for the direct-to-LDS kernels'
+    halo: forward pass and training step in a workspace with a guard behind it, against the chained single calls (each of
+    which sizes its own scratch), bit for bit."""
+    N, H, W, hidden, classes = shp
+    inp = synth.vgg19_inputs(N, H, W, hidden, classes, seed=H + W)
+    logits, loss, want = _step_from_single_op_calls(inp, dtype, *shp)
+    guard = 64 << 20
+    for training in (False, True):
+        m = Vgg19(dtype, *shp, lr=0.01, training=training)
+        m.pack(inp.conv_w, inp.conv_b, inp.fc_w, inp.fc_b)
+        n = m.ws.numel()
+        buf = torch.zeros((n + guard,), dtype=torch.uint8, device="cuda")
+        buf[n:] = 0xA5
+        m.ws = buf[:n]
+        got = None
+        if training:
+            got = m.train_step(dev(inp.x), dev(inp.labels), want_grads=True)
+        else:
+            m.forward(dev(inp.x))
+        torch.cuda.synchronize()
+        assert (buf[n:] == 0xA5).all()
+        if dtype == B.BF16 and not training:
+            # the forward pass runs the first two layers as one kernel, which adds the first layer's 27 products in
+            # another order: bf16 roundings of slightly different sums, held to the usual bound of a bf16 pass
+            assert max_rel_err(m.logits.cpu().numpy(), logits.cpu().numpy()) <= TOL[dtype]
+        else:
+            assert torch.equal(m.logits, logits)
+        if training:
+            assert torch.equal(m.loss, loss)
+            for k in ("conv_w", "conv_b", "fc_w", "fc_b"):
+                for l, (a, b) in enumerate(zip(got[k], want[k])):
+                    assert torch.equal(a, b), (k, l, float((a - b).abs().max()))
+
+
 def test_bf16_training_needs_the_master_copy():
     cfg = B.make_config(B.BF16, 2, 32, 32, 512, 10, 0.01)          # no master copy
     assert B.vgg19_train_workspace_bytes(cfg) == 0
