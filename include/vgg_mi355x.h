@@ -145,8 +145,9 @@ int vgg_convert(int src_dtype, int dst_dtype, size_t n, const void *src, void *d
  * compute units and a long contraction): VGG_F32: several workgroups then
  * share a tile, each summing a range of input channels into fp32 partial
  * results in the workspace, and a second kernel adds them in a fixed order
- * and applies bias and f (VGG_BF16 adds them inside a workgroup; the query
- * answers as for VGG_F32 all the same).  It returns 0 when neither applies. */
+ * and applies bias and f (VGG_BF16 adds up to eight ranges inside a workgroup
+ * and then leaves the partial results' space untouched; the query answers as
+ * for VGG_F32 all the same).  It returns 0 when neither applies. */
 size_t vgg_conv3x3_fwd_workspace_bytes(int dtype, int N, int H, int W, int Cin, int Cout);
 int vgg_conv3x3_fwd(int dtype, int N, int H, int W, int Cin, int Cout, const void *x_nhwc,
                     const void *w_packed, const float *bias, void *y_nhwc, int relu, void *ws,

@@ -1082,6 +1082,8 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
 constexpr int kSmallPx = 64;         // pixels per tile
 constexpr int kSmallHaloRows = 256;  // most halo rows of a tile (the launch picks patches where consecutive pixels need more)
 
+constexpr int kSmallRanges = 8;      // most ranges of the contraction
+
 template <int NJ, int G, bool TWO>   // TWO: waves may have two ranges
 __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs p)
 {
@@ -1477,7 +1479,7 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     if (c.ksplit > 1) {
         const TileGeom t = conv_small_geom(N, H, W, pool);
         const int tiles = t.ntiles * ((Cout + 31) / 32), G = tiles <= 256 && c.ksplit > 4 ? 8 : 4;
-        if (tiles <= (chunks >= 12 || Cout <= 64 ? 1024 : 512) && (!pool || t.mode == 1) && c.ksplit <= 8 && conv_small_lds(G, t.S, 1, c.ksplit) <= 160 * 1024) {
+        if (tiles <= (chunks >= 12 || Cout <= 64 ? 1024 : 512) && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, 1, c.ksplit) <= 160 * 1024) {
             c.g = t;
             c.kernel = G == 8 ? kSmall8 : kSmall4;
             c.bn = 32;
@@ -1492,10 +1494,10 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.
     // (that kernel's halo offsets inside a tile are 32 bits: at most 18 image rows of a patch, or 320 + 2 rows)
     const bool reach = (size_t)(20 * (size_t)W + 512) * CinP * sizeof(bf16_t) < ((size_t)1 << 32);
-    if (Cout <= 64 && c.ksplit > 1) {                   // (split over workgroups, as fp32)
-        if (wide) { c.ksplit = 1; c.kchunks = chunks; }
-        return c;
-    }
+    // Split over workgroups, as fp32: at most 64 output channels, or more ranges than a workgroup takes (576 input channels
+    // and up; on the tiles below a few workgroups would walk the whole contraction: 14x14 batch 1, 1024 -> 1024 20 us
+    // on 256 workgroups, 68 on 16; 7x7 batch 1, 2048 -> 512 20 / 130).
+    if (!wide && c.ksplit > 1 && (Cout <= 64 || c.ksplit > kSmallRanges)) return c;
     const int ksplit = c.ksplit, kchunks = c.kchunks;   // (of the kernels below only the 128-pixel tiles fold their sums)
     c.ksplit = 1; c.kchunks = chunks;
     if (Cout > 64 && (dma || dma_big) && reach && (!narrow || chunks >= 3 || wide_tiles >= 256)) {

@@ -230,3 +230,21 @@ def test_partial_sums_of_a_split_convolution_fit_what_the_query_asks_for():
     for n, h, w, ci, co in ((1, 56, 96, 256, 256), (1, 24, 200, 256, 256), (1, 97, 97, 128, 128)):
         assert B.vgg_conv3x3_plan(B.PLAN_FWD, B.F32, n, h, w, ci, co)[5] == 1
         assert B.vgg_conv3x3_fwd_workspace_bytes(B.F32, n, h, w, ci, co) == 0
+
+
+# Which kernel a bf16 convolution takes where a wrong line costs most: (N, H, W, Cin, Cout, kernels), on both sides of
+# each line of the rule.
+BF16_ROUTES = [
+    # more than eight ranges: over workgroups
+    (1, 14, 14, 512, 512, (13,)), (1, 14, 14, 576, 512, (1,)), (1, 14, 14, 1024, 1024, (1,)), (1, 7, 7, 2048, 512, (1,)),
+    (2, 12, 36, 768, 132, (1,)), (1, 63, 63, 1024, 192, (2,)), (3, 28, 28, 1024, 128, (1,)),
+]
+
+
+def test_bf16_convolution_routes():
+    for n, h, w, ci, co, kernels in BF16_ROUTES:
+        info = B.vgg_conv3x3_plan(B.PLAN_FWD, B.BF16, n, h, w, ci, co)
+        assert info[0] in kernels, (n, h, w, ci, co, info)
+        assert B.vgg_conv3x3_plan(B.PLAN_BWD_DATA, B.BF16, n, h, w, co, ci) == info
+        if info[0] in (1, 2) and info[5] > 1:
+            assert B.vgg_conv3x3_fwd_workspace_bytes(B.BF16, n, h, w, ci, co) >= info[5] * n * h * w * co * 4

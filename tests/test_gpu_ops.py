@@ -400,6 +400,32 @@ def test_conv3x3_bf16_small_and_medium_launches(shape, kernel):
     assert (buf[n:] == -7.0).all()
 
 
+@pytest.mark.parametrize("shape", [(1, 14, 14, 576, 512), (2, 7, 9, 1024, 200), (3, 20, 19, 768, 132), (2, 12, 36, 576, 72)])
+def test_conv3x3_bf16_split_over_workgroups(shape):
+    """More ranges than the waves of one workgroup share (more than 512 input channels): the ranges go to workgroups of
+    their own again.  Forward and masked data gradient against the oracle; without a workspace the call is refused."""
+    dtype = B.BF16
+    N, H, W, Cin, Cout = shape
+    plan = B.vgg_conv3x3_plan(B.PLAN_FWD, dtype, N, H, W, Cin, Cout)
+    assert plan[0] in (1, 2) and plan[5] > 8 and plan[6] == plan[4] * -(-Cout // 64) * plan[5]
+    d = synth.conv_layer_inputs(N, H, W, Cin, Cout, seed=sum(shape))
+    x = to_nhwc(d["x"], dtype)
+    y = torch.empty((N, H, W, Cout), dtype=TDT[dtype], device="cuda")
+    ws = ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(dtype, N, H, W, Cin, Cout))
+    B.vgg_conv3x3_fwd(dtype, N, H, W, Cin, Cout, x, _pack(dtype, d["w"]), dev(d["b"]), y, 1, ws)
+    torch.cuda.synchronize()
+    assert max_rel_err(from_nhwc(y), R.conv3x3_fwd(d["x"], d["w"], d["b"], relu=True)) <= TOL[dtype]
+    with pytest.raises(B.VggError):
+        B.vgg_conv3x3_fwd(dtype, N, H, W, Cin, Cout, x, _pack(dtype, d["w"]), dev(d["b"]), y, 1, None)
+    d = synth.conv_layer_inputs(N, H, W, Cout, Cin, seed=sum(shape) + 1)
+    assert B.vgg_conv3x3_plan(B.PLAN_BWD_DATA, dtype, N, H, W, Cout, Cin) == plan
+    xs = to_nhwc(d["x"], dtype)
+    ws = ws_bytes(B.vgg_conv3x3_bwd_data_workspace_bytes(dtype, N, H, W, Cout, Cin))
+    B.vgg_conv3x3_bwd_data(dtype, N, H, W, Cout, Cin, to_nhwc(d["dy"], dtype), _pack(dtype, d["w"], flip=1), xs, y, ws)
+    torch.cuda.synchronize()
+    assert max_rel_err(from_nhwc(y), R.conv3x3_bwd_data(d["dy"], d["w"]) * (from_nhwc(xs) > 0)) <= TOL[dtype]
+
+
 @pytest.mark.parametrize("shape", FULL_SIZE_LAYERS)
 def test_conv3x3_bf16_full_size_on_sampled_pixels(shape):
     """Forward and data gradient at the benchmark's sizes, in the launch configuration it times; the oracle
