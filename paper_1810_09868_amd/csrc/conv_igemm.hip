@@ -54,8 +54,7 @@ struct ConvArgs {
     float *part;        // [ksplit][M][Cout] partial sums when the contraction is split over workgroups, else null
     int ksplit;         // workgroups per tile (>= 1)
     int kchunks;        // channel chunks per workgroup
-    int halo_bufs;      // conv3x3_small_bf16_kernel: halo buffers per wave
-    FastDiv dTiles;     // ... division by the number of pixel tiles
+    FastDiv dTiles;     // conv3x3_small_bf16_kernel: division by the number of pixel tiles
     TileGeom g;
 };
 
@@ -1134,10 +1133,10 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
         const int row = lane + 64 * j;
         px[j] = row < p.g.S ? halo_pixel(p.g, org, row) : -1;
     }
-    const int bufs = p.rowsA * kDataBytes;                            // bytes of one halo buffer (rowsA a multiple of 16)
-    char *As = smem + wv * p.halo_bufs * bufs;                        // this wave's one or two buffers
+    const int bufs = p.rowsA * kDataBytes;                            // bytes of a halo buffer (rowsA a multiple of 16)
+    char *As = smem + wv * bufs;                                      // this wave's buffer
     const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)As);
-    auto copy = [&](int c, int buf) __attribute__((always_inline)) {
+    auto copy = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < 4 * MAXPX; ++k) {
             if (k * 16 < p.rowsA) {
@@ -1146,12 +1145,12 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
                 const int seg = (lane & 3) ^ ((row >> 1) & 3);
                 const char *src = pk < 0 ? reinterpret_cast<const char *>(kZeroRow) : p.x + (size_t)pk * xrow + (size_t)c * kDataBytes;
                 src += seg * 16;
-                const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + buf * bufs + k * 1024);
+                const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + k * 1024);
                 asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "m0", "memory");
             }
         }
     };
-    if (c_first < nchunks) copy(c_first, 0);
+    if (c_first < nchunks) copy(c_first);
 
     int hrow[NI];   // halo row of tap (0,0) of this lane's pixels: lane l finds tile row l's
     {
@@ -1180,19 +1179,16 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
         }
     };
     take();
-    int buf = 0;
     for (int c = c_first; c < nchunks;) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this chunk's halo has landed (and its weights)
         const int cn = next_of(c);
-        if (p.halo_bufs == 2 && cn < nchunks) copy(cn, buf ^ 1);
-        const char *A = As + buf * bufs;
 #pragma unroll
         for (int t = 0; t < TAPS; ++t) {
             bf16x8 a[NI];
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const int row = hrow[i] + (t / 3) * pitch + t % 3;
-                a[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(A + row * kDataBytes + ((g ^ (row >> 1)) & 3) * 16));
+                a[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(As + row * kDataBytes + ((g ^ (row >> 1)) & 3) * 16));
             }
 #pragma unroll
             for (int i = 0; i < NI; ++i)
@@ -1201,10 +1197,9 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bw[t][j]), a[i], acc[i][j], 0, 0, 0);
             if (cn < nchunks) load_w(cn, t);
         }
-        if (p.halo_bufs == 2) buf ^= 1;
-        else if (cn < nchunks) {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // (one buffer: this chunk's reads are done)
-            copy(cn, 0);
+        if (cn < nchunks) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // (this chunk's reads are done)
+            copy(cn);
         }
         if (c + 1 == c_first + p.kchunks && wv + G < p.ksplit) take();
         c = cn;
@@ -1279,10 +1274,11 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
     }
 }
 
-// LDS bytes of a launch with one or two halo buffers per wave
-static size_t conv_small_lds(int G, int S, int bufs, int ksplit)
+// LDS bytes of a launch.  One halo buffer per wave: a second one, copied a chunk ahead, never gained (5174 launches: 1.00
+// to 1.05 times the time) and cost up to 1.8 times where it left a CU one workgroup instead of two.
+static size_t conv_small_lds(int G, int S, int ksplit)
 {
-    const size_t halo = (size_t)G * bufs * round_up16(S) * kDataBytes, red = (size_t)ksplit * kSmallPx * (2 * 16 + 4) * 4;
+    const size_t halo = (size_t)G * round_up16(S) * kDataBytes, red = (size_t)ksplit * kSmallPx * (2 * 16 + 4) * 4;
     return halo > red ? halo : red;
 }
 template <int G>
@@ -1294,13 +1290,11 @@ static int launch_conv_small(const ConvArgs &a0, const TileGeom &g, hipStream_t 
     a.tiles_n = (a.Cout + NJ * 16 - 1) / (NJ * 16);
     a.rowsA = round_up16(g.S);
     a.dTiles = make_fast_div(g.ntiles);
-    // a second halo buffer when a wave has more than one chunk and it fits
-    a.halo_bufs = a.CinP / 32 > G && conv_small_lds(G, g.S, 2, a.ksplit) <= 160 * 1024 ? 2 : 1;
     auto kern = conv3x3_small_bf16_kernel<NJ, G, false>;
     if constexpr (G == 4)
         if (a.ksplit > G) kern = conv3x3_small_bf16_kernel<NJ, G, true>;
     if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return VGG_ERR_LAUNCH;
-    const size_t lds = conv_small_lds(G, g.S, a.halo_bufs, a.ksplit);
+    const size_t lds = conv_small_lds(G, g.S, a.ksplit);
     hipLaunchKernelGGL(kern, dim3((unsigned)(g.ntiles * a.tiles_n)), dim3(G * 64), lds, stream, a);
     return launch_status();
 }
@@ -1479,7 +1473,7 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     if (c.ksplit > 1) {
         const TileGeom t = conv_small_geom(N, H, W, pool);
         const int tiles = t.ntiles * ((Cout + 31) / 32), G = tiles <= 256 && c.ksplit > 4 ? 8 : 4;
-        if (tiles <= (chunks >= 12 || Cout <= 64 ? 1024 : 512) && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, 1, c.ksplit) <= 160 * 1024) {
+        if (tiles <= (chunks >= 12 || Cout <= 64 ? 1024 : 512) && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, c.ksplit) <= 160 * 1024) {
             c.g = t;
             c.kernel = G == 8 ? kSmall8 : kSmall4;
             c.bn = 32;
