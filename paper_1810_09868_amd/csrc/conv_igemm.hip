@@ -1465,15 +1465,21 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     }
     // bf16.  Shapes whose contraction is split (conv_split) form the same partial sums and add them in the same order,
     // but inside a workgroup.  Few tiles: the waves of a workgroup share the ranges (64 x 32 tiles; eight waves where
-    // every CU gets at most one workgroup).  Measured against the best of the other kernels (us): 512 -> 512 at 14x14,
-    // batch 1 (128 tiles) 9.3 / 13.5; at 28x28, batch 1 (224) 10.1 / 19.3, batch 2 (448) 15.1 / 22; batch 4 (896)
-    // 28 / 35 against 256 -> 512 there 17.4 / 15.4: the line lies at 512 tiles, at 1024 for long contractions
-    // (at most 64 output channels have no 128-wide tile to go to).
+    // every CU gets at most one workgroup).  Against the split over workgroups, over 2430 launches: up to 256 tiles 0.14
+    // to 0.95 of its time; up to 512 (two to a CU, what the LDS holds) 0.6 to 0.97 while a wave walks at most six chunks,
+    // 0.9 to 1.4 beyond; up to 1024 0.7 to 1.05 with one range of at most four chunks per wave, 1.05 to 1.7 with two.
+    // (512 -> 512 at 14x14, batch 1, 9.1 us instead of 13.4; at 28x28, batch 1, 9.9 / 19.3, batch 2 16.7 / 22.7.)  At 8
+    // chunks, more than 64 output channels and more than 512 tiles the 128-pixel tiles below are faster still (256 -> 512
+    // at 28x28, batch 4: 15.4 us, 17.4 here).
     if (!pool || !conv3x3_pool_fusable(dtype, H, W, Cout)) conv_split(dtype, c.g, CinP, Cout, c.ksplit, c.kchunks);
     if (c.ksplit > 1) {
         const TileGeom t = conv_small_geom(N, H, W, pool);
         const int tiles = t.ntiles * ((Cout + 31) / 32), G = tiles <= 256 && c.ksplit > 4 ? 8 : 4;
-        if (tiles <= (chunks >= 12 || Cout <= 64 ? 1024 : 512) && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, c.ksplit) <= 160 * 1024) {
+        const int chain = (c.ksplit + G - 1) / G * c.kchunks;   // chunks that a wave walks
+        // (wide images have no other split to go to)
+        const bool few = tiles <= 256 || (tiles <= 512 && (wide || chain <= 6)) ||
+                         (tiles <= 1024 && (chunks > 8 || Cout <= 64) && (wide ? chunks >= 12 || Cout <= 64 : c.ksplit <= G && chain <= 4));
+        if (few && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, c.ksplit) <= 160 * 1024) {
             c.g = t;
             c.kernel = G == 8 ? kSmall8 : kSmall4;
             c.bn = 32;
@@ -1488,10 +1494,10 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.
     // (that kernel's halo offsets inside a tile are 32 bits: at most 18 image rows of a patch, or 320 + 2 rows)
     const bool reach = (size_t)(20 * (size_t)W + 512) * CinP * sizeof(bf16_t) < ((size_t)1 << 32);
-    // Split over workgroups, as fp32: at most 64 output channels, or more ranges than a workgroup takes (576 input channels
-    // and up; on the tiles below a few workgroups would walk the whole contraction: 14x14 batch 1, 1024 -> 1024 20 us
-    // on 256 workgroups, 68 on 16; 7x7 batch 1, 2048 -> 512 20 / 130).
-    if (!wide && c.ksplit > 1 && (Cout <= 64 || c.ksplit > kSmallRanges)) return c;
+    // Split over workgroups, as fp32: at most 64 output channels, or a contraction of more than 8 chunks (on the tiles
+    // below a few workgroups would walk all of it: 14x14 batch 1, 1024 -> 1024 20 us on 256 workgroups, 68 on 16; 7x7 batch 1,
+    // 2048 -> 512 20 / 130; 50x66 batch 1, 1024 -> 512 48 / 69; at 8 chunks 0.61 to 1.02 of its time there).
+    if (!wide && c.ksplit > 1 && (Cout <= 64 || chunks > 8)) return c;
     const int ksplit = c.ksplit, kchunks = c.kchunks;   // (of the kernels below only the 128-pixel tiles fold their sums)
     c.ksplit = 1; c.kchunks = chunks;
     if (Cout > 64 && (dma || dma_big) && reach && (!narrow || chunks >= 3 || wide_tiles >= 256)) {

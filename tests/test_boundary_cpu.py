@@ -238,6 +238,13 @@ BF16_ROUTES = [
     # more than eight ranges: over workgroups
     (1, 14, 14, 512, 512, (13,)), (1, 14, 14, 576, 512, (1,)), (1, 14, 14, 1024, 1024, (1,)), (1, 7, 7, 2048, 512, (1,)),
     (2, 12, 36, 768, 132, (1,)), (1, 63, 63, 1024, 192, (2,)), (3, 28, 28, 1024, 128, (1,)),
+    # the small kernel: up to 512 tiles with short chains per wave, up to 1024 with one short range per wave
+    (10, 14, 14, 512, 512, (12,)), (12, 14, 14, 512, 512, (1,)), (5, 30, 33, 768, 256, (1,)), (21, 12, 36, 576, 128, (1,)),
+    (8, 12, 36, 1024, 320, (1,)), (19, 5, 50, 1024, 132, (2,)), (7, 53, 52, 768, 8, (2,)), (15, 5, 50, 384, 512, (12,)),
+    (2, 28, 28, 512, 512, (12,)), (30, 28, 28, 256, 36, (12,)), (3, 36, 100, 1024, 128, (12,)),
+    # 128-pixel tiles that fold the ranges' sums: eight chunks
+    (4, 28, 28, 256, 516, (8,)), (2, 56, 56, 256, 256, (9,)), (5, 28, 28, 576, 512, (1,)), (1, 50, 66, 1024, 512, (2,)),
+    (13, 38, 16, 1024, 256, (1,)),
 ]
 
 
