@@ -1487,11 +1487,13 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         }
     }
     // Weights in registers: more than 64 output channels, and a contraction of at least three chunks unless
-    // there is a tile for every CU (below that the 64-wide direct-to-LDS launch is as fast).  The tile by the time of the CU with most of them, in units of
-    // a 256-pixel tile's (one wave per SIMD multiplies nearly as fast as two, so a CU's tiles simply add up):
-    // 320 pixels cost 1.25, 128 pixels 0.56.  Measured (us) for 512 channels, 256 / 320 / 128 pixels: 28x28 batch
-    // 10 (124, 100, 248 tiles) 44 / 54 / 35, batch 16 (196, 160, 392) 46 / 55 / 50, batch 32 (392, 316, 784) 88 /
-    // 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.
+    // there is a tile for every CU (below that the 64-wide direct-to-LDS launch is as fast).  The tile by the time of the
+    // CU with most of them, in units of a 256 x 128 tile's (one wave per SIMD multiplies nearly as fast as two, so a CU's
+    // tiles simply add up): 320 pixels cost 1.25, 128 pixels 0.56, 64-wide direct-to-LDS tiles 0.6.  Measured (us) for 512
+    // channels, 256 / 320 / 128 pixels: 28x28 batch 10 (124, 100, 248 tiles) 44 / 54 / 35, batch 16 (196, 160, 392) 46 /
+    // 55 / 50, batch 32 (392, 316, 784) 88 / 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.  64-wide tiles win
+    // where the channels fill a last 128-wide column by half or less: 28x36x20, 96 -> 132 20 us, 27 on 128-wide ones;
+    // 53x56 batch 12, 96 -> 192 19 / 25.
     // (that kernel's halo offsets inside a tile are 32 bits: at most 18 image rows of a patch, or 320 + 2 rows)
     const bool reach = (size_t)(20 * (size_t)W + 512) * CinP * sizeof(bf16_t) < ((size_t)1 << 32);
     // Split over workgroups, as fp32: at most 64 output channels, or a contraction of more than 8 chunks (on the tiles
@@ -1501,17 +1503,22 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     const int ksplit = c.ksplit, kchunks = c.kchunks;   // (of the kernels below only the 128-pixel tiles fold their sums)
     c.ksplit = 1; c.kchunks = chunks;
     if (Cout > 64 && (dma || dma_big) && reach && (!narrow || chunks >= 3 || wide_tiles >= 256)) {
-        c.kernel = dma ? kWreg : kWregBig;
-        c.bn = 128;
-        if (!narrow) return c;
         auto rounds = [](int tiles) { return (tiles + 255) / 256; };
         float best = (float)rounds(wide_tiles);
+        if (narrow && ksplit == 1 && 0.6f * rounds(c.g.ntiles * ((Cout + 63) / 64)) < best)
+            best = 0.6f * rounds(c.g.ntiles * ((Cout + 63) / 64));
+        else {
+            c.kernel = dma ? kWreg : kWregBig;
+            c.bn = 128;
+        }
+        if (!narrow) return c;
         if (!pool) {
             const TileGeom t = make_tile_geom(N, H, W, 320);
             const float cost = 1.25f * rounds(t.ntiles * cols);
             if (t.S <= kWregHaloRowsBig && cost < best) {
                 best = cost;
                 c.g = t;
+                c.bn = 128;
                 c.kernel = t.S <= kWregHaloRows ? kWregTall : kWregTallBig;
             }
         }
@@ -1519,6 +1526,7 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         const int tiles = t.ntiles * cols;
         if (t.S <= kWregHaloRows && 0.56f * rounds(tiles) < best) {
             c.g = t;
+            c.bn = 128;
             const bool big = t.S > kWregHaloRowsHalf;
             // (one tile per CU, alone there: with two taps of weights ahead each tap waits for L2; nine taps ahead
             // 36 -> 31.6 at 28x28 batch 10, 35 -> 27.4 at 14x14 batch 32; no gain on eight chunks)

@@ -245,6 +245,9 @@ BF16_ROUTES = [
     # 128-pixel tiles that fold the ranges' sums: eight chunks
     (4, 28, 28, 256, 516, (8,)), (2, 56, 56, 256, 256, (9,)), (5, 28, 28, 576, 512, (1,)), (1, 50, 66, 1024, 512, (2,)),
     (13, 38, 16, 1024, 256, (1,)),
+    # 64-wide tiles where the last 128-wide column would be half empty
+    (28, 36, 20, 96, 132, (1,)), (12, 53, 56, 96, 192, (2,)), (8, 56, 56, 192, 320, (2,)), (17, 30, 33, 384, 132, (1,)),
+    (28, 36, 20, 96, 256, (4,)), (8, 56, 56, 192, 256, (5,)), (40, 28, 28, 256, 192, (4,)),
 ]
 
 
