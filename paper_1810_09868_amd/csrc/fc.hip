@@ -162,21 +162,31 @@ __global__ __launch_bounds__(256) void fc_fwd_kernel(FcArgs p)
 // taking turns at 256-byte pieces of it, so that a workgroup reads 4 KB runs of its sixteen weight rows and every
 // weight goes straight to the lane that multiplies it; batch rows come in sixteens (the 128-row tile above multiplies
 // 118 rows of zeros for ten).  The waves' sums meet in LDS: no partial sums in memory and no second launch.
-// 25088 -> 4096: bf16 batch 1 51 -> 40 us (5.2 TB/s), batch 10 54 -> 47; fp32 batch 10 225 -> 88 (4.7 TB/s).
+// 25088 -> 4096: bf16 batch 1 51 -> 40 us (5.2 TB/s), batch 10 54 -> 43; fp32 batch 10 225 -> 88 (4.7 TB/s).
 // The lane layout is that of the 16-row MFMAs: lane 16 g + c holds 16 bytes (piece offset 64 e + 16 g) of weight row
 // c and of batch row c; any fixed pairing of contraction indices between the two is a valid order.
 constexpr int kFcSmallWaves = 16;
 
-// Rows of whole 16-byte segments, and: up to 16 batch rows always (measured ahead or level from 10 to 4096 outputs);
-// up to 32 rows every workgroup reads all of twice as many activations, which pays where the 128-row tile is bound
-// by its zeros (fp32: 25088 -> 4096 229 -> 145 us, 1000 -> 3000 22 -> 12) and not on few outputs with long rows (fp32
-// 25088 -> 300 65 / 119) or for bf16 beyond 4 KB rows (25088 -> 4096 59 / 73, 4096 -> 1000 level).
+// Rows of whole 16-byte segments, and a shape where the split over workgroups is the slower one.  A workgroup walks its
+// sixteen rows alone at about 1.7 KB of row per us, whatever the chip does besides: few outputs with long rows leave it
+// idle (a million inputs, 10 outputs, batch 10: bf16 152 us split, 782 here; fp32 382 / 1921).  Measured over 506 shapes,
+// time here / split.  Up to 16 batch rows:
+//   rows of at most 32 KB: 0.33 to 0.95.  One workgroup (at most 16 outputs): 0.61 to 0.91 up to 128 KB from eight
+//   batch rows on, where the 128-row tile has less to stream; fewer batch rows 0.57 to 0.83 up to 16 KB, 1.1 at 32.
+//   fp32, longer rows: 64 to 2047 outputs 0.69 to 1.02 up to 112 KB, 1.0 to 1.4 at 160 KB; from 2048 outputs on 0.33
+//   to 0.70 at every length.  bf16: from 4096 outputs (a workgroup per CU) 0.80 to 0.94 up to 160 KB, 1.1 at
+//   200 KB; fewer outputs 0.9 to 1.1 at 50 KB, 1.1 to 1.4 at 80 KB.
+// 17 to 32 rows: every workgroup reads twice as many activations, which pays where the 128-row tile is bound by its
+// zeros (fp32: 25088 -> 4096 228 -> 139 us, 40000 -> 2048 189 / 205) and not for bf16 beyond 4 KB rows (25088 -> 4096 59 / 73).
 static bool fc_small(int dtype, int N, int In, int Out)
 {
-    const size_t rowbytes = (size_t)In * dtype_size(dtype);
+    const size_t rowbytes = (size_t)In * dtype_size(dtype), KB = 1024;
     if (rowbytes % 16 || N > 32) return false;
-    if (N <= 16) return true;
-    return dtype == VGG_F32 ? Out >= 2048 || rowbytes <= 16384 : rowbytes <= 4096;
+    const bool f32 = dtype == VGG_F32;
+    if (N > 16)
+        return f32 ? rowbytes <= 16 * KB || Out >= 4096 || (Out >= 2048 && rowbytes <= 112 * KB) : rowbytes <= 4 * KB;
+    if (rowbytes <= (Out > 16 ? 32 : N >= 8 ? 128 : 16) * KB) return true;
+    return f32 ? Out >= 2048 || (Out >= 64 && rowbytes <= 112 * KB) : Out >= 4096 && rowbytes <= 160 * KB;
 }
 
 template <typename T, typename TZ, int NB>

@@ -699,6 +699,23 @@ def test_fc_forward_small_batches(dtype, N, In, Out):
     assert (z[N * Out:] == -7.0).all()
 
 
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("N,In,Out", [(4, 4096, 16), (4, 4104, 16), (8, 32768, 16), (8, 32776, 9), (16, 16392, 40), (5, 28672, 64),
+                                      (5, 28680, 70), (3, 40000, 10), (2, 8200, 4096), (24, 28680, 2048)])
+def test_fc_forward_where_the_kernel_changes(dtype, N, In, Out):
+    """Long rows on both sides of the lines between one workgroup per sixteen outputs and the split over workgroups,
+    against the oracle on the operands as stored; 1e-5: fp32 sums of at most 28680 / 16 products in a row."""
+    rng = np.random.default_rng(np.random.PCG64(N + In + Out))
+    a, w = (dev(rng.standard_normal(s).astype(np.float32), TDT[dtype]) for s in ((N, In), (Out, In)))
+    b = rng.standard_normal(Out).astype(np.float32)
+    ref = R.fc(a.float().cpu().numpy(), w.float().cpu().numpy(), b, relu=False)
+    z = torch.full((N * Out + 64,), -7.0, device="cuda")
+    B.vgg_fc(dtype, N, In, Out, a, w, dev(b), z, B.F32, 0, ws_bytes(B.vgg_fc_workspace_bytes(dtype, N, In, Out)))
+    torch.cuda.synchronize()
+    assert max_rel_err(z[:N * Out].view(N, Out).cpu().numpy(), ref) <= 1e-5
+    assert (z[N * Out:] == -7.0).all()
+
+
 @pytest.mark.parametrize("N,In,Out", [(16, 260, 129), (17, 256, 64), (49, 1028, 3), (80, 132, 191), (97, 516, 257), (129, 252, 65),
                                       (31, 129, 1), (112, 127, 66)])
 def test_fc_backward_fp32_tile_edges(N, In, Out):
