@@ -102,9 +102,11 @@ int maxpool2x2_bwd(int dtype, int N, int H, int W, int C, const void *dy, const 
 
 // ----------------------------------------------------------------- softmax
 // Maximum, sum of exponentials and normalisation per row (listing "softmax").  Rows of up to 4096 values are read
-// once and stay in registers: a wavefront per row up to 256 values, a workgroup per row beyond.  Bound by the launch
-// and the reductions.  100 rows of 1000: 9.1 us before (one wavefront walked each row three times, sixteen
-// dependent loads a time).  V: values per thread, 0: longer rows, read three times.
+// once and stay in registers: a wavefront per row up to 512 values, a workgroup per row beyond.  Bound by the launch
+// and the reductions, many rows by memory.  100 rows of 1000: 9.1 us before (one wavefront walked each row three times, sixteen
+// dependent loads a time).  V: values per thread, 0: longer rows, read three times.  (A workgroup per row of 257 to
+// 512 values leaves most of its threads without one: 100000 rows of 300 90 us, 37 on a
+// wavefront each.)
 template <int WAVES>   // of the row: 1 or 4 (red: 4 floats of LDS, not used again by the caller)
 __device__ __forceinline__ float row_max(float v, float *red)
 {
@@ -186,6 +188,7 @@ int softmax_rows(int N, int K, const float *z, float *p, hipStream_t s)
 {
     const dim3 block(256), rows((unsigned)N), quads((unsigned)(((size_t)N + 3) / 4));
     if (K <= 256) hipLaunchKernelGGL((softmax_kernel<1, 4>), quads, block, 0, s, z, p, N, K);
+    else if (K <= 512) hipLaunchKernelGGL((softmax_kernel<1, 8>), quads, block, 0, s, z, p, N, K);
     else if (K <= 1024) hipLaunchKernelGGL((softmax_kernel<4, 4>), rows, block, 0, s, z, p, N, K);
     else if (K <= 4096) hipLaunchKernelGGL((softmax_kernel<4, 16>), rows, block, 0, s, z, p, N, K);
     else hipLaunchKernelGGL((softmax_kernel<4, 0>), rows, block, 0, s, z, p, N, K);

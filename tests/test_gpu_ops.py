@@ -765,7 +765,7 @@ def test_softmax_xent_sgd(shape):
     assert np.abs(th.cpu().numpy() - ref).max() <= 1e-6
 
 
-@pytest.mark.parametrize("shape", [(301, 256), (7, 257), (3, 1024), (3, 1025), (2, 4096), (2, 4097)])
+@pytest.mark.parametrize("shape", [(301, 256), (7, 257), (303, 300), (5, 512), (5, 513), (3, 1024), (3, 1025), (2, 4096), (2, 4097)])
 def test_softmax_xent_at_the_row_lengths_where_the_kernel_changes(shape):
     test_softmax_xent_sgd(shape)
 
