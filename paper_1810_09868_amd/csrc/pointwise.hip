@@ -184,11 +184,16 @@ __global__ __launch_bounds__(256) void xent_bwd_kernel(const float *__restrict__
     for (int k = threadIdx.x % tpr; k < K; k += tpr) dz[row * K + k] = (p[row * K + k] - (k == y ? 1.f : 0.f)) * invN;
 }
 
+// Most workgroups of 256 threads in a launch (threads along x are counted in 32 bits): beyond as many rows a workgroup
+// per row is not possible, a wavefront per row still is.
+constexpr unsigned kMaxBlocks = 0xffffffffu / 256;
+
 int softmax_rows(int N, int K, const float *z, float *p, hipStream_t s)
 {
     const dim3 block(256), rows((unsigned)N), quads((unsigned)(((size_t)N + 3) / 4));
     if (K <= 256) hipLaunchKernelGGL((softmax_kernel<1, 4>), quads, block, 0, s, z, p, N, K);
     else if (K <= 512) hipLaunchKernelGGL((softmax_kernel<1, 8>), quads, block, 0, s, z, p, N, K);
+    else if ((unsigned)N > kMaxBlocks) hipLaunchKernelGGL((softmax_kernel<1, 0>), quads, block, 0, s, z, p, N, K);
     else if (K <= 1024) hipLaunchKernelGGL((softmax_kernel<4, 4>), rows, block, 0, s, z, p, N, K);
     else if (K <= 4096) hipLaunchKernelGGL((softmax_kernel<4, 16>), rows, block, 0, s, z, p, N, K);
     else hipLaunchKernelGGL((softmax_kernel<4, 0>), rows, block, 0, s, z, p, N, K);
@@ -197,9 +202,12 @@ int softmax_rows(int N, int K, const float *z, float *p, hipStream_t s)
 
 int softmax_xent_bwd(int N, int K, const float *p, const int32_t *labels, float *loss, float *dz, hipStream_t s)
 {
-    const int tpr = K <= 256 ? 64 : 256;
-    const unsigned row_blocks = dz ? (unsigned)(((size_t)N * tpr + 255) / 256) : 0u, blocks = row_blocks + (loss ? 1u : 0u);
-    if (blocks) hipLaunchKernelGGL(xent_bwd_kernel, dim3(blocks), dim3(256), 0, s, p, labels, loss, dz, N, K, tpr, row_blocks);
+    const int tpr = K <= 256 || (unsigned)N >= kMaxBlocks ? 64 : 256;
+    const unsigned row_blocks = dz ? (unsigned)(((size_t)N * tpr + 255) / 256) : 0u;
+    const bool joint = loss && row_blocks < kMaxBlocks;   // (the loss's workgroup fits the rows' launch)
+    if (row_blocks + joint)
+        hipLaunchKernelGGL(xent_bwd_kernel, dim3(row_blocks + joint), dim3(256), 0, s, p, labels, loss, dz, N, K, tpr, row_blocks);
+    if (loss && !joint) hipLaunchKernelGGL(xent_bwd_kernel, dim3(1), dim3(256), 0, s, p, labels, loss, dz, N, K, tpr, 0u);
     return launch_status();
 }
 

@@ -770,6 +770,47 @@ def test_softmax_xent_at_the_row_lengths_where_the_kernel_changes(shape):
     test_softmax_xent_sgd(shape)
 
 
+def test_softmax_xent_with_more_rows_than_a_launch_has_workgroups():
+    """2^24 rows: one more than a launch of a workgroup per row can have.  Softmax of 513 classes and the loss and
+    gradient of 257, on rows that repeat a few patterns; the gradient alone of as many rows as a wavefront per row allows."""
+    N = 1 << 24
+    if torch.cuda.mem_get_info()[0] < 90 << 30:
+        pytest.skip("needs 90 GB of device memory")
+    rng = np.random.default_rng(24)
+    for K in (513, 257):
+        pat = (rng.standard_normal((64, K)) * 2).astype(np.float32)
+        z = dev(pat).repeat(N // 64, 1)
+        p = torch.empty_like(z)
+        B.vgg_softmax(N, K, z, p)
+        torch.cuda.synchronize()
+        ref = R.softmax(pat)
+        for r in (0, N // 2, N - 64):
+            assert max_rel_err(p[r:r + 64].cpu().numpy(), ref) <= 1e-5
+        if K == 257:
+            labels = torch.from_numpy(rng.integers(0, K, size=64).astype(np.int32)).cuda().repeat(N // 64)
+            loss = torch.zeros((1,), device="cuda")
+            B.vgg_softmax_xent_bwd(N, K, p, labels, loss, z, ws_bytes(N * 4))
+            torch.cuda.synchronize()
+            loss_ref, dz_ref = R.softmax_xent(ref, labels[:64].cpu().numpy())
+            # one lane adds 2^16 terms of about equal size one after another: at most 2^16 x 2^-24 of the sum
+            assert abs(loss.item() - loss_ref) <= 4e-3 * abs(loss_ref)
+            for r in (0, N // 2, N - 64):
+                assert max_rel_err(z[r:r + 64].cpu().numpy() * (N / 64), dz_ref) <= 1e-6
+        del z, p
+        torch.cuda.empty_cache()
+    N, K = (1 << 26) - 4, 2
+    p = torch.full((N, K), 0.5, device="cuda")
+    labels = torch.ones((N,), dtype=torch.int32, device="cuda")
+    dz = torch.empty_like(p)
+    loss = torch.zeros((1,), device="cuda")
+    B.vgg_softmax_xent_bwd(N, K, p, labels, loss, dz, ws_bytes(N * 4))
+    torch.cuda.synchronize()
+    for r in (0, N // 3, N - 1):
+        assert torch.equal((dz[r] * N).round(decimals=5).cpu(), torch.tensor([0.5, -0.5]))
+    assert 0.6 < loss.item() < 0.8      # log 2, to the precision of that many equal terms in fp32
+    torch.cuda.empty_cache()
+
+
 def test_layout_roundtrip_and_convert():
     rng = np.random.default_rng(9)
     x = rng.standard_normal((2, 3, 6, 10)).astype(np.float32)
