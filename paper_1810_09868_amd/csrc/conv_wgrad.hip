@@ -511,17 +511,19 @@ void wgrad_launch_reduce(const float *part, float *out, size_t n, const float *p
 
 // Patch width of the general kernel for an image size, 0: linear tiles.  16 or 14 where the image width divides into
 // patches (the last patch row of an image may stick out at the bottom: at most three rows of zeros); otherwise the one
-// of the two that pads less, when the padding costs less than what linear tiles pay: their halo (S rows for 64
-// pixels against 96 to 108, all of them copied) and 15 % for fetching halo rows across lanes.  64 -> 128 at 50x66, batch 10
-// (205 halo rows; patches pad by 10 %): 90 -> 69 us.
+// of the two that pads less, when it takes at most 1.3 times the linear tiles: a patch costs 0.65 to 0.85 of a
+// linear tile (whose halo is 110 to 500 rows for 64 pixels against 96 to 108, all of them copied, and has to be fetched
+// across lanes), but every one of them is multiplied whole and, with a workgroup of its own, adds a partial result.  Over 251 shapes:
+// up to 1.3 times the tiles 0.83 of the time on average, 1.13 at most; beyond 1.00 on average and 0.73 to 1.44 (24x41x12,
+// 256 -> 192 118 / 171 us).  64 -> 128 at 50x66, batch 10 (205 halo rows; 650 patches for 516 tiles): 90 -> 69 us.
 static int wgrad_patch_width(int N, int H, int W)
 {
     if (H < 4) return 0;
     if (W % 16 == 0) return 16;
     if (W % 14 == 0) return 14;
     const int p16 = (W + 15) / 16 * 16, p14 = (W + 13) / 14 * 14, tw = p14 < p16 ? 14 : 16;
-    const double padded = (double)(p14 < p16 ? p14 : p16) * ((H + 3) / 4 * 4) / ((double)W * H);
-    return padded < 1.15 * make_tile_geom(N, H, W, kPK).S / (6 * (tw + 2)) ? tw : 0;
+    const long patches = (long)N * ((W + tw - 1) / tw) * ((H + 3) / 4), tiles = ((long)N * H * W + kPK - 1) / kPK;
+    return patches * 10 <= tiles * 13 ? tw : 0;
 }
 
 static void wgrad_plan(int N, int H, int W, int CinP, int Cout, WgradArgs &a, bool thin = false)

@@ -511,8 +511,8 @@ def test_conv3x3_bwd_weight_bf16_on_8x8_patches(shape):
     _check_bwd_weight(B.BF16, shape, seed=sum(shape) + 5)
 
 
-@pytest.mark.parametrize("shape,kernel", [((3, 50, 66, 40, 72), 114), ((2, 9, 100, 16, 64), 116), ((1, 45, 60, 96, 36), 116),
-                                          ((2, 5, 31, 24, 68), 116), ((3, 13, 11, 64, 64), 100), ((2, 3, 130, 32, 64), 100)])
+@pytest.mark.parametrize("shape,kernel", [((3, 50, 66, 40, 72), 114), ((3, 8, 100, 16, 64), 116), ((1, 45, 60, 96, 36), 116), ((2, 9, 100, 16, 64), 100),
+                                          ((2, 8, 31, 24, 68), 116), ((2, 5, 31, 24, 68), 100), ((3, 13, 11, 64, 64), 100), ((2, 3, 130, 32, 64), 100)])
 def test_conv3x3_bwd_weight_fp32_patches_that_stick_out(shape, kernel):
     """fp32 weight gradient on patches that the image does not divide into (both widths), and sizes next to the line
     that keep linear tiles, against the oracle."""
