@@ -412,10 +412,14 @@ void wgrad_bf16_plan(int N, int H, int W, int CinP, int Cout, WgradBf16Args &a)
     // One round of two resident workgroups per CU.  Every workgroup writes 9 x 64 x 64 partial sums that the
     // reduction reads back, 75 MB each way for 512 workgroups whatever the layer: a second round of
     // workgroups (for balance) doubled that and measured 11 % slower over the whole stack.
+    // The split is that of 4 x 16 patches, and 8 x 8 ones take as many tiles fewer per workgroup as they are fewer in all:
+    // never more workgroups or partial sums.  (Split for themselves, 63 instead of 65 tiles an image made 516 workgroups
+    // of 510, a second round: 50x66 batch 30, 96 -> 192 63 -> 88 us; or twice the partial sums: batch 2, 200 -> 8 20 -> 25.)
     int splits = (512 + groups - 1) / groups;
-    if (splits > a.ntiles) splits = a.ntiles;
+    if (splits > N * t16) splits = N * t16;
     if (splits < 1) splits = 1;
-    a.tiles_per_split = (a.ntiles + splits - 1) / splits;
+    a.tiles_per_split = (N * t16 + splits - 1) / splits;
+    if (a.tw == 8) a.tiles_per_split = (int)(((long)a.tiles_per_split * t8 + t16 - 1) / t16);
     a.splits = (a.ntiles + a.tiles_per_split - 1) / a.tiles_per_split;
     a.narrow = CinP <= kCI / 2;
 }

@@ -261,3 +261,22 @@ def test_bf16_convolution_routes():
         assert B.vgg_conv3x3_plan(B.PLAN_BWD_DATA, B.BF16, n, h, w, co, ci) == info
         if info[0] in (1, 2) and info[5] > 1:
             assert B.vgg_conv3x3_fwd_workspace_bytes(B.BF16, n, h, w, ci, co) >= info[5] * n * h * w * co * 4
+
+
+def test_bf16_weight_gradient_on_8x8_patches_takes_no_more_workgroups():
+    # 8x8 patches are taken where they are fewer; what the launch and the reduction then do must not grow: no more
+    # workgroups and no more partial results than 4x16 patches split over one round of two workgroups per compute unit.
+    fewer = 0
+    for n in (1, 2, 3, 5, 9, 11, 26, 30, 52, 100):
+        for h, w in ((50, 66), (81, 81), (97, 97), (20, 19), (40, 120), (56, 56), (7, 7), (30, 33), (5, 50), (24, 200), (33, 6)):
+            for ci, co in ((16, 192), (32, 64), (64, 64), (96, 192), (200, 8), (256, 256), (768, 256)):
+                t16, t8 = -(-w // 16) * -(-h // 4), -(-w // 8) * -(-h // 8)
+                info = B.vgg_conv3x3_plan(B.PLAN_BWD_WEIGHT, B.BF16, n, h, w, ci, co)
+                assert info[4] == n * min(t8, t16)
+                groups = -(-co // 64) * -(-B.vgg_padded_channels(B.BF16, ci) // 64)
+                splits = min(-(-512 // groups), n * t16)
+                splits = -(-n * t16 // -(-n * t16 // splits))
+                assert info[6] <= groups * splits, (n, h, w, ci, co, info)
+                assert info[5] <= splits * (2 if info[0] == 117 else 1)
+                fewer += t8 < t16
+    assert fewer > 100
