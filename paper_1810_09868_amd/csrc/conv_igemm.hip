@@ -662,7 +662,7 @@ __global__ __launch_bounds__(WM *WN * 64, WM *WN == 8 ? 4 : 3) void conv3x3_igem
 // wave is not multiplying.
 // All vector-memory waits are written by hand (the loads are inline assembly), counting the loads and
 // copies issued since the one waited for; the schedule is static, so the counts are constants.  A variant must
-// not spill: a load in flight over a spilled register would be lost.
+// not spill: a load in flight over a spilled register would be lost (the build refuses one that does).
 // The result leaves from registers, also pooled or masked: 128 -> 128 at 112x112, batch 32, masked 139 -> 130 us
 // against the transposing pass through LDS.
 // ---------------------------------------------------------------------------

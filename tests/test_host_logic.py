@@ -50,3 +50,19 @@ def test_oracle_routines_under_host_sanitizers(tmp_path):
     out = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
     assert not _has_sanitizer_report(out.stderr)
+
+
+def test_build_refuses_a_spilling_variant_of_a_kernel_with_loads_in_flight():
+    from paper_1810_09868_amd import build as b
+    remark = "x.hip:1:1: remark: %s [-Rpass-analysis=kernel-resource-usage]\n"
+
+    def kernel(name, scratch, spills):
+        return "".join(remark % t for t in ("Function Name: " + name, "    ScratchSize [bytes/lane]: %d" % scratch,
+                                            "    SGPRs Spill: 9", "    VGPRs Spill: %d" % spills))
+
+    k = "conv3x3_igemm_wreg_kernel"
+    clean = kernel("_ZN" + k + "ILi2E", 0, 0) + kernel("_ZN5other", 64, 12) + kernel("_ZN" + k + "ILi3E", 0, 0)
+    assert b.spilling_kernels(clean, k) == (2, [])
+    assert b.spilling_kernels(clean + kernel("_ZN" + k + "ILi4E", 0, 3), k) == (3, ["_ZN" + k + "ILi4E"])
+    assert b.spilling_kernels(clean + kernel("_ZN" + k + "ILi5E", 16, 0), k) == (3, ["_ZN" + k + "ILi5E"])
+    assert k in open(os.path.join(b.CSRC, "conv_igemm.hip")).read() and b.NO_SPILLS == {"conv_igemm.hip": k}
