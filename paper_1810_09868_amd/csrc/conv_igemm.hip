@@ -1057,9 +1057,9 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
                 const int col = n0 + wn * 64 + (j + (ge & 1)) * 16 + (ge >> 1) * 8;
                 if (in && col < p.Cout) {
                     *reinterpret_cast<u32x4 *>(pool + at + col) = v;
-                    if (p.argmax) {
-                        typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
-                        *reinterpret_cast<u32x2_t *>(p.argmax + at + col) = u32x2_t{sw[0], sw[1]};
+                    if (p.argmax) {   // (bytes, of any alignment)
+                        const unsigned pos[2] = {sw[0], sw[1]};
+                        __builtin_memcpy(p.argmax + at + col, pos, 8);
                     }
                 }
             }
