@@ -1,5 +1,8 @@
 """Per-operation parity of the HIP kernels against the fp64 CPU oracle, through
 the C ABI, on seeded inputs at sizes that span several tiles and ragged tails."""
+import ctypes
+import subprocess
+
 import numpy as np
 import pytest
 import torch
@@ -348,10 +351,64 @@ def test_conv3x3_bf16_320_pixel_tiles_element_by_element():
     assert max_rel_err(from_nhwc(dx), ref * (from_nhwc(xsrc) > 0)) <= TOL[dtype]
 
 
+def _check_pooled(run, y, y2):
+    """run(y or None, pooled, argmax): a bf16 convolution with its pool, un-pooled result kept or not; y: what the
+    convolution alone gives.  Pooled values and positions bit for bit those of the separate pool, nothing written past
+    them, and positions at an address that is a multiple of nothing (they are bytes)."""
+    N, H, W, Cout = y.shape
+    n = N * (H // 2) * (W // 2) * Cout
+    po_chk = torch.empty((N, H // 2, W // 2, Cout), dtype=y.dtype, device="cuda")
+    arg_chk = torch.empty((N, H // 2, W // 2, Cout), dtype=torch.uint8, device="cuda")
+    B.vgg_maxpool2x2(B.BF16, N, H, W, Cout, y, po_chk, arg_chk)
+    for keep, shift in ((True, 0), (False, 3)):
+        po = torch.full((n + 1024,), -7.0, dtype=y.dtype, device="cuda")
+        arg = torch.full((n + 1024,), 9, dtype=torch.uint8, device="cuda")
+        run(y2 if keep else None, po, arg[shift:])
+        torch.cuda.synchronize()
+        if keep:
+            assert torch.equal(y2.view(torch.int16), y.view(torch.int16))
+        assert torch.equal(po[:n].view(torch.int16), po_chk.view(torch.int16).flatten())
+        assert torch.equal(arg[shift:shift + n], arg_chk.flatten())
+        assert (po[n:] == -7.0).all() and (arg[shift + n:] == 9).all() and (arg[:shift] == 9).all()
+
+
+def _internal_conv():
+    """The launcher behind the convolution entry points: the whole passes call it with pools that the public entry
+    point does not take (images that 16-pixel patches do not divide, on the kernel for launches of few tiles)."""
+    out = subprocess.run(["nm", "-D", "--defined-only", B.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    names = [w for line in out.splitlines() for w in line.split()[-1:] if w.startswith("_ZN3vgg13conv3x3_igemmE")]
+    assert len(names) == 1, names
+    f = B.lib()[names[0]]
+    v, i = ctypes.c_void_p, ctypes.c_int
+    f.argtypes, f.restype = [i] * 6 + [v] * 7 + [i, v, ctypes.c_size_t, v], i
+    return f
+
+
+@pytest.mark.parametrize("shape", [(1, 14, 14, 512, 512), (3, 14, 14, 512, 512), (1, 28, 28, 512, 512), (1, 56, 56, 256, 256), (2, 30, 44, 256, 40),
+                                   (1, 20, 30, 416, 72), (2, 12, 100, 512, 64)])
+def test_conv3x3_bf16_small_launches_with_their_pool(shape):
+    """The pool that whole passes at small batches take in the kernel for launches of few tiles, patches sticking out of the
+    image on both sides: against the same convolution without it and the separate pool, bit for bit."""
+    dtype = B.BF16
+    N, H, W, Cin, Cout = shape
+    assert B.vgg_conv3x3_plan(B.PLAN_FWD, dtype, N, H, W, Cin, Cout)[0] in (12, 13)
+    d = synth.conv_layer_inputs(N, H, W, Cin, Cout, seed=sum(shape) + 3)
+    x, wp, b = to_nhwc(d["x"], dtype), _pack(dtype, d["w"]), dev(d["b"])
+    y = torch.empty((N, H, W, Cout), dtype=TDT[dtype], device="cuda")
+    B.vgg_conv3x3_fwd(dtype, N, H, W, Cin, Cout, x, wp, b, y, 1, ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(dtype, N, H, W, Cin, Cout)))
+    conv, stream = _internal_conv(), torch.cuda.current_stream().cuda_stream
+
+    def run(yy, po, arg):
+        assert conv(dtype, N, H, W, Cin, Cout, x.data_ptr(), wp.data_ptr(), b.data_ptr(), None, yy.data_ptr() if yy is not None else None,
+                    po.data_ptr(), arg.data_ptr(), 1, None, 0, stream) == 0
+
+    _check_pooled(run, y, torch.empty_like(y))
+
+
 @pytest.mark.parametrize("shape,kernel", [
     ((1, 14, 14, 512, 512), 13),    # eight waves, two chunks each; consecutive pixels that end inside a tile
     ((2, 30, 44, 256, 36), 12),     # two chunks per wave; patches that stick out on both sides; a ragged channel tile
-    ((5, 16, 48, 288, 100), 12),    # nine chunks in three ranges; patches that divide the image (the pool can be fused)
+    ((5, 16, 48, 288, 100), 12),    # nine chunks in three ranges; patches that divide the image
     ((1, 56, 56, 416, 64), 13),     # thirteen chunks in five ranges, the last one short
     ((10, 14, 14, 512, 512), 12),   # eight ranges for four waves (496 tiles)
     ((3, 30, 70, 96, 132), 9),      # an image row longer than the halo of 256 pixels
@@ -362,6 +419,8 @@ def test_conv3x3_bf16_320_pixel_tiles_element_by_element():
     ((9, 30, 57, 384, 200), 11),    # ... with the larger halo
     ((9, 24, 16, 96, 512), 8),      # 128-pixel patches
     ((6, 30, 57, 96, 200), 9),      # 128 consecutive pixels, the larger halo, a ragged channel tile
+    ((9, 32, 16, 96, 520), 8),      # 128-pixel patches whose pool can be fused, a ragged channel tile
+    ((5, 32, 32, 384, 512), 10),    # ... with nine taps of weights ahead
 ])
 def test_conv3x3_bf16_small_and_medium_launches(shape, kernel):
     """The kernels that launches of few tiles take, at the edges of their tiles and splits: forward and masked data
@@ -381,14 +440,10 @@ def test_conv3x3_bf16_small_and_medium_launches(shape, kernel):
     assert max_rel_err(from_nhwc(y), R.conv3x3_fwd(d["x"], d["w"], d["b"], relu=True)) <= TOL[dtype]
     assert (buf[n:] == -7.0).all()
     if H % 16 == 0 and W % 16 == 0 and Cout % 8 == 0:
+        assert B.vgg_conv3x3_plan(B.PLAN_FWD_POOL, dtype, N, H, W, Cin, Cout)[0] == kernel
         y2 = torch.empty_like(y)
-        po = torch.empty((N, H // 2, W // 2, Cout), dtype=TDT[dtype], device="cuda")
-        arg = torch.empty((N, H // 2, W // 2, Cout), dtype=torch.uint8, device="cuda")
-        po_chk, arg_chk = torch.empty_like(po), torch.empty_like(arg)
-        B.vgg_conv3x3_fwd_pool(dtype, N, H, W, Cin, Cout, x, wp, dev(d["b"]), y2, po, 1, ws, argmax=arg)
-        B.vgg_maxpool2x2(dtype, N, H, W, Cout, y2, po_chk, arg_chk)
-        torch.cuda.synchronize()
-        assert torch.equal(po.view(torch.int16), po_chk.view(torch.int16)) and torch.equal(arg, arg_chk)
+        _check_pooled(lambda yy, po, arg: B.vgg_conv3x3_fwd_pool(dtype, N, H, W, Cin, Cout, x, wp, dev(d["b"]), yy, po, 1, ws,
+                                                                 argmax=arg), y, y2)
     d = synth.conv_layer_inputs(N, H, W, Cout, Cin, seed=sum(shape) + 1)
     assert B.vgg_conv3x3_plan(B.PLAN_BWD_DATA, dtype, N, H, W, Cout, Cin)[0] == kernel
     xs = to_nhwc(d["x"], dtype)
