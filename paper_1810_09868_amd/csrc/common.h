@@ -287,4 +287,13 @@ inline TileGeom make_tile_geom(int N, int H, int W, int rows)
     return g;
 }
 
+// Pixels from a tile's first halo pixel inside the image to its last one, at most, for tiles of up to 320 pixels: 22 rows of
+// a 20 x 16 patch, or 320 consecutive pixels and a row more on either side.
+inline long halo_reach(int W) { return 22l * W + 512; }
+__host__ __device__ __forceinline__ int halo_first_pixel(const TileGeom &g, const TileOrigin &o)
+{
+    if (!g.mode) return o.m0 > g.W + 2 ? o.m0 - g.W - 2 : 0;
+    return (o.n * g.H + (o.h0 > 0 ? o.h0 - 1 : 0)) * g.W + (o.w0 > 0 ? o.w0 - 1 : 0);
+}
+
 }  // namespace vgg

@@ -720,7 +720,7 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     // moves on by a chunk), and the lanes that copy.  Slots of pixels outside the image are zeroed here, once, in
     // both buffers, and their lanes sit the copies out; the lanes of pad slots, which nobody reads, copy from the base, so that no copy
     // is ever without a lane (the waits below count copies).
-    const int px0 = p.g.mode ? (org.n * p.g.H + max(org.h0 - 1, 0)) * p.g.W + max(org.w0 - 1, 0) : max(org.m0 - p.g.W - 2, 0);
+    const int px0 = halo_first_pixel(p.g, org);
     unsigned aoff[NQ];
     unsigned long long alanes[NQ];
     {
@@ -1315,7 +1315,7 @@ static int launch_conv_wreg(const ConvArgs &a0, const TileGeom &g, hipStream_t s
         return launch_status();
     };
     if ((a.pool && a.y) || (a.Cout & 7)) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiGeneral, FOLD>);
-    if constexpr (TM % 2 == 0 && !FOLD)   // (320-pixel tiles are never patches; sums are not folded where a pool is fused)
+    if constexpr (TM % 2 == 0 && !FOLD)   // (a pool is planned neither on 320-pixel tiles nor where sums are folded)
         if (a.pool) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPooled, FOLD>);
     if (a.mask) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiMasked, FOLD>);
     return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPlain, FOLD>);
@@ -1498,8 +1498,8 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // 55 / 50, batch 32 (392, 316, 784) 88 / 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.  64-wide tiles win
     // where the channels fill a last 128-wide column by half or less: 28x36x20, 96 -> 132 20 us, 27 on 128-wide ones;
     // 53x56 batch 12, 96 -> 192 19 / 25; 53x73 batch 53 on patches, 64 -> 132 101 / 131.
-    // (that kernel's halo offsets inside a tile are 32 bits: at most 18 image rows of a patch, or 320 + 2 rows)
-    const bool reach = (size_t)(20 * (size_t)W + 512) * CinP * sizeof(bf16_t) < ((size_t)1 << 32);
+    // (that kernel's halo offsets inside a tile are 32 bits)
+    const bool reach = (size_t)halo_reach(W) * CinP * sizeof(bf16_t) < ((size_t)1 << 32);
     // Split over workgroups, as fp32: at most 64 output channels, or a contraction of more than 8 chunks (on the tiles
     // below a few workgroups would walk all of it: 14x14 batch 1, 1024 -> 1024 20 us on 256 workgroups, 68 on 16; 7x7 batch 1,
     // 2048 -> 512 20 / 130; 50x66 batch 1, 1024 -> 512 48 / 69; at 8 chunks 0.61 to 1.02 of its time there).
@@ -1553,9 +1553,8 @@ size_t conv3x3_igemm_workspace(int dtype, int N, int H, int W, int CinP, int Cou
     return ksplit > 1 ? round_up((size_t)ksplit * N * H * W * Cout * 4, 256) : 0;
 }
 
-// For inspection: {kernel (0 register-staged, 1 / 2 / 3 direct-to-LDS with 384 / 448 / 192 halo rows), pixels per
-// tile, channels per tile, tile mode (0 consecutive pixels, 1 patches), pixel tiles, workgroups per tile (split
-// contraction), workgroups}.
+// For inspection: {kernel (ConvKernel), pixels per tile, channels per tile, tile mode (0 consecutive pixels, 1 patches),
+// pixel tiles, ranges of the contraction (kDma, kDmaBig: a workgroup each), workgroups}.
 void conv3x3_igemm_plan_info(int dtype, int N, int H, int W, int CinP, int Cout, bool pool, int info[7])
 {
     const ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool);
