@@ -362,7 +362,8 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *       workgroup); weight
  *       gradient: 100 linear tiles, 114 / 116 patches 14 / 16 pixels wide,
  *       103 the kernel for at most three input channels (fp32); 116 / 117
- *       the bf16 kernel and its variant for at most 32 input channels, 118
+ *       the bf16 kernel and its variant for at most 32 input channels, 108 /
+ *       109 the same on patches of 8 x 8 instead of 4 x 16 pixels, 118
  *       the bf16 kernel for at most three input channels on image widths
  *       that are multiples of 16 ([4]..[6] then describe 117's plan, which
  *       is what the workspace is sized for)
@@ -370,7 +371,8 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *   [3] 0: a tile is consecutive pixels, 1: a patch of one image
  *   [4] pixel tiles
  *   [5] ranges in which a tile's contraction is summed (forward, data
- *       gradient; kernels 1 and 2: by a workgroup each) or partial results that the fixed-order reduction adds (weight gradient)
+ *       gradient; kernels 1 and 2: by a workgroup each) or partial results
+ *       that the fixed-order reduction adds (weight gradient)
  *   [6] workgroups of the main launch */
 #define VGG_PLAN_FWD 0
 #define VGG_PLAN_FWD_POOL 1

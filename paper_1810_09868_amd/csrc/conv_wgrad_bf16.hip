@@ -442,13 +442,13 @@ size_t conv3x3_wgrad_bf16_workspace(int N, int H, int W, int CinP, int Cout)
 }
 
 // For inspection: {kernel (16: 4 x 16 patches; 17: the same with both waves of a tap group on one channel
-// half; 18: the thin kernel, when the caller passes cin -- the other entries then still describe 17's plan,
+// half; 8 / 9: those on 8 x 8 patches; 18: the thin kernel, when the caller passes cin -- the other entries then still describe 17's plan,
 // which is what the workspace is sized for), pixel tiles, partial results, tiles per split, workgroups}.
 void conv3x3_wgrad_bf16_plan_info(int N, int H, int W, int CinP, int Cout, int info[5], int cin)
 {
     WgradBf16Args a;
     wgrad_bf16_plan(N, H, W, CinP, Cout, a);
-    info[0] = a.narrow ? 17 : 16;
+    info[0] = a.tw == 8 ? (a.narrow ? 9 : 8) : (a.narrow ? 17 : 16);
     if (cin >= 1 && cin <= 3 && W % kThinPx == 0) {
         const int co_tiles = (Cout + 63) / 64;
         const int nb = wgrad_thin_blocks(N * H * (W / kThinPx), co_tiles);

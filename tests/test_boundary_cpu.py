@@ -272,11 +272,11 @@ def test_bf16_weight_gradient_on_8x8_patches_takes_no_more_workgroups():
             for ci, co in ((16, 192), (32, 64), (64, 64), (96, 192), (200, 8), (256, 256), (768, 256)):
                 t16, t8 = -(-w // 16) * -(-h // 4), -(-w // 8) * -(-h // 8)
                 info = B.vgg_conv3x3_plan(B.PLAN_BWD_WEIGHT, B.BF16, n, h, w, ci, co)
-                assert info[4] == n * min(t8, t16)
+                assert info[4] == n * min(t8, t16) and info[0] == (116 if t8 >= t16 else 108) + (ci <= 32)
                 groups = -(-co // 64) * -(-B.vgg_padded_channels(B.BF16, ci) // 64)
                 splits = min(-(-512 // groups), n * t16)
                 splits = -(-n * t16 // -(-n * t16 // splits))
                 assert info[6] <= groups * splits, (n, h, w, ci, co, info)
-                assert info[5] <= splits * (2 if info[0] == 117 else 1)
+                assert info[5] <= splits * (2 if ci <= 32 else 1)
                 fewer += t8 < t16
     assert fewer > 100
