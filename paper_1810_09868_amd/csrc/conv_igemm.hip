@@ -1070,9 +1070,9 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
 // ---------------------------------------------------------------------------
 // bf16, launches with fewer tiles than the chip has SIMDs to fill (small batches): a workgroup of G waves owns
 // 64 pixels x 16 NJ channels, and its waves share the contraction: p.ksplit ranges of p.kchunks channel chunks, taken
-// by the waves in turn (wave w: w and w + G), each with all nine taps.  What bounds such a launch is not the matrix pipe but the chain launch -> first loads ->
-// multiply -> combine, so the kernel has one of each: a wave copies its own chunk's halo into its own LDS
-// region and requests all nine taps' weights at once (9 NJ fragments in registers, plain loads; a tap's
+// by the waves in turn (wave w: w and w + G), each with all nine taps.  What bounds such a launch is not the matrix pipe but
+// the chain launch -> first loads -> multiply -> combine, so the kernel has one of each: a wave copies its own chunk's halo
+// into its own LDS region and requests all nine taps' weights at once (9 NJ fragments in registers, plain loads; a tap's
 // registers are refilled for the wave's next chunk as soon as its MFMAs are issued), no barrier until the end,
 // and the waves' sums meet in LDS instead of in a partial-sum buffer that a second launch has to read.
 // LDS rows are 64 bytes, segment s of row q at s ^ ((q >> 1) & 3): conflict-free for the fragment reads of

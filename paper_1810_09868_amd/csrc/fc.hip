@@ -165,6 +165,7 @@ __global__ __launch_bounds__(256) void fc_fwd_kernel(FcArgs p)
 // 25088 -> 4096: bf16 batch 1 51 -> 40 us (5.2 TB/s), batch 10 54 -> 43; fp32 batch 10 225 -> 88 (4.7 TB/s).
 // The lane layout is that of the 16-row MFMAs: lane 16 g + c holds 16 bytes (piece offset 64 e + 16 g) of weight row
 // c and of batch row c; any fixed pairing of contraction indices between the two is a valid order.
+// (Two blocks of sixteen rows do not fit the 128 registers of sixteen waves: 11 are spilled per lane.)
 constexpr int kFcSmallWaves = 16;
 
 // Rows of whole 16-byte segments, and a shape where the split over workgroups is the slower one.  A workgroup walks its
@@ -373,13 +374,13 @@ int fc_forward(int dtype, int N, int In, int Out, const void *a_, const void *w,
 
 // ------------------------------------------------- backward: dW = dz^T * a
 // fp32; bound by its MFMAs and, under them, by writing dW.  Workgroup: 128 (o) x 128 (i) block of dW; the batch is
-// the contraction index, staged through LDS 32 rows at a time, and no MFMA step is taken past the last row.  Wave w
-// owns outputs [32 w, 32 w + 32) and all 128 inputs: lane r reads four consecutive inputs with one 16-byte LDS read
-// and feeds them to four MFMA column tiles, so accumulator tile j of lane r holds input 4 r + j and the stores are
-// 16 bytes, 512 contiguous per row; 64 accumulator registers, so that four workgroups share a CU and some store
-// while others multiply.  (Operands straight from L2 without LDS: the loads between the MFMAs hold up their issue,
-// MFMA busy 0.47.)  25088 -> 4096, batch 100: 274 -> 224 us (128 rows were multiplied for 100, 4 bytes stored per
-// lane); MFMA busy 0.67.
+// the contraction index, staged through LDS 32 rows at a time, and multiplied eight rows (four MFMA steps) at a time
+// up to the last one: 100 rows cost 104.  Wave w owns outputs [32 w, 32 w + 32) and all 128 inputs: lane r reads four
+// consecutive inputs with one 16-byte LDS read and feeds them to four MFMA column tiles, so accumulator tile j of lane r
+// holds input 4 r + j and the stores are 16 bytes, 512 contiguous per row; 64 accumulator registers, so that four
+// workgroups share a CU and some store while others multiply.  (Operands straight from L2 without LDS: the loads between
+// the MFMAs hold up their issue, MFMA busy 0.47.)  25088 -> 4096, batch 100: 274 -> 224 us (128 rows were multiplied for
+// 100, 4 bytes stored per lane); MFMA busy 0.67.
 // VEC: In is a multiple of 4; otherwise the four inputs are written one by one.
 
 // Four floats row[c..c+3], zeros at and beyond column C.  vec: the row is 16-byte aligned (C a multiple of 4).
@@ -643,7 +644,7 @@ __global__ void fc_da_finish_kernel(const float *__restrict__ part, const float 
     reinterpret_cast<vec *>(da)[i] = s;
 }
 
-// fill: workgroups to aim at.  The workspace query takes the bound 512 rounded up to whole splits of the tiles, the
+// launch: how many workgroups to aim at.  The workspace query takes 512 rounded up to whole splits of the tiles, the
 // launch 512 rounded down: 512 is what two workgroups per CU hold, and 588 instead of 490 (25088 -> 4096) would
 // leave a second round of 76.
 static void fc_da_plan(int N, int In, int Out, FcDaArgs &a, bool launch)
