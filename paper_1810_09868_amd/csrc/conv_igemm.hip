@@ -1438,14 +1438,15 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     if (wide && dtype == VGG_BF16) {
         // wide images (from about 60 pixels): the halo of consecutive pixels does not fit the direct-to-LDS kernels;
         // patches do, unless more than a third of their pixels would lie outside the image (128 -> 128 at 64x70, batch
-        // 10: 30 -> 19 us).  At most 32 input channels leave little to win on a padded pixel (24x72 batch 37, 32 -> 36 14.2 us,
-        // 16.7 on patches that pad by 1.28; 66x66 batch 30 22 / 26): at most a quarter then, except beyond
-        // 640 halo rows, which the staged kernel is slow to fetch (24x200 batch 43, 32 -> 8: 42 us, 17 on patches that
-        // pad by 1.39).  fp32 multiplies at a sixteenth of the rate and pays for every padded pixel:
-        // 0.8 to 1.6 times the staged kernel's time over 277 shapes, 0.98 on average, so it stays with that one.
+        // 10: 30 -> 19 us).  At most 64 input channels leave little to win on a padded pixel where it also costs several column
+        // tiles or element-wise stores (66x66 batch 15, 64 -> 256 38 us, 48 on patches that pad by 1.47; batch 30, 32 -> 36 22 /
+        // 26): at most 1.4 of the image then, except beyond 640 halo rows, which the staged kernel is slow to fetch (24x200
+        // batch 43, 32 -> 8 42 us, 17 on patches that pad by 1.39; 81x81 batch 20, 64 -> 64 26 / 17 at 1.40).  fp32 multiplies
+        // at a sixteenth of the rate and pays for every padded pixel: 0.8 to 1.6 times the staged kernel's time over 277
+        // shapes, 0.98 on average, so it stays with that one.
         const TileGeom patch = make_patch_geom(N, H, W, 256);
-        const int most = CinP > 32 || c.g.S > 640 ? 6 : 5;   // quarters of the image
-        if ((long)patch.ntiles * 256 * 4 <= (long)c.g.M * most) c.g = patch;
+        const bool little = CinP <= 64 && (Cout >= 128 || Cout % 8) && c.g.S <= 640;
+        if ((long)patch.ntiles * 256 * 10 <= (long)c.g.M * (little ? 14 : 15)) c.g = patch;
     }
     const bool dma = c.g.S <= kDmaHaloRows, dma_big = !dma && c.g.S <= kDmaHaloRowsBig;
     const int cols = (Cout + 127) / 128, wide_tiles = c.g.ntiles * cols;
@@ -1493,7 +1494,7 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // Weights in registers: more than 64 output channels, and a contraction of at least three chunks unless
     // there is a tile for every CU (below that the 64-wide direct-to-LDS launch is as fast).  The tile by the time of the
     // CU with most of them, in units of a 256 x 128 tile's (one wave per SIMD multiplies nearly as fast as two, so a CU's
-    // tiles simply add up): 320 pixels cost 1.25, 128 pixels 0.56, 64-wide direct-to-LDS tiles 0.6.  Measured (us) for 512
+    // tiles simply add up): 320 pixels cost 1.25, 128 pixels 0.56, 64-wide direct-to-LDS tiles 0.65.  Measured (us) for 512
     // channels, 256 / 320 / 128 pixels: 28x28 batch 10 (124, 100, 248 tiles) 44 / 54 / 35, batch 16 (196, 160, 392) 46 /
     // 55 / 50, batch 32 (392, 316, 784) 88 / 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.  64-wide tiles win
     // where the channels fill a last 128-wide column by half or less: 28x36x20, 96 -> 132 20 us, 27 on 128-wide ones;
@@ -1509,8 +1510,8 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     if (Cout > 64 && (dma || dma_big) && reach && (!narrow || chunks >= 3 || wide_tiles >= 256)) {
         auto rounds = [](int tiles) { return (tiles + 255) / 256; };
         float best = (float)rounds(wide_tiles);
-        if ((narrow || wide) && ksplit == 1 && 0.6f * rounds(c.g.ntiles * ((Cout + 63) / 64)) < best)
-            best = 0.6f * rounds(c.g.ntiles * ((Cout + 63) / 64));
+        const float cost64 = 0.65f * rounds(c.g.ntiles * ((Cout + 63) / 64));
+        if ((narrow || wide) && ksplit == 1 && cost64 < best) best = cost64;
         else {
             c.kernel = dma ? kWreg : kWregBig;
             c.bn = 128;

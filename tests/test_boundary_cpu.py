@@ -248,7 +248,8 @@ BF16_ROUTES = [
     # 64-wide tiles where the last 128-wide column would be half empty
     (28, 36, 20, 96, 132, (1,)), (12, 53, 56, 96, 192, (2,)), (8, 56, 56, 192, 320, (2,)), (17, 30, 33, 384, 132, (1,)),
     # wide images: patches, unless they pad a short contraction by more than a quarter
-    (37, 24, 72, 32, 36, (0,)), (53, 53, 73, 64, 132, (1,)), (30, 66, 66, 32, 36, (0,)), (43, 24, 200, 32, 8, (1,)),
+    (20, 81, 81, 64, 64, (1,)), (53, 53, 73, 64, 132, (1,)), (30, 66, 66, 32, 36, (0,)), (43, 24, 200, 32, 8, (1,)),
+    (15, 66, 66, 64, 256, (0,)), (24, 30, 33, 512, 320, (6, 7)),
     (20, 75, 75, 64, 64, (1,)), (20, 81, 81, 96, 64, (1,)), (20, 66, 66, 128, 64, (1,)),
     (28, 36, 20, 96, 256, (4,)), (8, 56, 56, 192, 256, (5,)), (40, 28, 28, 256, 192, (4,)),
 ]
