@@ -1438,14 +1438,14 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     if (wide && dtype == VGG_BF16) {
         // wide images (from about 60 pixels): the halo of consecutive pixels does not fit the direct-to-LDS kernels;
         // patches do, unless more than a third of their pixels would lie outside the image (128 -> 128 at 64x70, batch
-        // 10: 30 -> 19 us).  At most 64 input channels leave little to win on a padded pixel where it also costs several column
-        // tiles or element-wise stores (66x66 batch 15, 64 -> 256 38 us, 48 on patches that pad by 1.47; batch 30, 32 -> 36 22 /
+        // 10: 30 -> 19 us).  At most 32 input channels leave little to win on a padded pixel where it also costs several column
+        // tiles or element-wise stores (66x66 batch 9, 32 -> 1024 36 us, 42 on patches that pad by 1.47; batch 30, 32 -> 36 22 /
         // 26): at most 1.4 of the image then, except beyond 640 halo rows, which the staged kernel is slow to fetch (24x200
         // batch 43, 32 -> 8 42 us, 17 on patches that pad by 1.39; 81x81 batch 20, 64 -> 64 26 / 17 at 1.40).  fp32 multiplies
         // at a sixteenth of the rate and pays for every padded pixel: 0.8 to 1.6 times the staged kernel's time over 277
         // shapes, 0.98 on average, so it stays with that one.
         const TileGeom patch = make_patch_geom(N, H, W, 256);
-        const bool little = CinP <= 64 && (Cout >= 128 || Cout % 8) && c.g.S <= 640;
+        const bool little = CinP <= 32 && (Cout >= 128 || Cout % 8) && c.g.S <= 640;
         if ((long)patch.ntiles * 256 * 10 <= (long)c.g.M * (little ? 14 : 15)) c.g = patch;
     }
     const bool dma = c.g.S <= kDmaHaloRows, dma_big = !dma && c.g.S <= kDmaHaloRowsBig;
@@ -1473,9 +1473,9 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // every CU gets at most one workgroup).  Against the split over workgroups, over 2430 launches: up to 256 tiles 0.14
     // to 0.95 of its time; up to 512 (two to a CU, what the LDS holds) 0.6 to 0.97 while a wave walks at most six chunks,
     // 0.9 to 1.4 beyond; up to 1024 0.7 to 1.05 with one range of at most four chunks per wave, 1.05 to 1.7 with two.
-    // (512 -> 512 at 14x14, batch 1, 9.1 us instead of 13.4; at 28x28, batch 1, 9.9 / 19.3, batch 2 16.7 / 22.7.)  At 8
-    // chunks, more than 64 output channels and more than 512 tiles the 128-pixel tiles below are faster still (256 -> 512
-    // at 28x28, batch 4: 15.4 us, 17.4 here).
+    // (512 -> 512 at 14x14, batch 1, 9.1 us instead of 13.4; at 28x28, batch 1, 9.9 / 19.3, batch 2 16.7 / 22.7.)  Below 12
+    // chunks, with more than 64 output channels and more than 512 tiles the 128-pixel tiles below are faster still (256 ->
+    // 512 at 28x28, batch 4: 15.4 us, 17.4 here; 320 -> 128 at 20x19, batch 43 20.7 / 25.3).
     if (!pool || !conv3x3_pool_fusable(dtype, H, W, Cout)) conv_split(dtype, c.g, CinP, Cout, c.ksplit, c.kchunks);
     if (c.ksplit > 1) {
         const TileGeom t = conv_small_geom(N, H, W, pool);
@@ -1483,7 +1483,7 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         const int chain = (c.ksplit + G - 1) / G * c.kchunks;   // chunks that a wave walks
         // (wide images have no other split to go to)
         const bool few = tiles <= 256 || (tiles <= 512 && (wide || chain <= 6)) ||
-                         (tiles <= 1024 && (chunks > 8 || Cout <= 64) && (wide ? chunks >= 12 || Cout <= 64 : c.ksplit <= G && chain <= 4));
+                         (tiles <= 1024 && (chunks >= 12 || Cout <= 64) && (wide || (c.ksplit <= G && chain <= 4)));
         if (few && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, c.ksplit) <= 160 * 1024) {
             c.g = t;
             c.kernel = G == 8 ? kSmall8 : kSmall4;
@@ -1494,25 +1494,27 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // Weights in registers: more than 64 output channels, and a contraction of at least three chunks unless
     // there is a tile for every CU (below that the 64-wide direct-to-LDS launch is as fast).  The tile by the time of the
     // CU with most of them, in units of a 256 x 128 tile's (one wave per SIMD multiplies nearly as fast as two, so a CU's
-    // tiles simply add up): 320 pixels cost 1.25, 128 pixels 0.56, 64-wide direct-to-LDS tiles 0.65.  Measured (us) for 512
+    // tiles simply add up): 320 pixels cost 1.25, 128 pixels 0.56, 64-wide direct-to-LDS tiles 0.67.  Measured (us) for 512
     // channels, 256 / 320 / 128 pixels: 28x28 batch 10 (124, 100, 248 tiles) 44 / 54 / 35, batch 16 (196, 160, 392) 46 /
     // 55 / 50, batch 32 (392, 316, 784) 88 / 115 / 105; 14x14 batch 50 (156, 124, 308) 44 / 55 / 50.  64-wide tiles win
     // where the channels fill a last 128-wide column by half or less: 28x36x20, 96 -> 132 20 us, 27 on 128-wide ones;
     // 53x56 batch 12, 96 -> 192 19 / 25; 53x73 batch 53 on patches, 64 -> 132 101 / 131.
     // (that kernel's halo offsets inside a tile are 32 bits)
     const bool reach = (size_t)halo_reach(W) * CinP * sizeof(bf16_t) < ((size_t)1 << 32);
-    // Split over workgroups, as fp32: at most 64 output channels, or a contraction of more than 8 chunks (on the tiles
-    // below a few workgroups would walk all of it: 14x14 batch 1, 1024 -> 1024 20 us on 256 workgroups, 68 on 16; 7x7 batch 1,
-    // 2048 -> 512 20 / 130; 50x66 batch 1, 1024 -> 512 48 / 69; at 8 chunks 0.61 to 1.02 of its time there).
-    if (!wide && c.ksplit > 1 && (Cout <= 64 || chunks > 8)) return c;
+    // Split over workgroups, as fp32: at most 64 output channels, or a contraction of more than 12 chunks or five ranges
+    // (on the tiles below a few workgroups would walk all of it: 14x14 batch 1, 1024 -> 1024 20 us on 256 workgroups, 68 on 16;
+    // 7x7 batch 1, 2048 -> 512 20 / 130; 50x66 batch 1, 1024 -> 512 48 / 69; with less 0.61 to 1.02 of its time there).
+    if (!wide && c.ksplit > 1 && (Cout <= 64 || chunks > 12 || c.ksplit > 5)) return c;
     const int ksplit = c.ksplit, kchunks = c.kchunks;   // (of the kernels below only the 128-pixel tiles fold their sums)
     c.ksplit = 1; c.kchunks = chunks;
     if (Cout > 64 && (dma || dma_big) && reach && (!narrow || chunks >= 3 || wide_tiles >= 256)) {
         auto rounds = [](int tiles) { return (tiles + 255) / 256; };
         float best = (float)rounds(wide_tiles);
-        const float cost64 = 0.65f * rounds(c.g.ntiles * ((Cout + 63) / 64));
-        if ((narrow || wide) && ksplit == 1 && cost64 < best) best = cost64;
-        else {
+        const float cost64 = 0.67f * rounds(c.g.ntiles * ((Cout + 63) / 64));
+        if ((narrow || wide) && ksplit == 1 && cost64 < best) {
+            best = cost64;
+            c.bn = 64;
+        } else {
             c.kernel = dma ? kWreg : kWregBig;
             c.bn = 128;
         }

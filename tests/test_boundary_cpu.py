@@ -244,12 +244,12 @@ BF16_ROUTES = [
     (2, 28, 28, 512, 512, (12,)), (30, 28, 28, 256, 36, (12,)), (3, 36, 100, 1024, 128, (12,)),
     # 128-pixel tiles that fold the ranges' sums: eight chunks
     (4, 28, 28, 256, 516, (8,)), (2, 56, 56, 256, 256, (9,)), (5, 28, 28, 576, 512, (1,)), (1, 50, 66, 1024, 512, (2,)),
-    (13, 38, 16, 1024, 256, (1,)),
+    (13, 38, 16, 1024, 256, (1,)), (43, 20, 19, 320, 128, (8,)), (4, 7, 42, 384, 1024, (2,)),
     # 64-wide tiles where the last 128-wide column would be half empty
     (28, 36, 20, 96, 132, (1,)), (12, 53, 56, 96, 192, (2,)), (8, 56, 56, 192, 320, (2,)), (17, 30, 33, 384, 132, (1,)),
     # wide images: patches, unless they pad a short contraction by more than a quarter
     (20, 81, 81, 64, 64, (1,)), (53, 53, 73, 64, 132, (1,)), (30, 66, 66, 32, 36, (0,)), (43, 24, 200, 32, 8, (1,)),
-    (15, 66, 66, 64, 256, (0,)), (24, 30, 33, 512, 320, (6, 7)),
+    (9, 66, 66, 32, 1024, (0,)), (12, 17, 16, 320, 576, (8,)), (6, 24, 200, 512, 200, (4,)), (24, 30, 33, 512, 320, (6, 7)),
     (20, 75, 75, 64, 64, (1,)), (20, 81, 81, 96, 64, (1,)), (20, 66, 66, 128, 64, (1,)),
     (28, 36, 20, 96, 256, (4,)), (8, 56, 56, 192, 256, (5,)), (40, 28, 28, 256, 192, (4,)),
 ]
@@ -260,6 +260,8 @@ def test_bf16_convolution_routes():
         info = B.vgg_conv3x3_plan(B.PLAN_FWD, B.BF16, n, h, w, ci, co)
         assert info[0] in kernels, (n, h, w, ci, co, info)
         assert B.vgg_conv3x3_plan(B.PLAN_BWD_DATA, B.BF16, n, h, w, co, ci) == info
+        if info[0] in (1, 2):
+            assert info[2] == 64 and info[6] == info[4] * -(-co // 64) * info[5]
         if info[0] in (1, 2) and info[5] > 1:
             assert B.vgg_conv3x3_fwd_workspace_bytes(B.BF16, n, h, w, ci, co) >= info[5] * n * h * w * co * 4
 
