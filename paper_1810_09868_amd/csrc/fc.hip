@@ -170,13 +170,15 @@ constexpr int kFcSmallWaves = 16;
 
 // Rows of whole 16-byte segments, and a shape where the split over workgroups is the slower one.  A workgroup walks its
 // sixteen rows alone at about 1.7 KB of row per us, whatever the chip does besides: few outputs with long rows leave it
-// idle (a million inputs, 10 outputs, batch 10: bf16 152 us split, 782 here; fp32 382 / 1921).  Measured over 506 shapes,
-// time here / split.  Up to 16 batch rows:
-//   rows of at most 32 KB: 0.33 to 0.95.  One workgroup (at most 16 outputs): 0.61 to 0.91 up to 128 KB from eight
-//   batch rows on, where the 128-row tile has less to stream; fewer batch rows 0.57 to 0.83 up to 16 KB, 1.1 at 32.
-//   fp32, longer rows: 64 to 2047 outputs 0.69 to 1.02 up to 112 KB, 1.0 to 1.4 at 160 KB; from 2048 outputs on 0.33
-//   to 0.70 at every length.  bf16: from 4096 outputs (a workgroup per CU) 0.80 to 0.94 up to 160 KB, 1.1 at
-//   200 KB; fewer outputs 0.9 to 1.1 at 50 KB, 1.1 to 1.4 at 80 KB.
+// idle (a million inputs, 10 outputs, batch 10: bf16 152 us split, 782 here; fp32 382 / 1921).
+// Up to 16 batch rows the longest row, in KB, over 1900 shapes (time here / split below it, and just beyond):
+//   one workgroup (at most 16 outputs)  192 from four batch rows on (0.51 to 0.9; 1.4 at half a megabyte), else 40 (0.55 to
+//                                       0.90; 1.24)
+//   up to 63 outputs                    80 (0.55 to 0.99; 1.26)
+//   fp32  up to 511 outputs 112 (0.57 to 1.02; 1.28), up to 1023 160 (0.5 to 0.89; 1.17), up to 2047 256 (0.37 to 0.75; 1.2 at
+//         a megabyte), more: any (0.17 to 0.75)
+//   bf16  up to 511 outputs 64 (0.6 to 1.04; 1.19), up to 2999 44 (0.57 to 1.04; 1.35), more 200 (0.64 to 1.05; 1.11)
+// and half as long again for rows that are not whole 64-byte units, which the split's kernel reads in pieces.
 // 17 to 32 rows: every workgroup reads twice as many activations, which pays where the 128-row tile is bound by its
 // zeros (fp32: 25088 -> 4096 228 -> 139 us, 40000 -> 2048 189 / 205) and not for bf16 beyond 4 KB rows (25088 -> 4096 59 / 73).
 static bool fc_small(int dtype, int N, int In, int Out)
@@ -186,8 +188,10 @@ static bool fc_small(int dtype, int N, int In, int Out)
     const bool f32 = dtype == VGG_F32;
     if (N > 16)
         return f32 ? rowbytes <= 16 * KB || Out >= 4096 || (Out >= 2048 && rowbytes <= 112 * KB) : rowbytes <= 4 * KB;
-    if (rowbytes <= (Out > 16 ? 32 : N >= 8 ? 128 : 16) * KB) return true;
-    return f32 ? Out >= 2048 || (Out >= 64 && rowbytes <= 112 * KB) : Out >= 4096 && rowbytes <= 160 * KB;
+    if (f32 && Out >= 2048) return true;
+    size_t longest = Out <= 16 ? (N >= 4 ? 192 : 40) : 80;
+    if (Out >= 64) longest = f32 ? (Out < 512 ? 112 : Out < 1024 ? 160 : 256) : (Out < 512 ? 64 : Out < 3000 ? 44 : 200);
+    return rowbytes <= (rowbytes % 64 ? longest * 3 / 2 : longest) * KB;
 }
 
 template <typename T, typename TZ, int NB>
