@@ -1435,18 +1435,23 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     ConvPlan c;
     c.g = make_tile_geom(N, H, W, 256);
     const bool wide = c.g.S > kDmaHaloRowsBig;
-    if (wide && dtype == VGG_BF16) {
+    if (wide) {
         // wide images (from about 60 pixels): the halo of consecutive pixels does not fit the direct-to-LDS kernels;
-        // patches do, unless more than a third of their pixels would lie outside the image (128 -> 128 at 64x70, batch
-        // 10: 30 -> 19 us).  At most 32 input channels leave little to win on a padded pixel where it also costs several column
+        // patches do, unless more than a third of their pixels would lie outside the image (bf16 128 -> 128 at 64x70,
+        // batch 10: 30 -> 19 us).
+        // bf16: at most 32 input channels leave little to win on a padded pixel where it also costs several column
         // tiles or element-wise stores (66x66 batch 9, 32 -> 1024 36 us, 42 on patches that pad by 1.47; batch 30, 32 -> 36 22 /
         // 26): at most 1.4 of the image then, except beyond 640 halo rows, which the staged kernel is slow to fetch (24x200
-        // batch 43, 32 -> 8 42 us, 17 on patches that pad by 1.39; 81x81 batch 20, 64 -> 64 26 / 17 at 1.40).  fp32 multiplies
-        // at a sixteenth of the rate and pays for every padded pixel: 0.8 to 1.6 times the staged kernel's time over 277
-        // shapes, 0.98 on average, so it stays with that one.
+        // batch 43, 32 -> 8 42 us, 17 on patches that pad by 1.39; 81x81 batch 20, 64 -> 64 26 / 17 at 1.40).
+        // fp32 multiplies at a sixteenth of the rate and pays for every padded pixel, so only 64-wide tiles of which no CU
+        // gets more than before: 322 of 505 shapes, 0.86 of the staged kernel's time on average, 0.99 at most (the others
+        // 1.2 on average; 66x66 batch 9, 384 -> 64 backwards 175 us, 280 on patches).
         const TileGeom patch = make_patch_geom(N, H, W, 256);
+        const int cols64 = (Cout + 63) / 64;
         const bool little = CinP <= 32 && (Cout >= 128 || Cout % 8) && c.g.S <= 640;
-        if ((long)patch.ntiles * 256 * 10 <= (long)c.g.M * (little ? 14 : 15)) c.g = patch;
+        const bool pays = dtype == VGG_BF16 || ((Cout <= 64 || patch.ntiles * ((Cout + 127) / 128) < 512) &&
+                                                (patch.ntiles * cols64 + 255) / 256 <= (c.g.ntiles * cols64 + 255) / 256);
+        if (pays && (long)patch.ntiles * 256 * 10 <= (long)c.g.M * (dtype == VGG_BF16 && little ? 14 : 15)) c.g = patch;
     }
     const bool dma = c.g.S <= kDmaHaloRows, dma_big = !dma && c.g.S <= kDmaHaloRowsBig;
     const int cols = (Cout + 127) / 128, wide_tiles = c.g.ntiles * cols;

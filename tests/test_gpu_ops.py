@@ -481,6 +481,35 @@ def test_conv3x3_bf16_split_over_workgroups(shape):
     assert max_rel_err(from_nhwc(y), R.conv3x3_bwd_data(d["dy"], d["w"]) * (from_nhwc(xs) > 0)) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("shape,kernel", [((2, 46, 79, 32, 36), 1), ((1, 24, 200, 96, 64), 1), ((1, 97, 97, 48, 132), 1), ((3, 63, 65, 3, 20), 1),
+                                          ((9, 66, 66, 16, 192), 0), ((1, 6, 150, 16, 32), 0)])
+def test_conv3x3_f32_wide_images(shape, kernel):
+    """Rows too long for the direct-to-LDS kernels' halo of consecutive pixels: patches that stick out of the image where no
+    compute unit gets more tiles for it, else the staged kernel; nothing is split, no scratch is needed beyond the padded copy.
+    Forward against the oracle, nothing written past the tensor; data gradient of the mirrored layer with its mask."""
+    dtype = B.F32
+    N, H, W, Cin, Cout = shape
+    plan = B.vgg_conv3x3_plan(B.PLAN_FWD, dtype, N, H, W, Cin, Cout)
+    assert plan[0] == kernel and plan[3] == kernel and plan[5] == 1, plan
+    d = synth.conv_layer_inputs(N, H, W, Cin, Cout, seed=sum(shape))
+    n = N * H * W * Cout
+    buf = torch.full((n + 4096,), -7.0, device="cuda")
+    y = buf[:n].view(N, H, W, Cout)
+    ws = ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(dtype, N, H, W, Cin, Cout))
+    B.vgg_conv3x3_fwd(dtype, N, H, W, Cin, Cout, to_nhwc(d["x"], dtype), _pack(dtype, d["w"]), dev(d["b"]), y, 1, ws)
+    torch.cuda.synchronize()
+    assert max_rel_err(from_nhwc(y), R.conv3x3_fwd(d["x"], d["w"], d["b"], relu=True)) <= TOL[dtype]
+    assert (buf[n:] == -7.0).all()
+    d = synth.conv_layer_inputs(N, H, W, Cout, Cin, seed=sum(shape) + 1)
+    xs = to_nhwc(d["x"], dtype)
+    ws = ws_bytes(B.vgg_conv3x3_bwd_data_workspace_bytes(dtype, N, H, W, Cout, Cin))
+    buf.fill_(-7.0)
+    B.vgg_conv3x3_bwd_data(dtype, N, H, W, Cout, Cin, to_nhwc(d["dy"], dtype), _pack(dtype, d["w"], flip=1), xs, y, ws)
+    torch.cuda.synchronize()
+    assert max_rel_err(from_nhwc(y), R.conv3x3_bwd_data(d["dy"], d["w"]) * (from_nhwc(xs) > 0)) <= TOL[dtype]
+    assert (buf[n:] == -7.0).all()
+
+
 @pytest.mark.parametrize("shape", FULL_SIZE_LAYERS)
 def test_conv3x3_bf16_full_size_on_sampled_pixels(shape):
     """Forward and data gradient at the benchmark's sizes, in the launch configuration it times; the oracle
