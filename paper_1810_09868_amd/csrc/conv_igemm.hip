@@ -1395,7 +1395,7 @@ struct ConvPlan {
 
 // Split of the contraction, decided on tiles of 256 pixels.  Small batches: fewer tiles than CUs, each walking the whole
 // contraction alone.  Then the contraction is summed in ranges of (at least two) channel chunks, by a workgroup each,
-// whose partial sums a second kernel adds, or (bf16, more than 64 output channels) inside one workgroup in the same order.
+// whose partial sums a second kernel adds, or (bf16, where that is faster) inside one workgroup in the same order.
 static void conv_split(int dtype, const TileGeom &g, int CinP, int Cout, int &ksplit, int &kchunks)
 {
     const int chunks = CinP * dtype_size(dtype) / kDataBytes;

@@ -481,19 +481,24 @@ def test_conv3x3_bf16_split_over_workgroups(shape):
     assert max_rel_err(from_nhwc(y), R.conv3x3_bwd_data(d["dy"], d["w"]) * (from_nhwc(xs) > 0)) <= TOL[dtype]
 
 
-@pytest.mark.parametrize("shape,kernel", [((2, 46, 79, 32, 36), 1), ((1, 24, 200, 96, 64), 1), ((1, 97, 97, 48, 132), 1), ((3, 63, 65, 3, 20), 1),
-                                          ((9, 66, 66, 16, 192), 0), ((1, 6, 150, 16, 32), 0)])
-def test_conv3x3_f32_wide_images(shape, kernel):
-    """Rows too long for the direct-to-LDS kernels' halo of consecutive pixels: patches that stick out of the image where no
-    compute unit gets more tiles for it, else the staged kernel; nothing is split, no scratch is needed beyond the padded copy.
-    Forward against the oracle, nothing written past the tensor; data gradient of the mirrored layer with its mask."""
-    dtype = B.F32
+@pytest.mark.parametrize("dtype,shape,kernel", [
+    (B.F32, (2, 46, 79, 32, 36), 1), (B.F32, (1, 24, 200, 96, 64), 1), (B.F32, (1, 97, 97, 48, 132), 1), (B.F32, (3, 63, 65, 3, 20), 1),
+    (B.F32, (9, 66, 66, 16, 192), 0), (B.F32, (1, 6, 150, 16, 32), 0),
+    (B.BF16, (2, 46, 79, 32, 36), 1), (B.BF16, (3, 62, 75, 64, 200), 1), (B.BF16, (4, 36, 100, 96, 256), 4), (B.BF16, (2, 36, 100, 160, 520), 4),
+    (B.BF16, (1, 24, 200, 512, 64), 13), (B.BF16, (9, 66, 66, 32, 136), 0)])
+def test_conv3x3_wide_images(dtype, shape, kernel):
+    """Rows too long for the direct-to-LDS kernels' halo of consecutive pixels: patches that stick out of the image where that
+    pays, else the staged kernel; no partial sums in memory, no scratch beyond the padded copy.  Forward against the
+    oracle, nothing written past the tensor; data gradient of the mirrored layer with its mask."""
     N, H, W, Cin, Cout = shape
     plan = B.vgg_conv3x3_plan(B.PLAN_FWD, dtype, N, H, W, Cin, Cout)
-    assert plan[0] == kernel and plan[3] == kernel and plan[5] == 1, plan
+    assert plan[0] == kernel and plan[3] == (kernel != 0) and (plan[5] == 1 or kernel == 13), plan
+    cp, size = B.vgg_padded_channels(dtype, Cin), 4 if dtype == B.F32 else 2
+    padded = 0 if cp == Cin else -(-N * H * W * cp * size // 256) * 256
+    assert B.vgg_conv3x3_fwd_workspace_bytes(dtype, N, H, W, Cin, Cout) == padded
     d = synth.conv_layer_inputs(N, H, W, Cin, Cout, seed=sum(shape))
     n = N * H * W * Cout
-    buf = torch.full((n + 4096,), -7.0, device="cuda")
+    buf = torch.full((n + 4096,), -7.0, dtype=TDT[dtype], device="cuda")
     y = buf[:n].view(N, H, W, Cout)
     ws = ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(dtype, N, H, W, Cin, Cout))
     B.vgg_conv3x3_fwd(dtype, N, H, W, Cin, Cout, to_nhwc(d["x"], dtype), _pack(dtype, d["w"]), dev(d["b"]), y, 1, ws)
