@@ -4,9 +4,9 @@
 // is read from HBM exactly once and the batch rows are the MFMA's M side.
 #include "common.h"
 
-namespace vgg {
+#include <type_traits>
 
-constexpr int kFcRow = 80;  // LDS row: 64 data bytes + 16 pad (same fragment format as the convolution)
+namespace vgg {
 
 template <typename T> struct FcMma;
 template <> struct FcMma<float> {
@@ -27,11 +27,12 @@ template <> struct FcMma<bf16_t> {
 };
 
 // ------------------------------------------------------------------ forward
-// Workgroup: 128 batch rows x 128 outputs x a range of 64-byte K units.
-// Wave w owns outputs [32w, 32w+32) and all four 32-row blocks.  The
-// activations of a step (4 units = 256 bytes per row) go through LDS; each
-// weight fragment is read straight from global memory by the one lane that
-// needs it (a weight is used by exactly one wave).
+// Workgroup: up to 128 batch rows (MB blocks of 32) x 128 outputs x a range of 64-byte K units.
+// Wave w owns outputs [32w, 32w+32) and all row blocks.  Bound by streaming the weights (bf16) or by the MFMAs (fp32 from
+// about 64 rows on).  Both operands of a step (4 units = 256 bytes per row) are loaded as whole 256-byte runs of four rows,
+// and take the MFMA's layout through LDS, the weights in a block of the wave's own: loads in the MFMA's layout fetch
+// 32 bytes of 32 rows each, and a cache line four times over.  25088 -> 4096, whole calls: bf16 batch 100 71 -> 56 us, batch 32
+// 57 -> 39 (5.3 TB/s); fp32 batch 100 249 -> 222; bf16 4096 -> 4096, batch 100 21.3 -> 16.3.
 struct FcArgs {
     const char *a;   // [N][In]
     const char *w;   // [Out][In]
@@ -43,17 +44,13 @@ struct FcArgs {
     int tiles_m;          // row tiles
 };
 
-// 16 bytes at byte offset `off` of a row of `rowbytes` bytes, zeros at and beyond the row's end.
-// vec: rows are 16-byte aligned and a whole number of 16-byte segments (one load); otherwise the
-// segment is gathered element by element, so that any row length works.
+typedef unsigned fc_u32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes at byte offset `off` of a row of `rowbytes` bytes, zeros at and beyond the row's end, for rows that are not
+// whole 16-byte segments: gathered element by element, so that any row length works.
 template <typename T>
-__device__ __forceinline__ uint4 load_seg(const char *row, size_t off, size_t rowbytes, bool vec)
+__device__ __forceinline__ fc_u32x4 gather_seg(const char *row, size_t off, size_t rowbytes)
 {
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (vec) {
-        if (off < rowbytes) v = *reinterpret_cast<const uint4 *>(row + off);
-        return v;
-    }
+    fc_u32x4 v;
     T e[16 / sizeof(T)];
 #pragma unroll
     for (int k = 0; k < (int)(16 / sizeof(T)); ++k)
@@ -62,31 +59,34 @@ __device__ __forceinline__ uint4 load_seg(const char *row, size_t off, size_t ro
     return v;
 }
 
-// EXACT: every row is a whole number of 64-byte units (In a multiple of 16 fp32 / 32 bf16), the case
-// of the network's own layers.  Otherwise the last unit of a row is completed with zeros in registers.
-template <typename T, bool EXACT>
-__global__ __launch_bounds__(256) void fc_fwd_kernel(FcArgs p)
+// VEC: rows are whole 16-byte segments (one load each; past the range its last segment again, replaced by zeros on the way
+// to LDS: a load under a condition is waited for where the condition ends).
+// MB: 32-row blocks of the batch tile.  STREAM: the weights pass the caches by.
+template <typename T, bool VEC, int MB, bool STREAM>
+__global__ __launch_bounds__(256, 2) void fc_fwd_kernel(FcArgs p)
 {
-    __shared__ __align__(16) char As[4 * 128 * kFcRow];  // [unit][row][80]
+    typedef fc_u32x4 u32x4;
+    constexpr int kRow = 256 + 16;                          // LDS row of a step
+    __shared__ __align__(16) char As[MB * 32 * kRow];       // [batch row]
+    __shared__ __align__(16) char Ws[4 * 32 * kRow];        // [wave][output]
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int r = lane & 31, khalf = lane >> 5;
     int b = blockIdx.x;
     const int tn = b % p.tiles_n; b /= p.tiles_n;
     const int tm = b % p.tiles_m; b /= p.tiles_m;
     const int split = b;
-    const int row0 = tm * 128, o0 = tn * 128;
+    const int row0 = tm * (MB * 32), o0 = tn * 128;
     const int u_begin = split * p.units_per_split;
     const int u_end = min(u_begin + p.units_per_split, p.units);
     const size_t rowbytes = (size_t)p.In * sizeof(T);
-    const bool vec = EXACT || rowbytes % 16 == 0;
 
     const int ocol = o0 + wv * 32 + r;
     const bool ook = ocol < p.Out;
-    const char *wrow = p.w + (size_t)(ook ? ocol : 0) * rowbytes + khalf * 16;
+    char *const Wv = Ws + wv * (32 * kRow);
 
-    f32x16 acc[4];
+    f32x16 acc[MB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
 
@@ -94,62 +94,63 @@ __global__ __launch_bounds__(256) void fc_fwd_kernel(FcArgs p)
     // stream from HBM never pauses for the staging and the MFMAs.  The barriers are issued without
     // the fence of __syncthreads(), which would wait for those loads.
     auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    constexpr int NA = 4 * 128 * 4 / 256;   // activation segments per thread and step
-    auto load_w = [&](int u0, uint4 (&bf)[4][2]) __attribute__((always_inline)) {
-        const int nu = min(4, u_end - u0);
+    constexpr int NA = MB * 32 * 16 / 256;   // activation segments per thread and step
+    // Four whole 256-byte rows per load, rearranged through LDS: a load in the MFMA's layout touches 32 rows, a quarter of a
+    // cache line each.  (Rows past the last are the last again, never stored.)
+    const int seg = lane & 15;
+    const size_t end = min((size_t)u_end * 64, rowbytes);
+    auto load_w = [&](int u0, u32x4 (&wf)[8]) __attribute__((always_inline)) {
+        const size_t off = (size_t)u0 * 64 + seg * 16;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                bf[u][g] = make_uint4(0, 0, 0, 0);
-                if (u < nu && ook) {
-                    if (EXACT) bf[u][g] = *reinterpret_cast<const uint4 *>(wrow + (size_t)(u0 + u) * 64 + g * 32);
-                    else bf[u][g] = load_seg<T>(wrow - khalf * 16, (size_t)(u0 + u) * 64 + g * 32 + khalf * 16, rowbytes, vec);
-                }
-            }
-    };
-    auto load_a = [&](int u0, uint4 (&av)[NA]) __attribute__((always_inline)) {
-        const int nu = min(4, u_end - u0);
-#pragma unroll
-        for (int k = 0; k < NA; ++k) {
-            const int idx = tid + k * 256;
-            const int seg = idx & 3, row = (idx >> 2) & 127, u = idx >> 9;
-            av[k] = make_uint4(0, 0, 0, 0);
-            if (u < nu && row0 + row < p.N) {
-                if (EXACT) av[k] = *reinterpret_cast<const uint4 *>(p.a + (size_t)(row0 + row) * rowbytes + (size_t)(u0 + u) * 64 + seg * 16);
-                else av[k] = load_seg<T>(p.a + (size_t)(row0 + row) * rowbytes, (size_t)(u0 + u) * 64 + seg * 16, rowbytes, vec);
-            }
+        for (int q = 0; q < 8; ++q) {
+            const char *row = p.w + (size_t)min(o0 + wv * 32 + q * 4 + (lane >> 4), p.Out - 1) * rowbytes;
+            if (VEC) {
+                const u32x4 *src = reinterpret_cast<const u32x4 *>(row + min(off, end - 16));
+                wf[q] = STREAM ? __builtin_nontemporal_load(src) : *src;
+            } else wf[q] = gather_seg<T>(row, off, end);
         }
     };
-    uint4 bf_next[4][2], a_next[NA];
-    if (u_begin < u_end) { load_a(u_begin, a_next); load_w(u_begin, bf_next); }
+    auto load_a = [&](int u0, u32x4 (&av)[NA]) __attribute__((always_inline)) {
+        const size_t off = (size_t)u0 * 64 + seg * 16;
+#pragma unroll
+        for (int k = 0; k < NA; ++k) {
+            const char *row = p.a + (size_t)min(row0 + (tid >> 4) + k * 16, p.N - 1) * rowbytes;
+            if (VEC) av[k] = *reinterpret_cast<const u32x4 *>(row + min(off, end - 16));
+            else av[k] = gather_seg<T>(row, off, end);
+        }
+    };
+    u32x4 w_next[8];
+    u32x4 a_next[NA];
+    if (u_begin < u_end) { load_a(u_begin, a_next); load_w(u_begin, w_next); }
     for (int u0 = u_begin; u0 < u_end; u0 += 4) {
         barrier();  // the previous step's fragment reads are done
+        if (VEC && (size_t)(u0 + 4) * 64 > end && (size_t)u0 * 64 + seg * 16 >= end) {
 #pragma unroll
-        for (int k = 0; k < NA; ++k) {
-            const int idx = tid + k * 256;
-            *reinterpret_cast<uint4 *>(As + ((idx >> 9) * 128 + ((idx >> 2) & 127)) * kFcRow + (idx & 3) * 16) = a_next[k];
+            for (int k = 0; k < NA; ++k) a_next[k] = u32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < 8; ++q) w_next[q] = u32x4{0, 0, 0, 0};
         }
-        uint4 bf[4][2];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int k = 0; k < NA; ++k) *reinterpret_cast<u32x4 *>(As + ((tid >> 4) + k * 16) * kRow + seg * 16) = a_next[k];
 #pragma unroll
-            for (int g = 0; g < 2; ++g) bf[u][g] = bf_next[u][g];
-        if (u0 + 4 < u_end) { load_a(u0 + 4, a_next); load_w(u0 + 4, bf_next); }
+        for (int q = 0; q < 8; ++q) *reinterpret_cast<u32x4 *>(Wv + (q * 4 + (lane >> 4)) * kRow + seg * 16) = w_next[q];
+        if (u0 + 4 < u_end) { load_a(u0 + 4, a_next); load_w(u0 + 4, w_next); }
         barrier();  // the staged activations are visible
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int g = 0; g < 2; ++g)
+            for (int g = 0; g < 2; ++g) {
+                const uint4 bf = *reinterpret_cast<const uint4 *>(Wv + r * kRow + u * 64 + g * 32 + khalf * 16);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint4 af = *reinterpret_cast<const uint4 *>(As + (u * 128 + i * 32 + r) * kFcRow + g * 32 + khalf * 16);
-                    FcMma<T>::run(acc[i], af, bf[u][g]);
+                for (int i = 0; i < MB; ++i) {
+                    const uint4 af = *reinterpret_cast<const uint4 *>(As + (i * 32 + r) * kRow + u * 64 + g * 32 + khalf * 16);
+                    FcMma<T>::run(acc[i], af, bf);
                 }
+            }
     }
     if (ook) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int row = row0 + i * 32 + (e >> 2) * 8 + khalf * 4 + (e & 3);
@@ -158,90 +159,93 @@ __global__ __launch_bounds__(256) void fc_fwd_kernel(FcArgs p)
     }
 }
 
-// Small batches: bound by streaming the weights once.  Workgroup: 16 outputs x the whole contraction, sixteen waves
-// taking turns at 256-byte pieces of it, so that a workgroup reads 4 KB runs of its sixteen weight rows and every
-// weight goes straight to the lane that multiplies it; batch rows come in sixteens (the 128-row tile above multiplies
-// 118 rows of zeros for ten).  The waves' sums meet in LDS: no partial sums in memory and no second launch.
-// 25088 -> 4096: bf16 batch 1 51 -> 40 us (5.2 TB/s), batch 10 54 -> 43; fp32 batch 10 225 -> 88 (4.7 TB/s).
+// Small batches: bound by streaming the weights once.  Workgroup: 16 outputs x the whole contraction, its waves
+// taking turns at 256-byte pieces of it, so that a workgroup reads 4 KB runs of its sixteen weight rows; batch rows come in
+// sixteens (NB of them).  The waves' sums meet in LDS: no partial sums in memory and no second launch.
+// A piece of the weights is loaded as four whole rows per load and takes the MFMA's layout through the wave's own LDS
+// block, as the activations do: loaded straight in that layout every load touched sixteen rows and half of each cache
+// line it fetched.  25088 -> 4096: bf16 batch 1 38.5 -> 32.7 us, batch 10 43.2 -> 35.4 (5.8 TB/s; a bare read of as many bytes
+// takes 30.5); fp32 batch 10 80 -> 69, batch 20 138 -> 97.
 // The lane layout is that of the 16-row MFMAs: lane 16 g + c holds 16 bytes (piece offset 64 e + 16 g) of weight row
 // c and of batch row c; any fixed pairing of contraction indices between the two is a valid order.
-// (Two blocks of sixteen rows do not fit the 128 registers of sixteen waves: 11 are spilled per lane.)
-constexpr int kFcSmallWaves = 16;
+// Sixteen waves of 128 registers, or eight of 256 for two blocks of batch rows, which do not fit 128.  A third piece in
+// flight was slower (43 -> 45 us in the first form).
+constexpr int fc_small_waves(int NB) { return NB == 1 ? 16 : 8; }
 
 // Rows of whole 16-byte segments, and a shape where the split over workgroups is the slower one.  A workgroup walks its
-// sixteen rows alone at about 1.7 KB of row per us, whatever the chip does besides: few outputs with long rows leave it
-// idle (a million inputs, 10 outputs, batch 10: bf16 152 us split, 782 here; fp32 382 / 1921).
-// Up to 16 batch rows the longest row, in KB, over 1900 shapes (time here / split below it, and just beyond):
-//   one workgroup (at most 16 outputs)  192 from four batch rows on (0.51 to 0.9; 1.4 at half a megabyte), else 40 (0.55 to
-//                                       0.90; 1.24)
-//   up to 63 outputs                    80 (0.55 to 0.99; 1.26)
-//   fp32  up to 511 outputs 112 (0.57 to 1.02; 1.28), up to 1023 160 (0.5 to 0.89; 1.17), up to 2047 256 (0.37 to 0.75; 1.2 at
-//         a megabyte), more: any (0.17 to 0.75)
-//   bf16  up to 511 outputs 64 (0.6 to 1.04; 1.19), up to 2999 44 (0.57 to 1.04; 1.35), more 200 (0.64 to 1.05; 1.11)
-// and half as long again for rows that are not whole 64-byte units, which the split's kernel reads in pieces.
-// 17 to 32 rows: every workgroup reads twice as many activations, which pays where the 128-row tile is bound by its
-// zeros (fp32: 25088 -> 4096 228 -> 139 us, 40000 -> 2048 189 / 205) and not for bf16 beyond 4 KB rows (25088 -> 4096 59 / 73).
+// sixteen rows alone, at about 2.5 KB of row per us whatever the chip does besides, against the split's second launch and
+// partial sums: the longest row, in KB, over 1500 shapes (time here / split up to it, and beyond):
+//   up to 16 batch rows, outputs  up to 1499 10 (0.5 to 0.93; 0.97 to 1.1 at 12 KB), up to 2499 17 (0.5 to 0.96; 1.0 to 1.07 at 23 KB),
+//                                 more: bf16 50 (0.54 to 1.05; 0.95 to 1.34), fp32 100 (0.52 to 1.02; 0.83 to 1.4)
+//   17 to 32 (twice the activations per workgroup)  up to 2499 6.5 (0.55 to 1.0; 0.97 to 1.27 at 8 KB), up to 5000 17 (0.55 to 1.02;
+//                                 0.86 to 1.3), up to 8191 6.5 (0.7 to 1.0; 1.0 to 1.2), more: never (1.04 to 1.24)
+//   bf16, 8192 outputs and more, rows below 8 KB: 1.04 to 1.12
 static bool fc_small(int dtype, int N, int In, int Out)
 {
     const size_t rowbytes = (size_t)In * dtype_size(dtype), KB = 1024;
     if (rowbytes % 16 || N > 32) return false;
     const bool f32 = dtype == VGG_F32;
-    if (N > 16)
-        return f32 ? rowbytes <= 16 * KB || Out >= 4096 || (Out >= 2048 && rowbytes <= 112 * KB) : rowbytes <= 4 * KB;
-    if (f32 && Out >= 2048) return true;
-    size_t longest = Out <= 16 ? (N >= 4 ? 192 : 40) : 80;
-    if (Out >= 64) longest = f32 ? (Out < 512 ? 112 : Out < 1024 ? 160 : 256) : (Out < 512 ? 64 : Out < 3000 ? 44 : 200);
-    return rowbytes <= (rowbytes % 64 ? longest * 3 / 2 : longest) * KB;
+    if (N > 16) return Out < 8192 && rowbytes * 2 <= (Out >= 2500 && Out <= 5000 ? 34 : 13) * KB;
+    if (!f32 && Out >= 8192 && rowbytes < 8 * KB) return false;
+    return rowbytes <= (Out < 1500 ? 10 : Out < 2500 ? 17 : f32 ? 100 : 50) * KB;
 }
+// Weights of half the memory-side cache (256 MB) and more are not kept in any cache between two calls, and read once per call:
+// nontemporal loads stream 6.6 TB/s where plain ones reach 6.0 (25088 -> 4096 bf16, 10 rows: 37.6 -> 35.4 us; 32 MB of weights,
+// still cached: 8.2 -> 8.5).
+static bool fc_streams(int dtype, int In, int Out) { return (size_t)In * Out * dtype_size(dtype) >= (size_t)128 << 20; }
 
-template <typename T, typename TZ, int NB>
-__global__ __launch_bounds__(kFcSmallWaves * 64) void fc_fwd_small_kernel(const char *__restrict__ a, const char *__restrict__ w,
-                                                                          const float *__restrict__ bias, TZ *__restrict__ z, int N,
-                                                                          int In, int Out, int relu)
+template <typename T, typename TZ, int NB, bool STREAM>
+__global__ __launch_bounds__(fc_small_waves(NB) * 64) void fc_fwd_small_kernel(const char *__restrict__ a, const char *__restrict__ w,
+                                                                             const float *__restrict__ bias, TZ *__restrict__ z,
+                                                                             int N, int In, int Out, int relu)
 {
     typedef float f32x4m __attribute__((ext_vector_type(4)));
-    constexpr int ROW = 256 + 16;                         // LDS bytes per batch row of a wave's piece
+    constexpr int NW = fc_small_waves(NB);
+    constexpr int ROW = 256 + 16;                         // LDS bytes per row of a wave's piece
     constexpr int kRed = NB * 16 * 17;                    // sums of a wave
     static_assert(kRed * 4 <= NB * 16 * ROW, "the sums take the place of the activations");
-    extern __shared__ __align__(16) char smem[];          // [wave][NB * 16][ROW], later [wave][kRed]
+    extern __shared__ __align__(16) char smem[];          // [wave][16 weight rows, NB * 16 batch rows][ROW], later [wave][kRed]
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int o0 = blockIdx.x * 16;
     const size_t rowbytes = (size_t)In * sizeof(T);
     // (rows past the ends are clamped: what they yield is not stored)
-    const char *wrow = w + (size_t)min(o0 + c, Out - 1) * rowbytes;
-    char *As = smem + wv * (NB * 16 * ROW);
+    constexpr int kWave = (16 + NB * 16) * ROW;           // LDS bytes of a wave
+    char *Ws = smem + wv * kWave, *As = Ws + 16 * ROW;
     f32x4m acc[NB];
 #pragma unroll
     for (int x = 0; x < NB; ++x) acc[x] = f32x4m{0.f, 0.f, 0.f, 0.f};
-    // A piece's weights as the MFMA wants them; its activations four whole rows per load (a load in the MFMA's layout
-    // touches sixteen rows), rearranged through the wave's own LDS block, which needs no barrier.
-    struct Piece { uint4 w[4], a[NB * 4]; };
+    // Four whole rows of a piece per load, rearranged through the wave's own LDS block, which needs no barrier.
+    typedef fc_u32x4 u32x4;
+    struct Piece { u32x4 w[4], a[NB * 4]; };
     const int pieces = (int)((rowbytes + 255) / 256);
     auto load = [&](int k, Piece &v) __attribute__((always_inline)) {
         // (past the row's end: its last 16 bytes again, and zeros for both operands below)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const size_t off = (size_t)k * 256 + e * 64 + g * 16;
-            v.w[e] = *reinterpret_cast<const uint4 *>(wrow + (off < rowbytes ? off : rowbytes - 16));
-        }
         const size_t off = (size_t)k * 256 + c * 16, at = off < rowbytes ? off : rowbytes - 16;
 #pragma unroll
-        for (int i = 0; i < NB * 4; ++i) v.a[i] = *reinterpret_cast<const uint4 *>(a + (size_t)min(4 * i + g, N - 1) * rowbytes + at);
+        for (int i = 0; i < 4; ++i) {
+            const u32x4 *src = reinterpret_cast<const u32x4 *>(w + (size_t)min(o0 + 4 * i + g, Out - 1) * rowbytes + at);
+            if (STREAM) v.w[i] = __builtin_nontemporal_load(src);
+            else v.w[i] = *src;
+        }
+#pragma unroll
+        for (int i = 0; i < NB * 4; ++i) v.a[i] = *reinterpret_cast<const u32x4 *>(a + (size_t)min(4 * i + g, N - 1) * rowbytes + at);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto multiply = [&](int k, Piece &v) __attribute__((always_inline)) {
-        if ((size_t)(k + 1) * 256 > rowbytes) {
+        if ((size_t)(k + 1) * 256 > rowbytes && (size_t)k * 256 + c * 16 >= rowbytes) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if ((size_t)k * 256 + e * 64 + g * 16 >= rowbytes) v.w[e] = make_uint4(0, 0, 0, 0);
-            if ((size_t)k * 256 + c * 16 >= rowbytes) {
+            for (int i = 0; i < 4; ++i) v.w[i] = u32x4{0, 0, 0, 0};
 #pragma unroll
-                for (int i = 0; i < NB * 4; ++i) v.a[i] = make_uint4(0, 0, 0, 0);
-            }
+            for (int i = 0; i < NB * 4; ++i) v.a[i] = u32x4{0, 0, 0, 0};
         }
+        uint4 wf[4];
 #pragma unroll
-        for (int i = 0; i < NB * 4; ++i) *reinterpret_cast<uint4 *>(As + (4 * i + g) * ROW + c * 16) = v.a[i];
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4 *>(Ws + (4 * i + g) * ROW + c * 16) = v.w[i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wf[e] = *reinterpret_cast<const uint4 *>(Ws + c * ROW + e * 64 + g * 16);
+#pragma unroll
+        for (int i = 0; i < NB * 4; ++i) *reinterpret_cast<u32x4 *>(As + (4 * i + g) * ROW + c * 16) = v.a[i];
         uint4 af[NB][4];
 #pragma unroll
         for (int x = 0; x < NB; ++x)
@@ -252,11 +256,11 @@ __global__ __launch_bounds__(kFcSmallWaves * 64) void fc_fwd_small_kernel(const 
 #pragma unroll
             for (int x = 0; x < NB; ++x) {
                 if constexpr (sizeof(T) == 2) {
-                    acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v.w[e]), __builtin_bit_cast(bf16x8, af[x][e]), acc[x], 0, 0, 0);
+                    acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[e]), __builtin_bit_cast(bf16x8, af[x][e]), acc[x], 0, 0, 0);
                 } else {
-                    const f32x4 wf = __builtin_bit_cast(f32x4, v.w[e]), xf = __builtin_bit_cast(f32x4, af[x][e]);
+                    const f32x4 wv4 = __builtin_bit_cast(f32x4, wf[e]), xf = __builtin_bit_cast(f32x4, af[x][e]);
 #pragma unroll
-                    for (int k4 = 0; k4 < 4; ++k4) acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[k4], xf[k4], acc[x], 0, 0, 0);
+                    for (int k4 = 0; k4 < 4; ++k4) acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv4[k4], xf[k4], acc[x], 0, 0, 0);
                 }
             }
         __builtin_amdgcn_sched_barrier(0);
@@ -265,27 +269,26 @@ __global__ __launch_bounds__(kFcSmallWaves * 64) void fc_fwd_small_kernel(const 
     Piece v0, v1;
     const int last = pieces - 1;
     if (wv < pieces) load(wv, v0);
-    for (int k = wv; k < pieces; k += 2 * kFcSmallWaves) {   // (past the end: the last piece again, not used)
-        load(min(k + kFcSmallWaves, last), v1);
+    for (int k = wv; k < pieces; k += 2 * NW) {   // (past the end: the last piece again, not used)
+        load(min(k + NW, last), v1);
         multiply(k, v0);
-        if (k + kFcSmallWaves >= pieces) break;
-        load(min(k + 2 * kFcSmallWaves, last), v0);
-        multiply(k + kFcSmallWaves, v1);
+        if (k + NW >= pieces) break;
+        load(min(k + 2 * NW, last), v0);
+        multiply(k + NW, v1);
     }
     // register e of lane 16 g + c: output o0 + 4 g + e of batch row c (a wave's sums go to its own LDS block)
     float *red = reinterpret_cast<float *>(smem);
-    constexpr int kWave = NB * 16 * ROW / 4;
 #pragma unroll
     for (int x = 0; x < NB; ++x)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) red[wv * kWave + (x * 16 + c) * 17 + 4 * g + e] = acc[x][e];
+        for (int e = 0; e < 4; ++e) red[wv * (kWave / 4) + (x * 16 + c) * 17 + 4 * g + e] = acc[x][e];
     __syncthreads();
-    for (int i = tid; i < NB * 256; i += kFcSmallWaves * 64) {
+    for (int i = tid; i < NB * 256; i += NW * 64) {
         const int n = i >> 4, o = i & 15;
         if (n >= N || o0 + o >= Out) continue;
         float s = bias ? bias[o0 + o] : 0.f;
 #pragma unroll
-        for (int v = 0; v < kFcSmallWaves; ++v) s += red[v * kWave + n * 17 + o];
+        for (int v = 0; v < NW; ++v) s += red[v * (kWave / 4) + n * 17 + o];
         if (relu) s = fmaxf(s, 0.f);
         Elem<TZ>::store(z + (size_t)n * Out + o0 + o, s);
     }
@@ -294,38 +297,48 @@ __global__ __launch_bounds__(kFcSmallWaves * 64) void fc_fwd_small_kernel(const 
 template <typename T, typename TZ>
 static int launch_fc_small(const void *a, const void *w, const float *bias, void *z, int N, int In, int Out, int relu, hipStream_t s)
 {
-    auto launch = [&](auto kern, int nb) {
+    const int nb = N <= 16 ? 1 : 2;
+    auto launch = [&](auto kern) {
         if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return (int)VGG_ERR_LAUNCH;
-        const size_t lds = (size_t)kFcSmallWaves * nb * 16 * (256 + 16);
-        hipLaunchKernelGGL(kern, dim3((unsigned)((Out + 15) / 16)), dim3(kFcSmallWaves * 64), lds, s, (const char *)a, (const char *)w,
+        const int waves = fc_small_waves(nb);
+        const size_t lds = (size_t)waves * (16 + nb * 16) * (256 + 16);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((Out + 15) / 16)), dim3(waves * 64), lds, s, (const char *)a, (const char *)w,
                            bias, (TZ *)z, N, In, Out, relu);
         return launch_status();
     };
-    return N <= 16 ? launch(fc_fwd_small_kernel<T, TZ, 1>, 1) : launch(fc_fwd_small_kernel<T, TZ, 2>, 2);
+    const bool stream = fc_streams(sizeof(T) == 2 ? VGG_BF16 : VGG_F32, In, Out);
+    if (nb == 1) return stream ? launch(fc_fwd_small_kernel<T, TZ, 1, true>) : launch(fc_fwd_small_kernel<T, TZ, 1, false>);
+    return stream ? launch(fc_fwd_small_kernel<T, TZ, 2, true>) : launch(fc_fwd_small_kernel<T, TZ, 2, false>);
 }
 
-// z = f(bias + sum over splits), converted to TZ.
+// z = f(bias + sum over splits), converted to TZ.  Bound by reading the partial sums, eight of them in flight (one at a time
+// was a chain of loads: 16 splits of 100 x 4096 8.8 -> 6 us).
 template <typename TZ>
-__global__ void fc_finish_kernel(const float *__restrict__ part, const float *__restrict__ bias, TZ *__restrict__ z, int N,
-                                 int Out, int splits, int relu)
+__global__ __launch_bounds__(256) void fc_finish_kernel(const float *__restrict__ part, const float *__restrict__ bias, TZ *__restrict__ z,
+                                                        int N, int Out, int splits, int relu)
 {
     const size_t n = (size_t)N * Out;
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     float s = bias ? bias[i % Out] : 0.f;
+#pragma unroll 8
     for (int k = 0; k < splits; ++k) s += part[(size_t)k * n + i];
     if (relu) s = fmaxf(s, 0.f);
     Elem<TZ>::store(z + i, s);
 }
 
-static void fc_plan(int dtype, int N, int In, int Out, FcArgs &a)
+// launch: the query sizes the workspace for two workgroups per CU; the launch takes one per CU for rows of up to 32 KB, where
+// writing and reading the partial sums costs as much as streaming the weights (bf16 4096 -> 4096, batch 100: 20.0 -> 17.5 us;
+// 25088 -> 4096 bf16 54 / 55, fp32 217 / 230: there two share the CU's memory latency).
+static void fc_plan(int dtype, int N, int In, int Out, FcArgs &a, bool launch)
 {
     a.N = N; a.In = In; a.Out = Out;
     a.units = (In * dtype_size(dtype) + 63) / 64;
     a.tiles_n = (Out + 127) / 128;
     a.tiles_m = (N + 127) / 128;
     const int tiles = a.tiles_n * a.tiles_m;
-    int splits = (512 + tiles - 1) / tiles;
+    const int want = launch && a.units <= 512 && (dtype == VGG_BF16 || N <= 32) ? 256 : 512;
+    int splits = (want + tiles - 1) / tiles;
     const int max_splits = (a.units + 7) / 8;  // at least two steps per split
     if (splits > max_splits) splits = max_splits;
     if (splits < 1) splits = 1;
@@ -337,7 +350,7 @@ static int fc_splits(const FcArgs &a) { return (a.units + a.units_per_split - 1)
 size_t fc_workspace(int dtype, int N, int In, int Out)
 {
     FcArgs a;
-    fc_plan(dtype, N, In, Out, a);
+    fc_plan(dtype, N, In, Out, a, false);
     return round_up((size_t)fc_splits(a) * N * Out * 4, 256);
 }
 
@@ -352,20 +365,32 @@ int fc_forward(int dtype, int N, int In, int Out, const void *a_, const void *w,
                                    : launch_fc_small<float, float>(a_, w, bias, z, N, In, Out, relu, s);
     }
     FcArgs a;
-    fc_plan(dtype, N, In, Out, a);
+    fc_plan(dtype, N, In, Out, a, true);
     const int splits = fc_splits(a);
     a.a = static_cast<const char *>(a_);
     a.w = static_cast<const char *>(w);
     a.part = static_cast<float *>(ws);
     const dim3 grid((unsigned)(a.tiles_n * a.tiles_m * splits));
-    const bool exact = (size_t)In * dtype_size(dtype) % 64 == 0;
-    if (dtype == VGG_BF16) {
-        if (exact) hipLaunchKernelGGL((fc_fwd_kernel<bf16_t, true>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((fc_fwd_kernel<bf16_t, false>), grid, dim3(256), 0, s, a);
-    } else {
-        if (exact) hipLaunchKernelGGL((fc_fwd_kernel<float, true>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((fc_fwd_kernel<float, false>), grid, dim3(256), 0, s, a);
-    }
+    const bool vec = (size_t)In * dtype_size(dtype) % 16 == 0;
+    const bool stream = a.tiles_m == 1 && fc_streams(dtype, In, Out);
+    const int mb = N > 96 ? 4 : (N + 31) / 32;
+    auto launch = [&](auto elem, auto vc, auto st) {
+        typedef decltype(elem) T;
+        constexpr bool V = decltype(vc)::value, ST = decltype(st)::value;
+        switch (mb) {
+        case 1: hipLaunchKernelGGL((fc_fwd_kernel<T, V, 1, ST>), grid, dim3(256), 0, s, a); break;
+        case 2: hipLaunchKernelGGL((fc_fwd_kernel<T, V, 2, ST>), grid, dim3(256), 0, s, a); break;
+        case 3: hipLaunchKernelGGL((fc_fwd_kernel<T, V, 3, ST>), grid, dim3(256), 0, s, a); break;
+        default: hipLaunchKernelGGL((fc_fwd_kernel<T, V, 4, ST>), grid, dim3(256), 0, s, a);
+        }
+    };
+    auto launch_t = [&](auto elem) {
+        if (!vec) launch(elem, std::false_type{}, std::false_type{});
+        else if (stream) launch(elem, std::true_type{}, std::true_type{});
+        else launch(elem, std::true_type{}, std::false_type{});
+    };
+    if (dtype == VGG_BF16) launch_t(bf16_t{});
+    else launch_t(float{});
     if (hipGetLastError() != hipSuccess) return VGG_ERR_LAUNCH;
     const size_t n = (size_t)N * Out;
     const dim3 g2((unsigned)((n + 255) / 256));

@@ -805,6 +805,27 @@ def test_fc_forward_where_the_kernel_changes(dtype, N, In, Out):
     assert (z[N * Out:] == -7.0).all()
 
 
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("N,In,Out", [(33, 264, 129), (64, 520, 127), (65, 136, 130), (96, 1032, 200), (97, 4104, 40), (128, 24, 257), (257, 264, 128),
+                                      (40, 261, 65), (70, 1000, 33),
+                                      (3, 5120, 40), (3, 5136, 40), (16, 8704, 1500), (16, 8712, 1504), (2, 25608, 2504), (20, 3328, 96),
+                                      (32, 3336, 96), (17, 8712, 2504), (20, 1664, 8200), (1, 2048, 8208),
+                                      (5, 16388, 2052), (40, 16392, 2050), (9, 32776, 2056), (33, 32784, 2056)])
+def test_fc_forward_row_blocks_and_streamed_weights(dtype, N, In, Out):
+    """Every number of 32-row blocks of the split kernel, rows that end inside a step (whole 16-byte segments or not), both
+    sides of the lines to the kernel of small batches, and weights of 128 MB, which are read past the caches; against the
+    oracle on the operands as stored; 1e-5: fp32 sums of at most 32784 products in order."""
+    rng = np.random.default_rng(np.random.PCG64(N + In + Out))
+    a, w = (dev(rng.standard_normal(s, dtype=np.float32), TDT[dtype]) for s in ((N, In), (Out, In)))
+    b = rng.standard_normal(Out).astype(np.float32)
+    ref = R.fc(a.float().cpu().numpy(), w.float().cpu().numpy(), b, relu=False)
+    z = torch.full((N * Out + 64,), -7.0, device="cuda")
+    B.vgg_fc(dtype, N, In, Out, a, w, dev(b), z, B.F32, 0, ws_bytes(B.vgg_fc_workspace_bytes(dtype, N, In, Out)))
+    torch.cuda.synchronize()
+    assert max_rel_err(z[:N * Out].view(N, Out).cpu().numpy(), ref) <= 1e-5
+    assert (z[N * Out:] == -7.0).all()
+
+
 @pytest.mark.parametrize("N,In,Out", [(16, 260, 129), (17, 256, 64), (49, 1028, 3), (80, 132, 191), (97, 516, 257), (129, 252, 65),
                                       (31, 129, 1), (112, 127, 66)])
 def test_fc_backward_fp32_tile_edges(N, In, Out):
