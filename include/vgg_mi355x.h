@@ -359,8 +359,9 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *       224 / 384 halo rows, 10 / 11 those with nine taps of weights in
  *       flight, 12 / 13 the bf16 kernel for launches of few tiles (64 pixels
  *       x 32 channels, the contraction split over the four / eight waves of a
- *       workgroup); weight
- *       gradient: 100 linear tiles, 114 / 116 patches 14 / 16 pixels wide,
+ *       workgroup), 14 / 15 / 16 the fp32 implicit GEMM on the bf16 matrix
+ *       unit (three parts per value) with room for 384 / 448 / 192 halo rows;
+ *       weight gradient: 100 linear tiles, 114 / 116 patches 14 / 16 pixels wide,
  *       103 the kernel for at most three input channels (fp32); 116 / 117
  *       the bf16 kernel and its variant for at most 32 input channels, 108 /
  *       109 the same on patches of 8 x 8 instead of 4 x 16 pixels, 118

@@ -481,6 +481,65 @@ def test_conv3x3_bf16_split_over_workgroups(shape):
     assert max_rel_err(from_nhwc(y), R.conv3x3_bwd_data(d["dy"], d["w"]) * (from_nhwc(xs) > 0)) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("shape,kernel,bn", [
+    ((1, 9, 9, 48, 40), 14, 64), ((2, 32, 48, 32, 64), 14, 64), ((3, 20, 21, 40, 130), 14, 64), ((33, 64, 64, 16, 72), 14, 128),
+    ((5, 56, 56, 16, 132), 15, 64), ((43, 56, 56, 16, 132), 15, 128), ((43, 56, 56, 40, 128), 15, 128), ((50, 14, 14, 80, 512), 16, 64), ((100, 13, 14, 16, 268), 16, 64)])
+def test_conv3x3_fp32_in_three_parts(shape, kernel, bn):
+    """The fp32 kernels on the bf16 matrix unit: half a last chunk, ragged channels, every tile, pooled and masked.  Sums of at
+    most 720 products, each exact to 2^-24, in fp32: 2e-6 of the largest output against the oracle."""
+    N, H, W, Cin, Cout = shape
+    plan = B.vgg_conv3x3_plan(B.PLAN_FWD, B.F32, N, H, W, Cin, Cout)
+    assert plan[0] == kernel and plan[2] == bn, plan
+    d = synth.conv_layer_inputs(N, H, W, Cin, Cout, seed=sum(shape))
+    n = N * H * W * Cout
+    y = torch.full((n + 256,), -7.0, device="cuda")
+    ws = ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(B.F32, N, H, W, Cin, Cout))
+    x, w = to_nhwc(d["x"], B.F32), _pack(B.F32, d["w"])
+    B.vgg_conv3x3_fwd(B.F32, N, H, W, Cin, Cout, x, w, dev(d["b"]), y, 1, ws)
+    torch.cuda.synchronize()
+    got = y[:n].view(N, H, W, Cout)
+    assert max_rel_err(from_nhwc(got), R.conv3x3_fwd(d["x"], d["w"], d["b"], relu=True)) <= 2e-6
+    assert (y[n:] == -7.0).all()
+    if H % 16 == 0 and W % 16 == 0 and Cout % 4 == 0:
+        po, arg = torch.empty((N, H // 2, W // 2, Cout), device="cuda"), torch.empty((N, H // 2, W // 2, Cout), dtype=torch.uint8, device="cuda")
+        B.vgg_conv3x3_fwd_pool(B.F32, N, H, W, Cin, Cout, x, w, dev(d["b"]), None, po, 1, ws=ws, argmax=arg)
+        pref, aref = R.maxpool2x2(from_nhwc(got))
+        assert np.array_equal(from_nhwc(po), pref) and np.array_equal(arg.permute(0, 3, 1, 2).cpu().numpy(), aref)
+    if Cin % 16 == 0:                                         # data gradient of the mirrored layer
+        xs = torch.randn((N, H, W, Cout), device="cuda")
+        B.vgg_conv3x3_bwd_data(B.F32, N, H, W, Cout, Cin, x, w, xs, y, ws_bytes(B.vgg_conv3x3_bwd_data_workspace_bytes(B.F32, N, H, W, Cout, Cin)))
+        torch.cuda.synchronize()
+        ref = R.conv3x3_fwd(d["x"], d["w"], None, relu=False) * (from_nhwc(xs) > 0)
+        assert max_rel_err(from_nhwc(y[:n].view(N, H, W, Cout)), ref) <= 2e-6
+
+
+def test_conv3x3_fp32_in_three_parts_infinities_and_range():
+    """Infinities, NaN, overflow and values near both ends of the range come out as in fp32 arithmetic."""
+    N, H, W, Cin, Cout = 1, 16, 32, 32, 64
+    assert B.vgg_conv3x3_plan(B.PLAN_FWD, B.F32, N, H, W, Cin, Cout)[0] == 14
+    rng = np.random.default_rng(5)
+    x, w = rng.standard_normal((N, Cin, H, W)).astype(np.float32), rng.standard_normal((Cout, Cin, 3, 3)).astype(np.float32)
+    w[:8] = 1.0                                               # second and third parts are zero
+    w[8:12] = 0.0                                             # infinity times zero
+    x[0, 3, 2, 4], x[0, 5, 9, 20], x[0, 7, 9, 21], x[0, 9, 14, 9], x[0, 1, 5, 28] = np.inf, np.inf, -np.inf, np.nan, 3.2e38
+    y = torch.empty((N, H, W, Cout), device="cuda")
+    ws = ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(B.F32, N, H, W, Cin, Cout))
+    B.vgg_conv3x3_fwd(B.F32, N, H, W, Cin, Cout, to_nhwc(x, B.F32), _pack(B.F32, w), None, y, 0, ws)
+    torch.cuda.synchronize()
+    got = from_nhwc(y)
+    with np.errstate(all="ignore"):
+        ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double(), padding=1).float().numpy()
+    ok = ~np.isnan(ref)                                       # (a tile leaves through a maximum, which drops NaN for -infinity)
+    assert np.array_equal(np.isfinite(got), np.isfinite(ref)) and np.isposinf(ref).any() and (~ok).any()
+    for f in (np.isposinf, np.isneginf):
+        assert np.array_equal(f(got[ok]), f(ref[ok]))
+    for s in (2.0 ** -90, 2.0 ** 100):
+        xs = (rng.standard_normal((N, Cin, H, W)) * s).astype(np.float32)
+        B.vgg_conv3x3_fwd(B.F32, N, H, W, Cin, Cout, to_nhwc(xs, B.F32), _pack(B.F32, w), None, y, 0, ws)
+        torch.cuda.synchronize()
+        assert max_rel_err(from_nhwc(y), R.conv3x3_fwd(xs, w, None, relu=False)) <= 2e-6
+
+
 @pytest.mark.parametrize("dtype,shape,kernel", [
     (B.F32, (2, 46, 79, 32, 36), 1), (B.F32, (1, 24, 200, 96, 64), 1), (B.F32, (1, 97, 97, 48, 132), 1), (B.F32, (3, 63, 65, 3, 20), 1),
     (B.F32, (9, 66, 66, 16, 192), 0), (B.F32, (1, 6, 150, 16, 32), 0),
