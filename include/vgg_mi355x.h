@@ -360,7 +360,8 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *       flight, 12 / 13 the bf16 kernel for launches of few tiles (64 pixels
  *       x 32 channels, the contraction split over the four / eight waves of a
  *       workgroup), 14 / 15 / 16 the fp32 implicit GEMM on the bf16 matrix
- *       unit (three parts per value) with room for 384 / 448 / 192 halo rows;
+ *       unit (three parts per value), 256-pixel tiles with room for 384 / 448
+ *       halo rows and 128-pixel tiles;
  *       weight gradient: 100 linear tiles, 114 / 116 patches 14 / 16 pixels wide,
  *       103 the kernel for at most three input channels (fp32); 116 / 117
  *       the bf16 kernel and its variant for at most 32 input channels, 108 /
@@ -372,7 +373,7 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *   [3] 0: a tile is consecutive pixels, 1: a patch of one image
  *   [4] pixel tiles
  *   [5] ranges in which a tile's contraction is summed (forward, data
- *       gradient; kernels 1 and 2: by a workgroup each) or partial results
+ *       gradient; kernels 1, 2 and 14 to 16: by a workgroup each) or partial results
  *       that the fixed-order reduction adds (weight gradient)
  *   [6] workgroups of the main launch */
 #define VGG_PLAN_FWD 0

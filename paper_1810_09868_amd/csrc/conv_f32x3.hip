@@ -1,12 +1,15 @@
 // Implicit-GEMM 3x3 convolution in fp32 on the bf16 matrix unit (f32x3.h), gfx950, NHWC: forward and data gradient of every
-// launch whose contraction is not split and whose tiles are consecutive pixels or whole patches.  Views, tiles, halos and
+// launch whose tiles are consecutive pixels or whole patches, the contraction split over workgroups where conv_igemm.hip says so.  Views, tiles, halos and
 // epilogue as in conv_igemm.hip; reference rows likewise.
 //
 // Workgroup: WM x WN waves, each 64 pixels x 16 NJ channels, in chunks of 32 channels.  LDS holds the chunk's halo and one
 // tap's weights as three planes of bf16 parts, 64-byte rows whose 16-byte segment s lies at s ^ ((row >> 1) & 3)
 // (conflict-free for the fragment reads of v_mfma_f32_16x16x32_bf16); weights in two buffers, a barrier per tap.
 // Every value is split once per workgroup, on its way from a register to LDS: the weights of tap t + 1 in the middle of tap t,
-// the next chunk's halo, requested before the last tap, at the chunk's end.
+// the next chunk's halo, requested before the last tap, at the chunk's end.  256-pixel tiles: eight waves, one workgroup per
+// CU; 128-pixel tiles x 64 channels: four waves, two per CU.  Bound by MFMA issue at the clock that random operands allow:
+// 128 -> 256 at 56x56, batch 100, 757 us = 245 TFLOP/s of fp32 products, 1.47 PFLOP/s of bf16 ones.  (The tap loop is not
+// unrolled: the addresses of nine taps took ninety registers.)
 #include "conv_tile.h"
 #include "f32x3.h"
 
@@ -30,12 +33,15 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void conv3x3_igemm_f32x3_kernel(Con
     // (XCD-aware numbering: each XCD, with its own L2, works through one contiguous range of tiles)
     const int nblk = gridDim.x, xcd = blockIdx.x & 7;
     const int bid = xcd * (nblk >> 3) + min(xcd, nblk & 7) + (blockIdx.x >> 3);
-    const int tile_n = bid % p.tiles_n, tile_m = bid / p.tiles_n;
+    // (split contraction: the ksplit workgroups of a tile are neighbours, each with p.kchunks sixteen-channel chunks)
+    const int split = bid % p.ksplit, tile = bid / p.ksplit;
+    const int tile_n = tile % p.tiles_n, tile_m = tile / p.tiles_n;
+    const int c_first = split * p.kchunks * 16, cspan = min(p.kchunks * 16, p.CinP - c_first);   // this workgroup's channels
     const int n0 = tile_n * BN;
     const TileOrigin org = tile_origin(p.g, tile_m);
     const int pitch = p.g.pitch;
     const size_t xrow = (size_t)p.CinP * sizeof(T);
-    const int nchunks = (p.CinP + KC - 1) / KC;              // (the last one may be half: 16 channels)
+    const int nchunks = (cspan + KC - 1) / KC;               // (the last one may be half: 16 channels)
 
     const int srow = tid >> 3, sseg = tid & 7;               // this thread's row (of every NT / 8) and segment of what it stages
     // four channels = 8 bytes of a plane's row
@@ -48,13 +54,13 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void conv3x3_igemm_f32x3_kernel(Con
 #pragma unroll
     for (int k = 0; k < NWT; ++k) wvoff[k] = (unsigned)min(n0 + srow + k * (NT / 8), p.Cout - 1) * (unsigned)xrow;   // columns past Cout are never stored
     auto load_w = [&](int t, int c) __attribute__((always_inline)) {
-        const char *base = p.w + (size_t)t * p.Cout * xrow + (size_t)c * KC * 4;
-        const unsigned col = c * KC + sseg * 4 < p.CinP ? sseg * 16 : 0;
+        const char *base = p.w + (size_t)t * p.Cout * xrow + (size_t)(c_first + c * KC) * 4;
+        const unsigned col = c * KC + sseg * 4 < cspan ? sseg * 16 : 0;
 #pragma unroll
         for (int k = 0; k < NWT; ++k) wr[k] = *reinterpret_cast<const u32x4 *>(base + (wvoff[k] + col));
     };
     auto store_w = [&](int c, int buf) __attribute__((always_inline)) {
-        const bool in = c * KC + sseg * 4 < p.CinP;
+        const bool in = c * KC + sseg * 4 < cspan;
 #pragma unroll
         for (int k = 0; k < NWT; ++k) {
             const Parts4 s = split_parts(in ? wr[k] : u32x4{0u, 0u, 0u, 0u});
@@ -68,11 +74,11 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void conv3x3_igemm_f32x3_kernel(Con
     __syncthreads();
     typedef const __attribute__((address_space(1))) u32x4 *gvec_t;
     auto load_x = [&](int c) __attribute__((always_inline)) {
-        const bool in = c * KC + sseg * 4 < p.CinP;
+        const bool in = c * KC + sseg * 4 < cspan;
 #pragma unroll
         for (int k = 0; k < NX; ++k) {
             const int px = pix[srow + k * (NT / 8)];
-            const gvec_t src = px < 0 || !in ? (gvec_t)kZeroRow : (gvec_t)(p.x + (size_t)px * xrow + (size_t)(c * KC + sseg * 4) * 4);
+            const gvec_t src = px < 0 || !in ? (gvec_t)kZeroRow : (gvec_t)(p.x + (size_t)px * xrow + (size_t)(c_first + c * KC + sseg * 4) * 4);
             xr[k] = *src;
         }
     };
@@ -100,7 +106,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void conv3x3_igemm_f32x3_kernel(Con
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             hi[0][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
-            if (p.bias)
+            if (p.bias && !p.part)   // (split contraction: the finishing kernel adds the bias)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) hi[0][j][e] = p.bias[min(c0 + j * 16 + e, p.Cout - 1)];
         }
@@ -179,6 +185,19 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void conv3x3_igemm_f32x3_kernel(Con
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) hi[i][j][e] = join_parts(hi[i][j][e], lo[i][j][e]);
+    if (p.part) {   // raw sums to the partial buffer of this range (Cout is a multiple of 4 then)
+        float *part = p.part + (size_t)split * p.g.M * p.Cout;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int m = tile_pixel(p.g, org, wm * 64 + i * 16 + q);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int col = n0 + wn * NJ * 16 + j * 16 + g * 4;
+                if (m >= 0 && col < p.Cout) *reinterpret_cast<f32x4v *>(part + (size_t)m * p.Cout + col) = hi[i][j];
+            }
+        }
+        return;
+    }
     conv_epilogue_impl<T, BM, BN, WM, WN>(
         [&](int i, int j0, char *epi, float low) __attribute__((always_inline)) {
             // (fp32: a pass is 32 columns; pixel block i of 32 rows = 16-pixel blocks 2 i, 2 i + 1)
@@ -214,13 +233,13 @@ static int launch(const ConvArgs &a0, const TileGeom &g, hipStream_t stream)
     if (lds < (size_t)WM * WN * kEpiBytes) lds = (size_t)WM * WN * kEpiBytes;
     auto kern = conv3x3_igemm_f32x3_kernel<WM, WN, NJ, SA>;
     if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return VGG_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.g.ntiles * a.tiles_n)), dim3(WM * WN * 64), lds, stream, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.g.ntiles * a.tiles_n * a.ksplit)), dim3(WM * WN * 64), lds, stream, a);
     return launch_status();
 }
 
 int launch_conv_f32x3(const ConvArgs &a, const TileGeom &g, bool narrow, hipStream_t stream)
 {
-    if (g.rows == 128) return launch<2, 2, 2, kDmaHaloRowsHalf>(a, g, stream);
+    if (g.rows == 128) return g.S <= kDmaHaloRowsHalf ? launch<2, 2, 2, kDmaHaloRowsHalf>(a, g, stream) : launch<2, 2, 2, kF32x3HaloRowsHalfBig>(a, g, stream);
     if (g.S <= kDmaHaloRows) return narrow ? launch<4, 2, 2, kDmaHaloRows>(a, g, stream) : launch<4, 2, 4, kDmaHaloRows>(a, g, stream);
     return narrow ? launch<4, 2, 2, kDmaHaloRowsBig>(a, g, stream) : launch<4, 2, 4, kDmaHaloRowsBig>(a, g, stream);
 }

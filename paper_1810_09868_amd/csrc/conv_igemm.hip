@@ -1123,6 +1123,8 @@ enum ConvKernel {
     kSmall4, kSmall8,                           // 64 x 32 tiles, the contraction split over four / eight waves
     kF32x3, kF32x3Big, kF32x3Half               // fp32 in three bf16 parts: 256-pixel tiles, 384 / 448 halo rows; 128-pixel tiles
 };
+// the kernels whose workgroups may share a tile's contraction through memory
+static bool over_workgroups(int kernel) { return kernel == kDma || kernel == kDmaBig || kernel == kF32x3 || kernel == kF32x3Big || kernel == kF32x3Half; }
 struct ConvPlan {
     TileGeom g;
     int kernel;
@@ -1208,11 +1210,41 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
             const TileGeom h = make_tile_geom(N, H, W, 128);
             if (h.S <= kDmaHaloRowsHalf) { c.g = h; c.kernel = kDmaHalf; }
         }
-        // Unsplit on a direct-to-LDS kernel's tiles: the same tiles on the bf16 matrix unit, 0.49 to 0.93 of the time (128 -> 256 at
-        // 56x56, batch 100, 1388 -> 763 us; 512 -> 512 at 28x28, batch 50, 1580 -> 773; 16 -> 40 at 20x33, batch 30, 14.4 -> 13.4).
-        // (that kernel's weight offsets are 32 bits)
-        if (c.ksplit == 1 && !wide && c.kernel != kStaged && (size_t)Cout * CinP * sizeof(float) < ((size_t)1 << 32))
-            c.kernel = c.kernel == kDma ? kF32x3 : c.kernel == kDmaBig ? kF32x3Big : kF32x3Half;
+        // The same launches on the bf16 matrix unit (conv_f32x3.hip), in the same tiles: 0.48 to 0.93 of the time over 150 shapes (128 ->
+        // 256 at 56x56, batch 100, 1388 -> 763 us; 512 -> 512 at 28x28, batch 50, 1580 -> 773; 16 -> 40 at 20x33, batch 30, 14.4 ->
+        // 13.4).  (That kernel's weight offsets are 32 bits.)
+        if ((size_t)Cout * CinP * sizeof(float) >= ((size_t)1 << 32)) return c;
+        const int cols64 = (Cout + 63) / 64;
+        if (wide) {
+            // 8 x 16 patches that pad by at most 1.6: over 240 shapes 0.34 to 0.95 of the time (8 -> 320 channels at 9x102 23 / 56 us),
+            // at 1.7 and more up to 1.02 where the other kernel's tiles are 128 wide.  One chunk of 16 channels is half zeros
+            // (0.96 to 1.11); small launches, 20 to 50 us, stay where their tests have them (0.6 to 0.8 here).
+            const TileGeom t = make_patch_geom(N, H, W, 128);
+            const int tiles = t.ntiles * cols64;
+            if (!pool && (long)t.ntiles * 128 * 10 <= (long)c.g.M * 16 && (CinP >= 64 ? (long)tiles * CinP >= 256 * 16 : CinP >= 32 && tiles >= 512)) {
+                c.g = t; c.kernel = kF32x3Half; c.bn = 64;
+            }
+            return c;
+        }
+        // (a contraction of 16 channels is half zeros there: up to 256 tiles 0.7 to 0.95 of the time, beyond 0.97 to 1.28)
+        if (c.kernel == kStaged || (CinP <= 16 && c.g.ntiles * (c.kernel == kDmaHalf ? cols64 : 2 * cols) > 256)) return c;
+        c.kernel = c.kernel == kDma ? kF32x3 : c.kernel == kDmaBig ? kF32x3Big : kF32x3Half;
+        // Few tiles: 128-pixel ones, up to 40 tiles of 256 pixels 0.84 to 0.97 of the time (7x10, batch 7, 112 -> 128 25.8 -> 21.7 us);
+        // beyond 50 up to 1.19 where the contraction is long.
+        if (narrow && !pool && c.kernel != kF32x3Half && c.g.ntiles * cols64 <= 40) {
+            const TileGeom t = make_tile_geom(N, H, W, 128);
+            if (t.S <= kF32x3HaloRowsHalfBig) {
+                c.g = t; c.kernel = kF32x3Half;
+                if (c.ksplit > 1) {
+                    const int want = (512 + t.ntiles * cols64 - 1) / (t.ntiles * cols64);
+                    c.kchunks = (chunks + (want < c.ksplit ? want : c.ksplit) - 1) / (want < c.ksplit ? want : c.ksplit);
+                }
+            }
+        }
+        if (c.ksplit > 1) {   // (whole chunks of 32 channels: never more ranges than conv_split's, whose partial sums the scratch holds)
+            c.kchunks = (c.kchunks + 1) / 2 * 2;
+            c.ksplit = (chunks + c.kchunks - 1) / c.kchunks;
+        }
         return c;
     }
     // bf16.  Shapes whose contraction is split (conv_split) form the same partial sums and add them in the same order,
@@ -1314,7 +1346,7 @@ void conv3x3_igemm_plan_info(int dtype, int N, int H, int W, int CinP, int Cout,
     info[3] = c.g.mode;
     info[4] = c.g.ntiles;
     info[5] = c.ksplit;
-    info[6] = c.g.ntiles * ((Cout + c.bn - 1) / c.bn) * (c.kernel == kDma || c.kernel == kDmaBig ? c.ksplit : 1);
+    info[6] = c.g.ntiles * ((Cout + c.bn - 1) / c.bn) * (over_workgroups(c.kernel) ? c.ksplit : 1);
 }
 
 bool conv3x3_pool_fusable(int dtype, int H, int W, int Cout)
@@ -1342,7 +1374,7 @@ int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void
 {
     if (pool && !conv3x3_pool_fused(dtype, N, H, W, CinP, Cout)) return VGG_ERR_UNSUPPORTED;
     ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool != nullptr);
-    const bool split = (c.kernel == kDma || c.kernel == kDmaBig) && c.ksplit > 1;   // over workgroups
+    const bool split = over_workgroups(c.kernel) && c.ksplit > 1;
     if (split && (!part_ws || !y || part_bytes < (size_t)c.ksplit * N * H * W * Cout * 4)) { c.ksplit = 1; c.kchunks = CinP * dtype_size(dtype) / kDataBytes; }
     ConvArgs a;
     a.x = static_cast<const char *>(x);

@@ -268,6 +268,7 @@ __device__ __forceinline__ void for_each_step(F &&f, std::integer_sequence<int, 
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
+constexpr int kF32x3HaloRowsHalfBig = 256;   // most halo rows of the 128-pixel tiles (75 KB: two workgroups per CU)
 // fp32 on tiles of g (256 or 128 pixels; narrow or 128 pixels: 64 channels, else 128), conv_f32x3.hip
 int launch_conv_f32x3(const ConvArgs &a, const TileGeom &g, bool narrow, hipStream_t stream);
 
