@@ -888,10 +888,10 @@ def test_fc_forward_row_blocks_and_streamed_weights(dtype, N, In, Out):
 
 
 @pytest.mark.parametrize("N,In,Out", [(16, 260, 129), (17, 256, 64), (49, 1028, 3), (80, 132, 191), (97, 516, 257), (129, 252, 65),
-                                      (31, 129, 1), (112, 127, 66)])
+                                      (31, 129, 1), (112, 127, 66), (40, 260, 129), (41, 256, 96), (48, 508, 33), (64, 1028, 160), (128, 100, 258), (41, 30, 5)])
 def test_fc_backward_fp32_tile_edges(N, In, Out):
     """The fp32 backward kernels at the edges of their tiles (16-row blocks, 128- and 256-column tiles, 64-output
-    passes, odd rows, rows that are not 16-byte aligned): sums of at most 257 (129) products of N(0,1) values against
+    passes, odd rows, rows that are not 16-byte aligned, both sides of the line to the bf16 matrix unit): sums of at most 257 (129) products of N(0,1) values against
     the oracle; the rounding of such a sum is below 1e-6 of the largest, the tolerance 1e-5."""
     rng = np.random.default_rng(N + In + Out)
     a, dz = rng.standard_normal((N, In)).astype(np.float32), rng.standard_normal((N, Out)).astype(np.float32)
