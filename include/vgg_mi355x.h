@@ -362,7 +362,8 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *       workgroup), 14 / 15 / 16 the fp32 implicit GEMM on the bf16 matrix
  *       unit (three parts per value), 256-pixel tiles with room for 384 / 448
  *       halo rows and 128-pixel tiles;
- *       weight gradient: 100 linear tiles, 114 / 116 patches 14 / 16 pixels wide,
+ *       weight gradient: 100 linear tiles, 114 / 116 / 108 patches of 4 x 14,
+ *       4 x 16 or 8 x 8 pixels on the bf16 matrix unit (three parts per value),
  *       103 the kernel for at most three input channels (fp32); 116 / 117
  *       the bf16 kernel and its variant for at most 32 input channels, 108 /
  *       109 the same on patches of 8 x 8 instead of 4 x 16 pixels, 118

@@ -50,49 +50,9 @@ struct WgradArgs {
 
 // Taps [T0, T0 + NT) of one wave: the main loop over the workgroup's tiles and the final sums.
 // S0: MFMA step before which the wave prepares the next tile's copies.
-// Patch tiles of the weight-gradient kernel: 4 rows x TW columns of one image (TW = 16 or 14, so that the
-// VGG widths 224, 112 and 56, 28 divide; what sticks out of the image is zero), halo 6 x (TW + 2).  Unlike the linear tiles (TW = 0, TileGeom
-// mode 0) their halo rows are an affine function of the tile row, so every x address of the main loop is
-// one per-lane base plus an immediate.  p.geo carries N, H, W, tiles_w, tiles_hw and their divisions.
-template <int TW>
-__device__ __forceinline__ TileOrigin wg_origin(const TileGeom &g, int tile)
-{
-    if (TW == 0) return tile_origin(g, tile);
-    TileOrigin o;
-    o.n = fast_div(tile, g.dTilesHW);
-    const int rem = tile - o.n * g.tiles_hw;
-    const int ty = fast_div(rem, g.dTilesW);
-    o.h0 = ty * 4;
-    o.w0 = (rem - ty * g.tiles_w) * TW;
-    o.m0 = 0; o.q0 = 0;
-    return o;
-}
-// output pixel of tile row j (-1: none) and, for linear tiles, its halo row
-template <int TW>
-__device__ __forceinline__ void wg_row(const TileGeom &g, const TileOrigin &o, int j, int &m, int &hrow)
-{
-    if (TW == 0) { tile_row(g, o, j, m, hrow); return; }
-    constexpr int D = TW ? TW : 1;
-    const int dy = j / D, dx = j - dy * D;
-    const int h = o.h0 + dy, w = o.w0 + dx;
-    m = (j < 4 * TW && h < g.H && w < g.W) ? (o.n * g.H + h) * g.W + w : -1;
-    hrow = 0;
-}
-template <int TW>
-__device__ __forceinline__ int wg_halo_pixel(const TileGeom &g, const TileOrigin &o, int i)
-{
-    if (TW == 0) return halo_pixel(g, o, i);
-    const int hy = i / (TW + 2), hx = i - hy * (TW + 2);
-    const int h = o.h0 - 1 + hy, w = o.w0 - 1 + hx;
-    if (h < 0 || h >= g.H || w < 0 || w >= g.W) return -1;
-    return (o.n * g.H + h) * g.W + w;
-}
-
-template <int T0, int NT, int S0, int TW>
+template <int T0, int NT, int S0>
 __device__ __forceinline__ void wgrad_body(const WgradArgs &p, char *smem)
 {
-    constexpr bool PATCH = TW != 0;
-    constexpr int PK = PATCH ? 4 * TW : kPK;           // pixels of a tile that are multiplied (g is staged as kPK rows)
     const int buf_bytes = kPK * kGRow + p.SX * kXRow;   // [kPK][256] g rows, then [SX][128] x rows
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -138,12 +98,12 @@ __device__ __forceinline__ void wgrad_body(const WgradArgs &p, char *smem)
     };
     constexpr int kXBatch = 3;                 // x blocks of a wave whose copies are spread over the steps
     constexpr int kOps = kGOps + kXBatch;      // copies that are spread over the MFMA steps
-    static_assert(S0 + kOps <= PK / 4, "one copy per MFMA step");
+    static_assert(S0 + kOps <= kPK / 4, "one copy per MFMA step");
     // lane l looks up halo row (l & 7) of this wave's x block k0 + (l >> 3) (blocks k0 .. k0 + 7)
     auto x_lookup = [&](const TileOrigin &org, int k0) __attribute__((always_inline)) {
         const int kk = k0 + (lane >> 3);
         const int i = (wv + kWaves * kk) * 8 + (lane & 7);
-        return (kk < nxw && i < p.geo.S) ? wg_halo_pixel<TW>(p.geo, org, i) : -1;
+        return (kk < nxw && i < p.geo.S) ? halo_pixel(p.geo, org, i) : -1;
     };
     // source addresses of g copy k / of x copy k of a lookup; m_l: output pixel of tile row `lane`
     auto g_src = [&](int m_l, int k) __attribute__((always_inline)) {
@@ -167,13 +127,13 @@ __device__ __forceinline__ void wgrad_body(const WgradArgs &p, char *smem)
         }
     };
 
-    const int wrow0 = __builtin_amdgcn_readfirstlane(wp * (PK / 2));
+    const int wrow0 = __builtin_amdgcn_readfirstlane(wp * (kPK / 2));
     const int nfirst = min(nxw, kXBatch);
     int hrow_l = 0;  // halo row (tap 0,0) of tile row `lane` of the tile being multiplied
     if (t_begin < t_end) {
-        const TileOrigin org0 = wg_origin<TW>(p.geo, t_begin);
+        const TileOrigin org0 = tile_origin(p.geo, t_begin);
         int m_l;
-        wg_row<TW>(p.geo, org0, lane, m_l, hrow_l);
+        tile_row(p.geo, org0, lane, m_l, hrow_l);
 #pragma unroll
         for (int k = 0; k < kGOps; ++k) dma(g_src(m_l, k), g_dst(smem, k));
         const int px_l = x_lookup(org0, 0);
@@ -197,9 +157,9 @@ __device__ __forceinline__ void wgrad_body(const WgradArgs &p, char *smem)
         const int ncopy = more ? kGOps + nfirst : 0;
         auto prepare = [&]() __attribute__((always_inline)) {
             // all cross-lane reads first, then one wait: each of them has LDS latency
-            orgn = wg_origin<TW>(p.geo, more ? tile + 1 : tile);
+            orgn = tile_origin(p.geo, more ? tile + 1 : tile);
             int m_l;
-            wg_row<TW>(p.geo, orgn, lane, m_l, hrow_next);
+            tile_row(p.geo, orgn, lane, m_l, hrow_next);
             const int px_l = x_lookup(orgn, 0);
 #pragma unroll
             for (int k = 0; k < kGOps; ++k) srcs[k] = g_src(m_l, k);
@@ -213,19 +173,8 @@ __device__ __forceinline__ void wgrad_body(const WgradArgs &p, char *smem)
         const char *ga = Gs + (wrow0 + kp) * kGRow + (((wc * 32 + r) ^ (kp << 5)) << 2);
         // operands of step s+1 are read from LDS before the MFMAs of step s are issued
         float a_next, b_next[NT];
-        // (PATCH) tile row j = wrow0 + 2s + kp sits in halo row (j / TW) * (TW + 2) + j % TW; TW is even and
-        // wrow0 two whole patch rows, so the pixel pair of a step never straddles a patch row
-        const char *xpatch = Xs + (wp * 2 * (TW + 2) + kp) * kXRow + r * 4;
         auto fetch = [&](int s) __attribute__((always_inline)) {
             a_next = *reinterpret_cast<const float *>(ga + s * 2 * kGRow);
-            if (PATCH) {
-                constexpr int D = PATCH ? TW : 2;
-                const int ro = (((2 * s) / D) * (TW + 2) + (2 * s) % D) * kXRow;
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    b_next[t] = *reinterpret_cast<const float *>(xpatch + ro + (((T0 + t) / 3) * (TW + 2) + (T0 + t) % 3) * kXRow);
-                return;
-            }
             const int h0 = __builtin_amdgcn_readlane(hrow_l, wrow0 + 2 * s);
             const int h1 = __builtin_amdgcn_readlane(hrow_l, wrow0 + 2 * s + 1);
             const char *xb = Xs + (kp ? h1 : h0) * kXRow + r * 4;
@@ -235,7 +184,7 @@ __device__ __forceinline__ void wgrad_body(const WgradArgs &p, char *smem)
         };
         fetch(0);
 #pragma unroll
-        for (int s = 0; s < PK / 4; ++s) {
+        for (int s = 0; s < kPK / 4; ++s) {
             if (s == S0) prepare();
             if (s >= S0 && s - S0 < kOps && s - S0 < ncopy)
                 dma(srcs[s - S0], s - S0 < kGOps ? g_dst(nbase, s - S0) : x_dst(nbase, s - S0 - kGOps));
@@ -243,7 +192,7 @@ __device__ __forceinline__ void wgrad_body(const WgradArgs &p, char *smem)
             float bv[NT];
 #pragma unroll
             for (int t = 0; t < NT; ++t) bv[t] = b_next[t];
-            if (s + 1 < PK / 4) fetch(s + 1);
+            if (s + 1 < kPK / 4) fetch(s + 1);
             gsum += a;
 #pragma unroll
             for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bv[t], acc[t], 0, 0, 0);
@@ -290,13 +239,12 @@ __device__ __forceinline__ void wgrad_body(const WgradArgs &p, char *smem)
 // accumulator registers of a wave, so four waves fit on a SIMD; a wave of each tap group lands on
 // every SIMD (wave w runs on SIMD w % 4), which balances the 5:4 split; the two groups also prepare
 // the next tile at different points of a tile, so a SIMD always has waves that are multiplying.
-template <int TW>
 __global__ __launch_bounds__(kWaves * 64, 4) void conv3x3_wgrad_kernel(WgradArgs p)
 {
     extern __shared__ __align__(16) char smem[];
     // (wave-uniform branch: both bodies execute the same sequence of barriers)
-    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 8) == 0) wgrad_body<0, 5, 0, TW>(p, smem);
-    else wgrad_body<5, 4, (TW ? 4 * TW : kPK) / 8, TW>(p, smem);
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 8) == 0) wgrad_body<0, 5, 0>(p, smem);
+    else wgrad_body<5, 4, kPK / 8>(p, smem);
 }
 
 // Layers with at most three input channels (the first one): (tap, ci) pairs are the <= 27 columns
@@ -511,51 +459,66 @@ void wgrad_launch_reduce(const float *part, float *out, size_t n, const float *p
     launch_reduce(part, out, n, part2, out2, n2, splits, stream);
 }
 
-// Patch width of the general kernel for an image size, 0: linear tiles.  16 or 14 where the image width divides into
-// patches (the last patch row of an image may stick out at the bottom: at most three rows of zeros); otherwise the one
-// of the two that pads less, when it takes at most 1.3 times the linear tiles: a patch costs 0.65 to 0.85 of a
-// linear tile (whose halo is 110 to 500 rows for 64 pixels against 96 to 108, all of them copied, and has to be fetched
-// across lanes), but every one of them is multiplied whole and, with a workgroup of its own, adds a partial result.  Over 251 shapes:
-// up to 1.3 times the tiles 0.83 of the time on average, 1.13 at most; beyond 1.00 on average and 0.73 to 1.44 (24x41x12,
-// 256 -> 192 118 / 171 us).  64 -> 128 at 50x66, batch 10 (205 halo rows; 650 patches for 516 tiles): 90 -> 69 us.
-static int wgrad_patch_width(int N, int H, int W)
+int launch_wgrad_f32x3(const TileGeom &g, int CinP, int Cout, int splits, int tiles_per_split, const float *x, const float *grad, float *part,
+                       float *dbpart, hipStream_t stream);   // conv_wgrad_f32x3.hip
+
+static int wgrad_splits(int ntiles, int want, int &tiles_per_split)
 {
-    if (H < 4) return 0;
-    if (W % 16 == 0) return 16;
-    if (W % 14 == 0) return 14;
-    const int p16 = (W + 15) / 16 * 16, p14 = (W + 13) / 14 * 14, tw = p14 < p16 ? 14 : 16;
-    const long patches = (long)N * ((W + tw - 1) / tw) * ((H + 3) / 4), tiles = ((long)N * H * W + kPK - 1) / kPK;
-    return patches * 10 <= tiles * 13 ? tw : 0;
+    int splits = want < ntiles ? want : ntiles;
+    if (splits < 1) splits = 1;
+    tiles_per_split = (ntiles + splits - 1) / splits;
+    return (ntiles + tiles_per_split - 1) / tiles_per_split;
 }
+
+// Patches of the kernel on the bf16 matrix unit: four rows of 16 or 14 pixels, or 8 x 8, sticking out of the image where they do
+// not divide it; false: linear tiles on the fp32 MFMAs.  Four rows where the image width divides or they number at most 1.3 times
+// the linear tiles: 0.45 to 0.9 of the time of the fp32 MFMAs on the same patches.  Otherwise the shape with fewest, from 64
+// patches on and up to 2.2 times the linear tiles (what is multiplied for nothing included): over 104 shapes 0.65 of the linear kernel's time up to 1.4
+// times, 0.7 to 1.6, 0.82 (0.96 at most) beyond 1.7.
+static bool wgrad_patches(int N, int H, int W, int &TH, int &TW)
+{
+    const long tiles = ((long)N * H * W + kPK - 1) / kPK;
+    const int c14 = ((W + 13) / 14) * ((H + 3) / 4), c16 = ((W + 15) / 16) * ((H + 3) / 4), c8 = ((W + 7) / 8) * ((H + 7) / 8);
+    TH = 4;
+    if (H >= 4) {
+        TW = W % 16 == 0 ? 16 : W % 14 == 0 || (W + 13) / 14 * 14 < (W + 15) / 16 * 16 ? 14 : 16;
+        if (W % TW == 0 || (long)N * (TW == 14 ? c14 : c16) * 10 <= tiles * 13) return true;
+    }
+    const int c = c8 <= c16 && c8 <= c14 ? c8 : c16 <= c14 ? c16 : c14;
+    TH = c == c8 ? 8 : 4;
+    TW = c == c8 ? 8 : c == c16 ? 16 : 14;
+    return (long)N * c >= 64 && (long)N * c * 10 <= tiles * 22;
+}
+
+static bool wgrad_parts(const WgradArgs &a) { return a.geo.mode == 1; }   // (of a plan that is not the thin kernel's)
 
 static void wgrad_plan(int N, int H, int W, int CinP, int Cout, WgradArgs &a, bool thin = false)
 {
     a.geo = make_tile_geom(N, H, W, kPK);
-    const int TW = thin ? 0 : wgrad_patch_width(N, H, W);
-    if (TW != 0) {
-        a.geo.mode = 1; a.geo.TH = 4; a.geo.TW = TW;
-        a.geo.tiles_w = (W + TW - 1) / TW;
-        a.geo.tiles_hw = a.geo.tiles_w * ((H + 3) / 4);
-        a.geo.dTilesW = make_fast_div(a.geo.tiles_w);
-        a.geo.dTilesHW = make_fast_div(a.geo.tiles_hw);
-        a.geo.ntiles = N * a.geo.tiles_hw;
-        a.geo.pitch = TW + 2;
-        a.geo.S = 6 * (TW + 2);
-    }
-    a.SX = (a.geo.S + 7) & ~7;
-    if (a.SX < 8 * kWaves) a.SX = 8 * kWaves;  // every wave copies at least one halo block
     a.CinP = CinP; a.Cout = Cout;
     a.tiles_co = (Cout + kBCO - 1) / kBCO;
     a.tiles_ci = thin ? 1 : (CinP + kBCI - 1) / kBCI;
     const int groups = a.tiles_co * a.tiles_ci;
-    // One resident round of workgroups (two per CU).  Every workgroup writes its whole block of partial
-    // sums, which the reduction reads back -- 38 MB each way for 512 workgroups whatever the layer; four
-    // rounds (for balance) quadrupled that and measured 2.7 % slower over the whole stack.
-    int splits = (512 + groups - 1) / groups;
-    if (splits > a.geo.ntiles) splits = a.geo.ntiles;
-    if (splits < 1) splits = 1;
-    a.tiles_per_split = (a.geo.ntiles + splits - 1) / splits;
-    a.splits = (a.geo.ntiles + a.tiles_per_split - 1) / a.tiles_per_split;
+    // One resident round of workgroups (two per CU; on the bf16 matrix unit one, and never more partial sums than linear tiles
+    // would have).  Every workgroup writes its whole block of partial sums, which the reduction reads back -- 38 MB each way for
+    // 512 workgroups whatever the layer; four rounds (for balance) quadrupled that and measured 2.7 % slower over the whole stack.
+    const int linear = wgrad_splits((int)(((long)N * H * W + kPK - 1) / kPK), (512 + groups - 1) / groups, a.tiles_per_split);
+    int TH, TW;
+    if (!thin && wgrad_patches(N, H, W, TH, TW)) {
+        a.geo.mode = 1; a.geo.TH = TH; a.geo.TW = TW;
+        a.geo.tiles_w = (W + TW - 1) / TW;
+        a.geo.tiles_hw = a.geo.tiles_w * ((H + TH - 1) / TH);
+        a.geo.dTilesW = make_fast_div(a.geo.tiles_w);
+        a.geo.dTilesHW = make_fast_div(a.geo.tiles_hw);
+        a.geo.ntiles = N * a.geo.tiles_hw;
+        a.geo.pitch = TW + 2;
+        a.geo.S = (TH + 2) * (TW + 2);
+        a.splits = wgrad_splits(a.geo.ntiles, 256 / groups < linear ? 256 / groups : linear, a.tiles_per_split);
+    } else {
+        a.splits = wgrad_splits(a.geo.ntiles, (512 + groups - 1) / groups, a.tiles_per_split);
+    }
+    a.SX = (a.geo.S + 7) & ~7;
+    if (a.SX < 8 * kWaves) a.SX = 8 * kWaves;  // every wave copies at least one halo block
 }
 
 // The thin kernel serves layers with at most three input channels; it tiles the pixels linearly, so its
@@ -574,14 +537,14 @@ size_t conv3x3_wgrad_workspace(int N, int H, int W, int Cin, int CinP, int Cout)
     return wgrad_ws_bytes(a);
 }
 
-// For inspection: {kernel (0 linear tiles, 14 / 16 patch width, 3 thin), pixel tiles, splits, tiles per split,
+// For inspection: {kernel (0 linear tiles, 8 / 14 / 16 patch width, 3 thin), pixel tiles, splits, tiles per split,
 // workgroups}.
 void conv3x3_wgrad_plan_info(int N, int H, int W, int Cin, int CinP, int Cout, int info[5])
 {
     WgradArgs a;
     const bool thin = wgrad_is_thin(Cin, CinP);
     wgrad_plan(N, H, W, CinP, Cout, a, thin);
-    info[0] = thin ? 3 : (a.geo.mode == 1 ? a.geo.TW : 0);
+    info[0] = thin ? 3 : (!wgrad_parts(a) ? 0 : a.geo.TW);
     info[1] = a.geo.ntiles;
     info[2] = a.splits;
     info[3] = a.tiles_per_split;
@@ -602,25 +565,24 @@ int conv3x3_wgrad(int N, int H, int W, int Cin, int CinP, int Cout, const float 
     a.part = static_cast<float *>(ws);
     a.dbpart = db ? reinterpret_cast<float *>(static_cast<char *>(ws) + round_up((size_t)a.splits * nw * 4, 256))
                   : nullptr;
+    if (!thin && wgrad_parts(a)) {
+        const int rc = launch_wgrad_f32x3(a.geo, CinP, Cout, a.splits, a.tiles_per_split, x, g, a.part, a.dbpart, stream);
+        if (rc) return rc;
+        launch_reduce(a.part, dw, nw, a.dbpart, db, db ? (size_t)Cout : 0, a.splits, stream);
+        return launch_status();
+    }
     size_t lds = (size_t)2 * (kPK * kGRow + a.SX * kXRow);
     const size_t red = (size_t)2 * 9 * 16 * 64 * 4 + 64 * 4;
     if (lds < red) lds = red;
     if (lds > 160 * 1024) return VGG_ERR_UNSUPPORTED;
     if (lds > 64 * 1024 &&
-        !(raise_lds_limit(reinterpret_cast<const void *>(conv3x3_wgrad_kernel<0>)) &&
-          raise_lds_limit(reinterpret_cast<const void *>(conv3x3_wgrad_kernel<16>)) &&
-          raise_lds_limit(reinterpret_cast<const void *>(conv3x3_wgrad_kernel<14>)) &&
-          raise_lds_limit(reinterpret_cast<const void *>(conv3x3_wgrad_thin_kernel))))
+        !(raise_lds_limit(reinterpret_cast<const void *>(conv3x3_wgrad_kernel)) && raise_lds_limit(reinterpret_cast<const void *>(conv3x3_wgrad_thin_kernel))))
         return VGG_ERR_LAUNCH;
     const dim3 grid((unsigned)(a.tiles_co * a.tiles_ci * a.splits));
     if (thin)
         hipLaunchKernelGGL(conv3x3_wgrad_thin_kernel, grid, dim3(kWaves * 64), lds, stream, a, Cin);
-    else if (a.geo.mode == 1 && a.geo.TW == 16)
-        hipLaunchKernelGGL(conv3x3_wgrad_kernel<16>, grid, dim3(kWaves * 64), lds, stream, a);
-    else if (a.geo.mode == 1)
-        hipLaunchKernelGGL(conv3x3_wgrad_kernel<14>, grid, dim3(kWaves * 64), lds, stream, a);
     else
-        hipLaunchKernelGGL(conv3x3_wgrad_kernel<0>, grid, dim3(kWaves * 64), lds, stream, a);
+        hipLaunchKernelGGL(conv3x3_wgrad_kernel, grid, dim3(kWaves * 64), lds, stream, a);
     if (hipGetLastError() != hipSuccess) return VGG_ERR_LAUNCH;
     launch_reduce(a.part, dw, nw, a.dbpart, db, db ? (size_t)Cout : 0, a.splits, stream);
     return launch_status();

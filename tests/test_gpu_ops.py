@@ -661,6 +661,26 @@ def test_conv3x3_bwd_weight_bf16_on_8x8_patches(shape):
     _check_bwd_weight(B.BF16, shape, seed=sum(shape) + 5)
 
 
+@pytest.mark.parametrize("shape,kernel", [((12, 43, 19, 24, 72), 108), ((9, 18, 34, 33, 64), 108), ((70, 7, 7, 40, 132), 108), ((40, 14, 14, 96, 200), 114),
+                                          ((1, 64, 80, 16, 4), 116), ((2, 16, 32, 64, 64), 116), ((65, 3, 7, 16, 36), 100)])
+def test_conv3x3_bwd_weight_fp32_in_three_parts(shape, kernel):
+    """The fp32 weight gradient on the bf16 matrix unit: every patch shape, sticking out at the right and bottom, ragged
+    channels, one and several patches per workgroup.  Sums of at most 9288 products, each exact to 2^-24: 3e-6 of the largest
+    value against the oracle (fp32 sums of that length: 1e-6)."""
+    N, H, W, Cin, Cout = shape
+    assert B.vgg_conv3x3_plan(B.PLAN_BWD_WEIGHT, B.F32, N, H, W, Cin, Cout)[0] == kernel
+    _check_bwd_weight(B.F32, shape, seed=sum(shape) + 6)
+    d = synth.conv_layer_inputs(N, H, W, Cin, Cout, seed=sum(shape) + 6)
+    dw_ref, db_ref = R.conv3x3_bwd_weight(d["x"], d["dy"])
+    cp = B.vgg_padded_channels(B.F32, Cin)
+    dwp, db = torch.empty((9, Cout, cp), device="cuda"), torch.empty((Cout,), device="cuda")
+    B.vgg_conv3x3_bwd_weight(B.F32, N, H, W, Cin, Cout, to_nhwc(d["x"], B.F32), to_nhwc(d["dy"], B.F32), dwp, db,
+                             ws_bytes(B.vgg_conv3x3_bwd_weight_workspace_bytes(B.F32, N, H, W, Cin, Cout)))
+    torch.cuda.synchronize()
+    dw = dwp[:, :, :Cin].reshape(3, 3, Cout, Cin).permute(2, 3, 0, 1)
+    assert max_rel_err(dw.cpu().numpy(), dw_ref) <= 3e-6 and max_rel_err(db.cpu().numpy(), db_ref) <= 3e-6
+
+
 @pytest.mark.parametrize("shape,kernel", [((3, 50, 66, 40, 72), 114), ((3, 8, 100, 16, 64), 116), ((1, 45, 60, 96, 36), 116), ((2, 9, 100, 16, 64), 100),
                                           ((2, 8, 31, 24, 68), 116), ((2, 5, 31, 24, 68), 100), ((3, 13, 11, 64, 64), 100), ((2, 3, 130, 32, 64), 100)])
 def test_conv3x3_bwd_weight_fp32_patches_that_stick_out(shape, kernel):
