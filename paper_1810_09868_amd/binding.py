@@ -120,9 +120,20 @@ def _nbytes(t) -> int:
     return 0 if t is None else t.numel() * t.element_size()
 
 
+_RAW_STREAM = None
+
+
 def _stream() -> int:
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+    """The current device's current stream, as the C entry points take it.  Asked for on every call and without building a
+    torch Stream object: two short calls issued back to back are bound by what the host does between them (softmax and loss of
+    100 x 1000: 14.7 -> 9.1 us)."""
+    global _RAW_STREAM
+    if _RAW_STREAM is None:
+        import torch
+        torch.cuda.init()
+        raw, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        _RAW_STREAM = (lambda: raw(dev())) if raw and dev else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _RAW_STREAM()
 
 
 def _chk(rc: int, where: str):

@@ -928,6 +928,15 @@ def test_fc_backward_fp32_tile_edges(N, In, Out):
     assert (dw[Out * In:] == -7.0).all() and (da[N * In:] == -7.0).all()
 
 
+def test_calls_go_to_the_current_stream():
+    """The stream handed to the library is torch's current one: the default stream, a side stream, and again the default."""
+    side = torch.cuda.Stream()
+    assert B._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert B._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
+    assert B._stream() == torch.cuda.current_stream().cuda_stream != side.cuda_stream
+
+
 @pytest.mark.parametrize("shape", [(100, 1000), (2, 10), (5, 64), (3, 129), (1, 10), (1, 1), (4, 5000)])
 def test_softmax_xent_sgd(shape):
     N, K = shape
