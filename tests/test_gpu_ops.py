@@ -928,6 +928,24 @@ def test_fc_backward_fp32_tile_edges(N, In, Out):
     assert (dw[Out * In:] == -7.0).all() and (da[N * In:] == -7.0).all()
 
 
+@pytest.mark.parametrize("N,In,Out", [(1, 8, 1), (32, 136, 65), (33, 264, 129), (64, 128, 64), (65, 120, 63), (96, 1032, 200), (97, 40, 33),
+                                      (128, 256, 130), (129, 136, 257)])
+def test_fc_backward_bf16_row_blocks(N, In, Out):
+    """The bf16 backward kernels with every number of 32-row blocks, at the edges of their tiles (64-output steps, 128-input
+    tiles, 64-row passes).  All operands representable in bf16: fp32 sums of at most 257 products, 1e-5 of the largest."""
+    rng = np.random.default_rng(N * 7 + In + Out)
+    a, w, dz = (dev(rng.standard_normal(s).astype(np.float32), torch.bfloat16) for s in ((N, In), (Out, In), (N, Out)))
+    dw_ref, db_ref, da_ref = R.fc_bwd(*(v.float().cpu().numpy() for v in (a, w, dz)))
+    dw, da = torch.full((Out * In + 256,), -7.0, device="cuda"), torch.full((N * In + 256,), -7.0, device="cuda")
+    db = torch.empty((Out,), device="cuda")
+    B.vgg_fc_bwd(B.BF16, N, In, Out, a, w, dz.float(), dw, db, da, 1, ws_bytes(B.vgg_fc_bwd_workspace_bytes(B.BF16, N, In, Out)))
+    torch.cuda.synchronize()
+    assert max_rel_err(dw[:Out * In].view(Out, In).cpu().numpy(), dw_ref) <= 1e-5
+    assert max_rel_err(da[:N * In].view(N, In).cpu().numpy(), da_ref * (a.float().cpu().numpy() > 0)) <= 1e-5
+    assert max_rel_err(db.cpu().numpy(), db_ref) <= 1e-5
+    assert (dw[Out * In:] == -7.0).all() and (da[N * In:] == -7.0).all()
+
+
 def test_calls_go_to_the_current_stream():
     """The stream handed to the library is torch's current one: the default stream, a side stream, and again the default."""
     side = torch.cuda.Stream()
