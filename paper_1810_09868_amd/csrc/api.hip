@@ -72,7 +72,7 @@ int fc_backward(int N, int In, int Out, const float *a, const float *w, const fl
                 int relu_mask, void *ws, hipStream_t s);
 size_t fc_bwd_bf16_workspace(int N, int In, int Out);
 int fc_backward_bf16(int N, int In, int Out, const bf16_t *a, const bf16_t *w, const float *dz, float *dw, float *db, float *da,
-                     int relu_mask, void *ws, hipStream_t s);
+                     int relu_mask, void *ws, hipStream_t s, float lr = 0.f, bf16_t *copy = nullptr);
 
 namespace {
 
@@ -336,13 +336,16 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
     const char *fc_in[3] = {ws + L.pooled[15], ws + L.z1, ws + L.z2};
     float *fc_dz[3] = {F(ws + L.dz1), F(ws + L.dz2), F(ws + L.dlogits)};
     float *dflat = F(mixed ? ws + L.dflat32 : ws + L.gA);
+    // bf16: unless the caller asks for the gradients, the dense weights take their step where their gradient is formed.
+    const bool fused = mixed && !grads_out;
     for (int l = 2; l >= 0; --l) {
         float *da = l == 0 ? dflat : fc_dz[l - 1];
         if (!rec.skip(K_FCDW)) {
             if (mixed)
                 rec.rc = fc_backward_bf16(N, P.fc_in[l], P.fc_out[l], reinterpret_cast<const bf16_t *>(fc_in[l]),
-                                          reinterpret_cast<const bf16_t *>(pk + P.fc_w[l]), fc_dz[l], F(gr + Pm.fc_w[l]),
-                                          F(gr + Pm.fc_b[l]), da, 1, ws + L.fcbws, s);
+                                          reinterpret_cast<const bf16_t *>(pk + P.fc_w[l]), fc_dz[l],
+                                          F(fused ? pm + Pm.fc_w[l] : gr + Pm.fc_w[l]), F(gr + Pm.fc_b[l]), da, 1, ws + L.fcbws, s, c->lr,
+                                          fused ? reinterpret_cast<bf16_t *>(pk + P.fc_w[l]) : nullptr);
             else
                 rec.rc = fc_backward(N, P.fc_in[l], P.fc_out[l], reinterpret_cast<const float *>(fc_in[l]), F(pk + P.fc_w[l]),
                                      fc_dz[l], F(gr + P.fc_w[l]), F(gr + P.fc_b[l]), da, 1, ws + L.fcbws, s);
@@ -434,7 +437,7 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
         for (int l = 0; l < VGG19_NUM_CONV; ++l)
             VGG_STEP(rec, K_OTHER, sgd_update_master(kConvCh[l][1], F(pm + Pm.conv_b[l]), F(gr + Pm.conv_b[l]), c->lr,
                                                      pk + P.conv_b[l], VGG_F32, s));
-    if (!(fc_prop && group(Pm.fc_w[0], Pm.fc_b[0], P.fc_w[0], P.fc_b[0], VGG_BF16)))
+    if (!fused && !(fc_prop && group(Pm.fc_w[0], Pm.fc_b[0], P.fc_w[0], P.fc_b[0], VGG_BF16)))
         for (int l = 0; l < VGG19_NUM_FC; ++l)
             VGG_STEP(rec, K_OTHER, sgd_update_master((size_t)P.fc_in[l] * P.fc_out[l], F(pm + Pm.fc_w[l]), F(gr + Pm.fc_w[l]),
                                                      c->lr, pk + P.fc_w[l], VGG_BF16, s));
