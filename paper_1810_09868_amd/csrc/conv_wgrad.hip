@@ -385,71 +385,52 @@ __global__ __launch_bounds__(kWaves * 64, 4) void conv3x3_wgrad_thin_kernel(Wgra
     }
 }
 
-// out[i] = sum over the splits of part[k][i], in a fixed order.  A workgroup owns 256/RY outputs;
-// thread row y adds the splits k = y, y + RY, ... and the RY rows are then added through LDS, so
-// that launches with few outputs and many splits (bias gradients, thin layers) still fill the chip.
-// Two sets of partials with the same number of splits (the weights' and the bias') share a launch:
-// outputs [0, n) come from part, outputs [n, n + n2) from part2.
+// out[i] = sum over the splits of part[k][i], in a fixed order.  A thread owns four outputs (every count here is a
+// multiple of four), a workgroup 1024 / RY of them; thread row y adds the splits k = y, y + RY, ... and the RY rows are
+// then added through LDS, so that launches with few outputs and many splits (thin layers) still fill the chip.  Bound by
+// reading the partials, 75 MB for 512 workgroups of bf16 64 x 64 blocks: 15 us; 4 bytes per lane and load took 16 to 31.
+// Two sets of partials with the same number of splits (the weights' and the bias') share a launch: the quads [0, n4)
+// come from part, [n4, n4 + n24) from part2.
 template <int RY>
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *part, float *out, size_t n, const float *part2,
-                                                           float *out2, size_t n2, int splits)
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const f32x4 *part, f32x4 *out, size_t n4, const f32x4 *part2,
+                                                           f32x4 *out2, size_t n24, int splits)
 {
     constexpr int RX = 256 / RY;
-    __shared__ float red[256];
+    __shared__ f32x4 red[RY > 1 ? 256 : 1];
     const int x = threadIdx.x % RX, y = threadIdx.x / RX;
     size_t i = (size_t)blockIdx.x * RX + x;
-    const bool live = i < n + n2;
-    if (i >= n) { i -= n; part = part2; out = out2; n = n2; }
-    float s = 0.f;
-    if (live)
-        for (int k = y; k < splits; k += RY) s += part[(size_t)k * n + i];
-    if (RY == 1) {
-        if (live) out[i] = s;
-        return;
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    if (y == 0 && live) {
-        float t = 0.f;
-#pragma unroll
-        for (int r = 0; r < RY; ++r) t += red[r * RX + x];
-        out[i] = t;
-    }
-}
-
-// The same for few splits, one thread per four outputs (n and n2 multiples of four): bound by reading the partials,
-// 75 MB for 512 workgroups of bf16 64 x 64 blocks, 16.3 us with four bytes per lane and load -> 13.3.
-__global__ __launch_bounds__(256) void wgrad_reduce4_kernel(const f32x4 *part, f32x4 *out, size_t n, const f32x4 *part2, f32x4 *out2,
-                                                            size_t n2, int splits)
-{
-    size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n + n2) return;
-    if (i >= n) { i -= n; part = part2; out = out2; n = n2; }
+    if (i >= n4) { i -= n4; part = part2; out = out2; n4 = n24; }
+    const bool live = i < n4;
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int k = 0; k < splits; ++k) s += part[(size_t)k * n + i];
-    out[i] = s;
+    if (live)
+#pragma unroll 8
+        for (int k = y; k < splits; k += RY) s += part[(size_t)k * n4 + i];
+    if (RY > 1) {
+        red[threadIdx.x] = s;
+        __syncthreads();
+        if (y) return;
+        s = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < RY; ++r) s += red[r * RX + x];
+    }
+    if (live) out[i] = s;
 }
 
 static void launch_reduce(const float *part, float *out, size_t n, const float *part2, float *out2, size_t n2, int splits,
                           hipStream_t stream)
 {
-    const size_t total = n + n2;
-    // Sixteen rows of threads from 128 partial results on, or from 32 where a few outputs would leave most of the chip idle
-    // (below 40000 outputs, whole weight gradients: 0.82 to 0.98 of the time with four rows; above, 1.02 to 1.13).
-    if (splits >= 128 || (splits >= 32 && total < 40000))
-        hipLaunchKernelGGL(wgrad_reduce_kernel<16>, dim3((unsigned)((total + 15) / 16)), dim3(256), 0, stream, part, out, n, part2,
-                           out2, n2, splits);
-    else if (splits >= 16)
-        hipLaunchKernelGGL(wgrad_reduce_kernel<4>, dim3((unsigned)((total + 63) / 64)), dim3(256), 0, stream, part, out, n, part2,
-                           out2, n2, splits);
-    else if (n % 4 == 0 && n2 % 4 == 0 && aligned16(out) && aligned16(out2))
-        hipLaunchKernelGGL(wgrad_reduce4_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, stream,
+    const auto go = [&](auto kernel, int rows) {
+        const size_t per = 256 / rows;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(((n + n2) / 4 + per - 1) / per)), dim3(256), 0, stream,
                            reinterpret_cast<const f32x4 *>(part), reinterpret_cast<f32x4 *>(out), n / 4,
                            reinterpret_cast<const f32x4 *>(part2), reinterpret_cast<f32x4 *>(out2), n2 / 4, splits);
-    else
-        hipLaunchKernelGGL(wgrad_reduce_kernel<1>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, part, out, n, part2,
-                           out2, n2, splits);
+    };
+    // Rows by the number of partial results alone.  us for 4 bytes a load (as it was) / one / four / sixteen rows of quads,
+    // splits x outputs: 8 x 2.4e6 15.6 / 15.4 / 15.6 / 23.7, 32 x 590e3 18.7 / 15.0 / 14.8 / 14.8, 64 x 295e3 19.9 / 15.3 /
+    // 14.8 / 14.8, 128 x 147e3 24.8 / 14.6 / 15.0 / 15.2, 512 x 37e3 30.7 / 27.8 / 15.0 / 16.0, 1024 x 1728 23.0 / 51 / 18.5 / 8.4.
+    if (splits >= 128) go(wgrad_reduce_kernel<16>, 16);
+    else if (splits >= 16) go(wgrad_reduce_kernel<4>, 4);
+    else go(wgrad_reduce_kernel<1>, 1);
 }
 
 // (also used by the bf16 weight-gradient kernel; part2/out2 may be null with n2 = 0)

@@ -661,6 +661,17 @@ def test_conv3x3_bwd_weight_bf16_on_8x8_patches(shape):
     _check_bwd_weight(B.BF16, shape, seed=sum(shape) + 5)
 
 
+@pytest.mark.parametrize("dtype,shape,splits", [(B.F32, (1, 8, 8, 16, 4), (1, 1)), (B.F32, (2, 7, 9, 16, 24), (2, 15)),
+                                                (B.F32, (3, 30, 17, 16, 28), (16, 127)), (B.F32, (30, 56, 56, 16, 24), (128, 999)),
+                                                (B.BF16, (1, 8, 8, 16, 8), (1, 15)), (B.BF16, (3, 30, 17, 16, 24), (16, 127)),
+                                                (B.BF16, (20, 40, 40, 16, 40), (128, 999))])
+def test_conv3x3_bwd_weight_partial_sums(dtype, shape, splits):
+    """Each form of the pass that adds the partial sums, by their number, with outputs that end inside a workgroup."""
+    N, H, W, Cin, Cout = shape
+    assert splits[0] <= B.vgg_conv3x3_plan(B.PLAN_BWD_WEIGHT, dtype, N, H, W, Cin, Cout)[5] <= splits[1]
+    _check_bwd_weight(dtype, shape, seed=sum(shape) + 9)
+
+
 @pytest.mark.parametrize("shape,kernel", [((12, 43, 19, 24, 72), 108), ((9, 18, 34, 33, 64), 108), ((70, 7, 7, 40, 132), 108), ((40, 14, 14, 96, 200), 114),
                                           ((1, 64, 80, 16, 4), 116), ((2, 16, 32, 64, 64), 116), ((65, 3, 7, 16, 36), 100)])
 def test_conv3x3_bwd_weight_fp32_in_three_parts(shape, kernel):
