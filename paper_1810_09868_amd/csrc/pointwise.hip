@@ -469,31 +469,55 @@ int flip_packed_w(int dst_dtype, int CinP, int Cout, int CoutP, const float *src
 }
 
 // The same for several tensors in one launch (a training step flips fifteen of them, each a few
-// microseconds of work): workgroups [first[j], first[j+1]) serve tensor j.
+// microseconds of work): workgroups [first[j], first[j+1]) serve tensor j.  Bound by its bytes, 120 MB for bf16
+// copies: a workgroup turns 64 x 64 values of a tap around in LDS, so that a wavefront reads four runs of 256 bytes
+// and writes 1 KB without a gap (bf16; four runs of 256 bytes in fp32).  VGG-19: 50 us with 32 x 32 values and 4-byte loads, 30 now.
 template <typename TD>
 __global__ __launch_bounds__(256) void flip_packed_w_all_kernel(FlipJobs J)
 {
-    __shared__ float tile[32][33];
+    constexpr int V = 16 / (int)sizeof(TD);              // output channels of one 16-byte store
+    constexpr int kPitch = sizeof(TD) == 2 ? 66 : 65;    // columns 8 (4) rows apart in banks of their own
+    __shared__ float tile[64 * kPitch];
     int j = 0;
     while (j + 1 < J.n && (int)blockIdx.x >= J.first[j + 1]) ++j;
     const float *__restrict__ src = J.src[j];
     TD *__restrict__ dst = static_cast<TD *>(J.dst[j]);
     const int CinP = J.CinP[j], Cout = J.Cout[j], CoutP = J.CoutP[j];
-    const int nbx = (CinP + 31) / 32, nby = (CoutP + 31) / 32;
+    const int nbx = (CinP + 63) / 64, nby = (CoutP + 63) / 64;
     const int local = (int)blockIdx.x - J.first[j];
     const int bx = local % nbx, by = (local / nbx) % nby, t = local / (nbx * nby);
-    const int ci0 = bx * 32, co0 = by * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int ci0 = bx * 64, co0 = by * 64;
+    const int x4 = (threadIdx.x & 15) * 4, y = threadIdx.x >> 4;
+    f32x4 v[4];
 #pragma unroll
-    for (int r = ty; r < 32; r += 8) {
-        const int co = co0 + r, ci = ci0 + tx;
-        tile[r][tx] = (co < Cout && ci < CinP) ? src[((size_t)(8 - t) * Cout + co) * CinP + ci] : 0.f;
+    for (int r = 0; r < 4; ++r) {
+        const int co = min(co0 + y + 16 * r, Cout - 1), ci = min(ci0 + x4, CinP - 4);
+        v[r] = *reinterpret_cast<const f32x4 *>(src + ((size_t)(8 - t) * Cout + co) * CinP + ci);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float *d = tile + (y + 16 * r) * kPitch + x4;
+        const bool live = co0 + y + 16 * r < Cout;   // rows beyond the last output channel are padding: zeros
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = live ? v[r][e] : 0.f;
     }
     __syncthreads();
 #pragma unroll
-    for (int r = ty; r < 32; r += 8) {
-        const int ci = ci0 + r, co = co0 + tx;
-        if (ci < CinP && co < CoutP) Elem<TD>::store(dst + packed_w_index<TD>(t, ci, co, CinP, CoutP), tile[tx][r]);
+    for (int k = 0; k < 16 / V; ++k) {
+        const int i = k * 256 + threadIdx.x;
+        int ci, co;
+        if (sizeof(TD) == 2) { co = (i >> 7) * 16 + (i & 1) * 8; ci = (i >> 1) & 63; }
+        else                 { co = (i & 15) * 4; ci = i >> 4; }
+        if (ci0 + ci < CinP && co0 + co < CoutP) {
+            alignas(16) TD w[V];
+#pragma unroll
+            for (int e = 0; e < V; e += 4)
+                store4(w + e, tile[(co + e) * kPitch + ci], tile[(co + e + 1) * kPitch + ci], tile[(co + e + 2) * kPitch + ci],
+                       tile[(co + e + 3) * kPitch + ci]);
+            f32x4 o;
+            __builtin_memcpy(&o, w, 16);
+            *reinterpret_cast<f32x4 *>(dst + packed_w_index<TD>(t, ci0 + ci, co0 + co, CinP, CoutP)) = o;
+        }
     }
 }
 
@@ -503,8 +527,9 @@ int flip_packed_w_all(int dst_dtype, FlipJobs &jobs, hipStream_t s)
     if (jobs.n < 1 || jobs.n > kMaxFlipJobs) return VGG_ERR_UNSUPPORTED;
     int total = 0;
     for (int j = 0; j < jobs.n; ++j) {
+        if (jobs.CinP[j] % 4 || jobs.CoutP[j] % 8) return VGG_ERR_UNSUPPORTED;   // (what the 16-byte accesses need)
         jobs.first[j] = total;
-        total += ((jobs.CinP[j] + 31) / 32) * ((jobs.CoutP[j] + 31) / 32) * 9;
+        total += ((jobs.CinP[j] + 63) / 64) * ((jobs.CoutP[j] + 63) / 64) * 9;
     }
     jobs.first[jobs.n] = total;
     if (dst_dtype == VGG_BF16)
