@@ -40,7 +40,7 @@ void conv3x3_wgrad_plan_info(int N, int H, int W, int Cin, int CinP, int Cout, i
 size_t conv3x3_wgrad_bf16_workspace(int N, int H, int W, int CinP, int Cout);
 void conv3x3_wgrad_bf16_plan_info(int N, int H, int W, int CinP, int Cout, int info[5], int cin = 0);
 int conv3x3_wgrad_bf16(int N, int H, int W, int CinP, int Cout, const bf16_t *x, const bf16_t *g, float *dw, float *db,
-                       void *ws, size_t ws_bytes, hipStream_t stream, int x_channels = 0, int cin = 0);
+                       void *ws, size_t ws_bytes, hipStream_t stream, int x_channels = 0, int cin = 0, const ConvStep &step = {});
 // Channels per pixel of the NHWC copy of the images that the first layer's weight gradient reads: with bf16
 // operands one 16-byte segment (the three channels and five zeros) instead of a whole 64-byte row.
 inline int x0_channels(int dtype, int cinp0) { return dtype == VGG_BF16 ? 8 : cinp0; }
@@ -336,15 +336,16 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
     const char *fc_in[3] = {ws + L.pooled[15], ws + L.z1, ws + L.z2};
     float *fc_dz[3] = {F(ws + L.dz1), F(ws + L.dz2), F(ws + L.dlogits)};
     float *dflat = F(mixed ? ws + L.dflat32 : ws + L.gA);
-    // bf16: unless the caller asks for the gradients, the dense weights take their step where their gradient is formed.
+    // bf16: unless the caller asks for the gradients, the weights take their step where their gradient is formed.
     const bool fused = mixed && !grads_out;
+    char *gw = fused ? pm : gr;   // what the weight-gradient kernels write
     for (int l = 2; l >= 0; --l) {
         float *da = l == 0 ? dflat : fc_dz[l - 1];
         if (!rec.skip(K_FCDW)) {
             if (mixed)
                 rec.rc = fc_backward_bf16(N, P.fc_in[l], P.fc_out[l], reinterpret_cast<const bf16_t *>(fc_in[l]),
                                           reinterpret_cast<const bf16_t *>(pk + P.fc_w[l]), fc_dz[l],
-                                          F(fused ? pm + Pm.fc_w[l] : gr + Pm.fc_w[l]), F(gr + Pm.fc_b[l]), da, 1, ws + L.fcbws, s, c->lr,
+                                          F(gw + Pm.fc_w[l]), F(gr + Pm.fc_b[l]), da, 1, ws + L.fcbws, s, c->lr,
                                           fused ? reinterpret_cast<bf16_t *>(pk + P.fc_w[l]) : nullptr);
             else
                 rec.rc = fc_backward(N, P.fc_in[l], P.fc_out[l], reinterpret_cast<const float *>(fc_in[l]), F(pk + P.fc_w[l]),
@@ -378,9 +379,12 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
         const char *xin = l == 0 ? ws + L.x0 : (pool_after(l - 1) ? ws + L.pooled[l - 1] : ws + L.act[l - 1]);
         if (mixed)
             VGG_STEP(rec, K_WGRAD, conv3x3_wgrad_bf16(N, H, W, P.cinp[l], Cout, reinterpret_cast<const bf16_t *>(xin),
-                                                     reinterpret_cast<const bf16_t *>(gbuf[cur]), F(gr + Pm.conv_w[l]),
-                                                     F(gr + Pm.conv_b[l]), ws + L.wgws, L.wgws_bytes, s,
-                                                     l == 0 ? x0_channels(dt, P.cinp[0]) : 0, Cin));
+                                                     reinterpret_cast<const bf16_t *>(gbuf[cur]), F(gw + Pm.conv_w[l]),
+                                                     F(gw + Pm.conv_b[l]), ws + L.wgws, L.wgws_bytes, s,
+                                                     l == 0 ? x0_channels(dt, P.cinp[0]) : 0, Cin,
+                                                     fused ? ConvStep{c->lr, reinterpret_cast<bf16_t *>(pk + P.conv_w[l]),
+                                                                      F(pk + P.conv_b[l]), Cout, P.cinp[l]}
+                                                           : ConvStep{}));
         else
             VGG_STEP(rec, K_WGRAD, conv3x3_wgrad(N, H, W, kConvCh[l][0], P.cinp[l], Cout, reinterpret_cast<const float *>(xin),
                                                 F(gbuf[cur]), F(gr + P.conv_w[l]), F(gr + P.conv_b[l]), ws + L.wgws,
@@ -421,7 +425,7 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
     };
     bool fc_prop = true;
     for (int l = 0; l < VGG19_NUM_FC; ++l) fc_prop = fc_prop && Pm.fc_w[l] - Pm.fc_w[0] == 2 * (P.fc_w[l] - P.fc_w[0]);
-    {
+    if (!fused) {
         // convolution weights: the bf16 copies are in the blocked layout, the masters row-major
         SgdConvJobs jobs;
         jobs.n = VGG19_NUM_CONV;
@@ -433,7 +437,7 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
         }
         VGG_STEP(rec, K_OTHER, sgd_update_master_conv(jobs, c->lr, s));
     }
-    if (!group(Pm.conv_b[0], Pm.fc_w[0], P.conv_b[0], P.fc_w[0], VGG_F32))
+    if (!fused && !group(Pm.conv_b[0], Pm.fc_w[0], P.conv_b[0], P.fc_w[0], VGG_F32))
         for (int l = 0; l < VGG19_NUM_CONV; ++l)
             VGG_STEP(rec, K_OTHER, sgd_update_master(kConvCh[l][1], F(pm + Pm.conv_b[l]), F(gr + Pm.conv_b[l]), c->lr,
                                                      pk + P.conv_b[l], VGG_F32, s));

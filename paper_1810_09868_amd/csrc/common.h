@@ -35,6 +35,15 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) { return __builtin_bit_ca
 // The gradient step on one value, rounded once; every kernel that takes the step uses this form, so a
 // step fused into a gradient kernel and a separate update leave identical parameters.
 __device__ __forceinline__ float sgd_step(float theta, float grad, float lr) { return __builtin_fmaf(-lr, grad, theta); }
+// Where a weight gradient's last pass takes the step itself: what it would have written as gradients are then the fp32
+// master weights [9][Cout][CinP] and biases; the working copies beside them.
+struct ConvStep {
+    float lr;
+    bf16_t *copy;      // weights in the layout the convolution kernels read (null: no step, gradients are written)
+    float *bias_copy;
+    int Cout, CinP;
+};
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t h) { return __uint_as_float(((unsigned int)h) << 16); }
 
 template <typename T> struct Elem;

@@ -391,17 +391,21 @@ __global__ __launch_bounds__(kWaves * 64, 4) void conv3x3_wgrad_thin_kernel(Wgra
 // reading the partials, 75 MB for 512 workgroups of bf16 64 x 64 blocks: 15 us; 4 bytes per lane and load took 16 to 31.
 // Two sets of partials with the same number of splits (the weights' and the bias') share a launch: the quads [0, n4)
 // come from part, [n4, n4 + n24) from part2.
-template <int RY>
+// STEP: out and out2 are master weights and biases, requested before the sums (a training step of 32 images 4272 -> 4241 us:
+// the gradients, 80 MB, are neither written nor read again, and two launches less).
+template <int RY, bool STEP>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const f32x4 *part, f32x4 *out, size_t n4, const f32x4 *part2,
-                                                           f32x4 *out2, size_t n24, int splits)
+                                                           f32x4 *out2, size_t n24, int splits, ConvStep step)
 {
     constexpr int RX = 256 / RY;
     __shared__ f32x4 red[RY > 1 ? 256 : 1];
     const int x = threadIdx.x % RX, y = threadIdx.x / RX;
     size_t i = (size_t)blockIdx.x * RX + x;
-    if (i >= n4) { i -= n4; part = part2; out = out2; n4 = n24; }
+    const bool bias = i >= n4;
+    if (bias) { i -= n4; part = part2; out = out2; n4 = n24; }
     const bool live = i < n4;
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    f32x4 s = {0.f, 0.f, 0.f, 0.f}, theta = s;
+    if (STEP && live) theta = out[i];
     if (live)
 #pragma unroll 8
         for (int k = y; k < splits; k += RY) s += part[(size_t)k * n4 + i];
@@ -413,31 +417,42 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const f32x4 *part, f3
 #pragma unroll
         for (int r = 0; r < RY; ++r) s += red[r * RX + x];
     }
-    if (live) out[i] = s;
+    if (!live) return;
+    if (STEP) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[c] = sgd_step(theta[c], s[c], step.lr);
+        if (bias) reinterpret_cast<f32x4 *>(step.bias_copy)[i] = s;
+        else {
+            const unsigned e = (unsigned)i * 4, row = e / (unsigned)step.CinP, tap = row / (unsigned)step.Cout;
+            store4(step.copy + packed_w_index<bf16_t>((int)tap, (int)(row - tap * step.Cout), (int)(e - row * step.CinP), step.Cout,
+                                                      step.CinP), s.x, s.y, s.z, s.w);
+        }
+    }
+    out[i] = s;
 }
 
 static void launch_reduce(const float *part, float *out, size_t n, const float *part2, float *out2, size_t n2, int splits,
-                          hipStream_t stream)
+                          hipStream_t stream, const ConvStep &step = {})
 {
-    const auto go = [&](auto kernel, int rows) {
+    const auto go = [&](auto plain, auto stepping, int rows) {
         const size_t per = 256 / rows;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(((n + n2) / 4 + per - 1) / per)), dim3(256), 0, stream,
+        hipLaunchKernelGGL(step.copy ? stepping : plain, dim3((unsigned)(((n + n2) / 4 + per - 1) / per)), dim3(256), 0, stream,
                            reinterpret_cast<const f32x4 *>(part), reinterpret_cast<f32x4 *>(out), n / 4,
-                           reinterpret_cast<const f32x4 *>(part2), reinterpret_cast<f32x4 *>(out2), n2 / 4, splits);
+                           reinterpret_cast<const f32x4 *>(part2), reinterpret_cast<f32x4 *>(out2), n2 / 4, splits, step);
     };
     // Rows by the number of partial results alone.  us for 4 bytes a load (as it was) / one / four / sixteen rows of quads,
     // splits x outputs: 8 x 2.4e6 15.6 / 15.4 / 15.6 / 23.7, 32 x 590e3 18.7 / 15.0 / 14.8 / 14.8, 64 x 295e3 19.9 / 15.3 /
     // 14.8 / 14.8, 128 x 147e3 24.8 / 14.6 / 15.0 / 15.2, 512 x 37e3 30.7 / 27.8 / 15.0 / 16.0, 1024 x 1728 23.0 / 51 / 18.5 / 8.4.
-    if (splits >= 128) go(wgrad_reduce_kernel<16>, 16);
-    else if (splits >= 16) go(wgrad_reduce_kernel<4>, 4);
-    else go(wgrad_reduce_kernel<1>, 1);
+    if (splits >= 128) go(wgrad_reduce_kernel<16, false>, wgrad_reduce_kernel<16, true>, 16);
+    else if (splits >= 16) go(wgrad_reduce_kernel<4, false>, wgrad_reduce_kernel<4, true>, 4);
+    else go(wgrad_reduce_kernel<1, false>, wgrad_reduce_kernel<1, true>, 1);
 }
 
 // (also used by the bf16 weight-gradient kernel; part2/out2 may be null with n2 = 0)
 void wgrad_launch_reduce(const float *part, float *out, size_t n, const float *part2, float *out2, size_t n2, int splits,
-                         hipStream_t stream)
+                         hipStream_t stream, const ConvStep &step)
 {
-    launch_reduce(part, out, n, part2, out2, n2, splits, stream);
+    launch_reduce(part, out, n, part2, out2, n2, splits, stream, step);
 }
 
 int launch_wgrad_f32x3(const TileGeom &g, int CinP, int Cout, int splits, int tiles_per_split, const float *x, const float *grad, float *part,

@@ -39,7 +39,7 @@
 namespace vgg {
 
 void wgrad_launch_reduce(const float *part, float *out, size_t n, const float *part2, float *out2, size_t n2, int splits,
-                         hipStream_t stream);
+                         hipStream_t stream, const ConvStep &step);
 
 namespace {
 
@@ -372,17 +372,26 @@ __global__ __launch_bounds__(256) void conv3x3_wgrad_bf16_thin_kernel(WgradThinA
     }
 }
 
-// sums [co tiles][28][64] -> dw [9][Cout][CinP] (columns >= 3: zero), db [Cout]
-__global__ __launch_bounds__(256) void wgrad_bf16_thin_spread_kernel(const float *sums, float *dw, float *db, int Cout, int CinP)
+// sums [co tiles][28][64] -> dw [9][Cout][CinP] (columns >= 3: zero), db [Cout]; STEP: the master values' step instead
+template <bool STEP>
+__global__ __launch_bounds__(256) void wgrad_bf16_thin_spread_kernel(const float *sums, float *dw, float *db, int Cout, int CinP,
+                                                                     ConvStep step)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int n = 9 * Cout * CinP;
     if (i < n) {
         const int ci = i % CinP, co = (i / CinP) % Cout, t = i / (CinP * Cout);
-        dw[i] = ci < 3 ? sums[((size_t)(co >> 6) * kThinK + t * 3 + ci) * 64 + (co & 63)] : 0.f;
+        float v = ci < 3 ? sums[((size_t)(co >> 6) * kThinK + t * 3 + ci) * 64 + (co & 63)] : 0.f;
+        if (STEP) {
+            v = sgd_step(dw[i], v, step.lr);
+            step.copy[packed_w_index<bf16_t>(t, co, ci, Cout, CinP)] = f32_to_bf16(v);
+        }
+        dw[i] = v;
     } else if (i < n + Cout && db) {
         const int co = i - n;
-        db[co] = sums[((size_t)(co >> 6) * kThinK + 27) * 64 + (co & 63)];
+        float v = sums[((size_t)(co >> 6) * kThinK + 27) * 64 + (co & 63)];
+        if (STEP) step.bias_copy[co] = v = sgd_step(db[co], v, step.lr);
+        db[co] = v;
     }
 }
 
@@ -466,7 +475,7 @@ void conv3x3_wgrad_bf16_plan_info(int N, int H, int W, int CinP, int Cout, int i
 // need one 16-byte segment per pixel, not a whole 64-byte row.  cin (optional): the number of real input channels
 // when the caller knows it; one to three of them on an image whose width is a multiple of 16 take the thin kernel.
 int conv3x3_wgrad_bf16(int N, int H, int W, int CinP, int Cout, const bf16_t *x, const bf16_t *g, float *dw, float *db,
-                       void *ws, size_t ws_bytes, hipStream_t stream, int x_channels, int cin)
+                       void *ws, size_t ws_bytes, hipStream_t stream, int x_channels, int cin, const ConvStep &step)
 {
     if (Cout % 8 || CinP % 8) return VGG_ERR_UNSUPPORTED;
     if (x_channels == 0) x_channels = CinP;
@@ -488,10 +497,10 @@ int conv3x3_wgrad_bf16(int N, int H, int W, int CinP, int Cout, const bf16_t *x,
             float *sums = t.part + (size_t)nb * one;
             hipLaunchKernelGGL(conv3x3_wgrad_bf16_thin_kernel, dim3((unsigned)nb, (unsigned)co_tiles), dim3(256), 0, stream, t);
             if (hipGetLastError() != hipSuccess) return VGG_ERR_LAUNCH;
-            wgrad_launch_reduce(t.part, sums, one, nullptr, nullptr, 0, nb, stream);
+            wgrad_launch_reduce(t.part, sums, one, nullptr, nullptr, 0, nb, stream, {});
             const int total = 9 * Cout * CinP + Cout;
-            hipLaunchKernelGGL(wgrad_bf16_thin_spread_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, sums, dw, db,
-                               Cout, CinP);
+            hipLaunchKernelGGL(step.copy ? wgrad_bf16_thin_spread_kernel<true> : wgrad_bf16_thin_spread_kernel<false>,
+                               dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, sums, dw, db, Cout, CinP, step);
             return launch_status();
         }
     }
@@ -507,7 +516,7 @@ int conv3x3_wgrad_bf16(int N, int H, int W, int CinP, int Cout, const bf16_t *x,
     if (a.tw == 8) hipLaunchKernelGGL(conv3x3_wgrad_bf16_kernel<8>, grid, dim3(kNW * 64), 2 * kBuf, stream, a);
     else hipLaunchKernelGGL(conv3x3_wgrad_bf16_kernel<16>, grid, dim3(kNW * 64), 2 * kBuf, stream, a);
     if (hipGetLastError() != hipSuccess) return VGG_ERR_LAUNCH;
-    wgrad_launch_reduce(a.part, dw, nw, a.dbpart, db, db ? (size_t)Cout : 0, np, stream);
+    wgrad_launch_reduce(a.part, dw, nw, a.dbpart, db, db ? (size_t)Cout : 0, np, stream, step);
     return launch_status();
 }
 
