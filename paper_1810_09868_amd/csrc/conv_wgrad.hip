@@ -401,14 +401,14 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const f32x4 *part, f3
     __shared__ f32x4 red[RY > 1 ? 256 : 1];
     const int x = threadIdx.x % RX, y = threadIdx.x / RX;
     size_t i = (size_t)blockIdx.x * RX + x;
-    const bool bias = i >= n4;
+    // (threads beyond the last output read the first one's: a load under a condition is waited for where it ends)
+    const bool live = i < n4 + n24, bias = live && i >= n4;
     if (bias) { i -= n4; part = part2; out = out2; n4 = n24; }
-    const bool live = i < n4;
+    if (!live) i = 0;
     f32x4 s = {0.f, 0.f, 0.f, 0.f}, theta = s;
-    if (STEP && live) theta = out[i];
-    if (live)
+    if (STEP) theta = out[i];
 #pragma unroll 8
-        for (int k = y; k < splits; k += RY) s += part[(size_t)k * n4 + i];
+    for (int k = y; k < splits; k += RY) s += part[(size_t)k * n4 + i];
     if (RY > 1) {
         red[threadIdx.x] = s;
         __syncthreads();
