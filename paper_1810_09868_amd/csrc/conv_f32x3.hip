@@ -108,7 +108,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void conv3x3_igemm_f32x3_kernel(Con
             hi[0][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
             if (p.bias && !p.part)   // (split contraction: the finishing kernel adds the bias)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) hi[0][j][e] = p.bias[min(c0 + j * 16 + e, p.Cout - 1)];
+                for (int e = 0; e < 4; ++e) hi[0][j][e] = kPartsScale * p.bias[min(c0 + j * 16 + e, p.Cout - 1)];
         }
     }
     store_w(0, 0);

@@ -542,6 +542,103 @@ def test_conv3x3_fp32_in_three_parts_infinities_and_range():
         assert max_rel_err(from_nhwc(y), R.conv3x3_fwd(xs, w, None, relu=False)) <= 2e-6
 
 
+def _full_mantissas(shape, seed):
+    """fp32 values in [1, 2) with random 24-bit significands, among them 0x3f80ffff, of which a truncating split into 8-bit
+    parts leaves out the most."""
+    g = torch.Generator().manual_seed(seed)
+    v = torch.randint(0, 1 << 23, shape, generator=g, dtype=torch.int32) | 0x3f800000
+    v.view(-1)[::7] = 0x3f80ffff
+    return v.view(torch.float32).cuda()
+
+
+def _three_part_call(op, lone):
+    """(result, the same in 64 bits) of an fp32 call on the bf16 matrix unit, all operands positive; lone: one product per result."""
+    if op in ("dw", "da"):
+        N, In, Out = (64, 640, 512) if op == "dw" else (64, 1032, 4096)
+        a, w, dz = _full_mantissas((N, In), 1), _full_mantissas((Out, In), 2), _full_mantissas((N, Out), 3)
+        if lone:
+            keep = torch.zeros_like(dz)
+            keep[3 if op == "dw" else slice(None), slice(None) if op == "dw" else 7] = 1.0
+            dz = dz * keep
+        dw, db, da = torch.empty((Out, In), device="cuda"), torch.empty((Out,), device="cuda"), torch.empty((N, In), device="cuda")
+        B.vgg_fc_bwd(B.F32, N, In, Out, a, w, dz, dw, db, da, 0, ws_bytes(B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out)))
+        torch.cuda.synchronize()
+        return (dw, dz.double().t() @ a.double()) if op == "dw" else (da, dz.double() @ w.double())
+    N, H, W, Cin, Cout = (3, 28, 28, 512, 128) if op != "wgrad" else (9, 28, 28, 96, 128)
+    plan = B.vgg_conv3x3_plan({"fwd": B.PLAN_FWD, "bwd_data": B.PLAN_BWD_DATA, "wgrad": B.PLAN_BWD_WEIGHT}[op], B.F32, N, H, W,
+                              *((Cout, Cin) if op == "bwd_data" else (Cin, Cout)))
+    assert plan[0] in ((114,) if op == "wgrad" else (14, 15, 16)), plan
+    x, g = _full_mantissas((N, H, W, Cin), 4), _full_mantissas((N, H, W, Cout), 5)
+    pad = lambda t: torch.nn.functional.pad(t.double(), (0, 0, 1, 1, 1, 1))
+    if op == "wgrad":
+        if lone:
+            keep = torch.zeros_like(g)
+            keep[1, 9, 13] = 1.0
+            g = g * keep
+        dw, db = torch.empty((9, Cout, Cin), device="cuda"), torch.empty((Cout,), device="cuda")
+        B.vgg_conv3x3_bwd_weight(B.F32, N, H, W, Cin, Cout, x, g, dw, db, ws_bytes(B.vgg_conv3x3_bwd_weight_workspace_bytes(B.F32, N, H, W, Cin, Cout)))
+        torch.cuda.synchronize()
+        xp, g2 = pad(x), g.double().reshape(-1, Cout).t()
+        return dw, torch.stack([g2 @ xp[:, t // 3:t // 3 + H, t % 3:t % 3 + W].reshape(-1, Cin) for t in range(9)])
+    if lone:                                                  # one pixel of nine, one channel: every output meets one of them
+        keep = torch.zeros_like(x)
+        keep[:, 1::3, 1::3, 5] = 1.0
+        x = x * keep
+    w = _full_mantissas((9, Cout, Cin), 6)                    # (packed: Cin is a multiple of 16)
+    y = torch.empty((N, H, W, Cout), device="cuda")
+    if op == "fwd":
+        B.vgg_conv3x3_fwd(B.F32, N, H, W, Cin, Cout, x, w, None, y, 0, ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(B.F32, N, H, W, Cin, Cout)))
+    else:
+        B.vgg_conv3x3_bwd_data(B.F32, N, H, W, Cout, Cin, x, w, None, y, ws_bytes(B.vgg_conv3x3_bwd_data_workspace_bytes(B.F32, N, H, W, Cout, Cin)))
+    torch.cuda.synchronize()
+    xp = pad(x)
+    ref = sum(xp[:, t // 3:t // 3 + H, t % 3:t % 3 + W].reshape(-1, Cin) @ w[t].double().t() for t in range(9)).view(N, H, W, Cout)
+    return y[:, :27, :27], ref[:, :27, :27]                   # (lone: pixel 25 is the last kept one, row and column 27 meet none)
+
+
+@pytest.mark.parametrize("lone", [True, False])
+@pytest.mark.parametrize("op", ["fwd", "bwd_data", "wgrad", "dw", "da"])
+def test_fp32_products_in_three_parts_without_a_bias(op, lone):
+    """Every kernel that multiplies fp32 in three parts, positive operands with full significands.  One product: at most 2^-24 of
+    it is left out and the result rounded (2^-24).  Sums of 64 to 7056 products: no element off by more than 5e-6 (a sum's own
+    rounding), and in both no bias: a mean signed error of 1e-8, where rounding to nearest gives 1e-9 over as many results."""
+    got, ref = _three_part_call(op, lone)
+    err = (got.double() - ref) / ref
+    assert err.abs().max().item() <= (2.0 ** -23 if lone else 5e-6)
+    assert abs(err.mean().item()) <= 1e-8
+
+
+def test_fp32_in_three_parts_keeps_nan_and_the_largest_values():
+    """A NaN whose payload lies below the first part stays one; values that round to infinity in bf16 stay finite; infinities
+    as in fp32 arithmetic.  (Dense backward and weight gradient: their results pass through no maximum.)"""
+    N, In, Out = 48, 136, 64
+    g = torch.Generator().manual_seed(8)
+    a, w, dz = (torch.randn(s, generator=g) for s in ((N, In), (Out, In), (N, Out)))
+    nan, largest = torch.tensor([0x7f800001, -0x7ffffe], dtype=torch.int32).view(torch.float32), torch.finfo(torch.float32).max
+    a[5, 7], w[2, 9], a[6, 70], w[33, 100], a[9, 11] = nan[0], nan[1], float("inf"), float("-inf"), largest
+    dz[9], dz[:, 40] = 0.25 * torch.sign(dz[9]), 0.0
+    w[40, 50] = -largest
+    dz[12, 40] = 0.5
+    dw, da = torch.empty((Out, In), device="cuda"), torch.empty((N, In), device="cuda")
+    B.vgg_fc_bwd(B.F32, N, In, Out, a.cuda(), w.cuda(), dz.cuda(), dw, None, da, 0, ws_bytes(B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out)))
+    torch.cuda.synchronize()
+    for got, ref in ((dw.cpu(), dz.double().t() @ a.double()), (da.cpu(), dz.double() @ w.double())):
+        assert torch.equal(got.isnan(), ref.isnan()) and ref.isnan().any()
+        assert torch.equal(got.isposinf(), ref.isposinf()) and torch.equal(got.isneginf(), ref.isneginf()) and ref.isinf().any()
+        big = ref.isfinite() & (ref.abs() > 1e37)
+        assert big.any() and ((got[big].double() - ref[big]) / ref[big]).abs().max() <= 2.0 ** -23
+    N, H, W, Cin, Cout = 3, 28, 28, 32, 64
+    assert B.vgg_conv3x3_plan(B.PLAN_BWD_WEIGHT, B.F32, N, H, W, Cin, Cout)[0] == 114
+    x, gr = torch.randn((N, H, W, Cin), generator=g), torch.randn((N, H, W, Cout), generator=g)
+    x[0, 3, 4, 6], gr[1, 7, 8, 9] = nan[0], nan[1]
+    dw, db = torch.empty((9, Cout, Cin), device="cuda"), torch.empty((Cout,), device="cuda")
+    B.vgg_conv3x3_bwd_weight(B.F32, N, H, W, Cin, Cout, x.cuda(), gr.cuda(), dw, db, ws_bytes(B.vgg_conv3x3_bwd_weight_workspace_bytes(B.F32, N, H, W, Cin, Cout)))
+    torch.cuda.synchronize()
+    want = torch.zeros((9, Cout, Cin), dtype=torch.bool)
+    want[:, :, 6], want[:, 9] = True, True
+    assert torch.equal(dw.cpu().isnan(), want) and torch.equal(dw.cpu().isfinite(), ~want)
+
+
 @pytest.mark.parametrize("dtype,shape,kernel", [
     (B.F32, (2, 46, 79, 32, 36), 1), (B.F32, (1, 24, 200, 96, 64), 1), (B.F32, (1, 97, 97, 48, 132), 1), (B.F32, (3, 63, 65, 3, 20), 1),
     (B.F32, (9, 66, 66, 16, 192), 0), (B.F32, (1, 6, 150, 16, 32), 0),
