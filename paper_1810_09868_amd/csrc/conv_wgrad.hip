@@ -391,12 +391,47 @@ __global__ __launch_bounds__(kWaves * 64, 4) void conv3x3_wgrad_thin_kernel(Wgra
 // reading the partials, 75 MB for 512 workgroups of bf16 64 x 64 blocks: 15 us; 4 bytes per lane and load took 16 to 31.
 // Two sets of partials with the same number of splits (the weights' and the bias') share a launch: the quads [0, n4)
 // come from part, [n4, n4 + n24) from part2.
-// STEP: out and out2 are master weights and biases, requested before the sums (a training step of 32 images 4272 -> 4241 us:
+// kReduceStep: out and out2 are master weights and biases, requested before the sums (a training step of 32 images 4272 -> 4241 us:
 // the gradients, 80 MB, are neither written nor read again, and two launches less).
-template <int RY, bool STEP>
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const f32x4 *part, f32x4 *out, size_t n4, const f32x4 *part2,
-                                                           f32x4 *out2, size_t n24, int splits, ConvStep step)
+// kReduceRedo: partial sums of patches (conv_wgrad_f32x3.hip), which multiply zeros of g with real neighbours of x where a
+// patch is narrower than the MFMA's rows or sticks out of the image.  Where that x is infinite the product is NaN and no part of
+// the sum: a partial sum that is NaN is formed again from the patches' own pixels.  (Costs nothing here, where the sums are
+// read anyway; a test per patch in the main kernel cost 4 to 14 % of it.)
+enum ReduceKind { kReducePlain, kReduceStep, kReduceRedo };
+struct PartRedo {
+    const float *x, *g;   // null: no redo
+    int H, W, CinP, Cout, TH, TW, tiles_w, tiles_hw, ntiles, tiles_per_split;
+};
+// Partial sums i .. i + 3 of split k, pixel by pixel in fp32 arithmetic.
+__device__ __forceinline__ f32x4 redo_partial(const PartRedo &r, size_t i, int k)
 {
+    const int ci = (int)(i % r.CinP), co = (int)(i / r.CinP % r.Cout), tap = (int)(i / r.CinP / r.Cout);
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    const int end = min((k + 1) * r.tiles_per_split, r.ntiles);
+    for (int tile = k * r.tiles_per_split; tile < end; ++tile) {
+        const int n = tile / r.tiles_hw, ty = tile % r.tiles_hw / r.tiles_w, tx = tile % r.tiles_hw % r.tiles_w;
+        const int h1 = min((ty + 1) * r.TH, r.H), w1 = min((tx + 1) * r.TW, r.W);
+        f32x4 t = {0.f, 0.f, 0.f, 0.f};
+        for (int h = ty * r.TH; h < h1; ++h)
+            for (int w = tx * r.TW; w < w1; ++w) {
+                const int hx = h + tap / 3 - 1, wx = w + tap % 3 - 1;
+                f32x4 x = {0.f, 0.f, 0.f, 0.f};
+                if ((unsigned)hx < (unsigned)r.H && (unsigned)wx < (unsigned)r.W)
+                    x = *reinterpret_cast<const f32x4 *>(r.x + (((size_t)n * r.H + hx) * r.W + wx) * r.CinP + ci);
+                const float g = r.g[(((size_t)n * r.H + h) * r.W + w) * r.Cout + co];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) t[c] = __builtin_fmaf(g, x[c], t[c]);
+            }
+        sum += t;
+        if (sum[0] != sum[0] && sum[1] != sum[1] && sum[2] != sum[2] && sum[3] != sum[3]) break;
+    }
+    return sum;
+}
+template <int RY, int KIND>
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const f32x4 *part, f32x4 *out, size_t n4, const f32x4 *part2,
+                                                           f32x4 *out2, size_t n24, int splits, ConvStep step, PartRedo redo)
+{
+    constexpr bool STEP = KIND == kReduceStep;
     constexpr int RX = 256 / RY;
     __shared__ f32x4 red[RY > 1 ? 256 : 1];
     const int x = threadIdx.x % RX, y = threadIdx.x / RX;
@@ -409,6 +444,20 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const f32x4 *part, f3
     if (STEP) theta = out[i];
 #pragma unroll 8
     for (int k = y; k < splits; k += RY) s += part[(size_t)k * n4 + i];
+    auto nan = [](const f32x4 &v) { return v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]; };
+    if (KIND == kReduceRedo && !bias && nan(s)) {
+        s = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma nounroll
+        for (int k = y; k < splits; k += RY) {
+            f32x4 v = part[(size_t)k * n4 + i];
+            if (nan(v)) {
+                const f32x4 q = redo_partial(redo, i * 4, k);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = v[c] == v[c] ? v[c] : q[c];
+            }
+            s += v;
+        }
+    }
     if (RY > 1) {
         red[threadIdx.x] = s;
         __syncthreads();
@@ -432,20 +481,20 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const f32x4 *part, f3
 }
 
 static void launch_reduce(const float *part, float *out, size_t n, const float *part2, float *out2, size_t n2, int splits,
-                          hipStream_t stream, const ConvStep &step = {})
+                          hipStream_t stream, const ConvStep &step = {}, const PartRedo &redo = {})
 {
-    const auto go = [&](auto plain, auto stepping, int rows) {
+    const auto go = [&](auto plain, auto stepping, auto redoing, int rows) {
         const size_t per = 256 / rows;
-        hipLaunchKernelGGL(step.copy ? stepping : plain, dim3((unsigned)(((n + n2) / 4 + per - 1) / per)), dim3(256), 0, stream,
+        hipLaunchKernelGGL(step.copy ? stepping : redo.x ? redoing : plain, dim3((unsigned)(((n + n2) / 4 + per - 1) / per)), dim3(256), 0, stream,
                            reinterpret_cast<const f32x4 *>(part), reinterpret_cast<f32x4 *>(out), n / 4,
-                           reinterpret_cast<const f32x4 *>(part2), reinterpret_cast<f32x4 *>(out2), n2 / 4, splits, step);
+                           reinterpret_cast<const f32x4 *>(part2), reinterpret_cast<f32x4 *>(out2), n2 / 4, splits, step, redo);
     };
     // Rows by the number of partial results alone.  us for 4 bytes a load (as it was) / one / four / sixteen rows of quads,
     // splits x outputs: 8 x 2.4e6 15.6 / 15.4 / 15.6 / 23.7, 32 x 590e3 18.7 / 15.0 / 14.8 / 14.8, 64 x 295e3 19.9 / 15.3 /
     // 14.8 / 14.8, 128 x 147e3 24.8 / 14.6 / 15.0 / 15.2, 512 x 37e3 30.7 / 27.8 / 15.0 / 16.0, 1024 x 1728 23.0 / 51 / 18.5 / 8.4.
-    if (splits >= 128) go(wgrad_reduce_kernel<16, false>, wgrad_reduce_kernel<16, true>, 16);
-    else if (splits >= 16) go(wgrad_reduce_kernel<4, false>, wgrad_reduce_kernel<4, true>, 4);
-    else go(wgrad_reduce_kernel<1, false>, wgrad_reduce_kernel<1, true>, 1);
+    if (splits >= 128) go(wgrad_reduce_kernel<16, kReducePlain>, wgrad_reduce_kernel<16, kReduceStep>, wgrad_reduce_kernel<16, kReduceRedo>, 16);
+    else if (splits >= 16) go(wgrad_reduce_kernel<4, kReducePlain>, wgrad_reduce_kernel<4, kReduceStep>, wgrad_reduce_kernel<4, kReduceRedo>, 4);
+    else go(wgrad_reduce_kernel<1, kReducePlain>, wgrad_reduce_kernel<1, kReduceStep>, wgrad_reduce_kernel<1, kReduceRedo>, 1);
 }
 
 // (also used by the bf16 weight-gradient kernel; part2/out2 may be null with n2 = 0)
@@ -564,7 +613,9 @@ int conv3x3_wgrad(int N, int H, int W, int Cin, int CinP, int Cout, const float 
     if (!thin && wgrad_parts(a)) {
         const int rc = launch_wgrad_f32x3(a.geo, CinP, Cout, a.splits, a.tiles_per_split, x, g, a.part, a.dbpart, stream);
         if (rc) return rc;
-        launch_reduce(a.part, dw, nw, a.dbpart, db, db ? (size_t)Cout : 0, a.splits, stream);
+        const TileGeom &t = a.geo;
+        launch_reduce(a.part, dw, nw, a.dbpart, db, db ? (size_t)Cout : 0, a.splits, stream, {},
+                      PartRedo{x, g, H, W, CinP, Cout, t.TH, t.TW, t.tiles_w, t.tiles_hw, t.ntiles, a.tiles_per_split});
         return launch_status();
     }
     size_t lds = (size_t)2 * (kPK * kGRow + a.SX * kXRow);

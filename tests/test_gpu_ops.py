@@ -789,6 +789,32 @@ def test_conv3x3_bwd_weight_fp32_in_three_parts(shape, kernel):
     assert max_rel_err(dw.cpu().numpy(), dw_ref) <= 3e-6 and max_rel_err(db.cpu().numpy(), db_ref) <= 3e-6
 
 
+@pytest.mark.parametrize("shape,kernel", [((3, 28, 28, 32, 64), 114), ((1, 56, 56, 40, 72), 114), ((3, 50, 66, 40, 72), 114), ((1, 45, 60, 96, 36), 116),
+                                          ((2, 16, 32, 64, 64), 116), ((12, 43, 19, 24, 72), 108), ((70, 7, 7, 40, 132), 108)])
+def test_conv3x3_bwd_weight_fp32_in_three_parts_infinities(shape, kernel):
+    """An infinite or NaN x meets the pixels of g that the image has and no other: beside the columns and rows that a patch
+    multiplies beyond its own or the image's last ones, a tap's sum is infinite, NaN or finite as in 64 bits."""
+    N, H, W, Cin, Cout = shape
+    assert B.vgg_conv3x3_plan(B.PLAN_BWD_WEIGHT, B.F32, N, H, W, Cin, Cout)[0] == kernel
+    gen = torch.Generator().manual_seed(sum(shape))
+    x, g = torch.randn((N, H, W, Cin), generator=gen), torch.randn((N, H, W, Cout), generator=gen)
+    for c, (h, w, v) in enumerate([(3, W - 1, 1), (H - 1, 5, -1), (H - 1, W - 1, 1), (3, min(14, W - 2), 1), (2, min(15, W - 1), -1), (H - 1, 0, 1), (0, W - 1, 1),
+                                   (min(7, H - 1), 6, 1), (min(8, H - 2), min(8, W - 2), 1)]):
+        x[N - 1, h, w, c] = v * float("inf")
+    x[0, 1, W - 1, 9] = float("nan")
+    dw, db = torch.empty((9, Cout, B.vgg_padded_channels(B.F32, Cin)), device="cuda"), torch.empty((Cout,), device="cuda")
+    B.vgg_conv3x3_bwd_weight(B.F32, N, H, W, Cin, Cout, x.cuda(), g.cuda(), dw, db, ws_bytes(B.vgg_conv3x3_bwd_weight_workspace_bytes(B.F32, N, H, W, Cin, Cout)))
+    torch.cuda.synchronize()
+    xp, g2 = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1)), g.double().reshape(-1, Cout).t().contiguous()
+    ref = torch.stack([g2 @ xp[:, t // 3:t // 3 + H, t % 3:t % 3 + W].reshape(-1, Cin) for t in range(9)])
+    got = dw[:, :, :Cin].cpu()
+    for f in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(f(got), f(ref))
+    ok = ref.isfinite()
+    assert ok[:, :, 0].any() and not ok[:, :, 0].all()        # (the last column's infinity: not in the taps that look left of it)
+    assert (got[ok].double() - ref[ok]).abs().max() <= 3e-6 * ref[ok].abs().max()
+
+
 @pytest.mark.parametrize("shape,kernel", [((3, 50, 66, 40, 72), 114), ((3, 8, 100, 16, 64), 116), ((1, 45, 60, 96, 36), 116), ((2, 9, 100, 16, 64), 100),
                                           ((2, 8, 31, 24, 68), 116), ((2, 5, 31, 24, 68), 100), ((3, 13, 11, 64, 64), 100), ((2, 3, 130, 32, 64), 100)])
 def test_conv3x3_bwd_weight_fp32_patches_that_stick_out(shape, kernel):
