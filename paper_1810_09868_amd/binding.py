@@ -123,6 +123,15 @@ def _nbytes(t) -> int:
 _RAW_STREAM = None
 
 
+def _forget_stream():
+    """A forked child asks torch anew, which refuses a context that its parent made."""
+    global _RAW_STREAM
+    _RAW_STREAM = None
+
+
+os.register_at_fork(after_in_child=_forget_stream)
+
+
 def _stream() -> int:
     """The current device's current stream, as the C entry points take it.  Asked for on every call and without building a
     torch Stream object: two short calls issued back to back are bound by what the host does between them (softmax and loss of

@@ -283,3 +283,18 @@ def test_bf16_weight_gradient_on_8x8_patches_takes_no_more_workgroups():
                 assert info[5] <= splits * (2 if ci <= 32 else 1)
                 fewer += t8 < t16
     assert fewer > 100
+
+
+def test_a_forked_child_asks_torch_for_its_stream(monkeypatch):
+    """torch refuses the parent's GPU context in a forked child; a stream kept from before the fork must not go past that."""
+    monkeypatch.setattr(B, "_RAW_STREAM", lambda: 5)
+    assert B._stream() == 5
+    r, w = os.pipe()
+    pid = os.fork()
+    if pid == 0:
+        os.write(w, b"kept" if B._RAW_STREAM is not None else b"asks")
+        os._exit(0)
+    os.waitpid(pid, 0)
+    assert os.read(r, 8) == b"asks" and B._stream() == 5
+    os.close(r)
+    os.close(w)
