@@ -615,6 +615,25 @@ def test_train_step_without_gradient_output_leaves_the_same_parameters(dtype, si
     assert np.abs(fused.unpack()["fc_w"][2] - before).max() > 0
 
 
+def test_bf16_dense_update_over_several_passes_and_ragged_tiles():
+    # The dense kernels that take the step themselves, where the batch takes two of their 64-row passes and inputs and
+    # outputs end inside a 128-wide tile: the parameters that the separate update leaves, bit by bit, over two steps.
+    shape = (70, 32, 32, 160, 10)
+    inp = synth.vgg19_inputs(*shape, seed=11)
+    plain, fused = (Vgg19(B.BF16, *shape, lr=0.01, training=True) for _ in range(2))
+    for m in (plain, fused):
+        m.pack(inp.conv_w, inp.conv_b, inp.fc_w, inp.fc_b)
+    x, lab = dev(inp.x), dev(inp.labels)
+    for step in range(2):
+        before = fused.unpack()["fc_w"]
+        plain.train_step(x, lab, want_grads=True)
+        fused.train_step(x, lab, want_grads=False)
+        torch.cuda.synchronize()
+        assert torch.equal(plain.loss, fused.loss) and torch.equal(plain.logits, fused.logits), step
+        assert torch.equal(plain.packed, fused.packed), step
+        assert all((a != b).any() for a, b in zip(before, fused.unpack()["fc_w"])), step
+
+
 def test_training_loop_as_one_graph_matches_eager_steps():
     # K steps recorded once and replayed as a single launch must leave exactly the parameters that K eager
     # steps leave (every kernel is deterministic); replayed several times, with eager work and
