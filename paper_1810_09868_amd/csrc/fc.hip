@@ -138,7 +138,8 @@ __global__ __launch_bounds__(256, 2) void fc_fwd_kernel(FcArgs p)
         if (u0 + 4 < u_end) { load_a(u0 + 4, a_next); load_w(u0 + 4, w_next); }
         barrier();  // the staged activations are visible
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u) {
+            if (!VEC && u0 + u >= u_end) break;   // (zeros only; 145 x 6 -> 1863 in fp32 13.2 -> 10.7 us)
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 const uint4 bf = *reinterpret_cast<const uint4 *>(Wv + r * kRow + u * 64 + g * 32 + khalf * 16);
@@ -148,6 +149,7 @@ __global__ __launch_bounds__(256, 2) void fc_fwd_kernel(FcArgs p)
                     FcMma<T>::run(acc[i], af, bf);
                 }
             }
+        }
     }
     if (ook) {
 #pragma unroll

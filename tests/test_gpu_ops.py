@@ -1022,7 +1022,7 @@ def test_fc_forward_where_the_kernel_changes(dtype, N, In, Out):
 
 @pytest.mark.parametrize("dtype", [B.F32, B.BF16])
 @pytest.mark.parametrize("N,In,Out", [(33, 264, 129), (64, 520, 127), (65, 136, 130), (96, 1032, 200), (97, 4104, 40), (128, 24, 257), (257, 264, 128),
-                                      (40, 261, 65), (70, 1000, 33),
+                                      (40, 261, 65), (70, 1000, 33), (142, 22, 18), (70, 3, 5), (130, 37, 33),
                                       (3, 5120, 40), (3, 5136, 40), (16, 8704, 1500), (16, 8712, 1504), (2, 25608, 2504), (20, 3328, 96),
                                       (32, 3336, 96), (17, 8712, 2504), (20, 1664, 8200), (1, 2048, 8208),
                                       (5, 16388, 2052), (40, 16392, 2050), (9, 32776, 2056), (33, 32784, 2056)])
