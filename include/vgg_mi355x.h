@@ -333,7 +333,12 @@ int vgg19_forward(const vgg_config *cfg, const float *x_nchw, const void *packed
  * ([N][classes]) may be NULL.  The fp32 update streams over the whole packed
  * block: the alignment gaps between its tensors (never read by any kernel)
  * take whatever the workspace holds at the matching positions, so zero the
- * workspace once if the block is to be compared byte for byte. */
+ * workspace once if the block is to be compared byte for byte.
+ * A call refused for its arguments leaves the parameters as they were.  One
+ * that returns VGG_ERR_LAUNCH has issued part of its work: the parameters may
+ * be partly stepped (bf16 without grads_or_null steps each tensor where its
+ * gradient is formed, during the backward pass; otherwise the step comes
+ * last) and are to be packed anew. */
 int vgg19_train_step(const vgg_config *cfg, const float *x_nchw, const int32_t *labels,
                      void *packed_inout, size_t packed_bytes, const vgg19_params *grads_or_null,
                      float *loss, float *logits, void *ws, size_t ws_bytes, void *stream);

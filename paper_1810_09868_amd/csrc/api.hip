@@ -336,7 +336,8 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
     const char *fc_in[3] = {ws + L.pooled[15], ws + L.z1, ws + L.z2};
     float *fc_dz[3] = {F(ws + L.dz1), F(ws + L.dz2), F(ws + L.dlogits)};
     float *dflat = F(mixed ? ws + L.dflat32 : ws + L.gA);
-    // bf16: unless the caller asks for the gradients, the weights take their step where their gradient is formed.
+    // bf16: unless the caller asks for the gradients, the weights take their step where their gradient is formed.  (A launch that
+    // fails after the first of these leaves some tensors stepped, as the header says; arguments and sizes are checked before.)
     const bool fused = mixed && !grads_out;
     char *gw = fused ? pm : gr;   // what the weight-gradient kernels write
     for (int l = 2; l >= 0; --l) {
