@@ -25,7 +25,8 @@ if ROOT not in sys.path:
 CONV = [(3, 64, 224), (64, 64, 224), (64, 128, 112), (128, 128, 112), (128, 256, 56), (256, 256, 56),
         (256, 256, 56), (256, 256, 56), (256, 512, 28), (512, 512, 28), (512, 512, 28), (512, 512, 28),
         (512, 512, 14), (512, 512, 14), (512, 512, 14), (512, 512, 14)]
-# MI355X dense MFMA peaks; fp32 products are formed by six bf16 MFMAs each (the fp32 MFMAs themselves peak at 157.3)
+# MI355X dense MFMA peaks; fp32 products are formed by six bf16 MFMAs each (the fp32 MFMAs themselves peak at 157.3): three
+# 8-bit parts per operand, rounded to nearest, of whose nine products the three smallest, at most 2^-24 of the whole, are left out
 PEAK_TFLOPS = {"bf16": 2500.0, "f32": 2500.0 / 6}
 HBM_GBS = 8000.0
 
@@ -250,7 +251,7 @@ def batch_sweep(dtype_name, batches, steps):
 
 
 def conv_microbench(steps):
-    """configs[1]: one conv3_1-style layer, fp32, 128 -> 256 channels, 56x56, batch 100, bias + ReLU, through the
+    """One conv3_1-style layer, fp32, 128 -> 256 channels, 56x56, batch 100, bias + ReLU, through the
     single-operation entry point; N(0,1) inputs, He-normal weights.  ms, TFLOP/s and share of the peak rate of
     fp32 products (six bf16 MFMAs each)."""
     import torch

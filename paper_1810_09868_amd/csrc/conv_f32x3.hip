@@ -8,7 +8,7 @@
 // Every value is split once per workgroup, on its way from a register to LDS: the weights of tap t + 1 in the middle of tap t,
 // the next chunk's halo, requested before the last tap, at the chunk's end.  256-pixel tiles: eight waves, one workgroup per
 // CU; 128-pixel tiles x 64 channels: four waves, two per CU.  Bound by MFMA issue at the clock that random operands allow:
-// 128 -> 256 at 56x56, batch 100, 757 us = 245 TFLOP/s of fp32 products, 1.47 PFLOP/s of bf16 ones.  (The tap loop is not
+// 128 -> 256 at 56x56, batch 100, 750 us = 247 TFLOP/s of fp32 products, 1.48 PFLOP/s of bf16 ones.  (The tap loop is not
 // unrolled: the addresses of nine taps took ninety registers.)
 #include "conv_tile.h"
 #include "f32x3.h"

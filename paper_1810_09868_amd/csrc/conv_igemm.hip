@@ -1213,13 +1213,15 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         }
         // The same launches on the bf16 matrix unit (conv_f32x3.hip), in the same tiles: 0.48 to 0.93 of the time over 150 shapes (128 ->
         // 256 at 56x56, batch 100, 1388 -> 763 us; 512 -> 512 at 28x28, batch 50, 1580 -> 773; 16 -> 40 at 20x33, batch 30, 14.4 ->
-        // 13.4).  (That kernel's weight offsets are 32 bits.)
+        // 13.4).  (That kernel's weight offsets are 32 bits: beyond 4 GiB of weights per tap, and only there, the direct-to-LDS kernel
+        // splits fp32 contractions.)
         if ((size_t)Cout * CinP * sizeof(float) >= ((size_t)1 << 32)) return c;
         const int cols64 = (Cout + 63) / 64;
         if (wide) {
             // 8 x 16 patches that pad by at most 1.6: over 240 shapes 0.34 to 0.95 of the time (8 -> 320 channels at 9x102 23 / 56 us),
             // at 1.7 and more up to 1.02 where the other kernel's tiles are 128 wide.  One chunk of 16 channels is half zeros
-            // (0.96 to 1.11); small launches, 20 to 50 us, stay where their tests have them (0.6 to 0.8 here).
+            // (0.96 to 1.11).  Launches below the last two sizes, 20 to 50 us, would take 0.6 to 0.8 of the time here; they keep the
+            // direct-to-LDS kernel, whose patches of wide fp32 images are tested at these sizes.
             const TileGeom t = make_patch_geom(N, H, W, 128);
             const int tiles = t.ntiles * cols64;
             if (!pool && (long)t.ntiles * 128 * 10 <= (long)c.g.M * 16 && (CinP >= 64 ? (long)tiles * CinP >= 256 * 16 : CinP >= 32 && tiles >= 512)) {

@@ -488,7 +488,7 @@ def test_conv3x3_bf16_split_over_workgroups(shape):
     ((5, 56, 56, 16, 132), 15, 64), ((43, 56, 56, 32, 132), 15, 128), ((43, 56, 56, 40, 128), 15, 128), ((50, 14, 14, 80, 512), 16, 64), ((100, 13, 14, 32, 268), 16, 64)])
 def test_conv3x3_fp32_in_three_parts(shape, kernel, bn):
     """The fp32 kernels on the bf16 matrix unit: half a last chunk, ragged channels, every tile, pooled and masked.  Sums of at
-    most 720 products, each exact to 2^-24, in fp32: 2e-6 of the largest output against the oracle."""
+    most 720 products, of each of which at most 2^-24 is left out, in fp32: 2e-6 of the largest output against the oracle."""
     N, H, W, Cin, Cout = shape
     plan = B.vgg_conv3x3_plan(B.PLAN_FWD, B.F32, N, H, W, Cin, Cout)
     assert plan[0] == kernel and plan[2] == bn, plan
