@@ -396,7 +396,8 @@ __global__ __launch_bounds__(kWaves * 64, 4) void conv3x3_wgrad_thin_kernel(Wgra
 // kReduceRedo: partial sums of patches (conv_wgrad_f32x3.hip), which multiply zeros of g with real neighbours of x where a
 // patch is narrower than the MFMA's rows or sticks out of the image.  Where that x is infinite the product is NaN and no part of
 // the sum: a partial sum that is NaN is formed again from the patches' own pixels.  (Costs nothing here, where the sums are
-// read anyway; a test per patch in the main kernel cost 4 to 14 % of it.)
+// read anyway; a test per patch in the main kernel cost 4 to 14 % of it.  With one infinity in the last pixel, 256 -> 256 at 56x56,
+// batch 100, takes 19 ms instead of 2.4, with nothing but NaN 2.4.)
 enum ReduceKind { kReducePlain, kReduceStep, kReduceRedo };
 struct PartRedo {
     const float *x, *g;   // null: no redo

@@ -407,12 +407,12 @@ int fc_forward(int dtype, int N, int In, int Out, const void *a_, const void *w,
 // ------------------------------------------------- backward: dW = dz^T * a
 // fp32, up to 40 batch rows; bound by its MFMAs and, under them, by writing dW.  Workgroup: 128 (o) x 128 (i) block of dW; the batch is
 // the contraction index, staged through LDS 32 rows at a time, and multiplied eight rows (four MFMA steps) at a time
-// up to the last one: 100 rows cost 104.  Wave w owns outputs [32 w, 32 w + 32) and all 128 inputs: lane r reads four
+// up to the last one: 33 rows cost 40.  Wave w owns outputs [32 w, 32 w + 32) and all 128 inputs: lane r reads four
 // consecutive inputs with one 16-byte LDS read and feeds them to four MFMA column tiles, so accumulator tile j of lane r
 // holds input 4 r + j and the stores are 16 bytes, 512 contiguous per row; 64 accumulator registers, so that four
 // workgroups share a CU and some store while others multiply.  (Operands straight from L2 without LDS: the loads between
-// the MFMAs hold up their issue, MFMA busy 0.47.)  25088 -> 4096, batch 100: 274 -> 224 us (128 rows were multiplied for
-// 100, 4 bytes stored per lane); MFMA busy 0.67.
+// the MFMAs hold up their issue.)  25088 -> 4096: 10 rows 77 us, 32 rows 87 (4.8 TB/s of dW), 40 rows 111; from 41 rows on the
+// kernel below takes over.
 // VEC: In is a multiple of 4; otherwise the four inputs are written one by one.
 
 // Four floats row[c..c+3], zeros at and beyond column C.  vec: the row is 16-byte aligned (C a multiple of 4).
@@ -992,7 +992,7 @@ int fc_backward(int N, int In, int Out, const float *a, const float *w, const fl
                 int relu_mask, void *ws, hipStream_t s)
 {
     const dim3 grid((unsigned)(((In + 127) / 128) * ((Out + 127) / 128)));
-    // From about 50 rows on the bf16 matrix unit, both products: 25088 -> 4096, batch 100 395 -> 346 us, 4096 -> 4096 87 -> 70, all of
+    // From about 50 rows on the bf16 matrix unit, both products: 25088 -> 4096, batch 100 395 -> 352 us, 4096 -> 4096 87 -> 71, all of
     // 80 sizes 0.82 to 0.92 on average (1.04 at most, 100 outputs); 32 rows 0.99, 16 rows 1.07, where the weights and dW stream.
     const bool parts = N > 40;
     auto dw_kernel = parts ? (In % 4 == 0 ? fc_dw_f32x3_kernel<true> : fc_dw_f32x3_kernel<false>) : (In % 4 == 0 ? fc_dw_kernel<true> : fc_dw_kernel<false>);
