@@ -508,7 +508,7 @@ __global__ __launch_bounds__(256, 4) void fc_dw_kernel(const float *__restrict__
     }
 }
 
-// The same on the bf16 matrix unit (f32x3.h), for more than 40 batch rows; bound by splitting the operands, the MFMAs and
+// The same on the bf16 matrix unit (f32x3.h), for more than 128 batch rows or where no workspace is given; bound by splitting the operands, the MFMAs and
 // writing dW together.  Workgroup: 128 (o) x 128 (i) block of dW; the batch is the contraction index, staged through LDS 32 rows
 // at a time as three planes of bf16 parts, and multiplied sixteen rows at a time up to the last one: 100 rows cost 112.  A
 // thread loads sixteen batch rows of one output and of one input, so that they leave for LDS already transposed: rows of 32
@@ -767,7 +767,7 @@ __global__ __launch_bounds__(256, 2) void fc_da_kernel(FcDaArgs p)
         }
 }
 
-// The same on the bf16 matrix unit (f32x3.h).  Workgroup, one per CU: eight waves, 16 NB batch rows x 256 inputs x a range of
+// The same on the bf16 matrix unit (f32x3.h), for more than 128 batch rows.  Workgroup, one per CU: eight waves, 16 NB batch rows x 256 inputs x a range of
 // outputs (the contraction index), 32 at a time.  Both operands go through LDS as three planes of bf16 parts, rows of 32
 // outputs = 64 bytes whose 16-byte segment s lies at s ^ ((row >> 1) & 3); a thread loads sixteen outputs of one input, so
 // that they leave for LDS already transposed.  Two buffers and one barrier per step: one wave of a SIMD splits and stores
@@ -904,6 +904,329 @@ __global__ __launch_bounds__(512, 2) void fc_da_f32x3_kernel(FcDaArgs p)
     }
 }
 
+// ------------------------------------ fp32 backward on the bf16 matrix unit, more than 40 batch rows
+// dz in parts (f32x3.h), once per call, in the layouts that the two products' fragments have: per 32 outputs ("step") blocks of
+// 1 KB, which a wave's 64 lanes read 16 bytes each, in order.  25088 -> 4096: 6 us, db among them (4.7 alone).  With it the bias gradient, in fc_db_kernel's order.
+//   rows (da): [step][16-row block][part], lane 16 g + q: outputs 8 g .. 8 g + 7 of row q
+//   cols (dW): [step][16-row block][part], lane 32 k + r: rows 8 k .. 8 k + 7 of output r
+// Rows and outputs past the ends are zeros.
+__global__ __launch_bounds__(512) void fc_dz_parts_kernel(const float *__restrict__ dz, char *__restrict__ rows, char *__restrict__ cols,
+                                                          float *__restrict__ db, int N, int Out, int nb)
+{
+    const int tid = threadIdx.x, step = blockIdx.x, o0 = step * 32;
+    auto store = [&](char *dst, const float(&v)[8]) __attribute__((always_inline)) {
+        f32x3_u32x4 x, y;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { x[j] = __float_as_uint(v[j]); y[j] = __float_as_uint(v[j + 4]); }
+        const Parts4 s = split_parts(x), t = split_parts(y);
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            *reinterpret_cast<f32x3_u32x4 *>(dst + e * 1024) = f32x3_u32x4{s.p[e][0], s.p[e][1], t.p[e][0], t.p[e][1]};
+    };
+    for (int u = tid; u < nb * 128; u += 512) {
+        const bool by_row = u < nb * 64;
+        const int w = by_row ? u : u - nb * 64;
+        const int row = by_row ? w >> 2 : (w >> 5) * 8, o = o0 + (by_row ? (w & 3) * 8 : w & 31);
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = dz[(size_t)min(row + (by_row ? 0 : j), N - 1) * Out + min(o + (by_row ? j : 0), Out - 1)];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = row + (by_row ? 0 : j) < N && o + (by_row ? j : 0) < Out ? v[j] : 0.f;
+        if (by_row) store(rows + ((size_t)step * nb + (w >> 6)) * 3072 + ((w & 3) * 16 + ((w >> 2) & 15)) * 16, v);
+        else store(cols + ((size_t)step * nb + (w >> 6)) * 3072 + (w & 63) * 16, v);
+    }
+    if (!db) return;
+    __shared__ float part[4][32];
+    const int col = tid & 31, wv = tid >> 5, o = o0 + col;
+    if (wv < 4) {
+        float s = 0.f;
+        if (o < Out) {
+#pragma unroll 8
+            for (int n = wv; n < N; n += 4) s += dz[(size_t)n * Out + o];
+        }
+        part[wv][col] = s;
+    }
+    __syncthreads();
+    if (wv == 0 && o < Out) db[o] = (part[0][col] + part[1][col]) + (part[2][col] + part[3][col]);
+}
+
+// The steps of dz that both products walk: 3 NB blocks of 1 KB, copied straight to one of four LDS buffers by the eight waves, three
+// steps ahead.  The barrier of a step lies in its middle: it says that the next step's copies are there, so that a step begins, with
+// its first fragments read during the one before, without a wait; and that the last step's buffer is free.  Global loads and
+// stores of a wave complete in order: "at most n younger ones outstanding" means that a copy is there.
+template <int NB>
+struct DzSteps {
+    static constexpr int BYTES = NB * 3072, BUFFERS = 4;
+    const char *src;     // + lane * 16
+    unsigned lds;        // of the first buffer
+    int wv;
+    __device__ __forceinline__ DzSteps(const char *planes, const char *buf)
+        : src(planes + (threadIdx.x & 63) * 16),
+          lds(__builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) const char *)buf)),
+          wv(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {}
+    __device__ __forceinline__ void copy(int step, int buffer) const
+    {
+        const char *s = src + (size_t)step * BYTES;
+#pragma unroll
+        for (int k = 0; k < (3 * NB + 7) / 8; ++k) {
+            const int b = wv + 8 * k;
+            if (b < 3 * NB) {
+                const unsigned dst = __builtin_amdgcn_readfirstlane(lds + (buffer & (BUFFERS - 1)) * BYTES + b * 1024);
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(s + b * 1024) : "m0", "memory");
+            }
+        }
+    }
+    template <int YOUNGER> static __device__ __forceinline__ void wait()
+    {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(YOUNGER) : "memory");
+    }
+};
+// a buffer of `bytes` bytes at `base`: loads beyond it give zero, stores beyond it are dropped
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, int bytes)
+{
+    // (the compiler takes some of these for different in every lane, and would loop over them)
+    const uintptr_t b = reinterpret_cast<uintptr_t>(base);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b), hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((uintptr_t)hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+
+// dW = dz^T a, up to 128 batch rows; bound by the MFMAs (six per product) and by writing dW.  Eight waves, one workgroup per CU; wave w
+// owns inputs 32 w .. 32 w + 31 of a tile of 256, whose batch rows it keeps in registers, split, in the MFMA's layout; 32
+// outputs of dz at a time come through LDS.  So a value of the input is split once per tile and workgroup, not once per 128 x 128 block
+// of dW, and nothing but MFMAs, fragment reads and stores is left in the loop.  The (tile, 32 outputs) units are shared out evenly.
+// Stores: 32 lanes write 128 bytes of a row.  25088 -> 4096, 100 rows: 109 us (196 with both operands split per block), the MFMAs alone 97.
+template <int NB>
+__global__ __launch_bounds__(512, 2) void fc_dw_parts_kernel(const float *__restrict__ a, const char *__restrict__ cols,
+                                                             float *__restrict__ dw, int N, int In, int Out, int units)
+{
+    extern __shared__ __align__(16) char lds[];
+    const int lane = threadIdx.x & 63, r = lane & 31, kp = lane >> 5;
+    const DzSteps<NB> dz(cols, lds);
+    const int steps = (Out + 31) / 32;
+    const int begin = (int)((long)units * blockIdx.x / gridDim.x), end = (int)((long)units * (blockIdx.x + 1) / gridDim.x);
+    if (begin >= end) return;
+    int t = begin, tile = begin / steps, s = begin - tile * steps;
+    auto next = [&](int v) __attribute__((always_inline)) { return v + 1 == steps ? 0 : v + 1; };
+    dz.copy(s, 0);
+    if (t + 1 < end) dz.copy(next(s), 1);
+    if (t + 2 < end) dz.copy(next(next(s)), 2);
+    dz.template wait<0>();
+    bf16x8 df[2][3];
+    auto read = [&](int unit, int k, bf16x8(&to)[3]) __attribute__((always_inline)) {
+        const char *const plane = lds + ((unit - begin) & (DzSteps<NB>::BUFFERS - 1)) * DzSteps<NB>::BYTES + k * 3072 + lane * 16;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) to[e] = *reinterpret_cast<const bf16x8 *>(plane + e * 1024);
+    };
+    while (t < end) {
+        const int col = tile * 256 + dz.wv * 32 + r;
+        bf16x8 af[NB][3];
+        {
+            // (rows past the end are beyond the buffer: zeros; inputs past the end: other values, never stored)
+            f32x3_u32x4 raw[NB][2];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const auto rows = buffer_of(a + (size_t)min(k * 16, N) * In, max(min(16, N - k * 16), 0) * In * 4);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    raw[k][j >> 2][j & 3] = __builtin_amdgcn_raw_buffer_load_b32(rows, (int)((unsigned)col * 4u + (kp * 8 + j) * 4u * In), 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const f32x3_u32x4(&v)[2] = raw[k];
+                const Parts4 x = split_parts(v[0]), y = split_parts(v[1]);
+#pragma unroll
+                for (int e = 0; e < 3; ++e) af[k][e] = __builtin_bit_cast(bf16x8, f32x3_u32x4{x.p[e][0], x.p[e][1], y.p[e][0], y.p[e][1]});
+            }
+        }
+        // (inputs past the end: beyond every buffer below, with any row added)
+        const unsigned at = (col < In ? (unsigned)col * 4u : 0x80000000u) + (unsigned)kp * 16u * In;
+        // A step multiplies into one set of accumulators while the other set, the step before, is added up and stored between
+        // its MFMAs: the waves of a workgroup walk in step, and would leave the matrix unit idle together.
+        const int last = min(end, t + steps - s);
+        auto store = [&](__amdgpu_buffer_rsrc_t out, const f32x16 &hi, const f32x16 &lo, int e) __attribute__((always_inline)) {
+            // (nt: streamed out, 411 MB for the first dense layer)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(join_parts(hi[e], lo[e])), out, (int)(at + ((e >> 2) * 8 + (e & 3)) * 4u * In), 0, 2);
+        };
+        auto rows_of = [&](int step) __attribute__((always_inline)) { return buffer_of(dw + (size_t)step * 32 * In, min(32, Out - step * 32) * In * 4); };
+        auto out = buffer_of(dw, 0);   // of the step before (none: the stores are dropped)
+        auto step = [&](f32x16 &hi, f32x16 &lo, const f32x16 &hi0, const f32x16 &lo0, auto odd) __attribute__((always_inline)) {
+            constexpr int P = decltype(odd)::value * NB;   // (fragments alternate between two sets of registers, also across steps)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) hi[e] = lo[e] = 0.f;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (k == NB / 2) {
+                    // younger than the next step's copies, three steps old, are the 16 stores of each of the last two steps
+                    if (t <= begin + 2) dz.template wait<0>();
+                    else dz.template wait<32>();
+                    if (t + 3 < end) dz.copy(next(next(next(s))), t + 3 - begin);
+                }
+                if (k + 1 < NB) read(t, k + 1, df[(k + 1 + P) & 1]);
+                else read(t + 1, 0, df[(NB + P) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                auto term = [&](f32x16 &acc, int de, int ae, int m) __attribute__((always_inline)) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(df[(k + P) & 1][de], af[k][ae], acc, 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (e * (6 * NB) / 16 == k * 6 + m) {
+                            store(out, hi0, lo0, e);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                };
+                term(lo, 0, 1, 0); term(hi, 0, 0, 1); term(lo, 1, 0, 2); term(lo, 1, 1, 3); term(lo, 0, 2, 4); term(lo, 2, 0, 5);
+            }
+            out = rows_of(s);
+            s = next(s);
+            ++t;
+        };
+        f32x16 hi[2], lo[2];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) hi[1][e] = lo[1][e] = 0.f;
+        read(t, 0, df[0]);
+        while (true) {
+            step(hi[0], lo[0], hi[1], lo[1], std::integral_constant<int, 0>());
+            if (t == last) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) store(out, hi[0], lo[0], e);
+                break;
+            }
+            step(hi[1], lo[1], hi[0], lo[0], std::integral_constant<int, 1>());
+            if (t == last) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) store(out, hi[1], lo[1], e);
+                break;
+            }
+        }
+        ++tile;
+    }
+}
+
+// da = dz W.  Eight waves, one workgroup per CU; 16 NB batch rows x 256 inputs x a range of outputs (the contraction index), 32 at
+// a time; bound by the MFMAs (six per product), splitting the weights and streaming them.  A weight is used by one wave only:
+// lane 16 g + q loads outputs 8 g .. 8 g + 7 of inputs 2 q and 2 q + 1 of the wave's 32 (128 bytes of four rows per load) straight to
+// its register, a step ahead, and splits them between the MFMAs of the step before; dz comes in parts through LDS.  The weights are
+// the first operand, so that a lane holds eight neighbouring inputs of a batch row.  25088 -> 4096, 100 rows: 128 us (158 with weights and dz
+// split on their way through LDS); 121 with all weights in L2, 117 without splitting.
+template <int NB, bool VEC>   // VEC: In is even
+__global__ __launch_bounds__(512, 2) void fc_da_parts_kernel(FcDaArgs p, const char *__restrict__ rows)
+{
+    typedef float f32x4m __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) char lds[];
+    const int lane = threadIdx.x & 63, q = lane & 15, g = lane >> 4, b = blockIdx.x;
+    const int ti = b % p.tiles_i, split = b / p.tiles_i;
+    const int o_begin = split * p.o_per_split, o_end = min(o_begin + p.o_per_split, p.Out);
+    const int begin = o_begin / 32, end = (o_end + 31) / 32;
+    const DzSteps<NB> dz(rows, lds);
+    const int col = ti * 256 + dz.wv * 32 + 2 * q;
+
+    f32x4m hi[NB][2], lo[NB][2];
+#pragma unroll
+    for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) hi[x][y] = lo[x][y] = f32x4m{0.f, 0.f, 0.f, 0.f};
+    dz.copy(begin, 0);
+    if (begin + 1 < end) dz.copy(begin + 1, 1);
+    if (begin + 2 < end) dz.copy(begin + 2, 2);
+    // Weights: unit u holds rows 2 u, 2 u + 1 of the lane's eight.  Rows past the range are beyond the buffer, zeros (and no traffic);
+    // columns past the end read some other weight or zero and are never stored.
+    const unsigned at = (unsigned)g * 32u * p.In + (unsigned)col * 4u;
+    auto weights = [&](int step) __attribute__((always_inline)) {
+        const int o0 = min(step, end) * 32;
+        return buffer_of(p.w + (size_t)o0 * p.In, max(min(32, o_end - o0), 0) * p.In * 4);
+    };
+    unsigned raw[4][4];   // [unit][2 * input + row]
+    auto request = [&](__amdgpu_buffer_rsrc_t w, int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int off = (int)(at + (2 * u + k) * 4u * p.In);
+            if constexpr (VEC) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(w, off, 0, 2);
+                raw[u][k] = v[0];
+                raw[u][2 + k] = v[1];
+            } else {
+                raw[u][k] = __builtin_amdgcn_raw_buffer_load_b32(w, off, 0, 2);
+                raw[u][2 + k] = __builtin_amdgcn_raw_buffer_load_b32(w, off + 4, 0, 2);
+            }
+        }
+    };
+    struct Frag { f32x3_u32x4 v[3][2]; };   // [part][input of the pair]
+    auto split_unit = [&](Frag &f, int u) __attribute__((always_inline)) {
+        const Parts4 s = split_parts(f32x3_u32x4{raw[u][0], raw[u][1], raw[u][2], raw[u][3]});
+#pragma unroll
+        for (int e = 0; e < 3; ++e) { f.v[e][0][u] = s.p[e][0]; f.v[e][1][u] = s.p[e][1]; }
+    };
+    Frag w[2];
+    {
+        const auto first = weights(begin), second = weights(begin + 1);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) request(first, u);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { split_unit(w[0], u); request(second, u); }
+    }
+    bf16x8 d[2][3];
+    auto read = [&](int step, int x, bf16x8(&to)[3]) __attribute__((always_inline)) {
+        const char *const plane = lds + ((step - begin) & (DzSteps<NB>::BUFFERS - 1)) * DzSteps<NB>::BYTES + x * 3072 + lane * 16;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) to[e] = *reinterpret_cast<const bf16x8 *>(plane + e * 1024);
+    };
+    int s = begin;
+    auto step = [&](const Frag &w, Frag &n, auto odd) __attribute__((always_inline)) {
+        constexpr int P = decltype(odd)::value * NB;   // (fragments of dz alternate between two sets of registers, also across steps)
+        const auto ahead = weights(s + 2);
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (x == NB / 2) {
+                // (younger than the next step's copies, three steps old, are the eight weight loads of each of the last two steps)
+                if (s <= begin + 2) dz.template wait<0>();
+                else dz.template wait<16>();
+                if (s + 3 < end) dz.copy(s + 3, s + 3 - begin);
+            }
+            if (x + 1 < NB) read(s, x + 1, d[(x + 1 + P) & 1]);
+            else read(s + 1, 0, d[(NB + P) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            auto terms = [&](f32x4m(&acc)[2], int we, int de) __attribute__((always_inline)) {
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+                    acc[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w.v[we][y]), d[(x + P) & 1][de], acc[y], 0, 0, 0);
+            };
+            terms(hi[x], 0, 0); terms(lo[x], 0, 1); terms(lo[x], 1, 0); terms(lo[x], 1, 1); terms(lo[x], 0, 2); terms(lo[x], 2, 0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (u * NB / 4 == x) { split_unit(n, u); request(ahead, u); }
+        }
+        ++s;
+    };
+    dz.template wait<0>();
+    read(begin, 0, d[0]);
+    while (true) {
+        step(w[0], w[1], std::integral_constant<int, 0>());
+        if (s >= end) break;
+        step(w[1], w[0], std::integral_constant<int, 1>());
+        if (s >= end) break;
+    }
+    // register e of lane 16 g + q, pair member y: input 8 g + 2 e + y of batch row q
+    const int ic = ti * 256 + dz.wv * 32 + 8 * g;
+#pragma unroll
+    for (int x = 0; x < NB; ++x) {
+        const int row = x * 16 + q;
+        if (row >= p.N) continue;
+        float *dst = p.part + ((size_t)split * p.N + row) * p.In + ic;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = join_parts(hi[x][e & 1][e >> 1], lo[x][e & 1][e >> 1]);
+        if ((p.In & 3) == 0) {
+            if (ic < p.In) store4(dst, v[0], v[1], v[2], v[3]);
+            if (ic + 4 < p.In) store4(dst + 4, v[4], v[5], v[6], v[7]);
+        } else
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (ic + e < p.In) dst[e] = v[e];
+    }
+}
+
 // da = (sum over splits) [* (a > 0)], V values per thread (V divides n)
 template <int V>
 __global__ void fc_da_finish_kernel(const float *__restrict__ part, const float *__restrict__ a, float *__restrict__ da, size_t n,
@@ -941,16 +1264,26 @@ static void fc_da_plan(int N, int In, int Out, FcDaArgs &a, bool launch)
 }
 static int fc_da_splits(const FcDaArgs &a) { return (a.Out + a.o_per_split - 1) / a.o_per_split; }
 
+// dz in parts ahead of both products: up to 128 rows (one row tile, since the input's batch rows fill the registers; with two, 0.96 to
+// 1.10 of the time of 18 shapes), and 32-bit offsets inside 32 rows of W and dW.  41 to 128 rows: 0.88 of the time of the kernels that split
+// dz themselves over 242 shapes, 1.05 at most (25088 -> 4096, batch 100, 355 -> 255 us; 64 rows, 1104 -> 3335 34.6 / 35.8).  25 to 40
+// rows from 1024 outputs on: 0.69 to 1.01 of the fp32 kernels' time over 24 shapes (38 rows, 19488 -> 1509 94 -> 65 us; 32 rows, 25088 ->
+// 4096 173 / 174); with fewer outputs, where a workgroup takes its inputs apart for a few steps only, up to 1.20; with fewer
+// rows, where the weights and dW stream, up to 1.24.
+static bool fc_bwd_staged(int N, int In, int Out) { return (N > 40 || (N > 24 && Out >= 1024)) && N <= 128 && In < (1 << 24) - 256; }
+// bytes of one of the two copies of dz in parts
+static size_t fc_dz_parts_bytes(const FcDaArgs &a) { return (size_t)((a.Out + 31) / 32) * a.nb * 3072; }
+
 size_t fc_bwd_workspace(int N, int In, int Out)
 {
     FcDaArgs a;
     fc_da_plan(N, In, Out, a, false);
-    return round_up((size_t)fc_da_splits(a) * N * In * 4, 256);
+    return round_up((size_t)fc_da_splits(a) * N * In * 4, 256) + (fc_bwd_staged(N, In, Out) ? 2 * fc_dz_parts_bytes(a) : 0);
 }
 
 // The launch of the kernel on the bf16 matrix unit, one workgroup per CU: of the splits that the workspace holds it takes
 // the one with the least of rounds over 256 workgroups and partial sums, both in units of streaming the weights.
-static void fc_da_f32x3_plan(int N, int In, int Out, FcDaArgs &a)
+static void fc_da_parts_plan(int N, int In, int Out, FcDaArgs &a)
 {
     fc_da_plan(N, In, Out, a, false);
     const int most = fc_da_splits(a), tiles = a.tiles_i * a.tiles_m;
@@ -976,6 +1309,24 @@ static int launch_fc_da_f32x3(const FcDaArgs &p, int splits, hipStream_t s)
     return launch_status();
 }
 
+// dz in parts, both products (da: its partial sums), one row tile of two to eight blocks of sixteen.
+template <int NB>
+static int launch_fc_bwd_parts(const FcDaArgs &p, int splits, const float *a, float *dw, float *db, hipStream_t s)
+{
+    if constexpr (NB > 2)
+        if (p.nb != NB) return launch_fc_bwd_parts<NB - 1>(p, splits, a, dw, db, s);
+    const int steps = (p.Out + 31) / 32, units = p.tiles_i * steps;
+    char *const rows = reinterpret_cast<char *>(p.part) + round_up((size_t)splits * p.N * p.In * 4, 256), *const cols = rows + fc_dz_parts_bytes(p);
+    hipLaunchKernelGGL(fc_dz_parts_kernel, dim3((unsigned)steps), dim3(512), 0, s, p.dz, rows, cols, db, p.N, p.Out, NB);
+    const size_t lds = DzSteps<NB>::BUFFERS * DzSteps<NB>::BYTES;
+    if (!raise_lds_limit(reinterpret_cast<const void *>(fc_dw_parts_kernel<NB>))) return VGG_ERR_LAUNCH;
+    hipLaunchKernelGGL(fc_dw_parts_kernel<NB>, dim3((unsigned)min(units, 256)), dim3(512), lds, s, a, cols, dw, p.N, p.In, p.Out, units);
+    auto kern = p.In % 2 == 0 ? fc_da_parts_kernel<NB, true> : fc_da_parts_kernel<NB, false>;
+    if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return VGG_ERR_LAUNCH;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_i * splits)), dim3(512), lds, s, p, rows);
+    return launch_status();
+}
+
 template <int NB>
 static void launch_fc_da(const FcDaArgs &p, int splits, hipStream_t s)
 {
@@ -992,20 +1343,21 @@ int fc_backward(int N, int In, int Out, const float *a, const float *w, const fl
                 int relu_mask, void *ws, hipStream_t s)
 {
     const dim3 grid((unsigned)(((In + 127) / 128) * ((Out + 127) / 128)));
-    // From about 50 rows on the bf16 matrix unit, both products: 25088 -> 4096, batch 100 395 -> 352 us, 4096 -> 4096 87 -> 71, all of
-    // 80 sizes 0.82 to 0.92 on average (1.04 at most, 100 outputs); 32 rows 0.99, 16 rows 1.07, where the weights and dW stream.
-    const bool parts = N > 40;
-    auto dw_kernel = parts ? (In % 4 == 0 ? fc_dw_f32x3_kernel<true> : fc_dw_f32x3_kernel<false>) : (In % 4 == 0 ? fc_dw_kernel<true> : fc_dw_kernel<false>);
-    hipLaunchKernelGGL(dw_kernel, grid, dim3(256), 0, s, a, dz, dw, N, In, Out);
-    if (db) hipLaunchKernelGGL(fc_db_kernel, dim3((Out + 63) / 64), dim3(256), 0, s, dz, db, N, Out);
+    // (the parts of dz lie in the workspace, which is there where da is asked for)
+    const bool staged = da && fc_bwd_staged(N, In, Out), parts = staged || N > 40;
+    if (!staged) {
+        auto dw_kernel = parts ? (In % 4 == 0 ? fc_dw_f32x3_kernel<true> : fc_dw_f32x3_kernel<false>) : (In % 4 == 0 ? fc_dw_kernel<true> : fc_dw_kernel<false>);
+        hipLaunchKernelGGL(dw_kernel, grid, dim3(256), 0, s, a, dz, dw, N, In, Out);
+        if (db) hipLaunchKernelGGL(fc_db_kernel, dim3((Out + 63) / 64), dim3(256), 0, s, dz, db, N, Out);
+    }
     if (da) {
         FcDaArgs p;
-        if (parts) fc_da_f32x3_plan(N, In, Out, p);
+        if (parts) fc_da_parts_plan(N, In, Out, p);
         else fc_da_plan(N, In, Out, p, true);
         const int splits = fc_da_splits(p);
         p.dz = dz; p.w = w; p.part = static_cast<float *>(ws);
         if (parts) {
-            const int rc = launch_fc_da_f32x3<8>(p, splits, s);
+            const int rc = staged ? launch_fc_bwd_parts<8>(p, splits, a, dw, db, s) : launch_fc_da_f32x3<8>(p, splits, s);
             if (rc) return rc;
         } else launch_fc_da<3>(p, splits, s);   // (up to 40 rows: three blocks of sixteen)
         const size_t n = (size_t)N * In;

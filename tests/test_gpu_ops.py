@@ -1062,6 +1062,27 @@ def test_fc_backward_fp32_tile_edges(N, In, Out):
     assert (dw[Out * In:] == -7.0).all() and (da[N * In:] == -7.0).all()
 
 
+@pytest.mark.parametrize("N,In,Out", [(25, 258, 1024), (24, 258, 1024), (32, 255, 1025), (41, 4097, 33), (57, 5002, 2602), (100, 2052, 5000), (128, 1026, 2600),
+                                      (128, 6400, 1030), (129, 1026, 200)])
+def test_fc_backward_fp32_staged_gradient(N, In, Out):
+    """fp32 backward with dz taken apart ahead of the products: the lines to the other kernels (24 and 25 rows at 1024 outputs, 128
+    and 129 rows), workgroups of dW with one and with several (input tile, 32 outputs) units and with more than the four LDS buffers hold,
+    of two input tiles, and ranges of outputs that end inside 32; every element against float64.  Sums of at most 5000 products of
+    N(0,1) values in fp32 are within 1e-6 of the largest, the tolerance is 1e-5.  Guards behind the results, the workspace NaN before."""
+    g = torch.Generator(device="cuda").manual_seed(N * In + Out)
+    a, w, dz = (torch.randn(s, generator=g, device="cuda") for s in ((N, In), (Out, In), (N, Out)))
+    dw, da = torch.full((Out * In + 256,), -7.0, device="cuda"), torch.full((N * In + 256,), -7.0, device="cuda")
+    db = torch.empty((Out,), device="cuda")
+    ws = ws_bytes(B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out))
+    ws.fill_(255)
+    B.vgg_fc_bwd(B.F32, N, In, Out, a, w, dz, dw, db, da, 1, ws)
+    torch.cuda.synchronize()
+    a, w, dz = a.double(), w.double(), dz.double()
+    for got, want in ((dw[:Out * In].view(Out, In), dz.t().contiguous() @ a), (db, dz.sum(0)), (da[:N * In].view(N, In), dz @ w * (a > 0))):
+        assert ((got - want).abs().max() / want.abs().max()).item() <= 1e-5
+    assert (dw[Out * In:] == -7.0).all() and (da[N * In:] == -7.0).all()
+
+
 @pytest.mark.parametrize("N,In,Out", [(1, 8, 1), (32, 136, 65), (33, 264, 129), (64, 128, 64), (65, 120, 63), (96, 1032, 200), (97, 40, 33),
                                       (128, 256, 130), (129, 136, 257)])
 def test_fc_backward_bf16_row_blocks(N, In, Out):
