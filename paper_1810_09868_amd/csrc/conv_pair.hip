@@ -5,25 +5,27 @@
 // (first two "convolution" rows and the first "reduce-window" of the appendix table's forward column; the
 // paper's compiler fuses operations so that intermediates stay on chip, section on XLA).  At batch 100 the
 // 64-channel 224 x 224 activation between the two layers is 642 MB: written once and read once it costs more
-// HBM time than either layer's arithmetic.  Here it never leaves the CU.  A workgroup owns a 16 x 32 pixel
+// HBM time than either layer's arithmetic.  Here it never leaves the CU.  A workgroup owns an 8 x 32 pixel
 // patch of the second layer's output:
-//   1. the 3 x 20 x 36 image halo of the patch goes to LDS, rounded to bf16, one 8-byte record (three
+//   1. the 3 x 12 x 36 image halo of the patch goes to LDS, rounded to bf16, one 8-byte record (three
 //      channels and a zero) per pixel (the next patch's is already in registers);
-//   2. the first layer is evaluated on the 18 x 34 pixel halo the second layer needs: contraction index
+//   2. the first layer is evaluated on the 10 x 34 pixel halo the second layer needs: contraction index
 //      k = 4 tap + ci, so that a lane's eight indices of an MFMA step are two whole records, and the bias
 //      rides on a tenth "tap" whose record is (1, 1, 0, 0) (weights there: the bias rounded to bf16 and
 //      the remainder), three steps of v_mfma_f32_32x32x16_bf16.  The result goes to LDS as two
 //      32-channel chunks of 80-byte rows, zero where the halo pixel lies outside the image (the second
 //      layer's zero padding).  The products are those of the stand-alone first-layer kernel; only the
 //      order in which the matrix unit adds the 27 of them differs;
-//   3. the second layer runs on that halo like the weights-in-registers implicit GEMM: a wave owns four patch
-//      rows (128 pixels) x 64 channels, its weight fragments come straight from global memory (L2) five
+//   3. the second layer runs on that halo like the weights-in-registers implicit GEMM: a wave owns two patch
+//      rows (64 pixels) x 64 channels, its weight fragments come straight from global memory (L2) five
 //      steps ahead, the sums run over (chunk, tap, k-group) in that kernel's order (same results);
 //   4. the 2x2 maximum is taken on the fp32 sums in registers (rows of a window are two accumulator blocks
 //      of the same lane, columns are neighbouring lanes), then ReLU and rounding (both monotonic, so the
 //      result is the maximum of the rounded values); pooled and/or un-pooled tensor leave through a
 //      per-wave LDS block as full 128-byte pixel rows.
-// One workgroup per CU (107 KB of LDS), persistent over the patches of its XCD's share.
+// Two workgroups per CU (58 KB of LDS each), persistent over the patches of their XCD's share.  Bound by the chain of phases between
+// barriers, which the other workgroup's matrix work fills: patches of 16 x 32 with one workgroup per CU evaluate 7 % fewer
+// first-layer pixels, and took 347 us at batch 100 (224 x 224, pooled tensor only) against 325, 20.6 against 8.6 for one image.
 // Needs H % 16 == 0 and W % 32 == 0; no pooling positions (the training step keeps the separate kernels,
 // whose outputs its backward pass reads).
 #include "common.h"
@@ -34,22 +36,21 @@ namespace vgg {
 namespace {
 
 constexpr int kC = 64;                               // channels of both layers
-constexpr int kTH = 16, kTW = 32;                    // output patch
-constexpr int kYR = kTH + 2, kYC = kTW + 2;          // first-layer halo: 18 x 34 pixels
-constexpr int kYRows = kYR * kYC;                    // 612
-constexpr int kYBlocks = (kYRows + 31) / 32;         // 20 blocks of 32 pixels
-static_assert(kYBlocks % 4 == 0, "every wave takes the same number of blocks");
-constexpr int kXR = kTH + 4, kXC = kTW + 4;          // image halo: 20 x 36
-constexpr int kXPix = kXR * kXC;                     // 720 pixel records of 8 bytes
+constexpr int NR = 2;                                // patch rows per wave
+constexpr int kTH = 4 * NR, kTW = 32;                // output patch
+constexpr int kYR = kTH + 2, kYC = kTW + 2;          // first-layer halo: 10 x 34 pixels
+constexpr int kYRows = kYR * kYC;                    // 340
+constexpr int kYBlocks = (kYRows + 127) / 128;       // blocks of 32 pixels per wave
+constexpr int kXR = kTH + 4, kXC = kTW + 4;          // image halo: 12 x 36
+constexpr int kXPix = kXR * kXC;                     // 432 pixel records of 8 bytes
 constexpr int kXOnes = kXPix, kXZero = kXPix + 1;    // two constant records: (1, 1, 0, 0) and zeros
 constexpr int kXBytes = (kXPix + 2) * 8;
-constexpr int kXPerThread = (kXPix + 255) / 256;     // 3
+constexpr int kXPerThread = (kXPix + 255) / 256;     // 2
 constexpr int kRowB = 80;                            // LDS bytes per halo row of a 32-channel chunk (64 + 16 pad)
-constexpr int kYBytes = 2 * kYRows * kRowB;          // 97920
+constexpr int kYBytes = 2 * kYRows * kRowB;          // 54400
 constexpr int kStageRow = 144;                       // epilogue staging: 64 channels + 16 bytes of padding
 constexpr int kSteps = 36;                           // (chunk, tap, k-group) steps of the second layer
-constexpr int kRing = 12, kAhead = kRing - 1;        // weight fragments in registers, prefetch distance (with one wave
-                                                     // per SIMD a step is short: eleven of them cover the L2 latency)
+constexpr int kRing = 6, kAhead = kRing - 1;         // weight fragments in registers, prefetch distance
 static_assert(kSteps % kRing == 0, "ring positions are static");
 static_assert(4 * 64 * kStageRow <= kYBytes, "staging blocks live in the halo buffer");
 
@@ -77,7 +78,7 @@ __device__ __forceinline__ void pair_for_each(F &&f, std::integer_sequence<int, 
     (f(std::integral_constant<int, S>{}), ...);
 }
 
-__global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
+__global__ __launch_bounds__(256, 2) void conv_pair_kernel(PairArgs p)
 {
     typedef bf16_t T;
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -90,21 +91,30 @@ __global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
     // ---- first layer's filter bank in registers: contraction index k = 4 tap + ci; tap 9 carries the bias
-    auto w1val = [&](int k, int co) -> float {
-        const int t = k >> 2, ci = k & 3;
-        if (t < 9) return ci < 3 ? Elem<T>::load(w1p + packed_w_index<T>(t, co, ci, kC, p.CinP1)) : 0.f;
-        const float b = p.b1 ? p.b1[co] : 0.f;
-        if (k == 36) return bf16_to_f32(f32_to_bf16(b));
-        if (k == 37) return b - bf16_to_f32(f32_to_bf16(b));
-        return 0.f;
-    };
+    // (loads from clamped positions and selects afterwards: loads under conditions would be waited for one by one)
     bf16x8 w1f[3][2];
 #pragma unroll
-    for (int s = 0; s < 3; ++s)
+    for (int j = 0; j < 2; ++j) {
+        const int co = j * 32 + r;
+        const float b = p.b1 ? p.b1[co] : 0.f;
+        const bf16_t b_hi = f32_to_bf16(b), b_lo = f32_to_bf16(b - bf16_to_f32(b_hi));
+        bf16_t raw[3][8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t)
+        for (int s = 0; s < 3; ++s)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) w1f[s][j][t] = (__bf16)w1val(s * 16 + khalf * 8 + t, j * 32 + r);
+            for (int t = 0; t < 8; ++t) {
+                const int tap = s * 4 + khalf * 2 + (t >> 2);
+                raw[s][t] = w1p[packed_w_index<T>(min(tap, 8), co, min(t & 3, 2), kC, p.CinP1)];
+            }
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int tap = s * 4 + khalf * 2 + (t >> 2), ci = t & 3;
+                const bf16_t v = tap < 9 ? (ci < 3 ? raw[s][t] : (bf16_t)0) : tap > 9 || ci > 1 ? (bf16_t)0 : ci ? b_lo : b_hi;
+                w1f[s][j][t] = __builtin_bit_cast(__bf16, v);
+            }
+    }
     if (tid == 0) {
         *reinterpret_cast<u32x2 *>(xs + kXOnes * 8) = u32x2{0x3F803F80u, 0u};
         *reinterpret_cast<u32x2 *>(xs + kXZero * 8) = u32x2{0u, 0u};
@@ -159,14 +169,15 @@ __global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
     // (without the memory fence of __syncthreads(), which would wait for the previous patch's output stores)
     auto lds_barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
-    // ---- second layer: this wave's four patch rows, all 64 channels
+    // ---- second layer: this wave's patch rows, all 64 channels
     // weight fragment (tap t, 16-channel block kb, output channels c..c+31): 1 KB at ((4 t + kb) 64 + c) 32 bytes
-    unsigned voff[2];
+    const auto w2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p.w2), 0, 9 * kC * kC * 2, 0x00020000);
+    int voff[2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) voff[j] = (unsigned)(j * 32 + r) * 32u + khalf * 16;
-    int arow[4];   // byte offset (inside a chunk) of tap (0,0) of this lane's pixel in each of the four rows
+    for (int j = 0; j < 2; ++j) voff[j] = (j * 32 + r) * 32 + khalf * 16;
+    int arow[NR];   // byte offset (inside a chunk) of tap (0,0) of this lane's pixel in each of the wave's rows
 #pragma unroll
-    for (int i = 0; i < 4; ++i) arow[i] = ((wv * 4 + i) * kYC + r) * kRowB + khalf * 16;
+    for (int i = 0; i < NR; ++i) arow[i] = ((wv * NR + i) * kYC + r) * kRowB + khalf * 16;
 
     // Workgroup b runs on XCD b % 8: each XCD takes a contiguous eighth of the patches (neighbouring patches
     // share image rows and cache lines, which then come from that XCD's L2).
@@ -186,10 +197,10 @@ __global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
         lds_barrier();
         if (tile + stride < last) load_halo(tile + stride, hv);   // lands during the arithmetic below
 
-        // ---- first layer on the 18 x 34 halo: wave w takes pixel blocks w, w + 4, ...  (The last block has
-        // only four pixels: its other lanes repeat the last pixel and store the same bytes to the same place.)
+        // ---- first layer on the 10 x 34 halo: wave w takes pixel blocks w, w + 4, ...  (Lanes past
+        // the last pixel repeat it and store the same bytes to the same place.)
 #pragma unroll
-        for (int bi = 0; bi < kYBlocks / 4; ++bi) {
+        for (int bi = 0; bi < kYBlocks; ++bi) {
             const int blk = wv + 4 * bi;
             const int q = min(blk * 32 + r, kYRows - 1);
             const int hy = q / kYC, hx = q - hy * kYC;
@@ -238,7 +249,7 @@ __global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
         lds_barrier();    // the whole halo of the first layer's output is in LDS
 
         // ---- second layer
-        f32x16 acc[4][2];
+        f32x16 acc[NR][2];
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -246,23 +257,24 @@ __global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
                 f32x4 b = {0.f, 0.f, 0.f, 0.f};
                 if (p.b2) b = *reinterpret_cast<const f32x4 *>(p.b2 + j * 32 + a * 8 + khalf * 4);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < NR; ++i)
 #pragma unroll
                     for (int k = 0; k < 4; ++k) acc[i][j][a * 4 + k] = b[k];
             }
         u32x4 bq[kRing][2];
-        auto w2_fragment = [&](int P) __attribute__((always_inline)) {   // step P = 18 chunk + 2 tap + k-group
+        auto w2_fragment = [&](int P, int j) __attribute__((always_inline)) {   // step P = 18 chunk + 2 tap + k-group
             const int c = P / 18, s = P % 18, t = s / 2, g = s % 2;
-            return p.w2 + (size_t)((t * 4 + 2 * c + g) * kC) * 32;
+            // (a scalar offset: 64-bit addresses of all steps, kept in vector registers over the patches, are more than there are)
+            return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(w2, voff[j], ((t * 4 + 2 * c + g) * kC) * 32, 0));
         };
         pair_for_each([&](auto ic) {
             constexpr int P = decltype(ic)::value;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) bq[P % kRing][j] = *reinterpret_cast<const u32x4 *>(w2_fragment(P) + voff[j]);
+            for (int j = 0; j < 2; ++j) bq[P % kRing][j] = w2_fragment(P, j);
         }, std::make_integer_sequence<int, kAhead>{});
-        u32x4 af[2][4];
+        u32x4 af[2][NR];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) af[0][i] = *reinterpret_cast<const u32x4 *>(ys + arow[i]);
+        for (int i = 0; i < NR; ++i) af[0][i] = *reinterpret_cast<const u32x4 *>(ys + arow[i]);
         pair_for_each([&](auto ic) {
             constexpr int P = decltype(ic)::value;
             constexpr int PN = P + 1;                    // step whose halo fragments are read during this one
@@ -271,7 +283,7 @@ __global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
             const u32x4 b0 = bq[P % kRing][0], b1 = bq[P % kRing][1];
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < NR; ++i) {
                 const bf16x8 a = __builtin_bit_cast(bf16x8, af[P & 1][i]);
                 acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b0), a, acc[i][0], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
@@ -280,7 +292,7 @@ __global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
                 acc[i][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b1), a, acc[i][1], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (i < 2 && P + kAhead < kSteps)
-                    bq[(P + kAhead) % kRing][i] = *reinterpret_cast<const u32x4 *>(w2_fragment(P + kAhead) + voff[i]);
+                    bq[(P + kAhead) % kRing][i] = w2_fragment(P + kAhead, i);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }, std::make_integer_sequence<int, kSteps>{});
@@ -292,8 +304,8 @@ __global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
         T *pout = reinterpret_cast<T *>(p.pool);
         const int seg = lane & 7, rowq = lane >> 3;
 #pragma unroll
-        for (int pair = 0; pair < 2; ++pair) {
-            const int hrow = h0 + wv * 4 + pair * 2;      // first of the two image rows
+        for (int pair = 0; pair < NR / 2; ++pair) {
+            const int hrow = h0 + wv * NR + pair * 2;      // first of the two image rows
             if (yout) {
 #pragma unroll
                 for (int ii = 0; ii < 2; ++ii)
@@ -348,7 +360,7 @@ __global__ __launch_bounds__(256, 1) void conv_pair_kernel(PairArgs p)
 
 bool conv_first_pair_ok(int dtype, int H, int W)
 {
-    return dtype == VGG_BF16 && H % kTH == 0 && W % kTW == 0;
+    return dtype == VGG_BF16 && H % 16 == 0 && W % kTW == 0;
 }
 
 // x NCHW fp32 [N][3][H][W]; w1 packed [9][64][CinP1], w2 packed [9][64][64] (bf16, the layout the convolutions
@@ -367,7 +379,8 @@ int conv_first_pair(int N, int H, int W, int CinP1, const float *x, const void *
     a.dTilesW = make_fast_div(a.tiles_w); a.dTilesHW = make_fast_div(a.tiles_hw);
     const size_t lds = kYBytes + kXBytes;
     if (!raise_lds_limit(reinterpret_cast<const void *>(conv_pair_kernel))) return VGG_ERR_LAUNCH;
-    const dim3 grid((unsigned)(a.ntiles < 256 ? a.ntiles : 256));
+    // (a multiple of eight: every XCD has a workgroup for each patch of its eighth)
+    const dim3 grid((unsigned)(a.ntiles < 512 ? (a.ntiles + 7) / 8 * 8 : 512));
     hipLaunchKernelGGL(conv_pair_kernel, grid, dim3(256), lds, stream, a);
     return launch_status();
 }
