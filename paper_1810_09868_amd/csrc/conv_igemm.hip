@@ -808,7 +808,7 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
 // bf16, launches with fewer tiles than the chip has SIMDs to fill (small batches): a workgroup of G waves owns
 // 64 pixels x 16 NJ channels, and its waves share the contraction: p.ksplit ranges of p.kchunks channel chunks, taken
 // by the waves in turn (wave w: w and w + G), each with all nine taps.  What bounds such a launch is not the matrix pipe but
-// the chain launch -> first loads -> multiply -> combine, so the kernel has one of each: a wave copies its own chunk's halo
+// the chain launch -> first loads -> multiply -> combine and the instructions along it, so the kernel has one of each: a wave copies its own chunk's halo
 // into its own LDS region and requests all nine taps' weights at once (9 NJ fragments in registers, plain loads; a tap's
 // registers are refilled for the wave's next chunk as soon as its MFMAs are issued), no barrier until the end,
 // and the waves' sums meet in LDS instead of in a partial-sum buffer that a second launch has to read.
@@ -826,7 +826,7 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
     typedef bf16_t T;
     constexpr int NI = 4, BN = NJ * 16, KC = 32, TAPS = 9;
     constexpr int RP = BN + 4;                    // floats per row of the combine buffer
-    constexpr int MAXPX = kSmallHaloRows / 64;    // halo rows per lane
+    static_assert(kSmallHaloRows <= G * 64, "a thread per halo row");
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane & 15, g = lane >> 4;
@@ -862,40 +862,60 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
 #pragma unroll
     for (int t = 0; t < TAPS; ++t) load_w(min(c_first, nchunks - 1), t);
 
-    // The pixel behind halo row `lane + 64 j` is found once, by one lane; a copy (16 rows x 64 bytes) fetches
-    // the row number of its lanes from there.
-    int px[MAXPX];
-#pragma unroll
-    for (int j = 0; j < MAXPX; ++j) {
-        const int row = lane + 64 * j;
-        px[j] = row < p.g.S ? halo_pixel(p.g, org, row) : -1;
+    // What bounds the front of such a launch is the instructions issued before the first multiplication (2.8 of 9 us at one
+    // image's 14x14 and 28x28 layers when every wave found its own pixels), so that is done once per workgroup: thread t finds the
+    // pixel behind halo row t, the last wave the halo rows of the tile's 64 pixels, and the table is shared through LDS.
+    int *const table = reinterpret_cast<int *>(smem + p.tableA);      // [rowsA] byte offsets into x, [64] halo rows of tap (0,0)
+    if (tid < p.rowsA) {
+        const int px = tid < p.g.S ? halo_pixel(p.g, org, tid) : -1;
+        table[tid] = px < 0 ? (int)0x80000000u : px * (int)xrow;      // (outside the image: beyond the buffer, which reads zeros)
     }
+    if (wv == G - 1) {
+        int m, h;
+        tile_row(p.g, org, lane, m, h);
+        table[p.rowsA + lane] = h;
+    }
+    // What a thread adds and stores after the multiplications: its four channels' bias and, without a pool, its pixels and mask.
+    constexpr int C4 = BN / 4, OUT = (kSmallPx * C4 + G * 64 - 1) / (G * 64);   // (channel quads of a tile row; of the tile per thread)
+    T *y = reinterpret_cast<T *>(p.y), *pool = reinterpret_cast<T *>(p.pool);
+    const int col = n0 + (tid % C4) * 4;
+    const f32x4v bias = *reinterpret_cast<const f32x4v *>(p.bias ? reinterpret_cast<const char *>(p.bias + min(col, p.Cout - 4))
+                                                                 : reinterpret_cast<const char *>(kZeroRow));
+    int pixel[OUT];
+    u32x2 mk[OUT];
+#pragma unroll
+    for (int k = 0; k < OUT; ++k) {
+        const int row = (k * G * 64 + tid) / C4;
+        pixel[k] = row < kSmallPx ? tile_pixel(p.g, org, row) : -1;   // (16-wide columns: more threads than quads)
+        mk[k] = *reinterpret_cast<const u32x2 *>(p.mask ? p.mask + ((size_t)max(pixel[k], 0) * p.Cout + min(col, p.Cout - 4)) * sizeof(T)
+                                                        : reinterpret_cast<const char *>(kZeroRow));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (not __syncthreads(), which would wait for the loads above)
+
     const int bufs = p.rowsA * kDataBytes;                            // bytes of a halo buffer (rowsA a multiple of 16)
     char *As = smem + wv * bufs;                                      // this wave's buffer
     const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)As);
+    // A copy moves 16 rows x 64 bytes; segment s of row q lies at s ^ ((q >> 1) & 3).
+    constexpr int COPIES = kSmallHaloRows / 16;
+    unsigned from[COPIES];
+#pragma unroll
+    for (int k = 0; k < COPIES; ++k)
+        if (k * 16 < p.rowsA) from[k] = (unsigned)table[k * 16 + (lane >> 2)] + (((lane & 3) ^ ((lane >> 3) & 3)) << 4);
+    int hrow[NI];   // halo row of tap (0,0) of this lane's pixels
+#pragma unroll
+    for (int i = 0; i < NI; ++i) hrow[i] = table[p.rowsA + i * 16 + q];
+    const u32x4 xbuf = {(unsigned)(uintptr_t)p.x, (unsigned)((uintptr_t)p.x >> 32), (unsigned)p.g.M * (unsigned)xrow, 0x00020000u};
     auto copy = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < 4 * MAXPX; ++k) {
+        for (int k = 0; k < COPIES; ++k) {
             if (k * 16 < p.rowsA) {
-                const int row = k * 16 + (lane >> 2);
-                const int pk = __shfl(px[k >> 2], row & 63, kWave);
-                const int seg = (lane & 3) ^ ((row >> 1) & 3);
-                const char *src = pk < 0 ? reinterpret_cast<const char *>(kZeroRow) : p.x + (size_t)pk * xrow + (size_t)c * kDataBytes;
-                src += seg * 16;
                 const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + k * 1024);
-                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "m0", "memory");
+                asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                             : : "s"(dst), "v"(from[k]), "s"(xbuf), "s"(c * kDataBytes) : "m0", "memory");
             }
         }
     };
     if (c_first < nchunks) copy(c_first);
-
-    int hrow[NI];   // halo row of tap (0,0) of this lane's pixels: lane l finds tile row l's
-    {
-        int m, h;
-        tile_row(p.g, org, lane, m, h);
-#pragma unroll
-        for (int i = 0; i < NI; ++i) hrow[i] = __shfl(h, i * 16 + q, kWave);
-    }
     f32x4v acc[NI][NJ];
 #pragma unroll
     for (int i = 0; i < NI; ++i)
@@ -961,51 +981,48 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
     } else if (wv < p.ksplit) park(acc, wv);
     __syncthreads();
     const float lo = p.relu ? 0.f : -__builtin_inff();
-    T *y = reinterpret_cast<T *>(p.y), *pool = reinterpret_cast<T *>(p.pool);
-    const T *mask = reinterpret_cast<const T *>(p.mask);
-    auto value = [&](int row, int c4, T(&out)[4]) __attribute__((always_inline)) {   // four channels of tile row `row`
-        const int col = n0 + c4 * 4;
-        f32x4v s = {0.f, 0.f, 0.f, 0.f};
-        if (p.bias) s = *reinterpret_cast<const f32x4v *>(p.bias + col);
-        for (int w = 0; w < p.ksplit; ++w) s += *reinterpret_cast<const f32x4v *>(red + (size_t)(w * kSmallPx + row) * RP + c4 * 4);
-        const int m = tile_pixel(p.g, org, row);
+    auto value = [&](int row, T(&out)[4]) __attribute__((always_inline)) {   // this thread's four channels of tile row `row`
+        f32x4v s = bias;
+        for (int w = 0; w < p.ksplit; ++w) s += *reinterpret_cast<const f32x4v *>(red + (size_t)(w * kSmallPx + row) * RP + (tid % C4) * 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) out[e] = f32_to_bf16(fmaxf(s[e], lo));
-        if (m >= 0 && mask) {
-            T mk[4];
-            __builtin_memcpy(mk, mask + (size_t)m * p.Cout + col, 8);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (!(bf16_to_f32(mk[e]) > 0.f)) out[e] = (T)0;
-        }
-        if (m >= 0 && y) __builtin_memcpy(y + (size_t)m * p.Cout + col, out, 8);
     };
-    constexpr int C4 = BN / 4;
+    if (col >= p.Cout) return;
     if (!pool) {
 #pragma unroll
-        for (int u0 = 0; u0 < kSmallPx * C4; u0 += G * 64) {
-            const int u = u0 + tid, row = u / C4, c4 = u % C4;
-            T out[4];
-            if (u < kSmallPx * C4 && n0 + c4 * 4 < p.Cout) value(row, c4, out);
+        for (int k = 0; k < OUT; ++k) {
+            if (pixel[k] < 0) continue;
+            T out[4], m[4];
+            value((k * G * 64 + tid) / C4, out);
+            __builtin_memcpy(m, &mk[k], 8);
+            if (p.mask) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (!(bf16_to_f32(m[e]) > 0.f)) out[e] = (T)0;
+            }
+            __builtin_memcpy(y + (size_t)pixel[k] * p.Cout + col, out, 8);
         }
         return;
     }
     // (patch tiles of 4 x 16 pixels: sixteen windows)
     for (int u = tid; u < kSmallPx / 4 * C4; u += G * 64) {
-        const int win = u / C4, c4 = u % C4, dy = win >> 3, dx = win & 7;
+        const int win = u / C4, dy = win >> 3, dx = win & 7;
         const int ph = (org.h0 >> 1) + dy, pw = (org.w0 >> 1) + dx;
-        if (n0 + c4 * 4 >= p.Cout || 2 * ph >= p.g.H || 2 * pw >= p.g.W) continue;
+        if (2 * ph >= p.g.H || 2 * pw >= p.g.W) continue;
         T best[4];
         unsigned char which[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             T v[4];
-            value((2 * dy + (k >> 1)) * kTileW + 2 * dx + (k & 1), c4, v);
+            const int row = (2 * dy + (k >> 1)) * kTileW + 2 * dx + (k & 1);
+            value(row, v);
+            const int m = tile_pixel(p.g, org, row);
+            if (m >= 0 && y) __builtin_memcpy(y + (size_t)m * p.Cout + col, v, 8);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (k == 0 || bf16_to_f32(v[e]) > bf16_to_f32(best[e])) { best[e] = v[e]; which[e] = (unsigned char)k; }
         }
-        const size_t at = (((size_t)org.n * (p.g.H >> 1) + ph) * (p.g.W >> 1) + pw) * p.Cout + n0 + c4 * 4;
+        const size_t at = (((size_t)org.n * (p.g.H >> 1) + ph) * (p.g.W >> 1) + pw) * p.Cout + col;
         __builtin_memcpy(pool + at, best, 8);
         if (p.argmax) __builtin_memcpy(p.argmax + at, which, 4);
     }
@@ -1016,22 +1033,22 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
 static size_t conv_small_lds(int G, int S, int ksplit)
 {
     const size_t halo = (size_t)G * round_up16(S) * kDataBytes, red = (size_t)ksplit * kSmallPx * (2 * 16 + 4) * 4;
-    return halo > red ? halo : red;
+    return (halo > red ? halo : red) + (round_up16(S) + kSmallPx) * sizeof(int);   // (the table behind either)
 }
-template <int G>
+template <int NJ, int G>
 static int launch_conv_small(const ConvArgs &a0, const TileGeom &g, hipStream_t stream)
 {
-    constexpr int NJ = 2;
     ConvArgs a = a0;
     a.g = g;
     a.tiles_n = (a.Cout + NJ * 16 - 1) / (NJ * 16);
     a.rowsA = round_up16(g.S);
     a.dTiles = make_fast_div(g.ntiles);
     auto kern = conv3x3_small_bf16_kernel<NJ, G, false>;
-    if constexpr (G == 4)
+    if constexpr (G == 4 && NJ == 2)   // (where columns are 16 wide every wave has one range)
         if (a.ksplit > G) kern = conv3x3_small_bf16_kernel<NJ, G, true>;
     if (!raise_lds_limit(reinterpret_cast<const void *>(kern))) return VGG_ERR_LAUNCH;
     const size_t lds = conv_small_lds(G, g.S, a.ksplit);
+    a.tableA = (int)(lds - (a.rowsA + kSmallPx) * sizeof(int));
     hipLaunchKernelGGL(kern, dim3((unsigned)(g.ntiles * a.tiles_n)), dim3(G * 64), lds, stream, a);
     return launch_status();
 }
@@ -1121,7 +1138,7 @@ enum ConvKernel {
     kWregHalf, kWregHalfBig,                    // ... 128-pixel tiles, 224 / 384 halo rows (the sums folded per range
                                                 //     where the contraction is split)
     kWregDeep, kWregDeepBig,                    // ... with nine taps of weights in flight
-    kSmall4, kSmall8,                           // 64 x 32 tiles, the contraction split over four / eight waves
+    kSmall4, kSmall8,                           // 64 x 32 or 64 x 16 tiles, the contraction split over four / eight waves
     kF32x3, kF32x3Big, kF32x3Half               // fp32 in three bf16 parts: 256-pixel tiles, 384 / 448 halo rows; 128-pixel tiles
 };
 // the kernels whose workgroups may share a tile's contraction through memory
@@ -1266,10 +1283,13 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         // (wide images have no other split to go to)
         const bool few = tiles <= 256 || (tiles <= 512 && (wide || chain <= 6)) ||
                          (tiles <= 1024 && (chunks >= 12 || Cout <= 64) && (wide || (c.ksplit <= G && chain <= 4)));
-        if (few && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, c.ksplit) <= 160 * 1024) {
+        // (that kernel's offsets into the input are 31 bits)
+        const bool near = (size_t)N * H * W * CinP * sizeof(bf16_t) < ((size_t)1 << 31);
+        if (few && near && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, c.ksplit) <= 160 * 1024) {
             c.g = t;
             c.kernel = G == 8 ? kSmall8 : kSmall4;
-            c.bn = 32;
+            // (up to half the CUs: columns of 16 channels, half the weights for each to fetch; 512 -> 512 at 14x14, batch 1, 9.4 -> 7.9 us)
+            c.bn = tiles <= 128 ? 16 : 32;
             return c;
         }
     }
@@ -1424,8 +1444,8 @@ int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void
             break;
         case kWregDeep: rc = launch_conv_wreg<2, 2, kWregHaloRowsHalf, 2, 1, 9>(a, g, stream); break;
         case kWregDeepBig: rc = launch_conv_wreg<2, 2, kWregHaloRows, 2, 1, 9>(a, g, stream); break;
-        case kSmall4: rc = launch_conv_small<4>(a, g, stream); break;
-        case kSmall8: rc = launch_conv_small<8>(a, g, stream); break;
+        case kSmall4: rc = c.bn == 16 ? launch_conv_small<1, 4>(a, g, stream) : launch_conv_small<2, 4>(a, g, stream); break;
+        case kSmall8: rc = c.bn == 16 ? launch_conv_small<1, 8>(a, g, stream) : launch_conv_small<2, 8>(a, g, stream); break;
         case kDma:
             rc = narrow ? launch_conv_dma<bf16_t, 256, 64, 4, 1, kDmaHaloRows>(a, g, stream)
                         : launch_conv_dma<bf16_t, 256, 128, 4, 2, kDmaHaloRows>(a, g, stream);

@@ -31,11 +31,13 @@ struct ConvArgs {
     float *part;        // [ksplit][M][Cout] partial sums when the contraction is split over workgroups, else null
     int ksplit;         // workgroups per tile (>= 1)
     int kchunks;        // channel chunks per workgroup
-    FastDiv dTiles;     // conv3x3_small_bf16_kernel: division by the number of pixel tiles
+    FastDiv dTiles;     // conv3x3_small_bf16_kernel: division by the number of pixel tiles,
+    int tableA;         // ... byte offset of its table of halo rows in LDS
     TileGeom g;
 };
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 static __device__ const u32x4 kZeroRow[4] = {};  // 64 zero bytes: what a halo row outside the image reads
 
 template <typename T> struct Mma;

@@ -455,6 +455,21 @@ def test_conv3x3_bf16_small_and_medium_launches(shape, kernel):
     assert (buf[n:] == -7.0).all()
 
 
+@pytest.mark.parametrize("shape,kernel,columns", [
+    ((1, 7, 9, 512, 20), 13, 16),       # a last column of four channels; one workgroup walks past the only tile's pixels
+    ((1, 16, 16, 256, 68), 12, 16),     # four waves; patches, a last column of four channels
+    ((1, 32, 16, 320, 140), 13, 16),    # five ranges for eight waves
+    ((1, 21, 58, 256, 36), 12, 16),     # patches that stick out of the image
+    ((1, 16, 64, 512, 252), 13, 16),    # 128 tiles of 32 channels, the last launch with columns of sixteen
+    ((1, 16, 64, 512, 260), 13, 32),    # ... and the first with columns of 32
+])
+def test_conv3x3_bf16_sixteen_channel_columns(shape, kernel, columns):
+    """Launches for at most half the CUs take columns of sixteen channels: as the other small launches, against the oracle."""
+    N, H, W, Cin, Cout = shape
+    assert B.vgg_conv3x3_plan(B.PLAN_FWD, B.BF16, N, H, W, Cin, Cout)[2] == columns
+    test_conv3x3_bf16_small_and_medium_launches(shape, kernel)
+
+
 @pytest.mark.parametrize("shape", [(1, 14, 14, 576, 512), (2, 7, 9, 1024, 200), (3, 20, 19, 768, 132), (2, 12, 36, 576, 72)])
 def test_conv3x3_bf16_split_over_workgroups(shape):
     """More ranges than the waves of one workgroup share (more than 512 input channels): the ranges go to workgroups of
