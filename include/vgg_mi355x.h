@@ -362,9 +362,10 @@ int vgg19_plan(const vgg_config *cfg, int training, int *kinds_host, int cap);
  *       384 / 448 halo rows, 6 / 7 the same with 320-pixel tiles and one
  *       workgroup per compute unit, 8 / 9 with 128-pixel tiles and room for
  *       224 / 384 halo rows, 10 / 11 those with nine taps of weights in
+ *       flight, 17 / 18 with 192-pixel tiles, two and nine taps of weights in
  *       flight, 12 / 13 the bf16 kernel for launches of few tiles (64 pixels
- *       x 32 channels, the contraction split over the four / eight waves of a
- *       workgroup), 14 / 15 / 16 the fp32 implicit GEMM on the bf16 matrix
+ *       x 32 or 16 channels, the contraction split over the four / eight waves
+ *       of a workgroup), 14 / 15 / 16 the fp32 implicit GEMM on the bf16 matrix
  *       unit (three parts per value), 256-pixel tiles with room for 384 / 448
  *       halo rows and 128-pixel tiles;
  *       weight gradient: 100 linear tiles, 114 / 116 / 108 patches of 4 x 14,

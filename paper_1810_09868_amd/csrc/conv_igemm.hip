@@ -430,7 +430,7 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
     constexpr int NQ = (SA * 5 + NT - 1) / NT;   // halo copies per thread and chunk
     constexpr int ABUF = NQ * NT * 16;           // bytes per halo buffer (>= SA * 80)
     constexpr int TAPS = 9;                      // RB: taps of weight fragments in registers, requested RB - 1 taps ahead
-    constexpr int LA = NI % 4 == 0 ? 3 : 4, RA = LA + 1;
+    constexpr int LA = NI % 4 == 0 ? 3 : NI == 6 ? 5 : 4, RA = LA + 1;
     static_assert(TAPS % RB == 0 && (TAPS * NI) % RA == 0, "ring positions must repeat every chunk");
     static_assert(NJ <= NI && NQ <= 3 * LA, "weight loads and halo copies share the slots after the MFMAs");
     // halo copies (three per pixel block, from block NI - LA of the last tap on) issued before that tap's last weight load
@@ -1069,7 +1069,7 @@ static int launch_conv_wreg(const ConvArgs &a0, const TileGeom &g, hipStream_t s
         return launch_status();
     };
     if ((a.pool && a.y) || (a.Cout & 7)) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiGeneral, FOLD>);
-    if constexpr (TM % 2 == 0 && !FOLD)   // (a pool is planned neither on 320-pixel tiles nor where sums are folded)
+    if constexpr (TM % 2 == 0 && !FOLD)   // (a pool is planned neither on 192- and 320-pixel tiles nor where sums are folded)
         if (a.pool) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPooled, FOLD>);
     if (a.mask) return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiMasked, FOLD>);
     return launch(conv3x3_igemm_wreg_kernel<WM, WN, SA, TM, OCC, RB, kEpiPlain, FOLD>);
@@ -1139,7 +1139,8 @@ enum ConvKernel {
                                                 //     where the contraction is split)
     kWregDeep, kWregDeepBig,                    // ... with nine taps of weights in flight
     kSmall4, kSmall8,                           // 64 x 32 or 64 x 16 tiles, the contraction split over four / eight waves
-    kF32x3, kF32x3Big, kF32x3Half               // fp32 in three bf16 parts: 256-pixel tiles, 384 / 448 halo rows; 128-pixel tiles
+    kF32x3, kF32x3Big, kF32x3Half,              // fp32 in three bf16 parts: 256-pixel tiles, 384 / 448 halo rows; 128-pixel tiles
+    kWregMid, kWregMidDeep                      // weights in registers, 192-pixel tiles, 384 halo rows; nine taps of weights in flight
 };
 // the kernels whose workgroups may share a tile's contraction through memory
 static bool over_workgroups(int kernel) { return kernel == kDma || kernel == kDmaBig || kernel == kF32x3 || kernel == kF32x3Big || kernel == kF32x3Half; }
@@ -1333,6 +1334,20 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         }
         const TileGeom t = make_tile_geom(N, H, W, 128);
         const int tiles = t.ntiles * cols;
+        // 192 pixels cost 0.78: in place of 256-pixel tiles 0.84 to 0.96 of the time of 169 shapes (96 -> 200 at 45x60, batch 7, 14.3 -> 12.9 us;
+        // 480 -> 112 at 25x52, batch 27, 45.6 -> 39.2), in place of 128-pixel ones with the larger halo 0.81 to 0.96 of 81, with the
+        // smaller one 0.94 to 1.07 of 50, so not there; nor, at up to three chunks, where a 256-pixel tile has the smaller halo (0.95).
+        const bool half = t.S <= kWregHaloRowsHalf && 0.56f * rounds(tiles) < best;
+        if (!pool && ksplit == 1 && !half && (chunks > 3 || c.kernel != kWreg)) {
+            const TileGeom mid = make_tile_geom(N, H, W, 192);
+            const float cost = 0.78f * rounds(mid.ntiles * cols);
+            if (mid.S <= kWregHaloRows && cost < best) {
+                best = cost;
+                c.g = mid;
+                c.bn = 128;
+                c.kernel = mid.ntiles * cols <= 256 && chunks >= 12 ? kWregMidDeep : kWregMid;
+            }
+        }
         if (t.S <= kWregHaloRows && 0.56f * rounds(tiles) < best) {
             c.g = t;
             c.bn = 128;
@@ -1436,6 +1451,8 @@ int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void
         case kWregBig: rc = launch_conv_wreg<2, 2, kWregHaloRowsBig>(a, g, stream); break;
         case kWregTall: rc = launch_conv_wreg<2, 2, kWregHaloRows, 5, 1>(a, g, stream); break;
         case kWregTallBig: rc = launch_conv_wreg<2, 2, kWregHaloRowsBig, 5, 1>(a, g, stream); break;
+        case kWregMid: rc = launch_conv_wreg<2, 2, kWregHaloRows, 3>(a, g, stream); break;
+        case kWregMidDeep: rc = launch_conv_wreg<2, 2, kWregHaloRows, 3, 1, 9>(a, g, stream); break;
         case kWregHalf:
             rc = a.ksplit > 1 ? launch_conv_wreg<2, 2, kWregHaloRowsHalf, 2, 2, 3, true>(a, g, stream) : launch_conv_wreg<2, 2, kWregHaloRowsHalf, 2, 3>(a, g, stream);
             break;

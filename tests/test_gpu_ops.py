@@ -470,6 +470,17 @@ def test_conv3x3_bf16_sixteen_channel_columns(shape, kernel, columns):
     test_conv3x3_bf16_small_and_medium_launches(shape, kernel)
 
 
+@pytest.mark.parametrize("shape,kernel", [
+    ((7, 45, 60, 96, 200), 17),         # three chunks; a last tile of 84 pixels, a last column of 72 channels
+    ((19, 36, 32, 128, 134), 17),       # patches of 12 x 16; a channel count that 16-byte stores do not divide
+    ((30, 24, 13, 416, 460), 18),       # thirteen chunks, nine taps of weights ahead; tiles that cross images
+    ((14, 41, 23, 128, 264), 17),       # a last column of eight channels
+])
+def test_conv3x3_bf16_192_pixel_tiles(shape, kernel):
+    """192-pixel tiles at their edges: as the other medium launches, against the oracle."""
+    test_conv3x3_bf16_small_and_medium_launches(shape, kernel)
+
+
 @pytest.mark.parametrize("shape", [(1, 14, 14, 576, 512), (2, 7, 9, 1024, 200), (3, 20, 19, 768, 132), (2, 12, 36, 576, 72)])
 def test_conv3x3_bf16_split_over_workgroups(shape):
     """More ranges than the waves of one workgroup share (more than 512 input channels): the ranges go to workgroups of
