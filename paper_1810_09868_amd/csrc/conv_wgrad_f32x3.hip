@@ -12,7 +12,8 @@
 //      row r at c ^ (r >> 3) & 1, which keeps the eight rows of half a wave on distinct banks.
 // Two buffers and one barrier per patch: a wave splits and stores the next patch half-way through its own.  64 -> 128 at 50x66,
 // batch 10: 69 -> 44 us (the fp32 MFMAs on 4 x 14 patches, 512 workgroups), 512 -> 512 at 28x28, batch 10, 298 -> 213.  Bound by
-// LDS reads (nine of ten clocks that the MFMAs would take) and the MFMAs, two waves per SIMD.  (A zero of g beside an infinite x makes
+// the MFMAs, two waves per SIMD: four tenths fewer LDS reads (the taps of a halo row shifted out of registers) and splitting at
+// different times in a SIMD's two waves changed nothing (1.00 of the time over 27 and 32 shapes).  (A zero of g beside an infinite x makes
 // a partial sum NaN here: the pass that adds them forms it again from the patches' own pixels.)
 #include "f32x3.h"
 
