@@ -26,8 +26,6 @@ bool raise_lds_limit(const void *kernel)
 int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void *x, const void *w, const float *bias,
                   const void *mask, void *y, void *pool, unsigned char *argmax, int relu, void *part_ws, size_t part_bytes,
                   hipStream_t stream);
-int conv3x3_pass(int dtype, int N, int H, int W, int CinP, int Cout, const void *x, const void *w, const float *bias, void *y, void *pool,
-                 void *part_ws, size_t part_bytes, hipStream_t stream);
 size_t conv3x3_igemm_workspace(int dtype, int N, int H, int W, int CinP, int Cout);
 bool conv3x3_pool_fusable(int dtype, int H, int W, int Cout);
 bool conv3x3_pool_fused(int dtype, int N, int H, int W, int CinP, int Cout);
@@ -287,15 +285,11 @@ void run_forward(const vgg_config *c, const PackedLayout &P, const WsLayout &L, 
         if (l == 0)   // (reads the NCHW batch itself; the padded NHWC copy above is only the weight gradient's operand)
             VGG_STEP(rec, K_CONV, conv_first(dt, N, c->H, c->W, P.cinp[0], x, pk + P.conv_w[0],
                                             reinterpret_cast<const float *>(pk + P.conv_b[0]), out, 1, s));
-        else if (!training)
-            VGG_STEP(rec, K_CONV, conv3x3_pass(dt, N, L.H[l], L.W[l], P.cinp[l], kConvCh[l][1], cur, pk + P.conv_w[l],
-                                              reinterpret_cast<const float *>(pk + P.conv_b[l]), fuse ? nullptr : out,
-                                              fuse ? ws + L.pooled[l] : nullptr, ws + L.convpart, L.convpart_bytes, s));
         else
             VGG_STEP(rec, K_CONV, conv3x3_igemm(dt, N, L.H[l], L.W[l], P.cinp[l], kConvCh[l][1], cur, pk + P.conv_w[l],
                                                reinterpret_cast<const float *>(pk + P.conv_b[l]), nullptr,
                                                fuse ? nullptr : out, fuse ? ws + L.pooled[l] : nullptr,
-                                               fuse ? reinterpret_cast<uint8_t *>(ws + L.argmax[l]) : nullptr, 1,
+                                               fuse && training ? reinterpret_cast<uint8_t *>(ws + L.argmax[l]) : nullptr, 1,
                                                ws + L.convpart, L.convpart_bytes, s));
         cur = out;
         if (fuse) {

@@ -1188,9 +1188,7 @@ static TileGeom conv_small_geom(int N, int H, int W, bool pool)
 
 bool conv3x3_pool_fusable(int dtype, int H, int W, int Cout);
 
-// pass: a launch of a forward pass.  Training keeps the order of its sums, since a rounding that falls the other way in one layer
-// grows over its steps (two images: 1e-3 of the loss after one step, 0.3 after five), and single layers keep training's.
-static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bool pool, bool pass)
+static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bool pool)
 {
     ConvPlan c;
     c.g = make_tile_geom(N, H, W, 256);
@@ -1279,27 +1277,17 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
     // chunks, with more than 64 output channels and more than 512 tiles the 128-pixel tiles below are faster still (256 ->
     // 512 at 28x28, batch 4: 15.4 us, 17.4 here; 320 -> 128 at 20x19, batch 43 20.7 / 25.3).
     if (!pool || !conv3x3_pool_fusable(dtype, H, W, Cout)) conv_split(dtype, c.g, CinP, Cout, c.ksplit, c.kchunks);
-    // Contractions of two to eight chunks that conv_split leaves whole: a range for every chunk, up to 512 such tiles.  260
-    // launches: up to 256 tiles 0.24 to 0.78 of the time of the kernels below, up to 512 0.55 to 0.93 (1.05 for one of
-    // two chunks), up to 768 0.77 to 1.34 (128 -> 256 at 56x56, batch 1, 11.5 -> 8.0 us).  253 more launches 0.56 on average, 0.98 at most.
-    bool whole = false;
-    if (c.ksplit == 1 && chunks >= 2 && chunks <= kSmallRanges && pass && Cout % 4 == 0 && (!pool || conv3x3_pool_fusable(dtype, H, W, Cout))) {
+    if (c.ksplit > 1) {
         const TileGeom t = conv_small_geom(N, H, W, pool);
-        whole = t.S <= kSmallHaloRows && (long)t.ntiles * ((Cout + 31) / 32) <= 512;
-    }
-    if (c.ksplit > 1 || whole) {
-        const int ranges = whole ? chunks : c.ksplit, range = whole ? 1 : c.kchunks;
-        const TileGeom t = conv_small_geom(N, H, W, pool);
-        const int tiles = t.ntiles * ((Cout + 31) / 32), G = tiles <= 256 && ranges > 4 ? 8 : 4;
-        const int chain = (ranges + G - 1) / G * range;   // chunks that a wave walks
+        const int tiles = t.ntiles * ((Cout + 31) / 32), G = tiles <= 256 && c.ksplit > 4 ? 8 : 4;
+        const int chain = (c.ksplit + G - 1) / G * c.kchunks;   // chunks that a wave walks
         // (wide images have no other split to go to)
         const bool few = tiles <= 256 || (tiles <= 512 && (wide || chain <= 6)) ||
-                         (tiles <= 1024 && (chunks >= 12 || Cout <= 64) && (wide || (ranges <= G && chain <= 4)));
+                         (tiles <= 1024 && (chunks >= 12 || Cout <= 64) && (wide || (c.ksplit <= G && chain <= 4)));
         // (that kernel's offsets into the input are 31 bits)
         const bool near = (size_t)N * H * W * CinP * sizeof(bf16_t) < ((size_t)1 << 31);
-        if (few && near && (!pool || t.mode == 1) && ranges <= kSmallRanges && conv_small_lds(G, t.S, ranges) <= 160 * 1024) {
+        if (few && near && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, c.ksplit) <= 160 * 1024) {
             c.g = t;
-            c.ksplit = ranges; c.kchunks = range;
             c.kernel = G == 8 ? kSmall8 : kSmall4;
             // (up to half the CUs: columns of 16 channels, half the weights for each to fetch; 512 -> 512 at 14x14, batch 1, 9.4 -> 7.9 us)
             c.bn = tiles <= 128 ? 16 : 32;
@@ -1389,7 +1377,7 @@ size_t conv3x3_igemm_workspace(int dtype, int N, int H, int W, int CinP, int Cou
 // pixel tiles, ranges of the contraction (kDma, kDmaBig: a workgroup each), workgroups}.
 void conv3x3_igemm_plan_info(int dtype, int N, int H, int W, int CinP, int Cout, bool pool, int info[7])
 {
-    const ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool, false);
+    const ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool);
     info[0] = c.kernel;
     info[1] = c.g.rows;
     info[2] = c.bn;
@@ -1410,7 +1398,7 @@ bool conv3x3_pool_fused(int dtype, int N, int H, int W, int CinP, int Cout)
 {
     if (conv3x3_pool_fusable(dtype, H, W, Cout)) return true;
     if (dtype != VGG_BF16 || H % 2 || W % 2 || Cout % 8) return false;
-    const int k = conv_plan(dtype, N, H, W, CinP, Cout, true, false).kernel;
+    const int k = conv_plan(dtype, N, H, W, CinP, Cout, true).kernel;
     return k == kSmall4 || k == kSmall8;
 }
 
@@ -1418,12 +1406,12 @@ bool conv3x3_pool_fused(int dtype, int N, int H, int W, int CinP, int Cout)
 // pool (optional): 2x2 max of y, only when conv3x3_pool_fused(); y may then be null; argmax (optional, with pool).
 // part_ws: part_bytes of scratch; where conv3x3_igemm_workspace() asks for more than that (or it is null), the
 // contraction is not split over workgroups.
-static int conv3x3_launch(bool pass, int dtype, int N, int H, int W, int CinP, int Cout, const void *x, const void *w,
-                          const float *bias, const void *mask, void *y, void *pool, unsigned char *argmax, int relu, void *part_ws,
-                          size_t part_bytes, hipStream_t stream)
+int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void *x, const void *w,
+                  const float *bias, const void *mask, void *y, void *pool, unsigned char *argmax, int relu, void *part_ws,
+                  size_t part_bytes, hipStream_t stream)
 {
     if (pool && !conv3x3_pool_fused(dtype, N, H, W, CinP, Cout)) return VGG_ERR_UNSUPPORTED;
-    ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool != nullptr, pass);
+    ConvPlan c = conv_plan(dtype, N, H, W, CinP, Cout, pool != nullptr);
     const bool split = over_workgroups(c.kernel) && c.ksplit > 1;
     if (split && (!part_ws || !y || part_bytes < (size_t)c.ksplit * N * H * W * Cout * 4)) { c.ksplit = 1; c.kchunks = CinP * dtype_size(dtype) / kDataBytes; }
     ConvArgs a;
@@ -1498,18 +1486,6 @@ static int conv3x3_launch(bool pass, int dtype, int N, int H, int W, int CinP, i
         hipLaunchKernelGGL(conv_split_finish_kernel<bf16_t>, grid, dim3(256), 0, stream, a.part, bias,
                            static_cast<const bf16_t *>(mask), static_cast<bf16_t *>(y), quads, Cout, c.ksplit, relu);
     return launch_status();
-}
-
-int conv3x3_igemm(int dtype, int N, int H, int W, int CinP, int Cout, const void *x, const void *w, const float *bias, const void *mask,
-                  void *y, void *pool, unsigned char *argmax, int relu, void *part_ws, size_t part_bytes, hipStream_t stream)
-{
-    return conv3x3_launch(false, dtype, N, H, W, CinP, Cout, x, w, bias, mask, y, pool, argmax, relu, part_ws, part_bytes, stream);
-}
-// A layer of a forward pass.
-int conv3x3_pass(int dtype, int N, int H, int W, int CinP, int Cout, const void *x, const void *w, const float *bias, void *y, void *pool,
-                 void *part_ws, size_t part_bytes, hipStream_t stream)
-{
-    return conv3x3_launch(true, dtype, N, H, W, CinP, Cout, x, w, bias, nullptr, y, pool, nullptr, 1, part_ws, part_bytes, stream);
 }
 
 }  // namespace vgg

@@ -44,7 +44,8 @@ class _Chain:
     model-level call documents, with every intermediate tensor kept on the device."""
 
 
-def _forward_chain(inp, dtype, N, H, W, hidden, classes):
+def _forward_chain(inp, dtype, N, H, W, hidden, classes, pair=False):
+    """pair: the first two layers in one call, as a bf16 forward pass without a backward pass has them."""
     tdt = TDT[dtype]
     c = _Chain()
     c.dtype, c.N, c.hidden, c.classes = dtype, N, hidden, classes
@@ -68,7 +69,9 @@ def _forward_chain(inp, dtype, N, H, W, hidden, classes):
         if l in _POOLED:
             pooled = torch.empty((N, h // 2, w // 2, co), dtype=tdt, device="cuda")
             arg = torch.empty((N, h // 2, w // 2, co), dtype=torch.uint8, device="cuda")
-            if l > 0 and h % 16 == 0 and w % 16 == 0:      # pool taken in the convolution's epilogue
+            if l == 1 and pair:
+                B.vgg_conv3x3_fwd_first_pair(dtype, N, h, w, dev(inp.x), first[0], first[1], wp, bias, None, pooled)
+            elif l > 0 and h % 16 == 0 and w % 16 == 0:      # pool taken in the convolution's epilogue
                 B.vgg_conv3x3_fwd_pool(dtype, N, h, w, cp, co, cur, wp, bias, None, pooled, 1, wsb, argmax=arg)
             else:
                 y = torch.empty((N, h, w, co), dtype=tdt, device="cuda")
@@ -79,7 +82,9 @@ def _forward_chain(inp, dtype, N, H, W, hidden, classes):
             h, w = h // 2, w // 2
         else:
             y = torch.empty((N, h, w, co), dtype=tdt, device="cuda")
-            if l == 0:      # the first convolution reads the NCHW batch itself
+            if l == 0 and pair:
+                first = (wp, bias)
+            elif l == 0:    # the first convolution reads the NCHW batch itself
                 B.vgg_conv3x3_fwd_first(dtype, N, h, w, dev(inp.x), wp, bias, y, 1)
             else:
                 B.vgg_conv3x3_fwd(dtype, N, h, w, cp, co, cur, wp, bias, y, 1, wsb)
@@ -522,6 +527,20 @@ def test_full_vgg19_forward_small_batches(dtype, N):
         ref = R.vgg19_forward(inp.x[n:n + 1], inp.conv_w, inp.conv_b, inp.fc_w, inp.fc_b)
         assert max_rel_err(logits[n:n + 1], ref["logits"]) <= TOL[dtype], n
         _check_probs(probs[n:n + 1], logits[n:n + 1], ref, dtype)
+
+
+@pytest.mark.parametrize("dtype", [B.F32, B.BF16])
+@pytest.mark.parametrize("shp", [(2, 32, 32, 512, 10), (1, 224, 224, 512, 10), (3, 96, 64, 64, 10)])
+def test_forward_equals_chained_single_op_calls(shp, dtype):
+    """A forward pass gives the bits of its layers called one by one: every layer sums in the order of vgg_conv3x3_fwd, whose
+    kernel vgg_conv3x3_plan names, also where images are so few that a layer has a handful of tiles."""
+    inp = synth.vgg19_inputs(*shp, seed=4)
+    c = _forward_chain(inp, dtype, *shp, pair=dtype == B.BF16)
+    m = Vgg19(dtype, *shp)
+    m.pack(inp.conv_w, inp.conv_b, inp.fc_w, inp.fc_b)
+    m.forward(dev(inp.x))
+    torch.cuda.synchronize()
+    assert torch.equal(m.logits, c.logits) and torch.equal(m.probs, c.probs)
 
 
 def test_forward_as_one_graph_matches_eager():

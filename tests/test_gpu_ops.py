@@ -470,44 +470,36 @@ def test_conv3x3_bf16_sixteen_channel_columns(shape, kernel, columns):
     test_conv3x3_bf16_small_and_medium_launches(shape, kernel)
 
 
-@pytest.mark.parametrize("shape", [
-    (1, 5, 9, 64, 20),         # two chunks, two waves without one; part of a tile, a last column of four channels
-    (3, 15, 8, 192, 144),      # six chunks for eight waves; tiles that cross images
-    (1, 32, 48, 160, 72),      # five chunks; patches that divide the image: pool
-    (2, 30, 44, 96, 200),      # patches that stick out, a last column of eight channels
-    (8, 32, 32, 96, 128),      # 512 tiles, the last launch that takes the kernel; pool
-    (8, 32, 32, 96, 132),      # 640 tiles: the kernels for larger launches
-    (6, 13, 26, 224, 260),     # seven chunks for four waves: two ranges each but the last
+@pytest.mark.parametrize("shape,kernel", [
+    ((1, 5, 9, 64, 20), 1),        # two chunks, part of one tile, a last column of four channels
+    ((3, 15, 8, 192, 144), 8),     # six chunks; tiles that cross images
+    ((1, 32, 48, 160, 72), 8),     # five chunks; patches that divide the image: pool
+    ((2, 30, 44, 96, 200), 9),     # a last column of 72 channels
+    ((8, 32, 32, 96, 128), 8),     # 64 tiles; pool
+    ((8, 32, 32, 96, 132), 8),     # a last column of four channels
+    ((6, 13, 26, 224, 260), 8),    # seven chunks
 ])
-def test_conv3x3_bf16_short_contractions_of_a_forward_pass(shape):
-    """Forward passes split contractions of two to eight chunks over the waves of a workgroup: against the oracle, element by
-    element, and the fused pool against the separate one, bit for bit."""
+def test_conv3x3_bf16_short_contractions_on_few_tiles(shape, kernel):
+    """Contractions of two to seven chunks on a few workgroups, which no kernel splits (forward passes and training share the
+    order of their sums): against the oracle, element by element, and the fused pool against the separate one, bit for bit."""
     dtype = B.BF16
     N, H, W, Cin, Cout = shape
-    out = subprocess.run(["nm", "-D", "--defined-only", B.LIB_PATH], capture_output=True, text=True, check=True).stdout
-    names = [w for line in out.splitlines() for w in line.split()[-1:] if w.startswith("_ZN3vgg12conv3x3_passE")]
-    assert len(names) == 1, names
-    conv, v, i = B.lib()[names[0]], ctypes.c_void_p, ctypes.c_int
-    conv.argtypes, conv.restype = [i] * 6 + [v] * 6 + [ctypes.c_size_t, v], i
+    info = B.vgg_conv3x3_plan(B.PLAN_FWD, dtype, N, H, W, Cin, Cout)
+    assert info[0] == kernel and info[5] == 1
     d = synth.conv_layer_inputs(N, H, W, Cin, Cout, seed=sum(shape))
     x, wp, b, n = to_nhwc(d["x"], dtype), _pack(dtype, d["w"]), dev(d["b"]), N * H * W * Cout
     ws = ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(dtype, N, H, W, Cin, Cout))
-
-    def run(y, pool):
-        assert conv(dtype, N, H, W, Cin, Cout, x.data_ptr(), wp.data_ptr(), b.data_ptr(), y.data_ptr() if y is not None else None,
-                    pool.data_ptr() if pool is not None else None, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
-
     buf = torch.full((n + 4096,), -7.0, dtype=TDT[dtype], device="cuda")
     y = buf[:n].view(N, H, W, Cout)
-    run(y, None)
+    B.vgg_conv3x3_fwd(dtype, N, H, W, Cin, Cout, x, wp, b, y, 1, ws)
     torch.cuda.synchronize()
     assert max_rel_err(from_nhwc(y), R.conv3x3_fwd(d["x"], d["w"], d["b"], relu=True)) <= TOL[dtype]
     assert (buf[n:] == -7.0).all()
     if H % 16 == 0 and W % 16 == 0 and Cout % 8 == 0:
         po = torch.full((n // 4 + 1024,), -7.0, dtype=TDT[dtype], device="cuda")
-        run(None, po)
-        chk, arg = torch.empty((N, H // 2, W // 2, Cout), dtype=TDT[dtype], device="cuda"), torch.empty((N, H // 2, W // 2, Cout), dtype=torch.uint8, device="cuda")
-        B.vgg_maxpool2x2(dtype, N, H, W, Cout, y, chk, arg)
+        B.vgg_conv3x3_fwd_pool(dtype, N, H, W, Cin, Cout, x, wp, b, None, po, 1, ws)
+        chk = torch.empty((N, H // 2, W // 2, Cout), dtype=TDT[dtype], device="cuda")
+        B.vgg_maxpool2x2(dtype, N, H, W, Cout, y, chk)
         torch.cuda.synchronize()
         assert torch.equal(po[:n // 4].view(torch.int16), chk.view(torch.int16).flatten()) and (po[n // 4:] == -7.0).all()
 
