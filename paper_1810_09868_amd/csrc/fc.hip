@@ -1266,11 +1266,9 @@ static int fc_da_splits(const FcDaArgs &a) { return (a.Out + a.o_per_split - 1) 
 
 // dz in parts ahead of both products: up to 128 rows (one row tile, since the input's batch rows fill the registers; with two, 0.96 to
 // 1.10 of the time of 18 shapes), and 32-bit offsets inside 32 rows of W and dW.  41 to 128 rows: 0.88 of the time of the kernels that split
-// dz themselves over 242 shapes, 1.05 at most (25088 -> 4096, batch 100, 355 -> 255 us; 64 rows, 1104 -> 3335 34.6 / 35.8).  25 to 40
-// rows from 1024 outputs on: 0.69 to 1.01 of the fp32 kernels' time over 24 shapes (38 rows, 19488 -> 1509 94 -> 65 us; 32 rows, 25088 ->
-// 4096 173 / 174); with fewer outputs, where a workgroup takes its inputs apart for a few steps only, up to 1.20; with fewer
-// rows, where the weights and dW stream, up to 1.24.
-static bool fc_bwd_staged(int N, int In, int Out) { return (N > 40 || (N > 24 && Out >= 1024)) && N <= 128 && In < (1 << 24) - 256; }
+// dz themselves over 242 shapes, 1.05 at most (25088 -> 4096, batch 100, 355 -> 255 us; 64 rows, 1104 -> 3335 34.6 / 35.8), same bits.  (25 to 40
+// rows stay on the fp32 MFMAs, as dW without da does: from 1024 outputs on 0.69 to 1.01 of the time here, but values of 2^-116 would be 4e-6 off.)
+static bool fc_bwd_staged(int N, int In) { return N > 40 && N <= 128 && In < (1 << 24) - 256; }
 // bytes of one of the two copies of dz in parts
 static size_t fc_dz_parts_bytes(const FcDaArgs &a) { return (size_t)((a.Out + 31) / 32) * a.nb * 3072; }
 
@@ -1278,7 +1276,7 @@ size_t fc_bwd_workspace(int N, int In, int Out)
 {
     FcDaArgs a;
     fc_da_plan(N, In, Out, a, false);
-    return round_up((size_t)fc_da_splits(a) * N * In * 4, 256) + (fc_bwd_staged(N, In, Out) ? 2 * fc_dz_parts_bytes(a) : 0);
+    return round_up((size_t)fc_da_splits(a) * N * In * 4, 256) + (fc_bwd_staged(N, In) ? 2 * fc_dz_parts_bytes(a) : 0);
 }
 
 // The launch of the kernel on the bf16 matrix unit, one workgroup per CU: of the splits that the workspace holds it takes
@@ -1309,11 +1307,11 @@ static int launch_fc_da_f32x3(const FcDaArgs &p, int splits, hipStream_t s)
     return launch_status();
 }
 
-// dz in parts, both products (da: its partial sums), one row tile of two to eight blocks of sixteen.
+// dz in parts, both products (da: its partial sums), one row tile of three to eight blocks of sixteen.
 template <int NB>
 static int launch_fc_bwd_parts(const FcDaArgs &p, int splits, const float *a, float *dw, float *db, hipStream_t s)
 {
-    if constexpr (NB > 2)
+    if constexpr (NB > 3)
         if (p.nb != NB) return launch_fc_bwd_parts<NB - 1>(p, splits, a, dw, db, s);
     const int steps = (p.Out + 31) / 32, units = p.tiles_i * steps;
     char *const rows = reinterpret_cast<char *>(p.part) + round_up((size_t)splits * p.N * p.In * 4, 256), *const cols = rows + fc_dz_parts_bytes(p);
@@ -1344,7 +1342,7 @@ int fc_backward(int N, int In, int Out, const float *a, const float *w, const fl
 {
     const dim3 grid((unsigned)(((In + 127) / 128) * ((Out + 127) / 128)));
     // (the parts of dz lie in the workspace, which is there where da is asked for)
-    const bool staged = da && fc_bwd_staged(N, In, Out), parts = staged || N > 40;
+    const bool staged = da && fc_bwd_staged(N, In), parts = N > 40;
     if (!staged) {
         auto dw_kernel = parts ? (In % 4 == 0 ? fc_dw_f32x3_kernel<true> : fc_dw_f32x3_kernel<false>) : (In % 4 == 0 ? fc_dw_kernel<true> : fc_dw_kernel<false>);
         hipLaunchKernelGGL(dw_kernel, grid, dim3(256), 0, s, a, dz, dw, N, In, Out);

@@ -1125,8 +1125,7 @@ def test_fc_backward_fp32_tile_edges(N, In, Out):
 @pytest.mark.parametrize("N,In,Out", [(25, 258, 1024), (24, 258, 1024), (32, 255, 1025), (41, 4097, 33), (57, 5002, 2602), (100, 2052, 5000), (128, 1026, 2600),
                                       (128, 6400, 1030), (129, 1026, 200)])
 def test_fc_backward_fp32_staged_gradient(N, In, Out):
-    """fp32 backward with dz taken apart ahead of the products: the lines to the other kernels (24 and 25 rows at 1024 outputs, 128
-    and 129 rows), workgroups of dW with one and with several (input tile, 32 outputs) units and with more than the four LDS buffers hold,
+    """fp32 backward with dz taken apart ahead of the products, and launches just outside its lines (24 to 32 rows, 129 rows): workgroups of dW with one and with several (input tile, 32 outputs) units and with more than the four LDS buffers hold,
     of two input tiles, and ranges of outputs that end inside 32; every element against float64.  Sums of at most 5000 products of
     N(0,1) values in fp32 are within 1e-6 of the largest, the tolerance is 1e-5.  Guards behind the results, the workspace NaN before."""
     g = torch.Generator(device="cuda").manual_seed(N * In + Out)
@@ -1141,6 +1140,43 @@ def test_fc_backward_fp32_staged_gradient(N, In, Out):
     for got, want in ((dw[:Out * In].view(Out, In), dz.t().contiguous() @ a), (db, dz.sum(0)), (da[:N * In].view(N, In), dz @ w * (a > 0))):
         assert ((got - want).abs().max() / want.abs().max()).item() <= 1e-5
     assert (dw[Out * In:] == -7.0).all() and (da[N * In:] == -7.0).all()
+
+
+@pytest.mark.parametrize("N,In,Out", [(24, 258, 1024), (25, 258, 1024), (32, 255, 1025), (40, 1028, 2600), (41, 257, 1100), (57, 1030, 160),
+                                      (100, 520, 2100), (128, 1026, 1024), (129, 136, 257), (200, 516, 130)])
+def test_fc_backward_fp32_weight_gradient_alone(N, In, Out):
+    """dW and db do not depend on whether da is asked for: the same bits with and without it, at batch sizes on both sides of every
+    line between the kernels, and against float64 (tolerance as above)."""
+    g = torch.Generator(device="cuda").manual_seed(N * In + Out)
+    a, w, dz = (torch.randn(s, generator=g, device="cuda") for s in ((N, In), (Out, In), (N, Out)))
+    got = []
+    for da in (torch.empty((N, In), device="cuda"), None):
+        dw, db = torch.full((Out * In + 256,), -7.0, device="cuda"), torch.empty((Out,), device="cuda")
+        ws = None if da is None else ws_bytes(B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out))
+        B.vgg_fc_bwd(B.F32, N, In, Out, a, w, dz, dw, db, da, 1, ws)
+        torch.cuda.synchronize()
+        assert (dw[Out * In:] == -7.0).all()
+        got.append((dw, db))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    dw, want = got[1][0][:Out * In].view(Out, In), dz.double().t().contiguous() @ a.double()
+    assert ((dw - want).abs().max() / want.abs().max()).item() <= 1e-5
+
+
+@pytest.mark.parametrize("scale", [-116, 0, 100])
+@pytest.mark.parametrize("N,In,Out", [(25, 260, 1024), (32, 256, 1024), (40, 255, 1026)])
+def test_fc_backward_fp32_whole_range_up_to_40_rows(N, In, Out, scale):
+    """Up to 40 batch rows the products are fp32 ones over the whole range of normal values: 1e-6 of the result's norm, six
+    times what sums of at most 1026 products round off (1.6e-7; three bf16 parts per value: 4e-6 at 2^-116)."""
+    g = torch.Generator(device="cuda").manual_seed(N * In + Out)
+    a, w, dz = (torch.randn(s, generator=g, device="cuda") for s in ((N, In), (Out, In), (N, Out)))
+    a, w = a * 2.0 ** scale, w * 2.0 ** scale
+    dw, da = torch.empty((Out, In), device="cuda"), torch.empty((N, In), device="cuda")
+    B.vgg_fc_bwd(B.F32, N, In, Out, a, w, dz, dw, None, da, 0, ws_bytes(B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out)))
+    torch.cuda.synchronize()
+    for got, want in ((dw, dz.double().t().contiguous() @ a.double()), (da, dz.double() @ w.double())):
+        err = ((got - want).norm() / want.norm()).item()
+        print("relative error %.1e" % err)
+        assert err <= 1e-6
 
 
 @pytest.mark.parametrize("N,In,Out", [(1, 8, 1), (32, 136, 65), (33, 264, 129), (64, 128, 64), (65, 120, 63), (96, 1032, 200), (97, 40, 33),
