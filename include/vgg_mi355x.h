@@ -275,7 +275,10 @@ int vgg_fc_static(int dtype, int N, int In, int Out, const void *a, const void *
  * bf16 where it enters a product (not for db), sums are fp32.  Any N, In, Out
  * > 0 for VGG_F32; VGG_BF16 needs In to be a multiple of 8
  * (VGG_ERR_UNSUPPORTED otherwise).  The workspace
- * is needed when da is requested and, for VGG_BF16, always. */
+ * is needed when da is requested and, for VGG_BF16, always.  VGG_F32: the
+ * size asked for at 41 to 128 rows holds two copies of dz in parts behind the
+ * partial sums of da; a workspace that holds the partial sums only is taken
+ * as well, here and in vgg19_train_step (same results, slower). */
 size_t vgg_fc_bwd_workspace_bytes(int dtype, int N, int In, int Out);
 int vgg_fc_bwd(int dtype, int N, int In, int Out, const void *a, const void *w, const void *dz,
                float *dw, float *db, void *da, int relu_mask, void *ws, size_t ws_bytes,

@@ -67,9 +67,9 @@ int permute_fc_cols(int dst_dtype, int Out, int C, int HW, int to_hwc, const flo
 size_t fc_workspace(int dtype, int N, int In, int Out);
 int fc_forward(int dtype, int N, int In, int Out, const void *a, const void *w, const float *bias, void *z, int z_dtype,
                int relu, void *ws, hipStream_t s);
-size_t fc_bwd_workspace(int N, int In, int Out);
+size_t fc_bwd_workspace(int N, int In, int Out, bool least = false);
 int fc_backward(int N, int In, int Out, const float *a, const float *w, const float *dz, float *dw, float *db, float *da,
-                int relu_mask, void *ws, hipStream_t s);
+                int relu_mask, void *ws, size_t ws_bytes, hipStream_t s);
 size_t fc_bwd_bf16_workspace(int N, int In, int Out);
 int fc_backward_bf16(int N, int In, int Out, const bf16_t *a, const bf16_t *w, const float *dz, float *dw, float *db, float *da,
                      int relu_mask, void *ws, hipStream_t s, float lr = 0.f, bf16_t *copy = nullptr);
@@ -144,7 +144,8 @@ struct WsLayout {
     size_t wflip[VGG19_NUM_CONV];      // data-gradient operands (flipped, transposed weights) of layers 1..15
     size_t dflat32;                    // bf16 training: fp32 gradient with respect to the flattened pool output
     size_t wgws_bytes;                 // size of the weight gradients' partial-sum buffer at wgws
-    size_t total;
+    size_t fcbws_bytes;                // size of the dense backward's scratch at fcbws
+    size_t least, total;               // bytes a call has to bring, bytes the query asks for
     int H[VGG19_NUM_CONV], W[VGG19_NUM_CONV];  // spatial size of each conv layer
 };
 
@@ -208,7 +209,7 @@ WsLayout ws_layout(const vgg_config *c, const PackedLayout &P, bool training)
     L.convpart = b.take(cpart);
     L.convpart_bytes = cpart;
     for (int l = 0; l < VGG19_NUM_CONV; ++l) L.wflip[l] = 0;
-    L.dlogits = L.dz2 = L.dz1 = L.gA = L.gB = L.grads = L.wgws = L.fcbws = L.dflat32 = L.wgws_bytes = 0;
+    L.dlogits = L.dz2 = L.dz1 = L.gA = L.gB = L.grads = L.wgws = L.fcbws = L.dflat32 = L.wgws_bytes = L.fcbws_bytes = 0;
     if (training) {
         L.dlogits = b.take(N * c->classes * 4);
         L.dz2 = b.take(N * c->fc_hidden * 4);
@@ -220,7 +221,7 @@ WsLayout ws_layout(const vgg_config *c, const PackedLayout &P, bool training)
         const bool mixed = c->dtype == VGG_BF16;
         L.grads = b.take(mixed ? packed_layout(c, true).total : P.total);
         if (mixed) L.dflat32 = b.take(N * P.fc_in[0] * 4);
-        size_t wg = 0, fb = 0;
+        size_t wg = 0, fb = 0, fb_least = 0;
         for (int l = 0; l < VGG19_NUM_CONV; ++l) {
             const size_t s = mixed ? conv3x3_wgrad_bf16_workspace(c->N, L.H[l], L.W[l], P.cinp[l], kConvCh[l][1])
                                    : conv3x3_wgrad_workspace(c->N, L.H[l], L.W[l], kConvCh[l][0], P.cinp[l], kConvCh[l][1]);
@@ -228,14 +229,27 @@ WsLayout ws_layout(const vgg_config *c, const PackedLayout &P, bool training)
         }
         for (int l = 0; l < VGG19_NUM_FC; ++l) {
             const size_t s = mixed ? fc_bwd_bf16_workspace(c->N, P.fc_in[l], P.fc_out[l]) : fc_bwd_workspace(c->N, P.fc_in[l], P.fc_out[l]);
+            const size_t least = mixed ? s : fc_bwd_workspace(c->N, P.fc_in[l], P.fc_out[l], true);
             if (s > fb) fb = s;
+            if (least > fb_least) fb_least = least;
         }
         L.wgws = b.take(wg);
         L.wgws_bytes = wg;
-        L.fcbws = b.take(fb);
+        L.fcbws = b.take(fb);   // (the last tensor: a workspace may end inside it)
+        L.fcbws_bytes = fb;
+        L.least = L.fcbws + round_up(fb_least, 256);
     }
     L.total = b.off;
+    if (!training) L.least = L.total;
     return L;
+}
+
+// Whether a workspace holds the layout; one that ends inside the dense backward's scratch leaves that the smaller.
+bool ws_holds(WsLayout &L, const void *ws, size_t ws_bytes)
+{
+    if (!ws || ws_bytes < L.least) return false;
+    if (ws_bytes - L.fcbws < L.fcbws_bytes) L.fcbws_bytes = ws_bytes - L.fcbws;
+    return true;
 }
 
 // Records the launch plan and, unless dry, stops at the first failing launch.
@@ -350,7 +364,7 @@ void run_train(const vgg_config *c, const PackedLayout &P, const WsLayout &L, co
                                           fused ? reinterpret_cast<bf16_t *>(pk + P.fc_w[l]) : nullptr);
             else
                 rec.rc = fc_backward(N, P.fc_in[l], P.fc_out[l], reinterpret_cast<const float *>(fc_in[l]), F(pk + P.fc_w[l]),
-                                     fc_dz[l], F(gr + P.fc_w[l]), F(gr + P.fc_b[l]), da, 1, ws + L.fcbws, s);
+                                     fc_dz[l], F(gr + P.fc_w[l]), F(gr + P.fc_b[l]), da, 1, ws + L.fcbws, L.fcbws_bytes, s);
         }
         rec.skip(K_FCDA);  // issued by the same call; listed for the plan
     }
@@ -784,13 +798,14 @@ int vgg_fc_bwd(int dtype, int N, int In, int Out, const void *a, const void *w, 
     if (!aligned16(a) || !aligned16(w) || !aligned16(dz) || !aligned16(dw) || (da && !aligned16(da)) || (ws && !aligned16(ws)))
         return VGG_ERR_ALIGN;
     // (bf16: the rounded copy of dz lives in the workspace, so it is needed even without da)
-    if ((da || dtype == VGG_BF16) && (!ws || ws_bytes < vgg_fc_bwd_workspace_bytes(dtype, N, In, Out))) return VGG_ERR_WORKSPACE;
+    const size_t need = dtype == VGG_F32 ? fc_bwd_workspace(N, In, Out, true) : fc_bwd_bf16_workspace(N, In, Out);
+    if ((da || dtype == VGG_BF16) && (!ws || ws_bytes < need)) return VGG_ERR_WORKSPACE;
     if (dtype == VGG_BF16)
         return fc_backward_bf16(N, In, Out, static_cast<const bf16_t *>(a), static_cast<const bf16_t *>(w),
                                 static_cast<const float *>(dz), dw, db, static_cast<float *>(da), relu_mask ? 1 : 0, ws,
                                 (hipStream_t)stream);
     return fc_backward(N, In, Out, static_cast<const float *>(a), static_cast<const float *>(w), static_cast<const float *>(dz),
-                       dw, db, static_cast<float *>(da), relu_mask ? 1 : 0, ws, (hipStream_t)stream);
+                       dw, db, static_cast<float *>(da), relu_mask ? 1 : 0, ws, ws_bytes, (hipStream_t)stream);
 }
 
 int vgg_softmax(int N, int K, const float *z, float *p, void *stream)
@@ -896,8 +911,8 @@ int vgg19_forward(const vgg_config *cfg, const float *x, const void *packed, flo
         (ws && !aligned16(ws)))
         return VGG_ERR_ALIGN;
     const PackedLayout P = packed_layout(cfg);
-    const WsLayout L = ws_layout(cfg, P, false);
-    if (!ws || ws_bytes < L.total) return VGG_ERR_WORKSPACE;
+    WsLayout L = ws_layout(cfg, P, false);
+    if (!ws_holds(L, ws, ws_bytes)) return VGG_ERR_WORKSPACE;
     Recorder rec{nullptr, 0, 0, false, VGG_OK};
     run_forward(cfg, P, L, x, static_cast<const char *>(packed), logits, probs, probs != nullptr, static_cast<char *>(ws),
                 false, (hipStream_t)stream, rec);
@@ -917,8 +932,8 @@ int vgg19_train_step(const vgg_config *cfg, const float *x, const int32_t *label
         return VGG_ERR_ALIGN;
     const PackedLayout P = packed_layout(cfg);
     if (packed_bytes < packed_total(cfg)) return VGG_ERR_WORKSPACE;
-    const WsLayout L = ws_layout(cfg, P, true);
-    if (!ws || ws_bytes < L.total) return VGG_ERR_WORKSPACE;
+    WsLayout L = ws_layout(cfg, P, true);
+    if (!ws_holds(L, ws, ws_bytes)) return VGG_ERR_WORKSPACE;
     Recorder rec{nullptr, 0, 0, false, VGG_OK};
     run_train(cfg, P, L, x, labels, static_cast<char *>(packed), grads, loss, logits, static_cast<char *>(ws),
               (hipStream_t)stream, rec);
@@ -936,8 +951,8 @@ int vgg19_timed(const vgg_config *cfg, int training, const float *x, const int32
     if (!aligned16(x) || !aligned16(packed) || (logits && !aligned16(logits)) || (ws && !aligned16(ws))) return VGG_ERR_ALIGN;
     const PackedLayout P = packed_layout(cfg);
     if (packed_bytes < (training ? packed_total(cfg) : P.total)) return VGG_ERR_WORKSPACE;
-    const WsLayout L = ws_layout(cfg, P, training != 0);
-    if (!ws || ws_bytes < L.total) return VGG_ERR_WORKSPACE;
+    WsLayout L = ws_layout(cfg, P, training != 0);
+    if (!ws_holds(L, ws, ws_bytes)) return VGG_ERR_WORKSPACE;
     const int need = vgg19_plan(cfg, training, nullptr, 0);
     if (need < 0) return need;
     if (cap < need) return VGG_ERR_WORKSPACE;

@@ -508,7 +508,8 @@ __global__ __launch_bounds__(256, 4) void fc_dw_kernel(const float *__restrict__
     }
 }
 
-// The same on the bf16 matrix unit (f32x3.h), for more than 128 batch rows or where no workspace is given; bound by splitting the operands, the MFMAs and
+// The same on the bf16 matrix unit (f32x3.h), for more than 128 batch rows or where dz in parts has no workspace (none
+// is asked for without da); bound by splitting the operands, the MFMAs and
 // writing dW together.  Workgroup: 128 (o) x 128 (i) block of dW; the batch is the contraction index, staged through LDS 32 rows
 // at a time as three planes of bf16 parts, and multiplied sixteen rows at a time up to the last one: 100 rows cost 112.  A
 // thread loads sixteen batch rows of one output and of one input, so that they leave for LDS already transposed: rows of 32
@@ -767,7 +768,7 @@ __global__ __launch_bounds__(256, 2) void fc_da_kernel(FcDaArgs p)
         }
 }
 
-// The same on the bf16 matrix unit (f32x3.h), for more than 128 batch rows.  Workgroup, one per CU: eight waves, 16 NB batch rows x 256 inputs x a range of
+// The same on the bf16 matrix unit (f32x3.h), where the dW kernel above runs.  Workgroup, one per CU: eight waves, 16 NB batch rows x 256 inputs x a range of
 // outputs (the contraction index), 32 at a time.  Both operands go through LDS as three planes of bf16 parts, rows of 32
 // outputs = 64 bytes whose 16-byte segment s lies at s ^ ((row >> 1) & 3); a thread loads sixteen outputs of one input, so
 // that they leave for LDS already transposed.  Two buffers and one barrier per step: one wave of a SIMD splits and stores
@@ -1272,11 +1273,12 @@ static bool fc_bwd_staged(int N, int In) { return N > 40 && N <= 128 && In < (1 
 // bytes of one of the two copies of dz in parts
 static size_t fc_dz_parts_bytes(const FcDaArgs &a) { return (size_t)((a.Out + 31) / 32) * a.nb * 3072; }
 
-size_t fc_bwd_workspace(int N, int In, int Out)
+// least: what a call has to bring, the partial sums of da; with less than the whole, the products split dz themselves.
+size_t fc_bwd_workspace(int N, int In, int Out, bool least)
 {
     FcDaArgs a;
     fc_da_plan(N, In, Out, a, false);
-    return round_up((size_t)fc_da_splits(a) * N * In * 4, 256) + (fc_bwd_staged(N, In) ? 2 * fc_dz_parts_bytes(a) : 0);
+    return round_up((size_t)fc_da_splits(a) * N * In * 4, 256) + (!least && fc_bwd_staged(N, In) ? 2 * fc_dz_parts_bytes(a) : 0);
 }
 
 // The launch of the kernel on the bf16 matrix unit, one workgroup per CU: of the splits that the workspace holds it takes
@@ -1338,11 +1340,11 @@ static void launch_fc_da(const FcDaArgs &p, int splits, hipStream_t s)
 }
 
 int fc_backward(int N, int In, int Out, const float *a, const float *w, const float *dz, float *dw, float *db, float *da,
-                int relu_mask, void *ws, hipStream_t s)
+                int relu_mask, void *ws, size_t ws_bytes, hipStream_t s)
 {
     const dim3 grid((unsigned)(((In + 127) / 128) * ((Out + 127) / 128)));
-    // (the parts of dz lie in the workspace, which is there where da is asked for)
-    const bool staged = da && fc_bwd_staged(N, In), parts = N > 40;
+    // (the parts of dz lie in the workspace, which is there where da is asked for, behind its partial sums if it holds both)
+    const bool staged = da && fc_bwd_staged(N, In) && ws_bytes >= fc_bwd_workspace(N, In, Out, false), parts = N > 40;
     if (!staged) {
         auto dw_kernel = parts ? (In % 4 == 0 ? fc_dw_f32x3_kernel<true> : fc_dw_f32x3_kernel<false>) : (In % 4 == 0 ? fc_dw_kernel<true> : fc_dw_kernel<false>);
         hipLaunchKernelGGL(dw_kernel, grid, dim3(256), 0, s, a, dz, dw, N, In, Out);

@@ -466,6 +466,36 @@ def test_wide_images_stay_inside_the_workspace(shp, dtype):
                     assert torch.equal(a, b), (k, l, float((a - b).abs().max()))
 
 
+def test_fp32_training_in_a_workspace_without_room_for_dz_in_parts():
+    """A training step takes a workspace that ends behind the dense backward's partial sums: the same parameters as in the whole
+    one, nothing written past it; one of 256 bytes less is refused."""
+    N, hidden, classes = 48, 64, 10
+    inp = synth.vgg19_inputs(N, 32, 32, hidden, classes, seed=6)
+    parts = lambda out: 2 * ((out + 31) // 32) * ((N + 15) // 16) * 3072
+    sizes = [(B.vgg_fc_bwd_workspace_bytes(B.F32, N, i, o), parts(o)) for i, o in ((512, hidden), (hidden, hidden), (hidden, classes))]
+    saved = max(s for s, _ in sizes) - max(s - p for s, p in sizes)
+    assert saved > 0
+    got = []
+    for less in (0, saved, saved + 256):
+        m = Vgg19(B.F32, N, 32, 32, hidden, classes, lr=0.01, training=True)
+        m.pack(inp.conv_w, inp.conv_b, inp.fc_w, inp.fc_b)
+        size = B.vgg19_train_workspace_bytes(m.cfg) - less
+        ws = torch.zeros((size + less + 4096,), dtype=torch.uint8, device="cuda")
+        ws[size:] = 255
+        m.ws = ws[:size]
+        if less > saved:
+            with pytest.raises(B.VggError, match="workspace"):
+                m.train_step(dev(inp.x), dev(inp.labels))
+        else:
+            m.train_step(dev(inp.x), dev(inp.labels))
+            torch.cuda.synchronize()
+            got.append((m.logits.clone(), m.loss.clone(), m.unpack()))
+        assert (ws[size:] == 255).all()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    for k, v in got[0][2].items():
+        assert all(np.array_equal(x, y) for x, y in zip(v, got[1][2][k])), k
+
+
 def test_bf16_training_needs_the_master_copy():
     cfg = B.make_config(B.BF16, 2, 32, 32, 512, 10, 0.01)          # no master copy
     assert B.vgg19_train_workspace_bytes(cfg) == 0

@@ -1179,6 +1179,39 @@ def test_fc_backward_fp32_whole_range_up_to_40_rows(N, In, Out, scale):
         assert err <= 1e-6
 
 
+def dz_parts_bytes(N, Out):
+    """What the workspace of the fp32 dense backward holds besides partial sums at 41 to 128 rows: two copies of dz in parts."""
+    return 2 * ((Out + 31) // 32) * ((N + 15) // 16) * 3072
+
+
+@pytest.mark.parametrize("N,In,Out", [(41, 4097, 33), (64, 1026, 200), (96, 260, 1028), (100, 8192, 2048), (128, 130, 514)])
+def test_fc_backward_fp32_workspace_of_partial_sums_only(N, In, Out):
+    """A workspace that holds da's partial sums but not dz in parts (one sized for 200 rows at 8192 -> 2048, say) takes the kernels that
+    split dz themselves: the same bits, nothing written past it; one of 256 bytes less is refused, before anything is written."""
+    g = torch.Generator(device="cuda").manual_seed(N * In + Out)
+    a, w, dz = (torch.randn(s, generator=g, device="cuda") for s in ((N, In), (Out, In), (N, Out)))
+    full = B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out)
+    least = full - dz_parts_bytes(N, Out)
+    if (N, In, Out) == (100, 8192, 2048):
+        assert least == B.vgg_fc_bwd_workspace_bytes(B.F32, 200, In, Out)
+    got = []
+    for size in (full, full - 256, least, least - 256):
+        dw, db, da = (torch.full(s, -7.0, device="cuda") for s in ((Out, In), (Out,), (N, In)))
+        ws = torch.full((full + 4096,), 255, dtype=torch.uint8, device="cuda")
+        call = lambda: B.vgg_fc_bwd(B.F32, N, In, Out, a, w, dz, dw, db, da, 1, ws[:size])
+        if size < least:
+            with pytest.raises(B.VggError, match="workspace"):
+                call()
+        else:
+            call()
+        torch.cuda.synchronize()
+        assert (ws[size:] == 255).all()
+        got.append((dw, db, da))
+    for other in got[1:3]:
+        assert all(torch.equal(x, y) for x, y in zip(got[0], other))
+    assert all((t == -7.0).all() for t in got[3])
+
+
 @pytest.mark.parametrize("N,In,Out", [(1, 8, 1), (32, 136, 65), (33, 264, 129), (64, 128, 64), (65, 120, 63), (96, 1032, 200), (97, 40, 33),
                                       (128, 256, 130), (129, 136, 257)])
 def test_fc_backward_bf16_row_blocks(N, In, Out):
