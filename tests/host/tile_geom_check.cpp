@@ -54,7 +54,7 @@ static bool check_period()
     unsigned long long seed = 88172645463325252ull;
     auto draw = [&](int n) { seed ^= seed << 13; seed ^= seed >> 7; seed ^= seed << 17; return (int)(seed % (unsigned)n) + 1; };
     for (int k = 0; k < 40000; ++k) {
-        const int rows = (const int[]){64, 128, 256, 320}[draw(4) - 1], N = draw(40), H = draw(k % 3 ? 40 : 200), W = draw(k % 5 ? 70 : 300);
+        const int rows = (const int[]){64, 128, 192, 256, 320}[draw(5) - 1], N = draw(40), H = draw(k % 3 ? 40 : 200), W = draw(k % 5 ? 70 : 300);
         const TileGeom g = make_tile_geom(N, H, W, rows);
         if (g.mode) continue;
         auto q = [&](int m) { return ((long)(m / (H * W)) * (H + 1) + m % (H * W) / W) * (W + 1) + m % W; };
@@ -100,7 +100,7 @@ int main()
                              {3, 24, 16}, {2, 40, 48}, {3, 50, 66}, {1, 24, 200}, {2, 31, 33}};
     long total = 0;
     for (auto &s : shapes)
-        for (int rows : {64, 128, 256, 320})
+        for (int rows : {64, 128, 192, 256, 320})
             for (bool patch : {false, true}) {
                 const long c = check(s[0], s[1], s[2], rows, patch);
                 if (c < 0) return 1;

@@ -134,7 +134,7 @@ def test_conv3x3_fwd_first_pair(shape):
     """The first two convolutions and the first pool as one call: against the oracle's three operations and
     against the library's separate calls (same products; the first layer adds its 27 in another order, so a
     few values differ by a rounding step).  The pooled tensor must be exactly the 2x2 maximum of the
-    un-pooled one.  The last shape has 352 patches, more than the launch has workgroups."""
+    un-pooled one.  The last shape has 704 patches, more than the launch's 512 workgroups."""
     N, H, W = shape
     dtype = B.BF16
     d1 = synth.conv_layer_inputs(N, H, W, 3, 64, seed=sum(shape))
@@ -611,17 +611,19 @@ def _full_mantissas(shape, seed):
     return v.view(torch.float32).cuda()
 
 
-def _three_part_call(op, lone):
-    """(result, the same in 64 bits) of an fp32 call on the bf16 matrix unit, all operands positive; lone: one product per result."""
+def _three_part_call(op, lone, N=64, parts=True):
+    """(result, the same in 64 bits) of an fp32 call on the bf16 matrix unit, all operands positive; lone: one product per result.
+    Dense backward: N rows; parts: whether the workspace has room for dz in parts."""
     if op in ("dw", "da"):
-        N, In, Out = (64, 640, 512) if op == "dw" else (64, 1032, 4096)
+        In, Out = (640, 512) if op == "dw" else (1032, 4096)
         a, w, dz = _full_mantissas((N, In), 1), _full_mantissas((Out, In), 2), _full_mantissas((N, Out), 3)
         if lone:
             keep = torch.zeros_like(dz)
             keep[3 if op == "dw" else slice(None), slice(None) if op == "dw" else 7] = 1.0
             dz = dz * keep
         dw, db, da = torch.empty((Out, In), device="cuda"), torch.empty((Out,), device="cuda"), torch.empty((N, In), device="cuda")
-        B.vgg_fc_bwd(B.F32, N, In, Out, a, w, dz, dw, db, da, 0, ws_bytes(B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out)))
+        size = B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out) - (0 if parts else dz_parts_bytes(N, Out))
+        B.vgg_fc_bwd(B.F32, N, In, Out, a, w, dz, dw, db, da, 0, ws_bytes(size))
         torch.cuda.synchronize()
         return (dw, dz.double().t() @ a.double()) if op == "dw" else (da, dz.double() @ w.double())
     N, H, W, Cin, Cout = (3, 28, 28, 512, 128) if op != "wgrad" else (9, 28, 28, 96, 128)
@@ -658,20 +660,34 @@ def _three_part_call(op, lone):
 
 @pytest.mark.parametrize("lone", [True, False])
 @pytest.mark.parametrize("op", ["fwd", "bwd_data", "wgrad", "dw", "da"])
-def test_fp32_products_in_three_parts_without_a_bias(op, lone):
+def test_fp32_products_in_three_parts_without_a_bias(op, lone, N=64, parts=True):
     """Every kernel that multiplies fp32 in three parts, positive operands with full significands.  One product: at most 2^-24 of
     it is left out and the result rounded (2^-24).  Sums of 64 to 7056 products: no element off by more than 5e-6 (a sum's own
     rounding), and in both no bias: a mean signed error of 1e-8, where rounding to nearest gives 1e-9 over as many results."""
-    got, ref = _three_part_call(op, lone)
+    got, ref = _three_part_call(op, lone, N, parts)
     err = (got.double() - ref) / ref
     assert err.abs().max().item() <= (2.0 ** -23 if lone else 5e-6)
     assert abs(err.mean().item()) <= 1e-8
 
 
-def test_fp32_in_three_parts_keeps_nan_and_the_largest_values():
+# Dense backward kernels that split dz themselves: workspaces without room for its parts (three to eight blocks of sixteen rows), and more than
+# 128 rows (blocks of two and three row tiles).
+SPLIT_DZ_ROWS = [(64, False), (80, False), (128, False), (200, True), (257, True)]
+
+
+@pytest.mark.parametrize("lone", [True, False])
+@pytest.mark.parametrize("N,parts", SPLIT_DZ_ROWS)
+@pytest.mark.parametrize("op", ["dw", "da"])
+def test_fp32_dense_products_in_three_parts_without_a_bias(op, N, parts, lone):
+    """The same, for the dense backward kernels that split dz themselves."""
+    test_fp32_products_in_three_parts_without_a_bias(op, lone, N, parts)
+
+
+@pytest.mark.parametrize("N,parts", [(48, False)] + SPLIT_DZ_ROWS)
+def test_fp32_dense_backward_in_three_parts_keeps_nan_and_the_largest_values(N, parts):
     """A NaN whose payload lies below the first part stays one; values that round to infinity in bf16 stay finite; infinities
-    as in fp32 arithmetic.  (Dense backward and weight gradient: their results pass through no maximum.)"""
-    N, In, Out = 48, 136, 64
+    as in fp32 arithmetic: both products, and dW where da is not asked for."""
+    In, Out = 136, 64
     g = torch.Generator().manual_seed(8)
     a, w, dz = (torch.randn(s, generator=g) for s in ((N, In), (Out, In), (N, Out)))
     nan, largest = torch.tensor([0x7f800001, -0x7ffffe], dtype=torch.int32).view(torch.float32), torch.finfo(torch.float32).max
@@ -679,14 +695,25 @@ def test_fp32_in_three_parts_keeps_nan_and_the_largest_values():
     dz[9], dz[:, 40] = 0.25 * torch.sign(dz[9]), 0.0
     w[40, 50] = -largest
     dz[12, 40] = 0.5
-    dw, da = torch.empty((Out, In), device="cuda"), torch.empty((N, In), device="cuda")
-    B.vgg_fc_bwd(B.F32, N, In, Out, a.cuda(), w.cuda(), dz.cuda(), dw, None, da, 0, ws_bytes(B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out)))
+    dw, da, alone = torch.empty((Out, In), device="cuda"), torch.empty((N, In), device="cuda"), torch.empty((Out, In), device="cuda")
+    size = B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out) - (0 if parts else dz_parts_bytes(N, Out))
+    B.vgg_fc_bwd(B.F32, N, In, Out, a.cuda(), w.cuda(), dz.cuda(), dw, None, da, 0, ws_bytes(size))
+    B.vgg_fc_bwd(B.F32, N, In, Out, a.cuda(), w.cuda(), dz.cuda(), alone, None, None, 0, None)
     torch.cuda.synchronize()
-    for got, ref in ((dw.cpu(), dz.double().t() @ a.double()), (da.cpu(), dz.double() @ w.double())):
+    dw_ref, da_ref = dz.double().t() @ a.double(), dz.double() @ w.double()
+    for got, ref in ((dw.cpu(), dw_ref), (alone.cpu(), dw_ref), (da.cpu(), da_ref)):
         assert torch.equal(got.isnan(), ref.isnan()) and ref.isnan().any()
         assert torch.equal(got.isposinf(), ref.isposinf()) and torch.equal(got.isneginf(), ref.isneginf()) and ref.isinf().any()
         big = ref.isfinite() & (ref.abs() > 1e37)
         assert big.any() and ((got[big].double() - ref[big]) / ref[big]).abs().max() <= 2.0 ** -23
+
+
+def test_fp32_in_three_parts_keeps_nan_and_the_largest_values():
+    """As above, dense backward with dz in parts ahead of the products, and the weight gradient of a convolution.  (Their results pass
+    through no maximum.)"""
+    test_fp32_dense_backward_in_three_parts_keeps_nan_and_the_largest_values(48, True)
+    nan = torch.tensor([0x7f800001, -0x7ffffe], dtype=torch.int32).view(torch.float32)
+    g = torch.Generator().manual_seed(8)
     N, H, W, Cin, Cout = 3, 28, 28, 32, 64
     assert B.vgg_conv3x3_plan(B.PLAN_BWD_WEIGHT, B.F32, N, H, W, Cin, Cout)[0] == 114
     x, gr = torch.randn((N, H, W, Cin), generator=g), torch.randn((N, H, W, Cout), generator=g)
