@@ -865,10 +865,12 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
     // What bounds the front of such a launch is the instructions issued before the first multiplication (2.8 of 9 us at one
     // image's 14x14 and 28x28 layers when every wave found its own pixels), so that is done once per workgroup: thread t finds the
     // pixel behind halo row t, the last wave the halo rows of the tile's 64 pixels, and the table is shared through LDS.
-    int *const table = reinterpret_cast<int *>(smem + p.tableA);      // [rowsA] byte offsets into x, [64] halo rows of tap (0,0)
+    // [rowsA] byte offsets from the halo's first pixel, [64] halo rows of tap (0,0)
+    int *const table = reinterpret_cast<int *>(smem + p.tableA);
+    const int px0 = halo_first_pixel(p.g, org);
     if (tid < p.rowsA) {
         const int px = tid < p.g.S ? halo_pixel(p.g, org, tid) : -1;
-        table[tid] = px < 0 ? (int)0x80000000u : px * (int)xrow;      // (outside the image: beyond the buffer, which reads zeros)
+        table[tid] = px < 0 ? (int)0x80000000u : (px - px0) * (int)xrow;   // (outside the image: beyond the buffer, reads zeros)
     }
     if (wv == G - 1) {
         int m, h;
@@ -904,7 +906,10 @@ __global__ __launch_bounds__(G * 64, 2) void conv3x3_small_bf16_kernel(ConvArgs 
     int hrow[NI];   // halo row of tap (0,0) of this lane's pixels
 #pragma unroll
     for (int i = 0; i < NI; ++i) hrow[i] = table[p.rowsA + i * 16 + q];
-    const u32x4 xbuf = {(unsigned)(uintptr_t)p.x, (unsigned)((uintptr_t)p.x >> 32), (unsigned)p.g.M * (unsigned)xrow, 0x00020000u};
+    // (from the halo's first pixel; offsets of pixels are below 2^31, the one that stands for "outside the image" is beyond)
+    const uintptr_t x0 = (uintptr_t)p.x + (size_t)px0 * xrow;
+    const u32x4 xbuf = {(unsigned)__builtin_amdgcn_readfirstlane((unsigned)x0), (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(x0 >> 32)),
+                        0x80000000u, 0x00020000u};
     auto copy = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < COPIES; ++k) {
@@ -1284,8 +1289,8 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         // (wide images have no other split to go to)
         const bool few = tiles <= 256 || (tiles <= 512 && (wide || chain <= 6)) ||
                          (tiles <= 1024 && (chunks >= 12 || Cout <= 64) && (wide || (c.ksplit <= G && chain <= 4)));
-        // (that kernel's offsets into the input are 31 bits)
-        const bool near = (size_t)N * H * W * CinP * sizeof(bf16_t) < ((size_t)1 << 31);
+        // (that kernel's offsets inside a tile are 31 bits)
+        const bool near = (size_t)halo_reach(W) * CinP * sizeof(bf16_t) < ((size_t)1 << 31);
         if (few && near && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, c.ksplit) <= 160 * 1024) {
             c.g = t;
             c.kernel = G == 8 ? kSmall8 : kSmall4;

@@ -515,6 +515,32 @@ def test_conv3x3_bf16_192_pixel_tiles(shape, kernel):
     test_conv3x3_bf16_small_and_medium_launches(shape, kernel)
 
 
+@pytest.mark.parametrize("shape,kernel", [((1, 160, 100, 70400, 8), 12), ((83, 14, 14, 70400, 8), 13)])
+def test_conv3x3_bf16_small_launches_of_large_inputs(shape, kernel):
+    """Few tiles of an input beyond 2 GiB (patches; consecutive pixels), whose offsets count from a tile's halo: images' corners and
+    edges and pixels behind the first 2 GiB against float64, zeros around the images included."""
+    N, H, W, Cin, Cout = shape
+    assert N * H * W * Cin * 2 > 2 ** 31 and B.vgg_conv3x3_plan(B.PLAN_FWD, B.BF16, N, H, W, Cin, Cout)[0] == kernel
+    g = torch.Generator(device="cuda").manual_seed(Cin)
+    x = torch.empty((N, H, W, Cin), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    w = (torch.randn((Cout, Cin, 3, 3), generator=g, device="cuda") / (9 * Cin) ** 0.5).bfloat16().float()
+    wp = torch.empty((9 * Cout * B.vgg_padded_channels(B.BF16, Cin),), dtype=torch.bfloat16, device="cuda")
+    B.vgg_conv_pack_weights(B.BF16, Cin, Cout, w, wp, 0)
+    y = torch.empty((N, H, W, Cout), dtype=torch.bfloat16, device="cuda")
+    B.vgg_conv3x3_fwd(B.BF16, N, H, W, Cin, Cout, x, wp, None, y, 0, ws_bytes(B.vgg_conv3x3_fwd_workspace_bytes(B.BF16, N, H, W, Cin, Cout)))
+    torch.cuda.synchronize()
+    past = 2 ** 31 // (2 * Cin)                               # the pixel that 2 GiB end in
+    w64 = w.double()
+    for m in {0, W - 1, H * W - 1, (N - 1) * H * W, past - 1, past, past + 1, past + W, N * H * W - W, N * H * W - 1}:
+        n, h, v = m // (H * W), m // W % H, m % W
+        want = torch.zeros((Cout,), dtype=torch.float64, device="cuda")
+        for t in range(9):
+            hh, vv = h + t // 3 - 1, v + t % 3 - 1
+            if 0 <= hh < H and 0 <= vv < W:
+                want += w64[:, :, t // 3, t % 3] @ x[n, hh, vv].double()
+        assert (y[n, h, v].double() - want).abs().max().item() <= 2.0 ** -7 * 4, m   # (results of N(0,1): below 4; half an ulp of bf16 is 2^-9 of them)
+
+
 @pytest.mark.parametrize("shape", [(1, 14, 14, 576, 512), (2, 7, 9, 1024, 200), (3, 20, 19, 768, 132), (2, 12, 36, 576, 72)])
 def test_conv3x3_bf16_split_over_workgroups(shape):
     """More ranges than the waves of one workgroup share (more than 512 input channels): the ranges go to workgroups of
