@@ -296,9 +296,9 @@ inline TileGeom make_tile_geom(int N, int H, int W, int rows)
     return g;
 }
 
-// Pixels from a tile's first halo pixel inside the image to its last one, at most, for tiles of up to 320 pixels: 22 rows of
-// a 20 x 16 patch, or 320 consecutive pixels and a row more on either side.
-inline long halo_reach(int W) { return 22l * W + 512; }
+// Pixels from a tile's first halo pixel inside the image to its last one, at most: tiles of up to 64 pixels 6 rows of a 4 x 16
+// patch, tiles of up to 320 pixels 22 rows of a 20 x 16 one, or as many consecutive pixels and a row more on either side.
+inline long halo_reach(int W, int rows = 320) { return rows <= 64 ? 6l * W + 128 : 22l * W + 512; }
 __host__ __device__ __forceinline__ int halo_first_pixel(const TileGeom &g, const TileOrigin &o)
 {
     if (!g.mode) return o.m0 > g.W + 2 ? o.m0 - g.W - 2 : 0;

@@ -1290,7 +1290,7 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         const bool few = tiles <= 256 || (tiles <= 512 && (wide || chain <= 6)) ||
                          (tiles <= 1024 && (chunks >= 12 || Cout <= 64) && (wide || (c.ksplit <= G && chain <= 4)));
         // (that kernel's offsets inside a tile are 31 bits)
-        const bool near = (size_t)halo_reach(W) * CinP * sizeof(bf16_t) < ((size_t)1 << 31);
+        const bool near = (size_t)halo_reach(W, kSmallPx) * CinP * sizeof(bf16_t) < ((size_t)1 << 31);
         if (few && near && (!pool || t.mode == 1) && c.ksplit <= kSmallRanges && conv_small_lds(G, t.S, c.ksplit) <= 160 * 1024) {
             c.g = t;
             c.kernel = G == 8 ? kSmall8 : kSmall4;

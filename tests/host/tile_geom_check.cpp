@@ -22,7 +22,7 @@ static long check(int N, int H, int W, int rows, bool patch = false)
         const int first = halo_first_pixel(g, o);
         for (int i = 0; i < g.S; ++i) {
             const int px = halo_pixel(g, o, i);
-            if (px >= 0 && (px < first || px - first >= halo_reach(W))) { printf("halo pixel %d is out of reach of %d N%d H%d W%d rows%d\n", px, first, N, H, W, rows); return -1; }
+            if (px >= 0 && (px < first || px - first >= halo_reach(W, rows))) { printf("halo pixel %d is out of reach of %d N%d H%d W%d rows%d\n", px, first, N, H, W, rows); return -1; }
         }
         for (int j = 0; j < rows; ++j) {
             int m, hrow;
