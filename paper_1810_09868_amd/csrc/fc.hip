@@ -508,8 +508,7 @@ __global__ __launch_bounds__(256, 4) void fc_dw_kernel(const float *__restrict__
     }
 }
 
-// The same on the bf16 matrix unit (f32x3.h), for more than 128 batch rows or where dz in parts has no workspace (none
-// is asked for without da); bound by splitting the operands, the MFMAs and
+// The same on the bf16 matrix unit (f32x3.h), for more than 40 batch rows where dz is not in parts ahead; bound by splitting the operands, the MFMAs and
 // writing dW together.  Workgroup: 128 (o) x 128 (i) block of dW; the batch is the contraction index, staged through LDS 32 rows
 // at a time as three planes of bf16 parts, and multiplied sixteen rows at a time up to the last one: 100 rows cost 112.  A
 // thread loads sixteen batch rows of one output and of one input, so that they leave for LDS already transposed: rows of 32
@@ -1265,11 +1264,23 @@ static void fc_da_plan(int N, int In, int Out, FcDaArgs &a, bool launch)
 }
 static int fc_da_splits(const FcDaArgs &a) { return (a.Out + a.o_per_split - 1) / a.o_per_split; }
 
-// dz in parts ahead of both products: up to 128 rows (one row tile, since the input's batch rows fill the registers; with two, 0.96 to
-// 1.10 of the time of 18 shapes), and 32-bit offsets inside 32 rows of W and dW.  41 to 128 rows: 0.88 of the time of the kernels that split
-// dz themselves over 242 shapes, 1.05 at most (25088 -> 4096, batch 100, 355 -> 255 us; 64 rows, 1104 -> 3335 34.6 / 35.8), same bits.  (25 to 40
-// rows stay on the fp32 MFMAs, as dW without da does: from 1024 outputs on 0.69 to 1.01 of the time here, but values of 2^-116 would be 4e-6 off.)
-static bool fc_bwd_staged(int N, int In) { return N > 40 && N <= 128 && In < (1 << 24) - 256; }
+// dz in parts ahead of both products: 41 to 128 rows (one row tile, since the input's batch rows fill the registers; with two, 0.96 to
+// 1.10 of the time of 18 shapes) and 32-bit offsets inside 32 rows of W and dW.  Against the kernels that split dz themselves, same
+// bits, over 1968 shapes (25088 -> 4096, batch 100, 355 -> 255 us): up to one (tile, 32 outputs) unit of dW per workgroup 0.76 to 1.01 of the
+// time.  With more, splitting dz ahead (3 us) and a tile's first step have to be paid by what those kernels lose, which is little while all
+// their blocks of 128 x 128 run at once, two per CU: up to 512 blocks 0.85 to 1.16, 1.01 on average (83 rows, 1360 -> 2496 36 / 41 us).
+// Beyond, 0.63 to 0.99 above 64 rows.  With fewer, writing dW counts as much as the MFMAs, and a wave's 128 bytes per row cost more
+// where rows do not begin at whole ones: 32 | In 0.70 to 1.01, 16 | In 0.80 to 1.04 (beyond 1024 blocks at most 0.96), other
+// multiples of four 0.87 to 1.15 (46 rows, 4296 -> 7526 88 / 101); on other rows those kernels store 4 bytes at a time too, 0.73 to 1.03, one 1.05.
+// (25 to 40 rows stay on the fp32 MFMAs, as dW without da does: from 1024 outputs on 0.69 to 1.01 of the time here, but values of 2^-116
+// would be 4e-6 off.)
+static bool fc_bwd_staged(int N, int In, int Out)
+{
+    if (N <= 40 || N > 128 || In >= (1 << 24) - 256) return false;
+    const long units = (long)((In + 255) / 256) * ((Out + 31) / 32), blocks = (long)((In + 127) / 128) * ((Out + 127) / 128);
+    if (units <= 256) return true;
+    return blocks > 512 && (N > 64 || In % 4 || In % 32 == 0 || (In % 16 == 0 && blocks > 1024));
+}
 // bytes of one of the two copies of dz in parts
 static size_t fc_dz_parts_bytes(const FcDaArgs &a) { return (size_t)((a.Out + 31) / 32) * a.nb * 3072; }
 
@@ -1278,7 +1289,7 @@ size_t fc_bwd_workspace(int N, int In, int Out, bool least)
 {
     FcDaArgs a;
     fc_da_plan(N, In, Out, a, false);
-    return round_up((size_t)fc_da_splits(a) * N * In * 4, 256) + (!least && fc_bwd_staged(N, In) ? 2 * fc_dz_parts_bytes(a) : 0);
+    return round_up((size_t)fc_da_splits(a) * N * In * 4, 256) + (!least && fc_bwd_staged(N, In, Out) ? 2 * fc_dz_parts_bytes(a) : 0);
 }
 
 // The launch of the kernel on the bf16 matrix unit, one workgroup per CU: of the splits that the workspace holds it takes
@@ -1344,7 +1355,7 @@ int fc_backward(int N, int In, int Out, const float *a, const float *w, const fl
 {
     const dim3 grid((unsigned)(((In + 127) / 128) * ((Out + 127) / 128)));
     // (the parts of dz lie in the workspace, which is there where da is asked for, behind its partial sums if it holds both)
-    const bool staged = da && fc_bwd_staged(N, In) && ws_bytes >= fc_bwd_workspace(N, In, Out, false), parts = N > 40;
+    const bool staged = da && fc_bwd_staged(N, In, Out) && ws_bytes >= fc_bwd_workspace(N, In, Out, false), parts = N > 40;
     if (!staged) {
         auto dw_kernel = parts ? (In % 4 == 0 ? fc_dw_f32x3_kernel<true> : fc_dw_f32x3_kernel<false>) : (In % 4 == 0 ? fc_dw_kernel<true> : fc_dw_kernel<false>);
         hipLaunchKernelGGL(dw_kernel, grid, dim3(256), 0, s, a, dz, dw, N, In, Out);

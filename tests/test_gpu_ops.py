@@ -628,6 +628,22 @@ def test_conv3x3_fp32_in_three_parts_infinities_and_range():
         assert max_rel_err(from_nhwc(y), R.conv3x3_fwd(xs, w, None, relu=False)) <= 2e-6
 
 
+def da_partial_sum_bytes(N, In, Out):
+    """Workspace of da's partial sums in the fp32 dense backward: 512 workgroups rounded up to whole splits of the tiles of 128 rows x
+    256 inputs, at least 64 outputs each."""
+    tiles = -(-In // 256) * -(-N // 128)
+    splits = max(1, min(-(-512 // tiles), -(-Out // 64)))
+    per_split = -(-(-(-Out // splits)) // 16) * 16
+    return -(-(-(-Out // per_split) * N * In * 4) // 256) * 256
+
+
+def dz_in_parts(N, In, Out):
+    """Whether the fp32 dense backward asks for room for dz in parts (two copies, 3 KB per 32 outputs and sixteen rows) as well."""
+    parts = B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out) - da_partial_sum_bytes(N, In, Out)
+    assert parts in (0, 2 * -(-Out // 32) * -(-N // 16) * 3072)
+    return parts > 0
+
+
 def _full_mantissas(shape, seed):
     """fp32 values in [1, 2) with random 24-bit significands, among them 0x3f80ffff, of which a truncating split into 8-bit
     parts leaves out the most."""
@@ -641,14 +657,15 @@ def _three_part_call(op, lone, N=64, parts=True):
     """(result, the same in 64 bits) of an fp32 call on the bf16 matrix unit, all operands positive; lone: one product per result.
     Dense backward: N rows; parts: whether the workspace has room for dz in parts."""
     if op in ("dw", "da"):
-        In, Out = (640, 512) if op == "dw" else (1032, 4096)
+        In, Out = (640, 512) if op == "dw" else (512, 4096) if parts and N <= 128 else (1032, 4096)
+        assert dz_in_parts(N, In, Out) == (N <= 128 and (op == "dw" or In == 512))
         a, w, dz = _full_mantissas((N, In), 1), _full_mantissas((Out, In), 2), _full_mantissas((N, Out), 3)
         if lone:
             keep = torch.zeros_like(dz)
             keep[3 if op == "dw" else slice(None), slice(None) if op == "dw" else 7] = 1.0
             dz = dz * keep
         dw, db, da = torch.empty((Out, In), device="cuda"), torch.empty((Out,), device="cuda"), torch.empty((N, In), device="cuda")
-        size = B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out) - (0 if parts else dz_parts_bytes(N, Out))
+        size = B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out) if parts else da_partial_sum_bytes(N, In, Out)
         B.vgg_fc_bwd(B.F32, N, In, Out, a, w, dz, dw, db, da, 0, ws_bytes(size))
         torch.cuda.synchronize()
         return (dw, dz.double().t() @ a.double()) if op == "dw" else (da, dz.double() @ w.double())
@@ -722,7 +739,8 @@ def test_fp32_dense_backward_in_three_parts_keeps_nan_and_the_largest_values(N, 
     w[40, 50] = -largest
     dz[12, 40] = 0.5
     dw, da, alone = torch.empty((Out, In), device="cuda"), torch.empty((N, In), device="cuda"), torch.empty((Out, In), device="cuda")
-    size = B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out) - (0 if parts else dz_parts_bytes(N, Out))
+    assert dz_in_parts(N, In, Out) == (N <= 128)
+    size = B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out) if parts else da_partial_sum_bytes(N, In, Out)
     B.vgg_fc_bwd(B.F32, N, In, Out, a.cuda(), w.cuda(), dz.cuda(), dw, None, da, 0, ws_bytes(size))
     B.vgg_fc_bwd(B.F32, N, In, Out, a.cuda(), w.cuda(), dz.cuda(), alone, None, None, 0, None)
     torch.cuda.synchronize()
@@ -1175,12 +1193,19 @@ def test_fc_backward_fp32_tile_edges(N, In, Out):
     assert (dw[Out * In:] == -7.0).all() and (da[N * In:] == -7.0).all()
 
 
-@pytest.mark.parametrize("N,In,Out", [(25, 258, 1024), (24, 258, 1024), (32, 255, 1025), (41, 4097, 33), (57, 5002, 2602), (100, 2052, 5000), (128, 1026, 2600),
-                                      (128, 6400, 1030), (129, 1026, 200)])
-def test_fc_backward_fp32_staged_gradient(N, In, Out):
-    """fp32 backward with dz taken apart ahead of the products, and launches just outside its lines (24 to 32 rows, 129 rows): workgroups of dW with one and with several (input tile, 32 outputs) units and with more than the four LDS buffers hold,
+@pytest.mark.parametrize("N,In,Out,parts", [
+    (25, 258, 1024, False), (24, 258, 1024, False), (32, 255, 1025, False), (41, 4097, 33, True), (57, 5002, 2602, True), (100, 2052, 5000, True),
+    (128, 1026, 2600, False), (128, 6400, 1030, False), (129, 1026, 200, False),
+    (40, 512, 1000, False), (50, 512, 4096, True), (50, 512, 4097, False),        # 40 and 41 rows; 256 and 258 units
+    (70, 4096, 2048, False), (70, 4098, 2048, True), (128, 4225, 2050, True),     # 512 and 528 blocks
+    (64, 4224, 2048, True), (64, 4232, 2048, False), (64, 4240, 2048, False), (64, 8464, 2048, True), (64, 4226, 2048, True),   # rows by alignment
+])
+def test_fc_backward_fp32_staged_gradient(N, In, Out, parts):
+    """fp32 backward with dz taken apart ahead of the products (parts), and launches just outside the lines to it: workgroups
+    of dW with one and with several (input tile, 32 outputs) units and with more than the four LDS buffers hold,
     of two input tiles, and ranges of outputs that end inside 32; every element against float64.  Sums of at most 5000 products of
     N(0,1) values in fp32 are within 1e-6 of the largest, the tolerance is 1e-5.  Guards behind the results, the workspace NaN before."""
+    assert dz_in_parts(N, In, Out) == parts
     g = torch.Generator(device="cuda").manual_seed(N * In + Out)
     a, w, dz = (torch.randn(s, generator=g, device="cuda") for s in ((N, In), (Out, In), (N, Out)))
     dw, da = torch.full((Out * In + 256,), -7.0, device="cuda"), torch.full((N * In + 256,), -7.0, device="cuda")
@@ -1232,11 +1257,6 @@ def test_fc_backward_fp32_whole_range_up_to_40_rows(N, In, Out, scale):
         assert err <= 1e-6
 
 
-def dz_parts_bytes(N, Out):
-    """What the workspace of the fp32 dense backward holds besides partial sums at 41 to 128 rows: two copies of dz in parts."""
-    return 2 * ((Out + 31) // 32) * ((N + 15) // 16) * 3072
-
-
 @pytest.mark.parametrize("N,In,Out", [(41, 4097, 33), (64, 1026, 200), (96, 260, 1028), (100, 8192, 2048), (128, 130, 514)])
 def test_fc_backward_fp32_workspace_of_partial_sums_only(N, In, Out):
     """A workspace that holds da's partial sums but not dz in parts (one sized for 200 rows at 8192 -> 2048, say) takes the kernels that
@@ -1244,7 +1264,8 @@ def test_fc_backward_fp32_workspace_of_partial_sums_only(N, In, Out):
     g = torch.Generator(device="cuda").manual_seed(N * In + Out)
     a, w, dz = (torch.randn(s, generator=g, device="cuda") for s in ((N, In), (Out, In), (N, Out)))
     full = B.vgg_fc_bwd_workspace_bytes(B.F32, N, In, Out)
-    least = full - dz_parts_bytes(N, Out)
+    least = da_partial_sum_bytes(N, In, Out)
+    assert dz_in_parts(N, In, Out)
     if (N, In, Out) == (100, 8192, 2048):
         assert least == B.vgg_fc_bwd_workspace_bytes(B.F32, 200, In, Out)
     got = []
