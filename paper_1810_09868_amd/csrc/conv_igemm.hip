@@ -810,7 +810,7 @@ __global__ __launch_bounds__(WM *WN * 64, OCC) void conv3x3_igemm_wreg_kernel(Co
 // by the waves in turn (wave w: w and w + G), each with all nine taps.  What bounds such a launch is not the matrix pipe but
 // the chain launch -> first loads -> multiply -> combine and the instructions along it, so the kernel has one of each: a wave copies its own chunk's halo
 // into its own LDS region and requests all nine taps' weights at once (9 NJ fragments in registers, plain loads; a tap's
-// registers are refilled for the wave's next chunk as soon as its MFMAs are issued), no barrier until the end,
+// registers are refilled for the wave's next chunk as soon as its MFMAs are issued), no barrier between the shared table and the end,
 // and the waves' sums meet in LDS instead of in a partial-sum buffer that a second launch has to read.
 // LDS rows are 64 bytes, segment s of row q at s ^ ((q >> 1) & 3): conflict-free for the fragment reads of
 // v_mfma_f32_16x16x32_bf16 (lane 16 g + q reads segment g of pixel q).
@@ -1339,7 +1339,7 @@ static ConvPlan conv_plan(int dtype, int N, int H, int W, int CinP, int Cout, bo
         }
         const TileGeom t = make_tile_geom(N, H, W, 128);
         const int tiles = t.ntiles * cols;
-        // 192 pixels cost 0.78: in place of 256-pixel tiles 0.84 to 0.96 of the time of 169 shapes (96 -> 200 at 45x60, batch 7, 14.3 -> 12.9 us;
+        // 192 pixels cost 0.78: in place of 256-pixel tiles 0.84 to 0.96 of the time of 169 shapes (96 -> 200 at 45x60, batch 7, 14.3 -> 12.4 us;
         // 480 -> 112 at 25x52, batch 27, 45.6 -> 39.2), in place of 128-pixel ones with the larger halo 0.81 to 0.96 of 81, with the
         // smaller one 0.94 to 1.07 of 50, so not there; nor, at up to three chunks, where a 256-pixel tile has the smaller halo (0.95).
         const bool half = t.S <= kWregHaloRowsHalf && 0.56f * rounds(tiles) < best;

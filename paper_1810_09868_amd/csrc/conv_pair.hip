@@ -24,8 +24,8 @@
 //      result is the maximum of the rounded values); pooled and/or un-pooled tensor leave through a
 //      per-wave LDS block as full 128-byte pixel rows.
 // Two workgroups per CU (58 KB of LDS each), persistent over the patches of their XCD's share.  Bound by the chain of phases between
-// barriers, which the other workgroup's matrix work fills: patches of 16 x 32 with one workgroup per CU evaluate 7 % fewer
-// first-layer pixels, and took 347 us at batch 100 (224 x 224, pooled tensor only) against 325, 20.6 against 8.6 for one image.
+// barriers, which the other workgroup's matrix work fills (matrix pipes busy 0.55 of the time, 0.44 with one): patches of 16 x 32 with one workgroup per CU have 10 % fewer
+// halo pixels (17 % fewer in whole blocks of 32 for four waves), and took 347 us at batch 100 (224 x 224, pooled tensor only) against 325, 20.6 against 8.6 for one image.
 // Needs H % 16 == 0 and W % 32 == 0; no pooling positions (the training step keeps the separate kernels,
 // whose outputs its backward pass reads).
 #include "common.h"

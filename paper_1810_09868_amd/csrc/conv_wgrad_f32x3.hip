@@ -11,8 +11,10 @@
 //   x: the halo (6 x 18 or 10 x 10) as it lies, [pixel][32 channels], since a tap shifts the pixels: transpose reads, the 32-byte half c of
 //      row r at c ^ (r >> 3) & 1, which keeps the eight rows of half a wave on distinct banks.
 // Two buffers and one barrier per patch: a wave splits and stores the next patch half-way through its own.  64 -> 128 at 50x66,
-// batch 10: 69 -> 44 us (the fp32 MFMAs on 4 x 14 patches, 512 workgroups), 512 -> 512 at 28x28, batch 10, 298 -> 213.  Bound by
-// the MFMAs, two waves per SIMD: four tenths fewer LDS reads (the taps of a halo row shifted out of registers) and splitting at
+// batch 10: 69 -> 44 us (the fp32 MFMAs on 4 x 14 patches, 512 workgroups), 512 -> 512 at 28x28, batch 10, 298 -> 213.  What
+// bounds it is not known; no unit is full.  On the first of these layers the matrix pipes are busy 0.31 of the time, vector instructions
+// (3.6 beside each MFMA) take half of a SIMD's issue cycles, the LDS is active 0.23; a wave waits to issue 0.37 of its time, for
+// counters and barriers 0.19.  Four tenths fewer LDS reads (the taps of a halo row shifted out of registers) and splitting at
 // different times in a SIMD's two waves changed nothing (1.00 of the time over 27 and 32 shapes).  (A zero of g beside an infinite x makes
 // a partial sum NaN here: the pass that adds them forms it again from the patches' own pixels.)
 #include "f32x3.h"

@@ -904,7 +904,7 @@ __global__ __launch_bounds__(512, 2) void fc_da_f32x3_kernel(FcDaArgs p)
     }
 }
 
-// ------------------------------------ fp32 backward on the bf16 matrix unit, more than 40 batch rows
+// ------------------------------------ fp32 backward on the bf16 matrix unit, dz in parts ahead (fc_bwd_staged)
 // dz in parts (f32x3.h), once per call, in the layouts that the two products' fragments have: per 32 outputs ("step") blocks of
 // 1 KB, which a wave's 64 lanes read 16 bytes each, in order.  25088 -> 4096: 6 us, db among them (4.7 alone).  With it the bias gradient, in fc_db_kernel's order.
 //   rows (da): [step][16-row block][part], lane 16 g + q: outputs 8 g .. 8 g + 7 of row q
@@ -990,7 +990,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, in
     return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((uintptr_t)hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
-// dW = dz^T a, up to 128 batch rows; bound by the MFMAs (six per product) and by writing dW.  Eight waves, one workgroup per CU; wave w
+// dW = dz^T a, up to 128 batch rows; bound by the MFMAs (six per product; pipes busy 0.61 of the time below) and by writing dW.  Eight waves, one workgroup per CU; wave w
 // owns inputs 32 w .. 32 w + 31 of a tile of 256, whose batch rows it keeps in registers, split, in the MFMA's layout; 32
 // outputs of dz at a time come through LDS.  So a value of the input is split once per tile and workgroup, not once per 128 x 128 block
 // of dW, and nothing but MFMAs, fragment reads and stores is left in the loop.  The (tile, 32 outputs) units are shared out evenly.
@@ -1104,7 +1104,7 @@ __global__ __launch_bounds__(512, 2) void fc_dw_parts_kernel(const float *__rest
 }
 
 // da = dz W.  Eight waves, one workgroup per CU; 16 NB batch rows x 256 inputs x a range of outputs (the contraction index), 32 at
-// a time; bound by the MFMAs (six per product), splitting the weights and streaming them.  A weight is used by one wave only:
+// a time; bound by the MFMAs (six per product; pipes busy 0.50 of the time below), splitting the weights and streaming them.  A weight is used by one wave only:
 // lane 16 g + q loads outputs 8 g .. 8 g + 7 of inputs 2 q and 2 q + 1 of the wave's 32 (128 bytes of four rows per load) straight to
 // its register, a step ahead, and splits them between the MFMAs of the step before; dz comes in parts through LDS.  The weights are
 // the first operand, so that a lane holds eight neighbouring inputs of a batch row.  25088 -> 4096, 100 rows: 128 us (158 with weights and dz
